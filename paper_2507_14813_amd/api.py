@@ -454,7 +454,7 @@ def enumerate_matches(graph: Graph, tree: Tree, stream=None):
     n = ctypes.c_int64(0)
     st = _default_stream(stream)
     _check(L.mg_enumerate(graph.handle, tree.handle, st, None, 0, ctypes.byref(n)))
-    rec = np.zeros((max(1, n.value), 6), dtype=np.int32)
+    rec = np.empty((max(1, n.value), 6), dtype=np.int32)
     _check(L.mg_enumerate(graph.handle, tree.handle, st, _p(rec), n.value, ctypes.byref(n)))
     rec = rec[:n.value]
     return rec[:, 0].copy(), rec[:, 1:].copy()

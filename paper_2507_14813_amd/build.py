@@ -33,7 +33,7 @@ def _run(cmd):
 
 # the search kernels: one file per (tree depth, time width), largest first
 HIP_SOURCES = tuple("search_d%d_t%d.hip" % (d, t) for d in (5, 4, 3, 2, 1) for t in (32, 64)) + \
-    ("comine.hip", "sched.hip")
+    ("comine.hip", "sched.hip", "ingest.hip")
 
 
 def _compile(name):

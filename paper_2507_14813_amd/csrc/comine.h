@@ -238,4 +238,10 @@ hipError_t static_scratch(unsigned long long **ptr);
 hipError_t launch_fill_u64(unsigned long long *p, uint32_t n, unsigned long long v,
                            hipStream_t stream);
 
+// Enumeration records (1 + kKMax words each: distinct motif, edge ids) into
+// the caller's numbering: motif q becomes first[q], edge e becomes order[e]
+// (order NULL: stays).
+hipError_t launch_map_matches(int32_t *rec, uint64_t n, const int32_t *first,
+                              const uint32_t *order, hipStream_t stream);
+
 }  // namespace mg

@@ -58,8 +58,8 @@ struct mg_graph {
     int time_bytes = 4;
     int device = 0;
     bool host_only = false;             // no device copy (MG_HOST_ONLY)
-    std::vector<int64_t> input_index;   // caller's index of each edge (empty: the same)
     mgh::DevBuf gsrc, gdst, gt, gx, out_eid, in_eid, out_off, out_adj, in_off, in_adj;
+    mgh::DevBuf order;                  // u32 per edge: the caller's index (none: the same)
     int64_t device_bytes = 0;
     std::unique_ptr<mgh::HostAdj> host;   // for the CPU backend, built on first use
     int8_t bipartite = -1;              // -1 unknown, else whether the undirected graph is

@@ -11,6 +11,7 @@
 #include <cstring>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <string>
@@ -20,6 +21,7 @@
 #include "../../include/mayura.h"
 #include "comine.h"
 #include "handles.h"
+#include "ingest.h"
 #include "sched.h"
 
 using mg::kVMax;
@@ -97,7 +99,7 @@ using namespace mgh;
 
 mg_graph::~mg_graph() {
     for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &out_eid, &in_eid, &out_off, &out_adj, &in_off,
-                      &in_adj})
+                      &in_adj, &order})
         dev_free(*b);
 }
 
@@ -114,78 +116,104 @@ void parallel_for(int64_t n, F f) {
     for (auto &x : th) x.join();
 }
 
-template <typename TT>
-int upload_graph(mg_graph *g, const std::vector<int32_t> &s, const std::vector<int32_t> &d,
-                 const std::vector<int64_t> &t, hipStream_t st) {
-    const int64_t E = g->E;
-    const int32_t V = g->V;
-    std::vector<TT> rt(E);
-    for (int64_t i = 0; i < E; ++i) rt[i] = (TT)(uint64_t)(t[i] - g->t_min);
-
-    // out/in adjacency (self-loops excluded), each list in time order:
-    // a counting sort by vertex over the time-ordered edge list is stable.
-    std::vector<uint32_t> oo(V + 1, 0), io(V + 1, 0);
-    for (int64_t i = 0; i < E; ++i)
-        if (s[i] != d[i]) { oo[s[i] + 1]++; io[d[i] + 1]++; }
-    for (int32_t v = 0; v < V; ++v) { oo[v + 1] += oo[v]; io[v + 1] += io[v]; }
-    const uint32_t A = oo[V];
-    std::vector<mg::Entry<TT>> oadj(A), iadj(A);
-    std::vector<uint32_t> oeid(A), ieid(A);   // edge id of every list entry
-    {
-        std::vector<uint32_t> po(oo.begin(), oo.end() - 1), pi(io.begin(), io.end() - 1);
-        for (int64_t i = 0; i < E; ++i) {
-            if (s[i] == d[i]) continue;
-            oeid[po[s[i]]] = (uint32_t)i;
-            ieid[pi[d[i]]] = (uint32_t)i;
-            mg::Entry<TT> &x = oadj[po[s[i]]++];
-            std::memset(&x, 0, sizeof x);
-            x.v = d[i]; x.t = rt[i];
-            mg::Entry<TT> &y = iadj[pi[d[i]]++];
-            std::memset(&y, 0, sizeof y);
-            y.v = s[i]; y.t = rt[i];
-        }
+// Frees a set of device buffers at the end of a scope.
+struct Scratch {
+    std::vector<DevBuf> bufs;
+    ~Scratch() { for (DevBuf &b : bufs) dev_free(b); }
+    int alloc(void **p, size_t bytes, hipStream_t st) {
+        bufs.emplace_back();
+        const int rc = dev_alloc(bufs.back(), bytes, (void *)st);
+        *p = bufs.back().ptr;
+        return rc;
     }
-    // per edge (u -> v at t): where the entries after time t start in out(u),
-    // in(u), out(v) and in(v) -- the first index with a later time
-    std::vector<uint32_t> gx(4 * (size_t)E, 0);
-    parallel_for(E, [&](int64_t i0, int64_t i1) {
-        auto after = [&](const std::vector<mg::Entry<TT>> &adj, const std::vector<uint32_t> &off,
-                         int32_t v, TT t) {
-            uint32_t lo = off[v], n = off[v + 1] - off[v];
-            while (n > 0) {
-                const uint32_t h = n >> 1;
-                if (adj[lo + h].t <= t) { lo += h + 1; n -= h + 1; }
-                else n = h;
-            }
-            return lo;
-        };
-        for (int64_t i = i0; i < i1; ++i) {
-            if (s[i] == d[i]) continue;
-            gx[4 * i + 0] = after(oadj, oo, s[i], rt[i]);
-            gx[4 * i + 1] = after(iadj, io, s[i], rt[i]);
-            gx[4 * i + 2] = after(oadj, oo, d[i], rt[i]);
-            gx[4 * i + 3] = after(iadj, io, d[i], rt[i]);
-        }
-    });
-    struct Up { DevBuf *b; const void *h; size_t n; };
-    Up ups[] = {
-        {&g->gsrc, s.data(), sizeof(int32_t) * E}, {&g->gdst, d.data(), sizeof(int32_t) * E},
-        {&g->gt, rt.data(), sizeof(TT) * E},
-        {&g->gx, gx.data(), sizeof(uint32_t) * 4 * E},
-        {&g->out_eid, oeid.data(), sizeof(uint32_t) * A},
-        {&g->in_eid, ieid.data(), sizeof(uint32_t) * A},
-        {&g->out_off, oo.data(), sizeof(uint32_t) * (V + 1)},
-        {&g->out_adj, oadj.data(), sizeof(mg::Entry<TT>) * A},
-        {&g->in_off, io.data(), sizeof(uint32_t) * (V + 1)},
-        {&g->in_adj, iadj.data(), sizeof(mg::Entry<TT>) * A},
+    template <typename T>
+    int get(T **p, size_t n, hipStream_t st) { return alloc((void **)p, sizeof(T) * n, st); }
+};
+
+int bit_width(uint64_t x) {
+    int b = 0;
+    while (x) { ++b; x >>= 1; }
+    return b;
+}
+
+#define LAUNCH_TRY(expr)                                                                  \
+    do {                                                                                  \
+        hipError_t e_ = (expr);                                                           \
+        if (e_ != hipSuccess)                                                             \
+            return fail(MG_EDEVICE, "graph ingest failed: %s", hipGetErrorString(e_));    \
+    } while (0)
+
+template <typename TT>
+mg::DevGraph<TT> dev_graph(const mg_graph *g);
+
+// Builds the device graph from checked edge arrays in device memory: sorts
+// the edges by time unless they are, then both sides' lists and the per-edge
+// list ranks (ingest.hip).  Returns once the stream has finished it.
+template <typename TT>
+int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int64_t *t, bool sorted,
+                 hipStream_t st) {
+    const uint32_t E = (uint32_t)g->E, V = (uint32_t)g->V;
+    const uint32_t A = (uint32_t)(g->E - g->self_loops);   // list entries
+    struct Need { DevBuf *b; size_t n; };
+    const Need needs[] = {
+        {&g->gsrc, sizeof(int32_t) * (size_t)E}, {&g->gdst, sizeof(int32_t) * (size_t)E},
+        {&g->gt, sizeof(TT) * (size_t)E},        {&g->gx, sizeof(uint32_t) * 4 * (size_t)E},
+        {&g->out_eid, sizeof(uint32_t) * (size_t)A}, {&g->in_eid, sizeof(uint32_t) * (size_t)A},
+        {&g->out_off, sizeof(uint32_t) * ((size_t)V + 1)},
+        {&g->out_adj, sizeof(mg::Entry<TT>) * (size_t)A},
+        {&g->in_off, sizeof(uint32_t) * ((size_t)V + 1)},
+        {&g->in_adj, sizeof(mg::Entry<TT>) * (size_t)A},
     };
     g->device_bytes = 0;
-    for (auto &u : ups) {
+    for (const Need &u : needs) {
         int rc = dev_alloc(*u.b, u.n, (void *)st);
         if (rc) return rc;
-        if (u.n) HIP_TRY(hipMemcpyAsync(u.b->ptr, u.h, u.n, hipMemcpyHostToDevice, st));
         g->device_bytes += (int64_t)u.n;
     }
+    Scratch tmp;
+    uint32_t *v[2], *key[2], *opos, *ipos;
+    void *sort_mem;
+    int rc = tmp.alloc(&sort_mem, mg::sort_scratch_bytes(E), st);
+    for (int i = 0; i < 2 && !rc; ++i) rc = tmp.get(&v[i], E, st);
+    for (int i = 0; i < 2 && !rc; ++i) rc = tmp.get(&key[i], E, st);
+    if (rc) return rc;
+    int at = 0;
+    if (!sorted) {
+        TT *tk[2];
+        for (int i = 0; i < 2 && !rc; ++i) rc = tmp.get(&tk[i], E, st);
+        if (!rc) rc = dev_alloc(g->order, sizeof(uint32_t) * (size_t)E, (void *)st);
+        if (rc) return rc;
+        LAUNCH_TRY(mg::launch_time_keys<TT>(t, g->t_min, E, tk[0], st));
+        LAUNCH_TRY(mg::sort_pairs<TT>(tk, v, true, E, bit_width((uint64_t)(g->t_max - g->t_min)),
+                                      sort_mem, &at, st));
+        HIP_TRY(hipMemcpyAsync(g->order.ptr, v[at], sizeof(uint32_t) * (size_t)E,
+                               hipMemcpyDeviceToDevice, st));
+        g->device_bytes += (int64_t)sizeof(uint32_t) * E;
+    }
+    rc = tmp.get(&opos, E, st);
+    if (!rc) rc = tmp.get(&ipos, E, st);
+    uint32_t *ikey = nullptr;
+    if (!rc) rc = tmp.get(&ikey, E, st);
+    if (rc) return rc;
+    auto *gsrc = (int32_t *)g->gsrc.ptr, *gdst = (int32_t *)g->gdst.ptr;
+    TT *gt = (TT *)g->gt.ptr;
+    if (E)
+        LAUNCH_TRY(mg::launch_place_edges<TT>(src, dst, t, g->t_min, (const uint32_t *)g->order.ptr,
+                                              E, V, gsrc, gdst, gt, key[0], ikey, st));
+    const int vb = bit_width(V);   // vertices and V itself (self-loops)
+    for (int side = 0; side < 2; ++side) {
+        uint32_t *k[2] = {side ? ikey : key[0], key[1]};
+        LAUNCH_TRY(mg::sort_pairs<uint32_t>(k, v, true, E, vb, sort_mem, &at, st));
+        DevBuf &eid = side ? g->in_eid : g->out_eid;
+        if (A)
+            HIP_TRY(hipMemcpyAsync(eid.ptr, v[at], sizeof(uint32_t) * (size_t)A,
+                                   hipMemcpyDeviceToDevice, st));
+        LAUNCH_TRY(mg::launch_lists<TT>(k[at], v[at], A, V, side ? gsrc : gdst, gt,
+                                        (uint32_t *)(side ? g->in_off : g->out_off).ptr,
+                                        (mg::Entry<TT> *)(side ? g->in_adj : g->out_adj).ptr,
+                                        side ? ipos : opos, st));
+    }
+    LAUNCH_TRY(mg::launch_ranks<TT>(dev_graph<TT>(g), opos, ipos, (uint4 *)g->gx.ptr, st));
     HIP_TRY(hipStreamSynchronize(st));
     return MG_OK;
 }
@@ -1289,58 +1317,77 @@ int mg_graph_create(const int32_t *src, const int32_t *dst, const int64_t *t, in
             return fail(MG_EINVAL, "unknown flags");
         if ((flags & MG_DEVICE_INPUT) && (flags & MG_HOST_ONLY))
             return fail(MG_EINVAL, "MG_DEVICE_INPUT and MG_HOST_ONLY exclude each other");
-        std::vector<int32_t> hs, hd;
-        std::vector<int64_t> ht;
-        if ((flags & MG_DEVICE_INPUT) && n_edges > 0) {
-            // device arrays: brought to the host, where the adjacency is built
-            hs.resize(n_edges);
-            hd.resize(n_edges);
-            ht.resize(n_edges);
-            hipStream_t st = (hipStream_t)stream;
-            HIP_TRY(hipMemcpyAsync(hs.data(), src, 4 * (size_t)n_edges, hipMemcpyDeviceToHost, st));
-            HIP_TRY(hipMemcpyAsync(hd.data(), dst, 4 * (size_t)n_edges, hipMemcpyDeviceToHost, st));
-            HIP_TRY(hipMemcpyAsync(ht.data(), t, 8 * (size_t)n_edges, hipMemcpyDeviceToHost, st));
-            HIP_TRY(hipStreamSynchronize(st));
-            src = hs.data();
-            dst = hd.data();
-            t = ht.data();
-        }
-        for (int64_t i = 0; i < n_edges; ++i)
-            if (src[i] < 0 || src[i] >= n_nodes || dst[i] < 0 || dst[i] >= n_nodes)
-                return fail(MG_EINVAL, "edge %lld has a vertex outside [0, %d)", (long long)i,
-                            n_nodes);
+        hipStream_t st = (hipStream_t)stream;
+        const bool on_device = (flags & MG_DEVICE_INPUT) && n_edges > 0;
+        // what the arrays hold: the first bad edge, order, self-loops, times
+        int64_t bad = -1, loops = 0, t_min = 0, t_max = 0;
         bool sorted = true;
-        for (int64_t i = 1; i < n_edges; ++i)
-            if (t[i] < t[i - 1]) { sorted = false; break; }
+        if (on_device) {
+            DevBuf d_f;
+            struct G { DevBuf *b; ~G() { dev_free(*b); } } guard{&d_f};
+            int rc = dev_alloc(d_f, sizeof(mg::EdgeFacts), stream);
+            if (rc) return rc;
+            LAUNCH_TRY(mg::launch_edge_facts(src, dst, t, (uint32_t)n_edges, n_nodes,
+                                             (mg::EdgeFacts *)d_f.ptr, st));
+            mg::EdgeFacts f;
+            HIP_TRY(hipMemcpyAsync(&f, d_f.ptr, sizeof f, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+            bad = f.first_bad == ~0ull ? -1 : (int64_t)f.first_bad;
+            sorted = f.unsorted == 0;
+            loops = (int64_t)f.loops;
+            t_min = mg::unbias_time(f.t_min);
+            t_max = mg::unbias_time(f.t_max);
+        } else if (n_edges > 0) {
+            std::mutex mu;
+            t_min = t_max = t[0];
+            parallel_for(n_edges, [&](int64_t i0, int64_t i1) {
+                int64_t b = -1, l = 0, lo = t[i0 < n_edges ? i0 : 0], hi = lo;
+                bool so = true;
+                for (int64_t i = i0; i < i1; ++i) {
+                    if (b < 0 && (src[i] < 0 || src[i] >= n_nodes || dst[i] < 0 || dst[i] >= n_nodes))
+                        b = i;
+                    l += src[i] == dst[i];
+                    so = so && (i == 0 || t[i] >= t[i - 1]);
+                    lo = std::min(lo, t[i]);
+                    hi = std::max(hi, t[i]);
+                }
+                std::lock_guard<std::mutex> lock(mu);
+                if (b >= 0 && (bad < 0 || b < bad)) bad = b;
+                loops += l;
+                sorted = sorted && so;
+                if (i1 > i0) { t_min = std::min(t_min, lo); t_max = std::max(t_max, hi); }
+            });
+        }
+        if (bad >= 0)
+            return fail(MG_EINVAL, "edge %lld has a vertex outside [0, %d)", (long long)bad, n_nodes);
         if ((flags & MG_SORTED_BY_T) && !sorted)
             return fail(MG_EINVAL, "MG_SORTED_BY_T given but t is not non-decreasing");
+        if ((uint64_t)t_max - (uint64_t)t_min >= 1ull << 63)
+            return fail(MG_EUNSUPPORTED, "time span >= 2^63");
         std::unique_ptr<mg_graph> g(new (std::nothrow) mg_graph);
         if (!g) return fail(MG_ENOMEM, "out of host memory");
         g->E = n_edges;
         g->V = n_nodes;
-        std::vector<int32_t> s(n_edges), d(n_edges);
-        std::vector<int64_t> tt(n_edges);
-        if (sorted) {
-            std::copy(src, src + n_edges, s.begin());
-            std::copy(dst, dst + n_edges, d.begin());
-            std::copy(t, t + n_edges, tt.begin());
-        } else {
-            std::vector<int64_t> ord(n_edges);
-            std::iota(ord.begin(), ord.end(), 0);
-            std::stable_sort(ord.begin(), ord.end(),
-                             [&](int64_t a, int64_t b) { return t[a] < t[b]; });
-            for (int64_t i = 0; i < n_edges; ++i) {
-                s[i] = src[ord[i]]; d[i] = dst[ord[i]]; tt[i] = t[ord[i]];
-            }
-            g->input_index = std::move(ord);
-        }
-        for (int64_t i = 0; i < n_edges; ++i) g->self_loops += (s[i] == d[i]);
-        g->t_min = n_edges ? tt[0] : 0;
-        g->t_max = n_edges ? tt[n_edges - 1] : 0;
-        if (n_edges && g->t_max - g->t_min < 0) return fail(MG_EUNSUPPORTED, "time span >= 2^63");
-        const uint64_t span = n_edges ? (uint64_t)(g->t_max - g->t_min) : 0;
-        g->time_bytes = span < 0xffffffffull ? 4 : 8;
+        g->self_loops = loops;
+        g->t_min = t_min;
+        g->t_max = t_max;
+        g->time_bytes = (uint64_t)t_max - (uint64_t)t_min < 0xffffffffull ? 4 : 8;
         if (flags & MG_HOST_ONLY) {
+            std::vector<int32_t> s(n_edges), d(n_edges);
+            std::vector<int64_t> tt(n_edges);
+            if (sorted) {
+                std::copy(src, src + n_edges, s.begin());
+                std::copy(dst, dst + n_edges, d.begin());
+                std::copy(t, t + n_edges, tt.begin());
+            } else {
+                std::vector<int64_t> ord(n_edges);
+                std::iota(ord.begin(), ord.end(), 0);
+                std::stable_sort(ord.begin(), ord.end(),
+                                 [&](int64_t a, int64_t b) { return t[a] < t[b]; });
+                for (int64_t i = 0; i < n_edges; ++i) {
+                    s[i] = src[ord[i]]; d[i] = dst[ord[i]]; tt[i] = t[ord[i]];
+                }
+            }
             g->host_only = true;
             g->device = -1;
             build_host(g.get(), std::move(s), std::move(d), std::move(tt));
@@ -1348,9 +1395,23 @@ int mg_graph_create(const int32_t *src, const int32_t *dst, const int64_t *t, in
             return MG_OK;
         }
         HIP_TRY(hipGetDevice(&g->device));
-        hipStream_t st = (hipStream_t)stream;
-        int rc = g->time_bytes == 4 ? upload_graph<uint32_t>(g.get(), s, d, tt, st)
-                                    : upload_graph<uint64_t>(g.get(), s, d, tt, st);
+        Scratch in;   // the input on the device
+        if (!on_device && n_edges > 0) {
+            int32_t *ds, *dd;
+            int64_t *dt;
+            int rc = in.get(&ds, (size_t)n_edges, st);
+            if (!rc) rc = in.get(&dd, (size_t)n_edges, st);
+            if (!rc) rc = in.get(&dt, (size_t)n_edges, st);
+            if (rc) return rc;
+            HIP_TRY(hipMemcpyAsync(ds, src, 4 * (size_t)n_edges, hipMemcpyHostToDevice, st));
+            HIP_TRY(hipMemcpyAsync(dd, dst, 4 * (size_t)n_edges, hipMemcpyHostToDevice, st));
+            HIP_TRY(hipMemcpyAsync(dt, t, 8 * (size_t)n_edges, hipMemcpyHostToDevice, st));
+            src = ds;
+            dst = dd;
+            t = dt;
+        }
+        int rc = g->time_bytes == 4 ? ingest_graph<uint32_t>(g.get(), src, dst, t, sorted, st)
+                                    : ingest_graph<uint64_t>(g.get(), src, dst, t, sorted, st);
         if (rc) return rc;
         *out = g.release();
         return MG_OK;
@@ -1426,31 +1487,45 @@ int mg_enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match 
         if (tr->deltas.size() != 1)
             return fail(MG_EUNSUPPORTED, "enumeration takes a tree with one window");
         static_assert(sizeof(mg_match) == 4 * (1 + mg::kKMax), "record layout");
-        // the count sizes the output
-        mg_count_opts o;
-        mg_count_opts_init(&o);
-        o.stream = stream;
-        std::vector<uint64_t> cnt(tr->n_motifs);
-        int rc = mg_count(g, tr, &o, cnt.data());
-        if (rc) return rc;
         std::vector<int32_t> first(tr->distinct.size(), -1);   // first caller motif per distinct one
         for (int32_t m = 0; m < tr->n_motifs; ++m)
             if (first[tr->motif_q[m]] < 0) first[tr->motif_q[m]] = m;
-        uint64_t total = 0;
-        for (size_t q = 0; q < first.size(); ++q) total += cnt[first[q]];
-        if (!out || (uint64_t)capacity < total) {
-            *n_matches = (int64_t)total;
-            return MG_OK;
+        mg_count_opts o;
+        mg_count_opts_init(&o);
+        o.stream = stream;
+        // The count sizes the output, unless the caller's own capacity is small
+        // enough to be taken as it is: then the search writes into that much
+        // and says how many matches there are.
+        constexpr uint64_t kDirectBytes = 256u << 20;
+        const bool direct = out && capacity > 0 && (uint64_t)capacity * sizeof(mg_match) <= kDirectBytes;
+        uint64_t room = direct ? (uint64_t)capacity : 0, total = 0;
+        if (!direct) {
+            std::vector<uint64_t> cnt(tr->n_motifs);
+            int rc = mg_count(g, tr, &o, cnt.data());
+            if (rc) return rc;
+            for (size_t q = 0; q < first.size(); ++q) total += cnt[first[q]];
+            if (!out || (uint64_t)capacity < total) {
+                *n_matches = (int64_t)total;
+                return MG_OK;
+            }
+            room = total;
+        } else {
+            int dev = 0;
+            HIP_TRY(hipGetDevice(&dev));
+            if (dev != g->device)
+                return fail(MG_EINVAL, "graph lives on device %d, current is %d", g->device, dev);
+            int rc = upload_tree(tr, dev, (hipStream_t)stream);
+            if (rc) return rc;
         }
         hipStream_t st = (hipStream_t)stream;
         DevBuf d_work, d_rec;
         struct G { DevBuf *a, *b; ~G() { dev_free(*a); dev_free(*b); } } guard{&d_work, &d_rec};
-        const size_t cnt_off = kQueueBytes, cur_off = cnt_off + 8 * n_slots(tr);
-        rc = dev_alloc(d_work, cur_off + 8, (void *)st);
-        if (!rc) rc = dev_alloc(d_rec, sizeof(mg_match) * std::max<uint64_t>(total, 1), (void *)st);
+        const size_t cnt_off = kQueueBytes, cur_off = cnt_off + 8 * n_slots(tr), first_off = cur_off + 8;
+        int rc = dev_alloc(d_work, first_off + 4 * first.size(), (void *)st);
+        if (!rc) rc = dev_alloc(d_rec, sizeof(mg_match) * std::max<uint64_t>(room, 1), (void *)st);
         if (rc) return rc;
-        HIP_TRY(hipMemsetAsync(d_work.ptr, 0, cur_off + 8, st));
         unsigned long long *w = (unsigned long long *)d_work.ptr;
+        HIP_TRY(mg::launch_fill_u64(w, (uint32_t)(first_off / 8), 0ull, st));
         o.leaf_scan = -1;   // every match goes through the candidate expansion
         hipError_t e = hipSuccess;
         if (g->E > 0) {
@@ -1459,33 +1534,35 @@ int mg_enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match 
                 fill_params<uint32_t>(p, g, tr, o, w, w + cnt_off / 8, nullptr, nullptr);
                 p.enum_out = (int32_t *)d_rec.ptr;
                 p.enum_cursor = w + cur_off / 8;
-                p.enum_cap = total;
+                p.enum_cap = room;
                 e = mg::launch_comine<uint32_t>(p, 0, st);
             } else {
                 mg::KParams<uint64_t> p{};
                 fill_params<uint64_t>(p, g, tr, o, w, w + cnt_off / 8, nullptr, nullptr);
                 p.enum_out = (int32_t *)d_rec.ptr;
                 p.enum_cursor = w + cur_off / 8;
-                p.enum_cap = total;
+                p.enum_cap = room;
                 e = mg::launch_comine<uint64_t>(p, 0, st);
             }
         }
         if (e != hipSuccess) return fail(MG_EDEVICE, "enumeration launch failed: %s", hipGetErrorString(e));
         uint64_t written = 0;
         HIP_TRY(hipMemcpyAsync(&written, w + cur_off / 8, 8, hipMemcpyDeviceToHost, st));
-        if (total) HIP_TRY(hipMemcpyAsync(out, d_rec.ptr, sizeof(mg_match) * total, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
+        if (direct) total = written;
         if (written != total)
             return fail(MG_EINTERNAL, "enumeration wrote %llu matches, the count is %llu",
                         (unsigned long long)written, (unsigned long long)total);
-        // motifs in the caller's numbering (a duplicate's first occurrence),
-        // edges in the caller's input order
-        for (uint64_t i = 0; i < total; ++i) {
-            mg_match &m = out[i];
-            m.motif = first[m.motif];
-            if (!g->input_index.empty())
-                for (int j = 0; j < mg::kKMax && m.edges[j] >= 0; ++j)
-                    m.edges[j] = (int32_t)g->input_index[m.edges[j]];
+        if (total && total <= room) {
+            // motifs in the caller's numbering (a duplicate's first occurrence),
+            // edges in the caller's input order
+            HIP_TRY(hipMemcpyAsync((char *)d_work.ptr + first_off, first.data(), 4 * first.size(),
+                                   hipMemcpyHostToDevice, st));
+            HIP_TRY(mg::launch_map_matches((int32_t *)d_rec.ptr, total,
+                                           (const int32_t *)((char *)d_work.ptr + first_off),
+                                           (const uint32_t *)g->order.ptr, st));
+            HIP_TRY(hipMemcpyAsync(out, d_rec.ptr, sizeof(mg_match) * total, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
         }
         *n_matches = (int64_t)total;
         return MG_OK;
