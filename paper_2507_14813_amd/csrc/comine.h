@@ -33,28 +33,42 @@ __host__ __device__ inline uint32_t queue_end(uint32_t n_roots, uint32_t n_queue
 }
 constexpr uint32_t kLeafScanDefault = 256;   // lane-counted leaf window limit
 
-// fields of an internal-node word (see below)
-__host__ __device__ inline uint32_t node_groups(uint32_t w) { return (w >> 20) & 31u; }
-__host__ __device__ inline uint32_t node_near(uint32_t w) { return (w >> 25) & 31u; }
+// A partial match's live word: bits 2 s + dir (s < 6: motif vertex, dir as
+// below) are clear when the list of that vertex is known to hold no entry
+// after the partial match and within its window; kLiveAll stands for the whole
+// edge list and is always set; bits kLivePair + 2 j and + 1 are clear when no
+// later edge within the window repeats matched edge j or runs against it; the
+// root's slot in the level-1 batch sits above.
+constexpr uint32_t kLiveAllBit = 12, kLivePair = 13, kLiveSlot = 21;
+constexpr uint32_t kLiveLists = (1u << 13) - 1u;
 constexpr uint32_t kLeafParent = 1u << 30;
-static_assert(2 * kVMax + 1 < 32, "groups of a node fit 5 bits");
 
 // group direction: which adjacency list holds the candidates
 enum : int { kDirOut = 0, kDirIn = 1, kDirAll = 2 };
 
 // Search tables, as uploaded to the device.
-//   inode[i]  internal (non-leaf) trie node i: first group | group count << 20
-//             | count of the leading groups on a list of motif vertex 0 or 1 << 25
-//             | leaf_parent << 30 (every child a leaf reached through a list
-//             of a bound vertex: all groups leaf_only)
-//   grp[2g], grp[2g+1]: eight words of group g:
-//     w0 = dir | anchor << 4 | nv << 8 | leaf_only << 12 | last_end << 13
+//   inode[i]  internal (non-leaf) trie node i:
+//     x = first group | leaf_parent << 30 (every child a leaf reached through
+//         a list of a bound vertex: all groups leaf_only)
+//     y = its lists, as live-word bits (2 anchor + dir, kLiveAllBit): one group
+//         per bit, in bit order
+//     z = the live-word bits of which at least one has to be set for anything
+//         to be found below the node when leaf windows are counted from pairs:
+//         the lists of its other groups and the pairs of those that are
+//   grp[3g..3g+2]: twelve words of group g:
+//     w0 = dir | anchor << 4 | nv << 8 | leaf_only << 12 | last_end << 13 |
+//          bound_by << 15
 //          (nv: vertices bound at the owning node; leaf_only: a per-vertex
 //          list whose children all end a motif; last_end: the anchor is the
 //          source (1) or destination (2) of the owning node's last edge, 0
-//          otherwise)
+//          otherwise; bound_by: the same for the node's second edge)
 //     w1..w6 = child reached when the scanned endpoint is bound motif vertex 0..5
 //     w7 = child reached when the scanned endpoint(s) are new vertices
+//     w8 = pair codes, four bits per bound motif vertex y whose entries are
+//          counted: 1 + 2 j + r when matched edge j is the latest one that
+//          joins the anchor and y, in this list's direction (r 0) or against
+//          it (r 1); 0 = not counted.  0 as a whole when some counted vertex
+//          has no such edge: the window has to be scanned
 //   A child word is 0 when there is no such child, else
 //     internal index (bits 0-15, if internal) | (query + 1) << 16 | internal << 31.
 // Counters: n_d per distinct motif, counter q * n_d + j holding the matches
@@ -62,7 +76,7 @@ enum : int { kDirOut = 0, kDirIn = 1, kDirAll = 2 };
 // window j - 1 (windows ascending); the count at window j is the sum of
 // slots 0..j.
 struct DevTree {
-    const uint32_t *inode;
+    const uint4 *inode;
     const uint4 *grp;
     int32_t n_q;        // distinct motifs
     int32_t root_q;     // query id of the one-edge prefix, -1 if none
@@ -82,6 +96,11 @@ template <typename TT> struct Entry;
 template <> struct Entry<uint32_t> { int32_t v; uint32_t t; };
 template <> struct Entry<uint64_t> { int32_t v; int32_t pad; uint64_t t; };
 
+// Four times, each that of the next entry of some list, kNever when it has
+// none (past every edge time).
+template <typename TT> struct alignas(16) Next4 { TT a, b, c, d; };
+template <typename TT> constexpr TT kNever = (TT)~(TT)0;
+
 template <typename TT>
 struct DevGraph {
     const int32_t *gsrc, *gdst;   // time-sorted edge list (all edges)
@@ -89,6 +108,16 @@ struct DevGraph {
     const uint4 *gx;              // per edge u -> v at t: the first index with a later
                                   // time in out(u), in(u), out(v), in(v) (self-loops:
                                   // unused)
+    const Next4<TT> *gn;          // the times of those entries
+    // Pairs: the edges ordered by (destination, source, time), so that the
+    // edges u -> v are consecutive and ascending in time
+    const TT *pair_t;             // their times
+    const uint4 *gp;              // per edge u -> v at t: the first pair entry with a
+                                  // later time and the end of the pair u -> v, then of
+                                  // v -> u (self-loops: 0)
+    const Next4<TT> *out_next;    // per out_adj entry u -> v: the next times of u -> v,
+    const Next4<TT> *in_next;     // v -> u, out(v), in(v); per in_adj entry: of u -> v,
+                                  // v -> u, out(u), in(u)
     const uint32_t *out_eid;      // edge id of every out_adj entry
     const uint32_t *in_eid;       // edge id of every in_adj entry
     const uint32_t *out_off;      // V+1
@@ -99,15 +128,15 @@ struct DevGraph {
 };
 
 // A piece of search left over when an epoch ends: the candidates of one
-// root-level window, entries [e0, e1) of the list of group g of the root
-// a -> b at time t_lo | t_hi << 32, with the root's windows in out(a), in(a),
+// root-level window, entries [e0, e1) of the list of group g of the root (edge
+// id `root`) a -> b at time t_lo | t_hi << 32, with the root's windows in out(a), in(a),
 // out(b), in(b) as far as it had found them (first entry and length, as the
 // per-wave root windows keep them).  The root itself was credited when it was
 // started.
 struct EpochCtx {
     int32_t a, b;
     uint32_t t_lo, t_hi;
-    uint32_t g, e0, e1, pad;
+    uint32_t g, e0, e1, root;
     uint32_t hlo[4];
     uint16_t hlen[4];
     uint32_t pad2[2];

@@ -58,7 +58,8 @@ struct mg_graph {
     int time_bytes = 4;
     int device = 0;
     bool host_only = false;             // no device copy (MG_HOST_ONLY)
-    mgh::DevBuf gsrc, gdst, gt, gx, out_eid, in_eid, out_off, out_adj, in_off, in_adj;
+    mgh::DevBuf gsrc, gdst, gt, gx, gn, gp, pair_t, out_next, in_next, out_eid, in_eid, out_off,
+        out_adj, in_off, in_adj;
     mgh::DevBuf order;                  // u32 per edge: the caller's index (none: the same)
     int64_t device_bytes = 0;
     std::unique_ptr<mgh::HostAdj> host;   // for the CPU backend, built on first use
@@ -74,8 +75,8 @@ struct mg_tree {
     std::vector<int32_t> motif_q;       // caller motif -> distinct id
     std::vector<mgh::Motif> distinct;
     std::vector<mgh::TrieNode> nodes;   // node 0 = prefix ((0,1))
-    std::vector<int32_t> node_tab;      // one word per internal node
-    std::vector<int32_t> grp_tab;       // 8 words per group
+    std::vector<int32_t> node_tab;      // 4 words per internal node
+    std::vector<int32_t> grp_tab;       // 12 words per group
     int32_t depth = 0, root_q = -1;
     int32_t kdepth = 0;    // depth of the kernel that searches it (DevTree::kdepth)
     mg_tree_info_t info{};

@@ -98,8 +98,8 @@ void dev_free(DevBuf &b) {
 using namespace mgh;
 
 mg_graph::~mg_graph() {
-    for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &out_eid, &in_eid, &out_off, &out_adj, &in_off,
-                      &in_adj, &order})
+    for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &gn, &gp, &pair_t, &out_next, &in_next, &out_eid,
+                      &in_eid, &out_off, &out_adj, &in_off, &in_adj, &order})
         dev_free(*b);
 }
 
@@ -158,6 +158,10 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
     const Need needs[] = {
         {&g->gsrc, sizeof(int32_t) * (size_t)E}, {&g->gdst, sizeof(int32_t) * (size_t)E},
         {&g->gt, sizeof(TT) * (size_t)E},        {&g->gx, sizeof(uint32_t) * 4 * (size_t)E},
+        {&g->gn, sizeof(mg::Next4<TT>) * (size_t)E}, {&g->gp, sizeof(uint32_t) * 4 * (size_t)E},
+        {&g->pair_t, sizeof(TT) * (size_t)A},
+        {&g->out_next, sizeof(mg::Next4<TT>) * (size_t)A},
+        {&g->in_next, sizeof(mg::Next4<TT>) * (size_t)A},
         {&g->out_eid, sizeof(uint32_t) * (size_t)A}, {&g->in_eid, sizeof(uint32_t) * (size_t)A},
         {&g->out_off, sizeof(uint32_t) * ((size_t)V + 1)},
         {&g->out_adj, sizeof(mg::Entry<TT>) * (size_t)A},
@@ -213,7 +217,22 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
                                         (mg::Entry<TT> *)(side ? g->in_adj : g->out_adj).ptr,
                                         side ? ipos : opos, st));
     }
-    LAUNCH_TRY(mg::launch_ranks<TT>(dev_graph<TT>(g), opos, ipos, (uint4 *)g->gx.ptr, st));
+    const mg::DevGraph<TT> dg = dev_graph<TT>(g);
+    LAUNCH_TRY(mg::launch_ranks<TT>(dg, opos, ipos, (uint4 *)g->gx.ptr, (mg::Next4<TT> *)g->gn.ptr, st));
+    // pair order: the out-lists' order (source, time) sorted by destination.
+    // Self-loops are in no pair: their records are zero.
+    if (g->self_loops) HIP_TRY(hipMemsetAsync(g->gp.ptr, 0, 16 * (size_t)E, st));
+    if (A) {
+        uint32_t *pv[2] = {v[0], v[1]}, *pk[2] = {key[0], key[1]};
+        HIP_TRY(hipMemcpyAsync(pv[0], g->out_eid.ptr, sizeof(uint32_t) * (size_t)A,
+                               hipMemcpyDeviceToDevice, st));
+        LAUNCH_TRY(mg::launch_gather(pv[0], gdst, A, pk[0], st));
+        LAUNCH_TRY(mg::sort_pairs<uint32_t>(pk, pv, false, A, vb, sort_mem, &at, st));
+        LAUNCH_TRY(mg::launch_pairs<TT>(dg, pv[at], A, opos, ipos, (int32_t *)ikey,
+                                        (TT *)g->pair_t.ptr, (uint4 *)g->gp.ptr,
+                                        (mg::Next4<TT> *)g->out_next.ptr,
+                                        (mg::Next4<TT> *)g->in_next.ptr, st));
+    }
     HIP_TRY(hipStreamSynchronize(st));
     return MG_OK;
 }
@@ -294,7 +313,7 @@ int build_tree(mg_tree *tr) {
         if (iidx[c] >= 0) w |= (uint32_t)iidx[c] | 0x80000000u;
         return (int32_t)w;
     };
-    tr->node_tab.assign(n_int > 0 ? n_int : 1, 0);
+    tr->node_tab.assign(4 * (size_t)std::max(n_int, 1), 0);
     tr->grp_tab.clear();
     tr->depth = 0;
     bool wide2 = false;   // an internal two-edge prefix on four vertices
@@ -303,51 +322,79 @@ int build_tree(mg_tree *tr) {
         tr->depth = std::max(tr->depth, nd.depth);
         if (nd.depth == 2 && nd.nv > 3 && !nd.kids.empty()) wide2 = true;
         if (nd.kids.empty()) continue;
-        // group the children by the list they scan
-        std::map<std::pair<int, int>, std::vector<int>> groups;
+        // the matched edges of the prefix, first edge first
+        std::vector<std::pair<int, int>> path;
+        for (int c = n; c >= 0; c = tr->nodes[c].parent)
+            path.insert(path.begin(), {tr->nodes[c].u, tr->nodes[c].v});
+        // group the children by the list they scan, in live-word bit order
+        std::map<int, std::vector<int>> groups;
         for (int c : nd.kids) {
             const TrieNode &ch = tr->nodes[c];
-            int dir, anc;
-            if (ch.u < nd.nv) { dir = mg::kDirOut; anc = ch.u; }
-            else if (ch.v < nd.nv) { dir = mg::kDirIn; anc = ch.v; }
-            else { dir = mg::kDirAll; anc = 0; }
-            groups[{dir, anc}].push_back(c);
+            const int bit = ch.u < nd.nv   ? 2 * ch.u + mg::kDirOut
+                            : ch.v < nd.nv ? 2 * ch.v + mg::kDirIn
+                                           : (int)mg::kLiveAllBit;
+            groups[bit].push_back(c);
         }
-        const int g0 = (int)tr->grp_tab.size() / 8;
+        const int g0 = (int)tr->grp_tab.size() / 12;
         if (g0 + (int)groups.size() > (1 << 20))
             return fail(MG_EUNSUPPORTED, "too many child groups");
-        // groups on a list of motif vertex 0 or 1 first: below the first
-        // level the search finds their windows inside the root's windows
-        std::vector<std::pair<std::pair<int, int>, std::vector<int>>> ordered;
-        for (int cls = 0; cls < 2; ++cls)
-            for (auto &kv : groups) {
-                const bool near = kv.first.first != mg::kDirAll && kv.first.second < 2;
-                if (near == (cls == 0)) ordered.push_back(kv);
-            }
-        int n_near = 0;
-        for (auto &kv : ordered)
-            n_near += (kv.first.first != mg::kDirAll && kv.first.second < 2) ? 1 : 0;
-        for (auto &kv : ordered) {
-            bool leaf_only = kv.first.first != mg::kDirAll;
+        uint32_t lists = 0, gate = 0;
+        for (auto &kv : groups) {
+            const bool all = kv.first == (int)mg::kLiveAllBit;
+            const int dir = all ? mg::kDirAll : kv.first & 1, anc = all ? 0 : kv.first >> 1;
+            bool leaf_only = !all;
             for (int c : kv.second) leaf_only = leaf_only && tr->nodes[c].kids.empty();
             // the anchor is the source (1) or destination (2) of the node's
             // own last edge: the window then starts where that edge's time
-            // ends in the anchor's list, known per edge
-            const int anc = kv.first.second;
-            const int last_end = kv.first.first == mg::kDirAll ? 0
-                                 : anc == nd.u ? 1 : anc == nd.v ? 2 : 0;
-            int32_t rec[8] = {kv.first.first | (anc << 4) | (nd.nv << 8) |
-                                  ((leaf_only ? 1 : 0) << 12) | (last_end << 13),
-                              0, 0, 0, 0, 0, 0, 0};
+            // ends in the anchor's list, known per edge; likewise, no earlier
+            // than there, for its second edge
+            auto end_of = [&](size_t j) {
+                return all || j >= path.size() || j == 0 ? 0
+                       : anc == path[j].first            ? 1
+                       : anc == path[j].second           ? 2
+                                                         : 0;
+            };
+            const int last_end = all ? 0 : anc == nd.u ? 1 : anc == nd.v ? 2 : 0;
+            int32_t rec[12] = {dir | (anc << 4) | (nd.nv << 8) | ((leaf_only ? 1 : 0) << 12) |
+                                   (last_end << 13) | (end_of(1) << 15)};
+            bool counted[kVMax] = {};
             for (int c : kv.second) {
                 const TrieNode &ch = tr->nodes[c];
                 // out-group: the scanned endpoint is the destination; a bound
                 // destination selects word 1+v, a new one word 7.  In- and
                 // whole-list groups only ever reach new vertices (word 7).
-                if (kv.first.first == mg::kDirOut && ch.v < nd.nv) rec[1 + ch.v] = child_word(c);
-                else rec[7] = child_word(c);
+                if (dir == mg::kDirOut && ch.v < nd.nv) {
+                    rec[1 + ch.v] = child_word(c);
+                    counted[ch.v] = true;
+                } else {
+                    rec[7] = child_word(c);
+                }
             }
-            tr->grp_tab.insert(tr->grp_tab.end(), rec, rec + 8);
+            // a leaf window's count is known from the pairs of its anchor with
+            // the counted vertices (with a new-vertex child, all bound ones)
+            // when each is joined to the anchor by a matched edge
+            uint32_t codes = 0, pair_bits = 0;
+            bool known = leaf_only;
+            for (int y = 0; y < nd.nv && known; ++y) {
+                if (y == anc || !(counted[y] || rec[7])) continue;
+                int code = 0;
+                for (size_t j = 0; j < path.size(); ++j) {
+                    // the list's entries run from the anchor (out) or to it (in)
+                    const std::pair<int, int> with =
+                        dir == mg::kDirOut ? std::make_pair(anc, y) : std::make_pair(y, anc);
+                    if (path[j] == with) code = 1 + 2 * (int)j;
+                    else if (path[j].first == with.second && path[j].second == with.first)
+                        code = 2 + 2 * (int)j;
+                }
+                known = code != 0;
+                codes |= (uint32_t)code << (4 * y);
+                if (code) pair_bits |= 1u << (mg::kLivePair + (uint32_t)code - 1);
+            }
+            if (!known) codes = 0;
+            rec[8] = (int32_t)codes;
+            lists |= 1u << kv.first;
+            gate |= codes && !rec[7] ? pair_bits : 1u << kv.first;
+            tr->grp_tab.insert(tr->grp_tab.end(), rec, rec + 12);
         }
         // a leaf parent: every match below it is one more edge on a list of
         // a bound vertex
@@ -356,11 +403,12 @@ int build_tree(mg_tree *tr) {
             const TrieNode &ch = tr->nodes[c];
             leaf_parent = leaf_parent && ch.kids.empty() && (ch.u < nd.nv || ch.v < nd.nv);
         }
-        tr->node_tab[iidx[n]] = (int32_t)((uint32_t)g0 | ((uint32_t)groups.size() << 20) |
-                                          ((uint32_t)n_near << 25) |
-                                          (leaf_parent ? mg::kLeafParent : 0u));
+        int32_t *w = &tr->node_tab[4 * (size_t)iidx[n]];
+        w[0] = (int32_t)((uint32_t)g0 | (leaf_parent ? mg::kLeafParent : 0u));
+        w[1] = (int32_t)lists;
+        w[2] = (int32_t)(leaf_parent ? gate : lists);
     }
-    if (tr->grp_tab.empty()) tr->grp_tab.assign(8, 0);
+    if (tr->grp_tab.empty()) tr->grp_tab.assign(12, 0);
     tr->root_q = tr->nodes[0].q;
     tr->kdepth = (tr->depth == 3 && wide2) ? 4 : tr->depth;
 
@@ -654,6 +702,11 @@ mg::DevGraph<TT> dev_graph(const mg_graph *g) {
     d.gdst = (const int32_t *)g->gdst.ptr;
     d.gt = (const TT *)g->gt.ptr;
     d.gx = (const uint4 *)g->gx.ptr;
+    d.gn = (const mg::Next4<TT> *)g->gn.ptr;
+    d.gp = (const uint4 *)g->gp.ptr;
+    d.pair_t = (const TT *)g->pair_t.ptr;
+    d.out_next = (const mg::Next4<TT> *)g->out_next.ptr;
+    d.in_next = (const mg::Next4<TT> *)g->in_next.ptr;
     d.out_eid = (const uint32_t *)g->out_eid.ptr;
     d.in_eid = (const uint32_t *)g->in_eid.ptr;
     d.out_off = (const uint32_t *)g->out_off.ptr;
@@ -666,7 +719,7 @@ mg::DevGraph<TT> dev_graph(const mg_graph *g) {
 
 mg::DevTree dev_tree(const mg_tree *tr) {
     mg::DevTree t{};
-    t.inode = (const uint32_t *)tr->d_node.ptr;
+    t.inode = (const uint4 *)tr->d_node.ptr;
     t.grp = (const uint4 *)tr->d_grp.ptr;
     t.n_q = (int32_t)tr->distinct.size();
     t.root_q = tr->root_q;

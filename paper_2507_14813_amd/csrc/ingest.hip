@@ -299,20 +299,84 @@ list_entries(const uint32_t *eid, uint32_t n_adj, const int32_t *other, const TT
 // out(v) by bisection.
 template <typename TT>
 __global__ void __launch_bounds__(kIB)
-list_ranks(const DevGraph<TT> g, const uint32_t *opos, const uint32_t *ipos, uint4 *gx) {
+list_ranks(const DevGraph<TT> g, const uint32_t *opos, const uint32_t *ipos, uint4 *gx,
+           Next4<TT> *gn) {
     const TT *ot = times_of(g.out_adj), *it = times_of(g.in_adj);
     for (uint64_t e = blockIdx.x * (uint64_t)kIB + threadIdx.x; e < g.n_edges;
          e += gridDim.x * (uint64_t)kIB) {
         const int32_t u = g.gsrc[e], v = g.gdst[e];
         uint4 x = make_uint4(0, 0, 0, 0);
+        Next4<TT> n{kNever<TT>, kNever<TT>, kNever<TT>, kNever<TT>};
         if (u != v) {
             const TT t = g.gt[e];
-            x.x = gallop_greater(ot, 1, opos[e] + 1, g.out_off[u + 1], t);
-            x.y = first_greater(it, 1, g.in_off[u], g.in_off[u + 1], t);
-            x.z = first_greater(ot, 1, g.out_off[v], g.out_off[v + 1], t);
-            x.w = gallop_greater(it, 1, ipos[e] + 1, g.in_off[v + 1], t);
+            const uint32_t eu = g.out_off[u + 1], iu = g.in_off[u + 1];
+            const uint32_t ev = g.out_off[v + 1], iv = g.in_off[v + 1];
+            x.x = gallop_greater(ot, 1, opos[e] + 1, eu, t);
+            x.y = first_greater(it, 1, g.in_off[u], iu, t);
+            x.z = first_greater(ot, 1, g.out_off[v], ev, t);
+            x.w = gallop_greater(it, 1, ipos[e] + 1, iv, t);
+            if (x.x < eu) n.a = ot[2 * (size_t)x.x];
+            if (x.y < iu) n.b = it[2 * (size_t)x.y];
+            if (x.z < ev) n.c = ot[2 * (size_t)x.z];
+            if (x.w < iv) n.d = it[2 * (size_t)x.w];
         }
         gx[e] = x;
+        gn[e] = n;
+    }
+}
+
+__global__ void __launch_bounds__(kIB)
+gather_keys(const uint32_t *eid, const int32_t *key_of, uint32_t n, uint32_t *keys) {
+    for (uint64_t j = blockIdx.x * (uint64_t)kIB + threadIdx.x; j < n; j += gridDim.x * (uint64_t)kIB)
+        keys[j] = (uint32_t)key_of[eid[j]];
+}
+
+template <typename TT>
+__global__ void __launch_bounds__(kIB)
+pair_entries(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, int32_t *psrc, TT *pair_t) {
+    for (uint64_t j = blockIdx.x * (uint64_t)kIB + threadIdx.x; j < n_adj;
+         j += gridDim.x * (uint64_t)kIB) {
+        const uint32_t e = pe[j];
+        psrc[j] = g.gsrc[e];
+        pair_t[j] = g.gt[e];
+    }
+}
+
+// Entry j of the pair order is edge u -> v at t.  The edges into v are the
+// entries [in_off[v], in_off[v + 1]) and ascend in source, so the pair's end
+// is found by galloping from j, and the pair v -> u by bisection among the
+// edges into u.
+template <typename TT>
+__global__ void __launch_bounds__(kIB)
+pair_links(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, const uint32_t *opos,
+           const uint32_t *ipos, const int32_t *psrc, const TT *pair_t, uint4 *gp,
+           Next4<TT> *out_next, Next4<TT> *in_next) {
+    for (uint64_t j = blockIdx.x * (uint64_t)kIB + threadIdx.x; j < n_adj;
+         j += gridDim.x * (uint64_t)kIB) {
+        const uint32_t e = pe[j];
+        const int32_t u = psrc[j], v = g.gdst[e];
+        const TT t = pair_t[j];
+        uint4 p = make_uint4(0, 0, 0, 0);
+        p.y = gallop_greater(psrc, 0, (uint32_t)j + 1, g.in_off[v + 1], u);
+        p.x = gallop_greater(pair_t, 0, (uint32_t)j + 1, p.y, t);
+        const uint32_t e0 = g.in_off[u], e1 = g.in_off[u + 1];
+        const uint32_t r0 = first_greater(psrc, 0, e0, e1, v - 1);
+        const uint32_t r1 = gallop_greater(psrc, 0, r0, e1, v);
+        if (r0 < r1) {
+            p.z = first_greater(pair_t, 0, r0, r1, t);
+            p.w = r1;
+        }
+        gp[e] = p;
+        const Next4<TT> n = g.gn[e];
+        Next4<TT> o;
+        o.a = p.x < p.y ? pair_t[p.x] : kNever<TT>;
+        o.b = p.z < p.w ? pair_t[p.z] : kNever<TT>;
+        o.c = n.c;
+        o.d = n.d;
+        out_next[opos[e]] = o;
+        o.c = n.a;
+        o.d = n.b;
+        in_next[ipos[e]] = o;
     }
 }
 
@@ -398,10 +462,29 @@ hipError_t launch_lists(const uint32_t *key, const uint32_t *eid, uint32_t n_adj
 
 template <typename TT>
 hipError_t launch_ranks(const DevGraph<TT> &g, const uint32_t *opos, const uint32_t *ipos,
-                        uint4 *gx, hipStream_t st) {
+                        uint4 *gx, Next4<TT> *gn, hipStream_t st) {
     if (g.n_edges == 0) return hipSuccess;
     hipLaunchKernelGGL(list_ranks<TT>, dim3(grid_for(g.n_edges, kIB)), dim3(kIB), 0, st, g, opos,
-                       ipos, gx);
+                       ipos, gx, gn);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather(const uint32_t *eid, const int32_t *key_of, uint32_t n, uint32_t *keys,
+                         hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(gather_keys, dim3(grid_for(n, kIB)), dim3(kIB), 0, st, eid, key_of, n, keys);
+    return hipGetLastError();
+}
+
+template <typename TT>
+hipError_t launch_pairs(const DevGraph<TT> &g, const uint32_t *pe, uint32_t n_adj,
+                        const uint32_t *opos, const uint32_t *ipos, int32_t *psrc, TT *pair_t,
+                        uint4 *gp, Next4<TT> *out_next, Next4<TT> *in_next, hipStream_t st) {
+    if (n_adj == 0) return hipSuccess;
+    const dim3 grid(grid_for(n_adj, kIB));
+    hipLaunchKernelGGL(pair_entries<TT>, grid, dim3(kIB), 0, st, g, pe, n_adj, psrc, pair_t);
+    hipLaunchKernelGGL(pair_links<TT>, grid, dim3(kIB), 0, st, g, pe, n_adj, opos, ipos, psrc,
+                       pair_t, gp, out_next, in_next);
     return hipGetLastError();
 }
 
@@ -420,7 +503,10 @@ template hipError_t sort_pairs<uint64_t>(uint64_t *const[2], uint32_t *const[2],
                                          const int32_t *, const TT *, uint32_t *, Entry<TT> *,    \
                                          uint32_t *, hipStream_t);                                \
     template hipError_t launch_ranks<TT>(const DevGraph<TT> &, const uint32_t *,                  \
-                                         const uint32_t *, uint4 *, hipStream_t);
+                                         const uint32_t *, uint4 *, Next4<TT> *, hipStream_t);    \
+    template hipError_t launch_pairs<TT>(const DevGraph<TT> &, const uint32_t *, uint32_t,        \
+                                         const uint32_t *, const uint32_t *, int32_t *, TT *,     \
+                                         uint4 *, Next4<TT> *, Next4<TT> *, hipStream_t);
 MG_INGEST(uint32_t)
 MG_INGEST(uint64_t)
 #undef MG_INGEST

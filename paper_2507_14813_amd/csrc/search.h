@@ -178,7 +178,7 @@ __device__ __forceinline__ uint32_t leaf_scan_wave(const KParams<TT> &p, const i
                                                    uint32_t g, uint32_t l0, uint32_t len,
                                                    const int lane, unsigned long long *cnt,
                                                    uint32_t nd, uint32_t j, bool move = false) {
-    const uint4 ga = p.tree.grp[2 * g], gb = p.tree.grp[2 * g + 1];
+    const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
     const uint32_t nvp = (ga.x >> 8) & 15;
     const Entry<TT> *__restrict__ e =
         ((ga.x & 15) == kDirOut ? p.g.out_adj : p.g.in_adj) + l0;
@@ -226,7 +226,7 @@ __device__ __forceinline__ uint32_t leaf_scan_wave_multi(const KParams<TT> &p,
                                                          uint32_t l0, uint32_t len, TT tf,
                                                          const int lane, unsigned long long *cnt,
                                                          uint32_t nd) {
-    const uint4 ga = p.tree.grp[2 * g], gb = p.tree.grp[2 * g + 1];
+    const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
     const uint32_t nvp = (ga.x >> 8) & 15;
     const Entry<TT> *__restrict__ e =
         ((ga.x & 15) == kDirOut ? p.g.out_adj : p.g.in_adj) + l0;
@@ -295,28 +295,31 @@ __device__ __forceinline__ uint32_t leaf_scan_wave_multi(const KParams<TT> &p,
 // 2 = its root edge and the slot of its parent one level up (enumeration,
 // which writes out every matched edge).
 // V: vertex slots, the most motif vertices bound at this level (vslots).
-template <typename TT, int L, int R, int V>
+template <typename TT, int D, int L, int R, int V>
 struct LevelBuf {
     static constexpr int S = V;              // vertex slots
     static constexpr int C = 2 * kWave;      // capacity
+    static constexpr bool E2 = L == 3 && D == 4;
     // phi[s - 2][i]: graph vertex of motif vertex s >= 2; motif vertices 0 and
     // 1 and t_first are the root's, kept once in the level-1 batch (slot r1)
     int32_t phi[S - 2][C];
     uint32_t eid[C];       // edge id of its last matched edge
+    uint32_t eid2[E2 ? C : 1];   // edge id of its second edge (level 3)
+    uint32_t live[C];      // its live word (comine.h), with its root's slot
     uint16_t node[C];      // internal trie node reached
-    uint16_t pincl[C];     // inclusive prefix of child-group counts: groups on
-    uint16_t pincl1[C];    // lists of motif vertex 0 or 1, then the others
-    uint8_t r1[C];         // slot of its root in the level-1 batch
+    uint16_t pincl[C];     // inclusive prefix of the counts of its live lists
     uint32_t root[R ? C : 1];
     uint8_t par[R == 2 && L > 2 ? C : 1];   // slot of its parent at level L - 1
 };
-template <typename TT, int R, int V>
-struct LevelBuf<TT, 1, R, V> {
+template <typename TT, int D, int R, int V>
+struct LevelBuf<TT, D, 1, R, V> {
     static constexpr int S = 2;
     static constexpr int C = kWave;
     int32_t phi[2][kWave];
     TT tfirst[kWave];
-    uint32_t root[R ? kWave : 1];
+    uint32_t root[kWave];        // edge id
+    uint8_t live[kWave];         // live bits of its lists (0-3) and of its pair (4, 5)
+    uint8_t pair[4 * kWave];     // live (root, list) pairs: slot | list << 6
 };
 
 // Vertex slots at level L of a kernel for trees of depth D: two per edge, at
@@ -330,7 +333,7 @@ constexpr int vslots(int D, int L) {
 
 template <typename TT, int D, int R, int L>
 struct LevelChain {
-    LevelBuf<TT, L, R, vslots(D, L)> buf;
+    LevelBuf<TT, D, L, R, vslots(D, L)> buf;
     LevelChain<TT, D, R, L + 1> next;
 };
 template <typename TT, int D, int R>
@@ -352,7 +355,6 @@ struct LevelChain<TT, D, R, D> {};
 template <typename TT, int D, int R>
 struct alignas(16) WaveLds {
     static constexpr int H = D > 1 ? 4 : 1;
-    uint8_t src[kWave];           // window compaction: lane holding the k-th window
     uint8_t flag[kWave];          // window-end marks of one pass
     uint32_t hlo[H][kWave];       // root windows (used when D > 2)
     uint16_t hlen[H][kWave];
@@ -380,8 +382,26 @@ __device__ __forceinline__ void set_root_slot(WaveLds<TT, D, R> &W, uint32_t slo
     for (int k = 0; k < 4; ++k) W.hlen[k][slot] = kNoHint;
 }
 
+// Live bits of root edge e with window end thi, as the level-1 batch keeps
+// them: bits 0-3 out(a), in(a), out(b), in(b), bits 4 and 5 its pair a -> b
+// and b -> a.
+template <typename TT>
+__device__ __forceinline__ uint32_t root_live(const KParams<TT> &p, uint32_t e, TT thi) {
+    const Next4<TT> n = p.g.gn[e];
+    const uint4 pr = p.g.gp[e];
+    uint32_t r = (n.a <= thi ? 1u : 0u) | (n.b <= thi ? 2u : 0u) | (n.c <= thi ? 4u : 0u) |
+                 (n.d <= thi ? 8u : 0u);
+    if (pr.x < pr.y && p.g.pair_t[pr.x] <= thi) r |= 16u;
+    if (pr.z < pr.w && p.g.pair_t[pr.z] <= thi) r |= 32u;
+    return r;
+}
+// the same as live-word bits
+__device__ __forceinline__ uint32_t root_bits(uint32_t r) {
+    return (r & 15u) | ((r >> 4) << kLivePair);
+}
+
 template <int L, typename TT, int D, int R, int M>
-__device__ __forceinline__ LevelBuf<TT, L, R, vslots(D, L)> &lvl(LevelChain<TT, D, R, M> &c) {
+__device__ __forceinline__ LevelBuf<TT, D, L, R, vslots(D, L)> &lvl(LevelChain<TT, D, R, M> &c) {
     if constexpr (L == M) return c.buf;
     else return lvl<L>(c.next);
 }
@@ -403,7 +423,7 @@ __device__ __forceinline__ void edge_chain(WaveLds<TT, D, 2> &W, uint32_t i, uin
     } else {
         auto &A = lvl<L>(W.lv);
         e[L - 1] = A.eid[i];
-        if constexpr (L == 2) edge_chain<1>(W, A.r1[i], e);
+        if constexpr (L == 2) edge_chain<1>(W, A.live[i] >> kLiveSlot, e);
         else edge_chain<L - 1>(W, A.par[i], e);
     }
 }
@@ -445,7 +465,7 @@ __device__ __forceinline__ uint32_t count_leaf_window(const KParams<TT> &p, uint
     constexpr int NQ = S - 1;
     const uint32_t anc = (hdr >> 4) & 15;
     const uint32_t nq = ((hdr >> 8) & 15) - 1u;   // bound vertices, the anchor left out
-    const uint4 ga = p.tree.grp[2 * g], gb = p.tree.grp[2 * g + 1];
+    const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
     const uint32_t words[6] = {ga.y, ga.z, ga.w, gb.x, gb.y, gb.z};
     int32_t q[NQ];
     uint32_t w[NQ];
@@ -495,31 +515,109 @@ __device__ __forceinline__ uint32_t leaf_compares(bool counting, uint32_t hdr) {
     return nqm;
 }
 
+// The window of the root in slot r1 in list k (out(a), in(a), out(b), in(b)),
+// a its vertex: [b, e) holds every deeper window on that list, and with true
+// they end at e; without, the root had no such window to find.
+template <typename TT, int D, int R>
+__device__ __forceinline__ bool root_window(const WaveLds<TT, D, R> &W, const uint32_t *off,
+                                            int32_t a, uint32_t k, uint32_t r1, uint32_t &b,
+                                            uint32_t &e) {
+    const uint32_t hl = W.hlen[k][r1], h = W.hlo[k][r1];
+    b = h;
+    e = h + hl;
+    if (hl == kNoHint) {
+        e = off[a + 1];   // it starts past the root's time
+        return false;
+    }
+    if (hl == kLongHint) {
+        b = off[a];
+        e = h;
+    }
+    return true;
+}
+
+// c matches less of the child in `word` at window slot j (the opposite of
+// credit_child).
+__device__ __forceinline__ void uncredit_child(uint32_t word, uint32_t c, unsigned long long *cnt,
+                                               uint32_t nd, uint32_t j, bool move = false) {
+    const uint32_t q1 = (word >> 16) & 0x7fffu;
+    if (!c || !q1) return;
+    atomicAdd(&cnt[(q1 - 1) * nd + j], 0ull - c);
+    if (move) atomicAdd(&cnt[(q1 - 1) * nd + j + 1], (unsigned long long)c);
+}
+
 // A partial match at level L whose trie node has leaf children only (every
 // match below it is one more edge), counted by the lane that found it, with
-// no level buffer: the lane finds and counts the window of each of the node's
-// groups in turn.  A window longer than p.leaf_scan entries is left to the
-// whole wave, which counts such windows between the lanes' turns.  ph[]: the
-// bound vertices, eid and tp: its last edge and that edge's time, tf: its
-// first time, r1: its root's slot in the level-1 batch (root windows).
-template <typename TT, int D, int MODE, int S>
+// no level buffer: the lane counts each of the node's groups whose list is
+// live in turn.
+//
+// A group with pair codes needs no look at its window's entries: the edges of
+// the window between the anchor and a bound vertex are the later edges of a
+// pair that some matched edge belongs to, consecutive in the pair order and
+// found from that edge by galloping over at most a few of them; the new-vertex
+// child gets the window's length less those.  (On 2M edges and the 36
+// three-edge motifs, such windows held 99.7 % of the entries of all leaf
+// windows, mostly the bursts of a hub scanned once per entry of the burst; on
+// 1M edges and 756 motifs of up to four edges 98 %.)
+//
+// The other windows are found and scanned: a window longer than p.leaf_scan
+// entries is left to the whole wave, which counts such windows between the
+// lanes' turns.  ph[]: the bound vertices, eid and tp: the last edge and its
+// time, eid2: the second edge (L 3), tf: the first time, live: the live word.
+template <typename TT, int D, int MODE, int L, int S>
 __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                                                   WaveLds<TT, D, keep_of(MODE)> &W,
                                                   unsigned long long *cnt, const int lane,
                                                   bool act, uint32_t node,
-                                                  const int32_t (&ph)[S], uint32_t eid, TT tp,
-                                                  TT tf, uint32_t r1, uint32_t nd) {
-    const uint32_t iw = act ? p.tree.inode[node] : 0u;
-    uint32_t gi = iw & 0xfffffu;
-    const uint32_t gend = gi + (act ? node_groups(iw) : 0u);
+                                                  const int32_t (&ph)[S], uint32_t eid,
+                                                  uint32_t eid2, TT tp, TT tf, uint32_t live,
+                                                  uint32_t nd) {
+    uint32_t g0 = 0, lists = 0;
+    if (act) {
+        const uint4 nw = p.tree.inode[node];
+        g0 = nw.x & 0xfffffu;
+        lists = nw.y;
+    }
+    uint32_t todo = lists & live & kLiveLists;
+    const uint32_t r1 = live >> kLiveSlot;
     const TT thi = sat_add(tf, p.delta_sat);
     for (;;) {
         bool pend = false;     // a window for the whole wave: group pg, [pl0, pl0 + plen)
         uint32_t pg = 0, pl0 = 0, plen = 0;
-        while (gi < gend) {
-            const uint32_t g = gi;
-            const uint32_t hdr = p.tree.grp[2 * g].x;
-            const uint32_t dir = hdr & 15, anc = (hdr >> 4) & 15;
+        while (todo) {
+            const uint32_t bit = (uint32_t)__builtin_ctz(todo);
+            todo &= todo - 1;
+            const uint32_t g = g0 + (uint32_t)__popc(lists & ((1u << bit) - 1u));
+            const uint32_t dir = bit & 1u, anc = bit >> 1;
+            const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
+            const uint32_t hdr = ga.x, codes = p.tree.grp[3 * g + 2].x;
+            for (uint32_t c = codes; c;) {
+                const uint32_t sh = (uint32_t)__builtin_ctz(c) & ~3u, code = (c >> sh) & 15u;
+                c &= ~(15u << sh);
+                if (!((live >> (kLivePair - 1u + code)) & 1u)) continue;
+                const uint32_t j = (code - 1u) >> 1;
+                uint32_t ej = eid;
+                if (j + 1u != (uint32_t)L) {
+                    ej = lvl<1>(W.lv).root[r1];
+                    if constexpr (L == 3) ej = j == 1 ? eid2 : ej;
+                }
+                const uint2 pr = reinterpret_cast<const uint2 *>(p.g.gp)[2 * (size_t)ej + ((code - 1u) & 1u)];
+                uint32_t lo = pr.x;
+                if (j + 1u != (uint32_t)L) lo = gallop_greater(p.g.pair_t, 0, lo, pr.y, tp);
+                uint32_t e = gallop_greater(p.g.pair_t, 0, lo, pr.y, thi);
+                const uint32_t word = child_word(ga, gb, (int)(sh >> 2));
+                credit_child(word, e - lo, cnt, nd, nd - 1);
+                uncredit_child(gb.w, e - lo, cnt, nd, nd - 1);
+                if constexpr (!single_of(MODE)) {
+                    for (uint32_t k = nd - 1; k-- > 0;) {
+                        e = first_greater(p.g.pair_t, 0, lo, e, sat_add(tf, window_lo(p, k)));
+                        if (e == lo) break;
+                        credit_child(word, e - lo, cnt, nd, k, true);
+                        uncredit_child(gb.w, e - lo, cnt, nd, k, true);
+                    }
+                }
+            }
+            if (codes && !gb.w) continue;
             // The out-list of a later vertex x whose children all end on a root
             // vertex (a or b; no new vertex): the edges x -> a and x -> b in the
             // window are also the entries equal to x in the windows of in(a)
@@ -529,27 +627,23 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
             uint32_t sw_lo[2] = {0, 0}, sw_hi[2] = {0, 0}, sw_word[2] = {0, 0}, sw_len = 0;
             int32_t sw_x = 0;
             if constexpr (single_of(MODE) && D == 3) {   // (measured slower for deeper trees)
-                if (dir == kDirOut && anc >= 2) {
-                    const uint4 ga = p.tree.grp[2 * g], gb = p.tree.grp[2 * g + 1];
-                    if ((gb.w | ga.w | gb.x | gb.y | gb.z) == 0) {
-                        const uint32_t hla = W.hlen[1][r1], hlb = W.hlen[3][r1];
-                        const bool oka = ga.y == 0 || (hla != kNoHint && hla != kLongHint);
-                        const bool okb = ga.z == 0 || (hlb != kNoHint && hlb != kLongHint);
-                        if (oka && okb) {
-                            swap = true;
+                if (dir == kDirOut && anc >= 2 && (gb.w | ga.w | gb.x | gb.y | gb.z) == 0) {
+                    const uint32_t hla = W.hlen[1][r1], hlb = W.hlen[3][r1];
+                    const bool la = ga.y && (live & 2u), lb = ga.z && (live & 8u);
+                    if ((!la || hla < kLongHint) && (!lb || hlb < kLongHint)) {
+                        swap = true;
 #pragma unroll
-                            for (int t = 0; t < S; ++t) sw_x |= ph[t] & -(int32_t)(anc == (uint32_t)t);
-                            const TT *tin = times_of(p.g.in_adj);
+                        for (int t = 0; t < S; ++t) sw_x |= ph[t] & -(int32_t)(anc == (uint32_t)t);
+                        const TT *tin = times_of(p.g.in_adj);
 #pragma unroll
-                            for (int sv = 0; sv < 2; ++sv) {
-                                sw_word[sv] = sv ? ga.z : ga.y;
-                                if (!sw_word[sv]) continue;
-                                const uint32_t k = 2u * (uint32_t)sv + 1u;   // in(a), in(b)
-                                const uint32_t hb = W.hlo[k][r1];
-                                sw_hi[sv] = hb + (sv ? hlb : hla);
-                                sw_lo[sv] = first_greater(tin, 1, hb, sw_hi[sv], tp);
-                                sw_len += sw_hi[sv] - sw_lo[sv];
-                            }
+                        for (int sv = 0; sv < 2; ++sv) {
+                            sw_word[sv] = sv ? ga.z : ga.y;
+                            if (!(sv ? lb : la)) continue;
+                            const uint32_t k = 2u * (uint32_t)sv + 1u;   // in(a), in(b)
+                            const uint32_t hb = W.hlo[k][r1];
+                            sw_hi[sv] = hb + (sv ? hlb : hla);
+                            sw_lo[sv] = first_greater(tin, 1, hb, sw_hi[sv], tp);
+                            sw_len += sw_hi[sv] - sw_lo[sv];
                         }
                     }
                 }
@@ -568,47 +662,48 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
             };
             if (swap && sw_len <= 16u) {   // short enough whatever x's window is
                 count_swapped();
-                ++gi;
                 continue;
             }
             const Entry<TT> *adj = dir == kDirOut ? p.g.out_adj : p.g.in_adj;
             const TT *ta = times_of(adj);
             uint32_t b = 0, e = 0, l0;
-            bool hinted = false, whole = true;   // whole: [b, e) is the anchor's list
-            if constexpr (D > 2) {
-                if (anc < 2) {
-                    // a root vertex's list: the window ends where the root's does
-                    const uint32_t k = anc * 2u + dir;
-                    const uint32_t hl = W.hlen[k][r1];
-                    hinted = hl != kNoHint;
-                    whole = !hinted || hl == kLongHint;
-                    b = W.hlo[k][r1];
-                    e = hl == kLongHint ? b : b + hl;
-                }
-            }
-            if (whole) {
-                // the anchor's vertex by masks: a select chain over ph[]
-                // would be turned into an indexed load from scratch memory
-                int32_t a = 0;
+            bool hinted = false;
+            // the anchor's vertex by masks: a select chain over ph[] would be
+            // turned into an indexed load from scratch memory
+            int32_t a = 0;
 #pragma unroll
-                for (int t = 0; t < S; ++t) a |= ph[t] & -(int32_t)(anc == (uint32_t)t);
-                const uint32_t *off = dir == kDirOut ? p.g.out_off : p.g.in_off;
-                const uint32_t end = e;
-                b = off[a];
-                e = hinted ? end : off[a + 1];
-            }
+            for (int t = 0; t < S; ++t) a |= ph[t] & -(int32_t)(anc == (uint32_t)t);
+            const uint32_t *off = dir == kDirOut ? p.g.out_off : p.g.in_off;
+            if (D > 2 && anc < 2) hinted = root_window(W, off, a, bit, r1, b, e);
+            else { b = off[a]; e = off[a + 1]; }
             const uint32_t le = (hdr >> 13) & 3u;
-            if (le) {
-                // the list of an endpoint of the last edge: its rank is kept
-                const uint32_t k = (le == 1 ? 0u : 2u) + (dir == kDirOut ? 0u : 1u);
-                l0 = reinterpret_cast<const uint32_t *>(p.g.gx)[4 * (size_t)eid + k];
+            uint32_t be = 0;
+            if constexpr (L == 3) be = anc >= 2 ? (hdr >> 15) & 3u : 0u;
+            if (le || be) {
+                // the list of an endpoint of the last edge: its rank is kept;
+                // of the second edge: the window starts no earlier than there
+                const uint32_t k = ((le ? le : be) == 1 ? 0u : 2u) + dir;
+                l0 = reinterpret_cast<const uint32_t *>(p.g.gx)[4 * (size_t)(le ? eid : eid2) + k];
+                if (!le) l0 = gallop_greater(ta, 1, l0, e, tp);
             } else {
                 l0 = first_greater(ta, 1, b, e, tp);
             }
             const uint32_t len = (hinted ? e : gallop_greater(ta, 1, l0, e, thi)) - l0;
+            if (codes) {
+                // the new-vertex child: the window's length (its pairs are off already)
+                credit_child(gb.w, len, cnt, nd, nd - 1);
+                if constexpr (!single_of(MODE)) {
+                    uint32_t x = l0 + len;
+                    for (uint32_t k = nd - 1; k-- > 0;) {
+                        x = gallop_greater(ta, 1, l0, x, sat_add(tf, window_lo(p, k)));
+                        if (x == l0) break;
+                        credit_child(gb.w, x - l0, cnt, nd, k, true);
+                    }
+                }
+                continue;
+            }
             if (swap && sw_len < len) {
                 count_swapped();
-                ++gi;
                 continue;
             }
             if (len > p.leaf_scan) {
@@ -617,7 +712,6 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
             }
             const uint32_t nqm = leaf_compares<S>(len > 0, hdr);
             if (len > 0) count_leaf_window<TT, D, MODE>(p, g, hdr, ph, tf, l0, len, nqm, cnt, nd);
-            ++gi;
         }
         for (uint64_t cm = __ballot(pend); cm; cm &= cm - 1) {
             const int src = (int)__builtin_ctzll(cm);
@@ -633,8 +727,7 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                 leaf_scan_wave_multi<TT, S>(p, wph, wg, wl0, wlen,
                                             lane_time(tf, src), lane, cnt, nd);
         }
-        if (pend) ++gi;
-        if (!__ballot(gi < gend)) break;
+        if (!__ballot(todo != 0)) break;
     }
 }
 
@@ -665,13 +758,17 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
     // graph vertex of motif vertex s, and t_first, of buffered partial match i
     auto vtx = [&](uint32_t s, uint32_t i) -> int32_t {
         if constexpr (L == 1) return A.phi[s][i];
-        else return s < 2 ? R1.phi[s][A.r1[i]] : A.phi[s < 2 ? 0 : s - 2][i];
+        else return s < 2 ? R1.phi[s][A.live[i] >> kLiveSlot] : A.phi[s < 2 ? 0 : s - 2][i];
+    };
+    auto slot_of = [&](uint32_t i) -> uint32_t {
+        if constexpr (L == 1) return i;
+        else return A.live[i] >> kLiveSlot;
     };
     auto tfirst_of = [&](uint32_t i) -> TT {
         if constexpr (L == 1) return A.tfirst[i];
-        else return R1.tfirst[A.r1[i]];
+        else return R1.tfirst[A.live[i] >> kLiveSlot];
     };
-    const uint32_t *__restrict__ inode = p.tree.inode;
+    const uint4 *__restrict__ inode = p.tree.inode;
     const uint4 *__restrict__ grp = p.tree.grp;
     const uint64_t le_mask = (lane == 63) ? ~0ull : ((2ull << lane) - 1);
     // windows counted at once (MODE 0 serves trees with one window only)
@@ -685,14 +782,14 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             bool mixed = false;
             for (uint32_t x0 = 0; x0 < nA; x0 += kWave) {
                 const uint32_t x = x0 + lane;
-                if (x < nA) mixed = mixed || (inode[A.node[x]] & kLeafParent) == 0;
+                if (x < nA) mixed = mixed || (inode[A.node[x]].x & kLeafParent) == 0;
             }
             if (!__ballot(mixed)) {
                 for (uint32_t x0 = 0; x0 < nA; x0 += kWave) {
                     const uint32_t x = x0 + lane;
                     const bool act = x < nA;
                     int32_t ph[SA];
-                    uint32_t node = 0, eid = 0, r1 = 0;
+                    uint32_t node = 0, eid = 0, eid2 = 0, live = 0;
                     TT tp = 0, tf = 0;
 #pragma unroll
                     for (int t = 0; t < SA; ++t) ph[t] = act ? vtx(t, x) : -1;
@@ -701,10 +798,11 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                         eid = A.eid[x];
                         tp = p.g.gt[eid];
                         tf = tfirst_of(x);
-                        r1 = A.r1[x];
+                        live = A.live[x];
+                        if constexpr (D == 4 && L == 3) eid2 = A.eid2[x];
                     }
-                    count_leaf_parent<TT, D, MODE, SA>(p, W, cnt, lane, act, node, ph, eid, tp, tf,
-                                                       r1, nd);
+                    count_leaf_parent<TT, D, MODE, L, SA>(p, W, cnt, lane, act, node, ph, eid,
+                                                          eid2, tp, tf, live, nd);
                 }
                 return;
             }
@@ -712,36 +810,45 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
     }
 
 
-    // child groups per buffered partial match -> inclusive prefix (at the
-    // root level every entry has the root's groups).  Below it the pairs are
-    // taken in two classes: groups on a list of motif vertex 0 or 1 (windows
-    // found inside the root's windows: short bisections) first, then the
-    // others, so that the lanes of one pass do bisections of similar length
-    // (pairs are numbered over both classes: the first P0 are of the first, so
-    // only the pass across the boundary mixes them).
-    uint32_t P = 0, P0 = 0, P1 = 0;
-    const uint32_t root_ng = node_groups(inode[0]);
+    // (partial match, list) pairs: the node's lists that are live.  At the root
+    // level they are written out, roots in order; deeper, the pairs per
+    // partial match become an inclusive prefix.  Lists of motif vertices 0 and
+    // 1 come first within a partial match.
+    uint32_t P = 0, Pn = 0;
+    uint4 node0 = make_uint4(0, 0, 0, 0);
     if constexpr (L == 1) {
-        P = ctx ? nA : nA * root_ng;   // a context is one window of its root
+        node0 = inode[0];
+        if (ctx) {
+            P = nA;   // a context is one window of its root
+        } else {
+            uint32_t act = 0;
+            if ((uint32_t)lane < nA) {
+                act = A.live[lane] & node0.y & 15u;
+                if constexpr (STATS)
+                    if (part == 0) st.v[kStatWinList] += (uint32_t)__popc(node0.y & 15u);
+            }
+            const uint32_t n = (uint32_t)__popc(act);
+            const uint32_t incl = incl_scan32(n, lane);
+            for (uint32_t at = incl - n; act; act &= act - 1)
+                A.pair[at++] = (uint8_t)((uint32_t)lane | ((uint32_t)__builtin_ctz(act) << 6));
+            Pn = lane_value(incl, kWave - 1);
+            P = Pn + (((node0.y >> kLiveAllBit) & 1u) ? nA : 0u);
+            wave_sync();
+        }
     } else {
         for (uint32_t x0 = 0; x0 < nA; x0 += kWave) {
             const uint32_t x = x0 + lane;
-            uint32_t n0 = 0, n1 = 0;
+            uint32_t n = 0;
             if (x < nA) {
-                const uint32_t w = inode[A.node[x]];
-                n0 = node_near(w);
-                n1 = node_groups(w) - n0;
+                const uint32_t lists = inode[A.node[x]].y;
+                n = (uint32_t)__popc(lists & A.live[x] & kLiveLists);
+                if constexpr (STATS)
+                    st.v[kStatWinList] += (uint32_t)__popc(lists & ~(1u << kLiveAllBit));
             }
-            const uint32_t i0 = incl_scan32(n0, lane) + P0;
-            const uint32_t i1 = incl_scan32(n1, lane) + P1;
-            if (x < nA) {
-                A.pincl[x] = (uint16_t)i0;
-                A.pincl1[x] = (uint16_t)i1;
-            }
-            P0 = lane_value(i0, kWave - 1);
-            P1 = lane_value(i1, kWave - 1);
+            const uint32_t incl = incl_scan32(n, lane) + P;
+            if (x < nA) A.pincl[x] = (uint16_t)incl;
+            P = lane_value(incl, kWave - 1);
         }
-        P = P0 + P1;
         wave_sync();
     }
 
@@ -787,25 +894,31 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                             len = c.e1 - c.e0;
                             given = true;
                         } else {
-                            lo = pi / root_ng;
-                            g = (inode[0] & 0xfffffu) + (pi - lo * root_ng);
+                            uint32_t bit = kLiveAllBit;
+                            if (pi < Pn) {
+                                const uint32_t c = A.pair[pi];
+                                lo = c & 63u;
+                                bit = c >> 6;
+                            } else {
+                                lo = pi - Pn;
+                            }
+                            g = (node0.x & 0xfffffu) + (uint32_t)__popc(node0.y & ((1u << bit) - 1u));
                         }
                     } else {
-                        const bool c1 = pi >= P0;   // second class
-                        const uint32_t pj = c1 ? pi - P0 : pi;
-                        const uint16_t *pin = c1 ? A.pincl1 : A.pincl;
                         uint32_t n = nA;
                         while (n > 0) {
                             const uint32_t h = n >> 1;
-                            if (pin[lo + h] <= pj) { lo += h + 1; n -= h + 1; }
+                            if (A.pincl[lo + h] <= pi) { lo += h + 1; n -= h + 1; }
                             else n = h;
                         }
-                        const uint32_t before = lo ? pin[lo - 1] : 0u;
-                        const uint32_t w = inode[A.node[lo]];
-                        g = (w & 0xfffffu) + (c1 ? node_near(w) : 0u) + (pj - before);
+                        const uint4 w = inode[A.node[lo]];
+                        uint32_t m = w.y & A.live[lo] & kLiveLists;
+                        for (uint32_t k = pi - (lo ? A.pincl[lo - 1] : 0u); k > 0; --k) m &= m - 1;
+                        const uint32_t bit = (uint32_t)__builtin_ctz(m);
+                        g = (w.x & 0xfffffu) + (uint32_t)__popc(w.y & ((1u << bit) - 1u));
                     }
                     x = lo;
-                    hdr = grp[2 * g].x;
+                    hdr = grp[3 * g].x;
                     if (given) {
                         all = (hdr & 15) == kDirAll;
                     } else {
@@ -825,24 +938,14 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                         } else {
                             ta = times_of(dir == kDirOut ? p.g.out_adj : p.g.in_adj);
                             sh = 1;
-                            bool whole = true;   // [b, e) is the anchor's whole list
-                            if constexpr (L > 1 && D > 2) {
-                                if (anc < 2) {
-                                    const uint32_t k = (uint32_t)anc * 2u + (uint32_t)dir;
-                                    const uint32_t r1 = A.r1[lo];
-                                    const uint32_t hl = W.hlen[k][r1];
-                                    hinted = hl != kNoHint;
-                                    whole = !hinted || hl == kLongHint;
-                                    b = W.hlo[k][r1];
-                                    e = hl == kLongHint ? b : b + hl;
-                                }
-                            }
-                            if (whole) {
-                                const int32_t a = vtx((uint32_t)anc, lo);
-                                const uint32_t *off = dir == kDirOut ? p.g.out_off : p.g.in_off;
-                                const uint32_t end = e;
+                            const int32_t a = vtx((uint32_t)anc, lo);
+                            const uint32_t *off = dir == kDirOut ? p.g.out_off : p.g.in_off;
+                            if (L > 1 && D > 2 && anc < 2) {
+                                hinted = root_window(W, off, a, (uint32_t)anc * 2u + (uint32_t)dir,
+                                                     L > 1 ? slot_of(lo) : 0u, b, e);
+                            } else {
                                 b = off[a];
-                                e = hinted ? end : off[a + 1];
+                                e = off[a + 1];
                             }
                             if constexpr (L == 1) {
                                 // the root edge's own entries: its windows start at
@@ -894,8 +997,9 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                 pc += uniform((uint32_t)__popcll(__ballot(take)));
                 const bool own = part == 0;   // this part keeps the per-window work
                 if constexpr (STATS) {
+                    // (windows of lists are counted with their partial match)
                     if (take && own) {
-                        st.v[all ? kStatWinAll : kStatWinList] += 1;
+                        if (all) st.v[kStatWinAll] += 1;
                         st.v[all ? kStatEntAll : kStatEntList] += len;
                     }
                 }
@@ -946,14 +1050,13 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                 if (nw) {
                     const uint32_t lk = keep ? len : 0u;
                     const uint32_t incl = incl_scan32(lk, lane);
-                    if (keep) W.src[mbcnt(km)] = (uint8_t)lane;
-                    wave_sync();
-                    const int from = (uint32_t)lane < nw ? (int)W.src[lane] : lane;
-                    wave_sync();
-                    wrec.x = __shfl(x | (g << 8), from);
-                    wrec.y = __shfl(l0, from);
-                    wrec.z = __shfl(incl - lk, from);
-                    wrec.w = __shfl(incl, from);
+                    // every lane sends its window to its place: the kept ones
+                    // first, the others behind them
+                    const int to = 4 * (int)(keep ? mbcnt(km) : nw + mbcnt(~km));
+                    wrec.x = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(x | (g << 8)));
+                    wrec.y = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)l0);
+                    wrec.z = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(incl - lk));
+                    wrec.w = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)incl);
                     if ((uint32_t)lane >= nw) wrec = make_uint4(0, 0, 0, 0);
                     T = lane_value(wrec.w, nw - 1);
                 }
@@ -995,7 +1098,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                         c.t_lo = (uint32_t)tf;
                         c.t_hi = (uint32_t)(tf >> 32);
                         c.g = og;
-                        c.pad = 0;
+                        c.root = A.root[ox];
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             c.hlo[k] = D > 2 ? W.hlo[k][ox] : 0u;
@@ -1033,6 +1136,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             const uint32_t oxg = __shfl(wrec.x, oi);
             const uint32_t olo = __shfl(wrec.y, oi);
             const uint32_t oex = __shfl(wrec.z, oi);
+            const uint32_t oend = __shfl(wrec.w, oi);
             const bool valid = f < T;
             const uint32_t ox = oxg & 255, og = oxg >> 8;
             const uint32_t ei = olo + (f - oex);
@@ -1040,15 +1144,15 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             uint32_t cw = 0;      // child word reached by this candidate
             TT tn = 0;            // its time
             int dir = 0;
-            uint32_t nvp = 0;
+            uint32_t nvp = 0, hit_s = 0;   // hit_s: motif vertex of the scanned endpoint
             int32_t nv0 = -1, nv1 = -1;
             int32_t ph[SA];
 #pragma unroll
             for (int s = 0; s < SA; ++s) ph[s] = 0;
             uint4 ga = make_uint4(0, 0, 0, 0), gb = ga;
             if (valid) {
-                ga = grp[2 * og];
-                gb = grp[2 * og + 1];
+                ga = grp[3 * og];
+                gb = grp[3 * og + 1];
                 dir = ga.x & 15;
                 nvp = (ga.x >> 8) & 15;
 #pragma unroll
@@ -1063,6 +1167,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                     for (int s = 0; s < SA; ++s) y = ((uint32_t)s < nvp && ph[s] == v) ? s : y;
                     // in-groups have no bound-target children, so their words are 0
                     cw = child_word(ga, gb, y);
+                    hit_s = y >= 0 ? (uint32_t)y : nvp;
                     nv0 = v;
                 }
             }
@@ -1102,7 +1207,32 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             if constexpr (L + 1 < D) {
                 auto &B = lvl<L + 1>(W.lv);
                 constexpr int SB = vslots(D, L + 1);
-                const bool push = (cw >> 31) != 0;
+                bool push = (cw >> 31) != 0;
+                // the child's live word: the scanned endpoint's lists and the
+                // new edge's pair as their next entries' times say, the list
+                // just scanned dead after its last entry, the rest inherited
+                uint32_t live = 0;
+                if (push) {
+                    if constexpr (L == 1) live = root_bits(A.live[ox]) | (1u << kLiveAllBit) | (ox << kLiveSlot);
+                    else live = A.live[ox];
+                    if (dir == kDirAll) {
+                        live |= (15u << (2 * nvp)) | (3u << (kLivePair + 2 * L));
+                    } else {
+                        const Next4<TT> nx = (dir == kDirOut ? p.g.out_next : p.g.in_next)[ei];
+                        const TT thi = sat_add(tfirst_of(ox), p.delta_sat);
+                        live &= ~(3u << (2 * hit_s));
+                        live |= (nx.c <= thi ? 1u : 0u) << (2 * hit_s);
+                        live |= (nx.d <= thi ? 2u : 0u) << (2 * hit_s);
+                        live |= (nx.a <= thi ? 1u : 0u) << (kLivePair + 2 * L);
+                        live |= (nx.b <= thi ? 2u : 0u) << (kLivePair + 2 * L);
+                        if ((L > 1 || !ctx) && f + 1 == oend)
+                            live &= ~(1u << (2 * ((ga.x >> 4) & 15u) + (uint32_t)dir));
+                    }
+                    // nothing below it: not kept (the statistics count it)
+                    const uint4 nw = inode[cw & 0xffffu];
+                    if constexpr (LOG) push = (live & nw.y) != 0;
+                    else if constexpr (!STATS) push = (live & nw.z) != 0;
+                }
                 const uint64_t pm = __ballot(push);
                 if (push) {
                     const uint32_t slot = nB + mbcnt(pm);
@@ -1115,8 +1245,8 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                     }
                     B.eid[slot] = cand_eid();
                     B.node[slot] = (uint16_t)(cw & 0xffffu);
-                    if constexpr (L == 1) B.r1[slot] = (uint8_t)ox;
-                    else B.r1[slot] = A.r1[ox];
+                    B.live[slot] = live;
+                    if constexpr (L == 2 && D == 4) B.eid2[slot] = A.eid[ox];
                     if constexpr (keep_of(MODE) > 0) B.root[slot] = A.root[ox];
                     if constexpr (keep_of(MODE) == 2 && L > 1) B.par[slot] = (uint8_t)ox;
                     if constexpr (STATS) st.v[kStatPush] += 1;
@@ -1163,9 +1293,11 @@ __device__ __forceinline__ void process_root_part(const KParams<TT> &p,
         if (lane == 0) {
             A.phi[0][0] = s;
             A.phi[1][0] = d;
-            A.tfirst[0] = p.g.gt[r];
+            const TT t = p.g.gt[r];
+            A.tfirst[0] = t;
             set_root_slot(W, 0, p.g.gx[r]);
-            if constexpr (keep_of(MODE) > 0) A.root[0] = r;
+            A.root[0] = r;
+            A.live[0] = (uint8_t)root_live(p, r, sat_add(t, p.delta_sat));
         }
         wave_sync();
         run_level<TT, D, MODE, 1>(p, W, cnt, lane, 1u, st, part, nparts);
@@ -1193,9 +1325,9 @@ __device__ __forceinline__ void process_roots(const KParams<TT> &p,
             d = p.g.gdst[r];
             ok = s != d;
         }
-        const uint64_t m = __ballot(ok);
-        if (p.tree.root_q >= 0 && lane == 0 && m)
-            atomicAdd(&cnt[p.tree.root_q * p.tree.n_d], (unsigned long long)__popcll(m));
+        const uint64_t all = __ballot(ok);
+        if (p.tree.root_q >= 0 && lane == 0 && all)
+            atomicAdd(&cnt[p.tree.root_q * p.tree.n_d], (unsigned long long)__popcll(all));
         if constexpr (MODE == 4) {
             if (p.tree.root_q >= 0) {
                 uint32_t e[kKMax] = {r, 0, 0, 0, 0};
@@ -1208,13 +1340,26 @@ __device__ __forceinline__ void process_roots(const KParams<TT> &p,
         }
         if constexpr (D > 1) {
             auto &A = lvl<1>(W.lv);
+            uint32_t live = 0;
+            TT t = 0;
+            if (ok) {
+                t = p.g.gt[r];
+                live = root_live(p, r, sat_add(t, p.delta_sat));
+                // a root with nothing in its windows ends here (the
+                // statistics still count its empty windows)
+                if constexpr (!STATS)
+                    ok = ((root_bits(live) | (1u << kLiveAllBit)) &
+                          (LOG ? p.tree.inode[0].y : p.tree.inode[0].z)) != 0;
+            }
+            const uint64_t m = __ballot(ok);
             if (ok) {
                 const uint32_t slot = mbcnt(m);
                 A.phi[0][slot] = s;
                 A.phi[1][slot] = d;
-                A.tfirst[slot] = p.g.gt[r];
+                A.tfirst[slot] = t;
                 set_root_slot(W, slot, p.g.gx[r]);
-                if constexpr (keep_of(MODE) > 0) A.root[slot] = r;
+                A.root[slot] = r;
+                A.live[slot] = (uint8_t)live;
             }
             const uint32_t n1 = uniform((uint32_t)__popcll(m));
             if (n1 > 0) {
@@ -1239,9 +1384,12 @@ __device__ __forceinline__ void process_contexts(const KParams<TT> &p,
         const uint32_t i = base + (uint32_t)lane;
         if (i < end) {
             const EpochCtx c = p.ctx_in[i];
+            const TT t = (TT)(((uint64_t)c.t_hi << 32) | c.t_lo);
             A.phi[0][lane] = c.a;
             A.phi[1][lane] = c.b;
-            A.tfirst[lane] = (TT)(((uint64_t)c.t_hi << 32) | c.t_lo);
+            A.tfirst[lane] = t;
+            A.root[lane] = c.root;
+            A.live[lane] = (uint8_t)root_live(p, c.root, sat_add(t, p.delta_sat));
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 W.hlo[k][lane] = c.hlo[k];

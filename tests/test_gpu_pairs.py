@@ -1,0 +1,74 @@
+"""Leaf windows counted from pairs, and windows skipped because no list entry
+lies in them: bursts between few pairs (long runs of one pair and of its
+reverse, ties, a pair that only ever runs one way), isolated edges, windows that
+end exactly on an edge, unbounded windows.  Whole numbers, equal to the
+oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2507_14813_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+THREE = W.enumerate_motifs(3, 3)
+FOUR = W.enumerate_motifs(3, 4)[::3] + W.enumerate_motifs(4, 4)[::9]
+MIXED = ([((0, 1), (0, 1)), ((0, 1), (1, 0), (0, 2)), ((0, 1), (2, 3), (3, 1))] +
+         W.random_extension_motifs(12, (2, 3, 4, 5), 5, 77))
+
+
+@pytest.fixture(scope="module")
+def api(oracle_mod):
+    import torch
+    assert torch.cuda.is_available(), "no GPU visible"
+    from paper_2507_14813_amd import api
+    api.lib()
+    return api
+
+
+def bursts(n_edges, seed, unit):
+    rng = np.random.default_rng(seed)
+    s, d, t = [], [], []
+    while len(s) < n_edges:
+        a, b = rng.choice(14, 2, replace=False)
+        k = int(rng.choice([1, 1, 2, 5, 40, 150]))
+        t0 = int(rng.integers(0, 60 * n_edges))
+        for _ in range(k):
+            flip = rng.random() < 0.3 and min(a, b) > 2
+            s.append(b if flip else a)
+            d.append(a if flip else b)
+            t.append(t0)
+            t0 += int(rng.choice([0, 1, 3, 9]))
+            if rng.random() < 0.3:
+                b = int(rng.choice([x for x in range(14) if x != a]))
+    return (np.array(s[:n_edges], np.int32), np.array(d[:n_edges], np.int32),
+            np.array(t[:n_edges], np.int64) * unit)
+
+
+@pytest.mark.parametrize("unit", [1, 2 ** 33])
+@pytest.mark.parametrize("motifs,n_edges", [(THREE, 6000), (FOUR, 2500), (MIXED, 1500)])
+def test_burst_counts_equal_oracle(api, motifs, n_edges, unit):
+    s, d, t = bursts(n_edges, n_edges + 1, unit)
+    g, og = api.Graph(s, d, t, 15), oracle.OracleGraph(s, d, t, 15)
+    deltas = [9 * unit, 120 * unit, 31 * unit]
+    print("bursts", len(motifs), n_edges, unit, flush=True)
+    want = np.array([[og.count(m, x) for m in motifs] for x in deltas], dtype=np.uint64)
+    for i, x in enumerate(deltas):
+        tr = api.Tree(motifs, x)
+        assert np.array_equal(api.count(g, tr), want[i])
+        assert np.array_equal(api.count(g, tr, leaf_scan=-1), want[i])
+        assert np.array_equal(api.count(g, tr, epoch_idle=1, max_epochs=3), want[i])
+    assert np.array_equal(api.count(g, api.Tree(motifs, deltas)), want)
+    assert np.array_equal(np.stack(api.count_batch([g] * 3, [api.Tree(motifs, x) for x in deltas])), want)
+
+
+def test_unbounded_window_and_isolated_edges(api):
+    s, d, t = bursts(60, 5, 1)
+    # edges that touch no other edge's vertices within any window
+    s = np.concatenate([s, np.arange(20, 60, 2)]).astype(np.int32)
+    d = np.concatenate([d, np.arange(21, 61, 2)]).astype(np.int32)
+    t = np.concatenate([t, np.arange(20) * 7]).astype(np.int64)
+    g, og = api.Graph(s, d, t, 61), oracle.OracleGraph(s, d, t, 61)
+    for x in (0, 2 ** 63 - 1):
+        want = np.array([og.count(m, x) for m in THREE], dtype=np.uint64)
+        assert np.array_equal(api.count(g, api.Tree(THREE, x)), want)
