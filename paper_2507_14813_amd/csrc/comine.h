@@ -55,6 +55,9 @@ enum : int { kDirOut = 0, kDirIn = 1, kDirAll = 2 };
 //     z = the live-word bits of which at least one has to be set for anything
 //         to be found below the node when leaf windows are counted from pairs:
 //         the lists of its other groups and the pairs of those that are
+//     w = of a leaf parent: the lists whose window has to be found (bits 0-12:
+//         no pair codes, or a new-vertex child) and those with pair codes
+//         (bits 16-28)
 //   grp[3g..3g+2]: twelve words of group g:
 //     w0 = dir | anchor << 4 | nv << 8 | leaf_only << 12 | last_end << 13 |
 //          bound_by << 15

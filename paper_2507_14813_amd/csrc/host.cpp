@@ -159,7 +159,7 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
         {&g->gsrc, sizeof(int32_t) * (size_t)E}, {&g->gdst, sizeof(int32_t) * (size_t)E},
         {&g->gt, sizeof(TT) * (size_t)E},        {&g->gx, sizeof(uint32_t) * 4 * (size_t)E},
         {&g->gn, sizeof(mg::Next4<TT>) * (size_t)E}, {&g->gp, sizeof(uint32_t) * 4 * (size_t)E},
-        {&g->pair_t, sizeof(TT) * (size_t)A},
+        {&g->pair_t, sizeof(TT) * ((size_t)A + 4)},   // read four entries at a time
         {&g->out_next, sizeof(mg::Next4<TT>) * (size_t)A},
         {&g->in_next, sizeof(mg::Next4<TT>) * (size_t)A},
         {&g->out_eid, sizeof(uint32_t) * (size_t)A}, {&g->in_eid, sizeof(uint32_t) * (size_t)A},
@@ -338,7 +338,7 @@ int build_tree(mg_tree *tr) {
         const int g0 = (int)tr->grp_tab.size() / 12;
         if (g0 + (int)groups.size() > (1 << 20))
             return fail(MG_EUNSUPPORTED, "too many child groups");
-        uint32_t lists = 0, gate = 0;
+        uint32_t lists = 0, gate = 0, by_pairs = 0, by_window = 0;
         for (auto &kv : groups) {
             const bool all = kv.first == (int)mg::kLiveAllBit;
             const int dir = all ? mg::kDirAll : kv.first & 1, anc = all ? 0 : kv.first >> 1;
@@ -393,6 +393,8 @@ int build_tree(mg_tree *tr) {
             if (!known) codes = 0;
             rec[8] = (int32_t)codes;
             lists |= 1u << kv.first;
+            if (codes) by_pairs |= 1u << kv.first;
+            if (!codes || rec[7]) by_window |= 1u << kv.first;
             gate |= codes && !rec[7] ? pair_bits : 1u << kv.first;
             tr->grp_tab.insert(tr->grp_tab.end(), rec, rec + 12);
         }
@@ -407,6 +409,7 @@ int build_tree(mg_tree *tr) {
         w[0] = (int32_t)((uint32_t)g0 | (leaf_parent ? mg::kLeafParent : 0u));
         w[1] = (int32_t)lists;
         w[2] = (int32_t)(leaf_parent ? gate : lists);
+        w[3] = (int32_t)(leaf_parent ? by_window | by_pairs << 16 : 0u);
     }
     if (tr->grp_tab.empty()) tr->grp_tab.assign(12, 0);
     tr->root_q = tr->nodes[0].q;

@@ -299,7 +299,7 @@ template <typename TT, int D, int L, int R, int V>
 struct LevelBuf {
     static constexpr int S = V;              // vertex slots
     static constexpr int C = 2 * kWave;      // capacity
-    static constexpr bool E2 = L == 3 && D == 4;
+    static constexpr bool E2 = L == 3;
     // phi[s - 2][i]: graph vertex of motif vertex s >= 2; motif vertices 0 and
     // 1 and t_first are the root's, kept once in the level-1 batch (slot r1)
     int32_t phi[S - 2][C];
@@ -307,7 +307,7 @@ struct LevelBuf {
     uint32_t eid2[E2 ? C : 1];   // edge id of its second edge (level 3)
     uint32_t live[C];      // its live word (comine.h), with its root's slot
     uint16_t node[C];      // internal trie node reached
-    uint16_t pincl[C];     // inclusive prefix of the counts of its live lists
+    uint16_t pincl[kWave]; // inclusive prefix of a batch's counts of live lists
     uint32_t root[R ? C : 1];
     uint8_t par[R == 2 && L > 2 ? C : 1];   // slot of its parent at level L - 1
 };
@@ -391,8 +391,9 @@ __device__ __forceinline__ uint32_t root_live(const KParams<TT> &p, uint32_t e, 
     const uint4 pr = p.g.gp[e];
     uint32_t r = (n.a <= thi ? 1u : 0u) | (n.b <= thi ? 2u : 0u) | (n.c <= thi ? 4u : 0u) |
                  (n.d <= thi ? 8u : 0u);
-    if (pr.x < pr.y && p.g.pair_t[pr.x] <= thi) r |= 16u;
-    if (pr.z < pr.w && p.g.pair_t[pr.z] <= thi) r |= 32u;
+    // a -> b again: an entry of out(a) and of in(b); b -> a: of in(a) and out(b)
+    if ((r & 9u) == 9u && pr.x < pr.y && p.g.pair_t[pr.x] <= thi) r |= 16u;
+    if ((r & 6u) == 6u && pr.z < pr.w && p.g.pair_t[pr.z] <= thi) r |= 32u;
     return r;
 }
 // the same as live-word bits
@@ -536,6 +537,31 @@ __device__ __forceinline__ bool root_window(const WaveLds<TT, D, R> &W, const ui
     return true;
 }
 
+// Entries of a pair, [pos, end) of the pair order, with lo < t <= hi.  Most
+// pairs have a few in a window, so four are looked at per load without a
+// search (lanes stay together; pair_t is padded by four entries); what is left
+// after eight is bisected.  (Galloping from the first entry instead: 4.9 ms
+// for 20M edges and 36 motifs, against 3.8.)
+template <typename TT>
+__device__ __forceinline__ uint32_t pair_count(const TT *__restrict__ t, uint32_t pos, uint32_t end,
+                                               TT lo, TT hi) {
+    uint32_t c = 0;
+    for (int it = 0; pos < end; ++it) {
+        if (it == 2) {
+            const uint32_t a = gallop_greater(t, 0, pos, end, lo);
+            return c + gallop_greater(t, 0, a, end, hi) - a;
+        }
+        TT v[4];
+        __builtin_memcpy(v, t + pos, sizeof v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            c += (v[k] > lo && v[k] <= hi && pos + (uint32_t)k < end) ? 1u : 0u;
+        if (pos + 4 >= end || v[3] > hi) break;
+        pos += 4;
+    }
+    return c;
+}
+
 // c matches less of the child in `word` at window slot j (the opposite of
 // credit_child).
 __device__ __forceinline__ void uncredit_child(uint32_t word, uint32_t c, unsigned long long *cnt,
@@ -546,39 +572,68 @@ __device__ __forceinline__ void uncredit_child(uint32_t word, uint32_t c, unsign
     if (move) atomicAdd(&cnt[(q1 - 1) * nd + j + 1], (unsigned long long)c);
 }
 
+// Counts the groups of a leaf parent's lists in `lists` (all with pair codes)
+// by pairs.  The window of such a group needs no look at its entries: its edges
+// between the anchor and a bound vertex are the later edges of a pair that some
+// matched edge belongs to, consecutive in the pair order and found from that
+// edge.  (On 2M edges and the 36 three-edge motifs, such windows held 99.7 % of
+// the entries of all leaf windows, mostly the bursts of a hub scanned once per
+// entry of the burst; on 1M edges and 756 motifs of up to four edges 98 %.)  A
+// new-vertex child gets the window's length, credited by count_leaf_parent,
+// less the pairs, taken off here.  node: the node's words, eid_of(j): matched
+// edge j, tp: the last edge's time, tf and thi: the window.
+template <typename TT, int MODE, typename EidOf>
+__device__ __forceinline__ void count_pairs(const KParams<TT> &p, unsigned long long *cnt,
+                                            const uint4 node, uint32_t lists, uint32_t live,
+                                            EidOf eid_of, TT tp, TT tf, TT thi, uint32_t nd) {
+    for (; lists; lists &= lists - 1) {
+        const uint32_t bit = (uint32_t)__builtin_ctz(lists);
+        const uint32_t g = (node.x & 0xfffffu) + (uint32_t)__popc(node.y & ((1u << bit) - 1u));
+        const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
+        for (uint32_t c = p.tree.grp[3 * g + 2].x; c;) {
+            const uint32_t sh = (uint32_t)__builtin_ctz(c) & ~3u, code = (c >> sh) & 15u;
+            c &= ~(15u << sh);
+            if (!((live >> (kLivePair - 1u + code)) & 1u)) continue;
+            const uint32_t ej = eid_of((code - 1u) >> 1);
+            const uint2 pr = reinterpret_cast<const uint2 *>(p.g.gp)[2 * (size_t)ej + ((code - 1u) & 1u)];
+            const uint32_t word = child_word(ga, gb, (int)(sh >> 2));
+            if constexpr (single_of(MODE)) {
+                const uint32_t n = pair_count(p.g.pair_t, pr.x, pr.y, tp, thi);
+                credit_child(word, n, cnt, 1u, 0u);
+                uncredit_child(gb.w, n, cnt, 1u, 0u);
+            } else {
+                const uint32_t lo = gallop_greater(p.g.pair_t, 0, pr.x, pr.y, tp);
+                uint32_t e = gallop_greater(p.g.pair_t, 0, lo, pr.y, thi);
+                credit_child(word, e - lo, cnt, nd, nd - 1);
+                uncredit_child(gb.w, e - lo, cnt, nd, nd - 1);
+                for (uint32_t k = nd - 1; k-- > 0;) {
+                    e = first_greater(p.g.pair_t, 0, lo, e, sat_add(tf, window_lo(p, k)));
+                    if (e == lo) break;
+                    credit_child(word, e - lo, cnt, nd, k, true);
+                    uncredit_child(gb.w, e - lo, cnt, nd, k, true);
+                }
+            }
+        }
+    }
+}
+
 // A partial match at level L whose trie node has leaf children only (every
-// match below it is one more edge), counted by the lane that found it, with
-// no level buffer: the lane counts each of the node's groups whose list is
-// live in turn.
-//
-// A group with pair codes needs no look at its window's entries: the edges of
-// the window between the anchor and a bound vertex are the later edges of a
-// pair that some matched edge belongs to, consecutive in the pair order and
-// found from that edge by galloping over at most a few of them; the new-vertex
-// child gets the window's length less those.  (On 2M edges and the 36
-// three-edge motifs, such windows held 99.7 % of the entries of all leaf
-// windows, mostly the bursts of a hub scanned once per entry of the burst; on
-// 1M edges and 756 motifs of up to four edges 98 %.)
-//
-// The other windows are found and scanned: a window longer than p.leaf_scan
-// entries is left to the whole wave, which counts such windows between the
-// lanes' turns.  ph[]: the bound vertices, eid and tp: the last edge and its
-// time, eid2: the second edge (L 3), tf: the first time, live: the live word.
+// match below it is one more edge): the lane counts the windows of the node's
+// lists in `todo` in turn (those that pairs do not count, and the lengths of
+// those with a new-vertex child that they do).  A window longer than
+// p.leaf_scan entries is left to the whole wave, which counts such windows
+// between the lanes' turns.  nw: the node's words, ph[]: the bound vertices,
+// eid and tp: the last edge and its time, eid2: the second edge (L 3), tf: the
+// first time, live: the live word.
 template <typename TT, int D, int MODE, int L, int S>
 __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                                                   WaveLds<TT, D, keep_of(MODE)> &W,
                                                   unsigned long long *cnt, const int lane,
-                                                  bool act, uint32_t node,
+                                                  const uint4 nw, uint32_t todo,
                                                   const int32_t (&ph)[S], uint32_t eid,
                                                   uint32_t eid2, TT tp, TT tf, uint32_t live,
                                                   uint32_t nd) {
-    uint32_t g0 = 0, lists = 0;
-    if (act) {
-        const uint4 nw = p.tree.inode[node];
-        g0 = nw.x & 0xfffffu;
-        lists = nw.y;
-    }
-    uint32_t todo = lists & live & kLiveLists;
+    const uint32_t g0 = nw.x & 0xfffffu, lists = nw.y;
     const uint32_t r1 = live >> kLiveSlot;
     const TT thi = sat_add(tf, p.delta_sat);
     for (;;) {
@@ -591,33 +646,6 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
             const uint32_t dir = bit & 1u, anc = bit >> 1;
             const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
             const uint32_t hdr = ga.x, codes = p.tree.grp[3 * g + 2].x;
-            for (uint32_t c = codes; c;) {
-                const uint32_t sh = (uint32_t)__builtin_ctz(c) & ~3u, code = (c >> sh) & 15u;
-                c &= ~(15u << sh);
-                if (!((live >> (kLivePair - 1u + code)) & 1u)) continue;
-                const uint32_t j = (code - 1u) >> 1;
-                uint32_t ej = eid;
-                if (j + 1u != (uint32_t)L) {
-                    ej = lvl<1>(W.lv).root[r1];
-                    if constexpr (L == 3) ej = j == 1 ? eid2 : ej;
-                }
-                const uint2 pr = reinterpret_cast<const uint2 *>(p.g.gp)[2 * (size_t)ej + ((code - 1u) & 1u)];
-                uint32_t lo = pr.x;
-                if (j + 1u != (uint32_t)L) lo = gallop_greater(p.g.pair_t, 0, lo, pr.y, tp);
-                uint32_t e = gallop_greater(p.g.pair_t, 0, lo, pr.y, thi);
-                const uint32_t word = child_word(ga, gb, (int)(sh >> 2));
-                credit_child(word, e - lo, cnt, nd, nd - 1);
-                uncredit_child(gb.w, e - lo, cnt, nd, nd - 1);
-                if constexpr (!single_of(MODE)) {
-                    for (uint32_t k = nd - 1; k-- > 0;) {
-                        e = first_greater(p.g.pair_t, 0, lo, e, sat_add(tf, window_lo(p, k)));
-                        if (e == lo) break;
-                        credit_child(word, e - lo, cnt, nd, k, true);
-                        uncredit_child(gb.w, e - lo, cnt, nd, k, true);
-                    }
-                }
-            }
-            if (codes && !gb.w) continue;
             // The out-list of a later vertex x whose children all end on a root
             // vertex (a or b; no new vertex): the edges x -> a and x -> b in the
             // window are also the entries equal to x in the windows of in(a)
@@ -748,8 +776,8 @@ struct Stats {
 template <typename TT, int D, int MODE, int L>
 __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, keep_of(MODE)> &W,
                                           unsigned long long *cnt, const int lane,
-                                          const uint32_t nA, Stats &st, const uint32_t part = 0,
-                                          const uint32_t nparts = 1,
+                                          const uint32_t base, const uint32_t nA, Stats &st,
+                                          const uint32_t part = 0, const uint32_t nparts = 1,
                                           const EpochCtx *ctx = nullptr) {
     constexpr bool STATS = MODE == 1, LOG = MODE == 2;
     auto &A = lvl<L>(W.lv);
@@ -774,41 +802,36 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
     // windows counted at once (MODE 0 serves trees with one window only)
     const uint32_t nd = single_of(MODE) ? 1u : (uint32_t)p.tree.n_d;
 
-    if constexpr (plain_of(MODE) && L > 1 && D <= 4) {
-        // a batch of leaf parents only (every match below is one more edge):
-        // one lane per partial match finds and counts all of its windows
-        // (measured faster for trees of up to four edges, slower for five)
-        if (p.leaf_scan != 0) {
-            bool mixed = false;
-            for (uint32_t x0 = 0; x0 < nA; x0 += kWave) {
-                const uint32_t x = x0 + lane;
-                if (x < nA) mixed = mixed || (inode[A.node[x]].x & kLeafParent) == 0;
-            }
-            if (!__ballot(mixed)) {
-                for (uint32_t x0 = 0; x0 < nA; x0 += kWave) {
-                    const uint32_t x = x0 + lane;
-                    const bool act = x < nA;
-                    int32_t ph[SA];
-                    uint32_t node = 0, eid = 0, eid2 = 0, live = 0;
-                    TT tp = 0, tf = 0;
+    // leaf parents are counted by their lanes, pairs where they were found
+    const bool direct = plain_of(MODE) && p.leaf_scan != 0;
+    bool counted = false;   // this lane's partial match is a leaf parent, done here
+    if constexpr (plain_of(MODE) && L > 1) {
+        if (direct) {
+            const uint32_t x = base + lane;
+            const bool act = (uint32_t)lane < nA;
+            uint4 nw = make_uint4(0, 0, 0, 0);
+            if (act) nw = inode[A.node[x]];
+            counted = (nw.x & kLeafParent) != 0;
+            if (__ballot(counted)) {
+                int32_t ph[SA];
+                uint32_t eid = 0, eid2 = 0, live = 0;
+                TT tp = 0, tf = 0;
 #pragma unroll
-                    for (int t = 0; t < SA; ++t) ph[t] = act ? vtx(t, x) : -1;
-                    if (act) {
-                        node = A.node[x];
-                        eid = A.eid[x];
-                        tp = p.g.gt[eid];
-                        tf = tfirst_of(x);
-                        live = A.live[x];
-                        if constexpr (D == 4 && L == 3) eid2 = A.eid2[x];
-                    }
-                    count_leaf_parent<TT, D, MODE, L, SA>(p, W, cnt, lane, act, node, ph, eid,
-                                                          eid2, tp, tf, live, nd);
+                for (int t = 0; t < SA; ++t) ph[t] = counted ? vtx(t, x) : -1;
+                if (counted) {
+                    eid = A.eid[x];
+                    tp = p.g.gt[eid];
+                    tf = tfirst_of(x);
+                    live = A.live[x];
+                    if constexpr (L == 3) eid2 = A.eid2[x];
                 }
-                return;
+                count_leaf_parent<TT, D, MODE, L, SA>(p, W, cnt, lane, nw,
+                                                      counted ? nw.w & live & kLiveLists : 0u, ph,
+                                                      eid, eid2, tp, tf, live, nd);
             }
+            if (!__ballot(act && !counted)) return;
         }
     }
-
 
     // (partial match, list) pairs: the node's lists that are live.  At the root
     // level they are written out, roots in order; deeper, the pairs per
@@ -836,19 +859,16 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             wave_sync();
         }
     } else {
-        for (uint32_t x0 = 0; x0 < nA; x0 += kWave) {
-            const uint32_t x = x0 + lane;
-            uint32_t n = 0;
-            if (x < nA) {
-                const uint32_t lists = inode[A.node[x]].y;
-                n = (uint32_t)__popc(lists & A.live[x] & kLiveLists);
-                if constexpr (STATS)
-                    st.v[kStatWinList] += (uint32_t)__popc(lists & ~(1u << kLiveAllBit));
-            }
-            const uint32_t incl = incl_scan32(n, lane) + P;
-            if (x < nA) A.pincl[x] = (uint16_t)incl;
-            P = lane_value(incl, kWave - 1);
+        uint32_t n = 0;
+        if ((uint32_t)lane < nA && !counted) {
+            const uint32_t lists = inode[A.node[base + lane]].y;
+            n = (uint32_t)__popc(lists & A.live[base + lane] & kLiveLists);
+            if constexpr (STATS)
+                st.v[kStatWinList] += (uint32_t)__popc(lists & ~(1u << kLiveAllBit));
         }
+        const uint32_t incl = incl_scan32(n, lane);
+        A.pincl[lane] = (uint16_t)incl;
+        P = lane_value(incl, kWave - 1);
         wave_sync();
     }
 
@@ -862,8 +882,8 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
     bool dumping = false, room = true;
     uint32_t polls = 0, used = 0;   // contexts this wave wrote (at most its share of ctx_cap)
 
+    bool done = false;
     for (;;) {
-        bool done = false;
         if constexpr (L == 1 && epochs_of(MODE)) {
             // (a wave dumps in one batch at most: the later batches of its
             // chunk search on)
@@ -911,9 +931,11 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                             if (A.pincl[lo + h] <= pi) { lo += h + 1; n -= h + 1; }
                             else n = h;
                         }
+                        const uint32_t before = lo ? A.pincl[lo - 1] : 0u;
+                        lo += base;
                         const uint4 w = inode[A.node[lo]];
                         uint32_t m = w.y & A.live[lo] & kLiveLists;
-                        for (uint32_t k = pi - (lo ? A.pincl[lo - 1] : 0u); k > 0; --k) m &= m - 1;
+                        for (uint32_t k = pi - before; k > 0; --k) m &= m - 1;
                         const uint32_t bit = (uint32_t)__builtin_ctz(m);
                         g = (w.x & 0xfffffu) + (uint32_t)__popc(w.y & ((1u << bit) - 1u));
                     }
@@ -1232,6 +1254,29 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                     const uint4 nw = inode[cw & 0xffffu];
                     if constexpr (LOG) push = (live & nw.y) != 0;
                     else if constexpr (!STATS) push = (live & nw.z) != 0;
+                    // a leaf parent's pairs are counted here, on the full
+                    // lanes of the candidate pass; only one with windows left
+                    // to look at (2 % of them on a bursty graph) is kept
+                    if constexpr (plain_of(MODE)) {
+                        if (direct && push && (nw.x & kLeafParent)) {
+                            auto eid_of = [&](uint32_t j) -> uint32_t {
+                                uint32_t e = 0;
+                                if (j == (uint32_t)L) return cand_eid();
+                                if constexpr (L == 1) {
+                                    e = A.root[ox];
+                                } else {
+                                    if (j == 0) e = R1.root[A.live[ox] >> kLiveSlot];
+                                    else e = A.eid[ox];
+                                    if constexpr (L == 3) e = j == 1 ? A.eid2[ox] : e;
+                                }
+                                return e;
+                            };
+                            const TT tf = tfirst_of(ox);
+                            count_pairs<TT, MODE>(p, cnt, nw, (nw.w >> 16) & live & kLiveLists, live,
+                                                  eid_of, tn, tf, sat_add(tf, p.delta_sat), nd);
+                            push = (nw.w & live & kLiveLists) != 0;
+                        }
+                    }
                 }
                 const uint64_t pm = __ballot(push);
                 if (push) {
@@ -1246,7 +1291,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                     B.eid[slot] = cand_eid();
                     B.node[slot] = (uint16_t)(cw & 0xffffu);
                     B.live[slot] = live;
-                    if constexpr (L == 2 && D == 4) B.eid2[slot] = A.eid[ox];
+                    if constexpr (L == 2) B.eid2[slot] = A.eid[ox];
                     if constexpr (keep_of(MODE) > 0) B.root[slot] = A.root[ox];
                     if constexpr (keep_of(MODE) == 2 && L > 1) B.par[slot] = (uint8_t)ox;
                     if constexpr (STATS) st.v[kStatPush] += 1;
@@ -1256,149 +1301,149 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             cc += kWave;
         }
         if constexpr (L + 1 < D) {
+            // 64 of them at a time, the last ones first (the others stay where
+            // they are), so that every batch but the last is full
             if (nB >= kWave || (done && nB > 0)) {
+                const uint32_t n = min(nB, (uint32_t)kWave);
+                nB -= n;
                 wave_sync();
-                run_level<TT, D, MODE, L + 1>(p, W, cnt, lane, nB, st);
+                run_level<TT, D, MODE, L + 1>(p, W, cnt, lane, nB, n, st);
                 wave_sync();
-                nB = 0;
             }
         }
-        if (done) break;
+        if (done && nB == 0) break;
     }
     if constexpr (L == 1) {
         if (dumping) st.dumped = true;
     }
 }
 
-// Search from part `part` of `nparts` of the root at position r (an edge id:
-// split items come only with p.roots NULL); part 0 credits the root itself.
-template <typename TT, int D, int MODE>
-__device__ __forceinline__ void process_root_part(const KParams<TT> &p,
-                                                  WaveLds<TT, D, keep_of(MODE)> &W,
-                                                  unsigned long long *cnt, const int lane,
-                                                  const uint32_t r, const uint32_t part,
-                                                  const uint32_t nparts, Stats &st) {
-    constexpr bool STATS = MODE == 1, LOG = MODE == 2;
-    const int32_t s = p.g.gsrc[r], d = p.g.gdst[r];
-    if (s == d) return;
-    if (part == 0) {
-        if (p.tree.root_q >= 0 && lane == 0) atomicAdd(&cnt[p.tree.root_q * p.tree.n_d], 1ull);
-        if constexpr (STATS) st.v[kStatRoots] += lane == 0 ? 1 : 0;
-        if constexpr (LOG) {
-            if (lane == 0) atomicAdd(&p.root_cost[r], 1ull);
-        }
-    }
-    if constexpr (D > 1) {
-        auto &A = lvl<1>(W.lv);
-        if (lane == 0) {
-            A.phi[0][0] = s;
-            A.phi[1][0] = d;
-            const TT t = p.g.gt[r];
-            A.tfirst[0] = t;
-            set_root_slot(W, 0, p.g.gx[r]);
-            A.root[0] = r;
-            A.live[0] = (uint8_t)root_live(p, r, sat_add(t, p.delta_sat));
-        }
-        wave_sync();
-        run_level<TT, D, MODE, 1>(p, W, cnt, lane, 1u, st, part, nparts);
-        wave_sync();
-    }
-}
+// A piece of work: roots [pos, end) of the root list (positions, or edge ids
+// when p.roots is NULL); with nparts > 1 part `part` of the search from the one
+// root `pos`; with ctx contexts [pos, end) of p.ctx_in (at most 64).
+struct Piece {
+    uint32_t pos, end, part, nparts;
+    bool ctx;
+};
 
-// Search from roots [base, end) of the root list (positions, or edge ids when
-// p.roots is NULL), 64 at a time.
-template <typename TT, int D, int MODE>
-__device__ __forceinline__ void process_roots(const KParams<TT> &p,
+// Searches the pieces that claim() hands out until it returns false.  Roots
+// with something live in their windows are gathered from one or more pieces
+// (with `gather`) until the level-1 batch is full, so that the passes below
+// run on full waves; split roots and contexts run on their own.
+template <typename TT, int D, int MODE, typename Claim>
+__device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                                               WaveLds<TT, D, keep_of(MODE)> &W,
                                               unsigned long long *cnt, const int lane,
-                                              const uint32_t base, const uint32_t end,
-                                              Stats &st) {
+                                              Claim claim, const bool gather, Stats &st) {
     constexpr bool STATS = MODE == 1, LOG = MODE == 2;
-    for (uint32_t b = base; b < end; b += kWave) {
-        const uint32_t i = b + (uint32_t)lane;
-        bool ok = i < end;
-        uint32_t r = 0;
-        int32_t s = 0, d = 0;
-        if (ok) {
-            r = p.roots ? p.roots[i] : i;
-            s = p.g.gsrc[r];
-            d = p.g.gdst[r];
-            ok = s != d;
-        }
-        const uint64_t all = __ballot(ok);
-        if (p.tree.root_q >= 0 && lane == 0 && all)
-            atomicAdd(&cnt[p.tree.root_q * p.tree.n_d], (unsigned long long)__popcll(all));
-        if constexpr (MODE == 4) {
-            if (p.tree.root_q >= 0) {
-                uint32_t e[kKMax] = {r, 0, 0, 0, 0};
-                write_matches(p, ok, (uint32_t)p.tree.root_q, e, 1);
+    Piece w{0, 0, 0, 1, false};
+    uint32_t n1 = 0;   // roots in the level-1 batch
+    for (;;) {
+        bool more = w.pos < w.end;
+        if (!more) more = claim(w);
+        const bool alone = more && (w.nparts > 1 || w.ctx);
+        bool run = !more || !gather || alone;
+        uint32_t part = 0, nparts = 1;
+        const EpochCtx *ctx = nullptr;
+        if (more && !(alone && n1 > 0)) {
+            if (epochs_of(MODE) && w.ctx) {
+                // each context becomes a root of the batch with its window
+                // and its root windows given
+                if constexpr (D > 1) {
+                    auto &A = lvl<1>(W.lv);
+                    const uint32_t i = w.pos + (uint32_t)lane;
+                    if (i < w.end) {
+                        const EpochCtx c = p.ctx_in[i];
+                        const TT t = (TT)(((uint64_t)c.t_hi << 32) | c.t_lo);
+                        A.phi[0][lane] = c.a;
+                        A.phi[1][lane] = c.b;
+                        A.tfirst[lane] = t;
+                        A.root[lane] = c.root;
+                        A.live[lane] = (uint8_t)root_live(p, c.root, sat_add(t, p.delta_sat));
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            W.hlo[k][lane] = c.hlo[k];
+                            W.hlen[k][lane] = c.hlen[k];
+                        }
+                    }
+                    ctx = p.ctx_in + w.pos;
+                    n1 = w.end - w.pos;
+                }
+                w.pos = w.end;
+            } else {
+                const uint32_t i = w.pos + (uint32_t)lane;
+                bool ok = i < w.end;
+                uint32_t r = 0;
+                int32_t s = 0, d = 0;
+                if (ok) {
+                    r = p.roots ? p.roots[i] : i;
+                    s = p.g.gsrc[r];
+                    d = p.g.gdst[r];
+                    ok = s != d;
+                }
+                uint32_t live = 0;
+                TT t = 0;
+                bool keep = D > 1 && ok;
+                if constexpr (D > 1) {
+                    if (ok) {
+                        t = p.g.gt[r];
+                        live = root_live(p, r, sat_add(t, p.delta_sat));
+                        // a root with nothing in its windows ends here (the
+                        // statistics still count its empty windows)
+                        if constexpr (!STATS)
+                            keep = ((root_bits(live) | (1u << kLiveAllBit)) &
+                                    (LOG ? p.tree.inode[0].y : p.tree.inode[0].z)) != 0;
+                    }
+                }
+                // as many as the batch has room for: the piece goes on at the
+                // first one left out
+                const uint64_t km = __ballot(keep);
+                const uint32_t slot = n1 + mbcnt(km);
+                const uint64_t over = __ballot(keep && slot >= (uint32_t)kWave);
+                const uint32_t took = over ? (uint32_t)__builtin_ctzll(over) : (uint32_t)kWave;
+                const bool mine = (uint32_t)lane < took;
+                if (w.part == 0) {
+                    const uint64_t all = __ballot(ok && mine);
+                    if (p.tree.root_q >= 0 && lane == 0 && all)
+                        atomicAdd(&cnt[p.tree.root_q * p.tree.n_d], (unsigned long long)__popcll(all));
+                    if constexpr (MODE == 4) {
+                        if (p.tree.root_q >= 0) {
+                            uint32_t e[kKMax] = {r, 0, 0, 0, 0};
+                            write_matches(p, ok && mine, (uint32_t)p.tree.root_q, e, 1);
+                        }
+                    }
+                    if constexpr (STATS) st.v[kStatRoots] += ok && mine ? 1 : 0;
+                    if constexpr (LOG) {
+                        if (ok && mine) atomicAdd(&p.root_cost[r], 1ull);
+                    }
+                }
+                if constexpr (D > 1) {
+                    auto &A = lvl<1>(W.lv);
+                    if (keep && mine) {
+                        A.phi[0][slot] = s;
+                        A.phi[1][slot] = d;
+                        A.tfirst[slot] = t;
+                        set_root_slot(W, slot, p.g.gx[r]);
+                        A.root[slot] = r;
+                        A.live[slot] = (uint8_t)live;
+                    }
+                    n1 += uniform((uint32_t)__popcll(km & (over ? (1ull << took) - 1ull : ~0ull)));
+                }
+                part = w.part;
+                nparts = w.nparts;
+                w.pos = min(w.pos + took, w.end);
+                run = run || n1 == (uint32_t)kWave;
             }
-        }
-        if constexpr (STATS) st.v[kStatRoots] += ok ? 1 : 0;
-        if constexpr (LOG) {
-            if (ok) atomicAdd(&p.root_cost[r], 1ull);
         }
         if constexpr (D > 1) {
-            auto &A = lvl<1>(W.lv);
-            uint32_t live = 0;
-            TT t = 0;
-            if (ok) {
-                t = p.g.gt[r];
-                live = root_live(p, r, sat_add(t, p.delta_sat));
-                // a root with nothing in its windows ends here (the
-                // statistics still count its empty windows)
-                if constexpr (!STATS)
-                    ok = ((root_bits(live) | (1u << kLiveAllBit)) &
-                          (LOG ? p.tree.inode[0].y : p.tree.inode[0].z)) != 0;
-            }
-            const uint64_t m = __ballot(ok);
-            if (ok) {
-                const uint32_t slot = mbcnt(m);
-                A.phi[0][slot] = s;
-                A.phi[1][slot] = d;
-                A.tfirst[slot] = t;
-                set_root_slot(W, slot, p.g.gx[r]);
-                A.root[slot] = r;
-                A.live[slot] = (uint8_t)live;
-            }
-            const uint32_t n1 = uniform((uint32_t)__popcll(m));
-            if (n1 > 0) {
+            if (run && n1 > 0) {
                 wave_sync();
-                run_level<TT, D, MODE, 1>(p, W, cnt, lane, n1, st);
+                run_level<TT, D, MODE, 1>(p, W, cnt, lane, 0u, n1, st, part, nparts, ctx);
                 wave_sync();
+                n1 = 0;
             }
         }
-    }
-}
-
-// Search contexts [base, end) of p.ctx_in (at most 64): each becomes a
-// root in the level-1 batch, with its window and its root windows given.
-template <typename TT, int D, int MODE>
-__device__ __forceinline__ void process_contexts(const KParams<TT> &p,
-                                                 WaveLds<TT, D, keep_of(MODE)> &W,
-                                                 unsigned long long *cnt, const int lane,
-                                                 const uint32_t base, const uint32_t end,
-                                                 Stats &st) {
-    if constexpr (D > 1) {
-        auto &A = lvl<1>(W.lv);
-        const uint32_t i = base + (uint32_t)lane;
-        if (i < end) {
-            const EpochCtx c = p.ctx_in[i];
-            const TT t = (TT)(((uint64_t)c.t_hi << 32) | c.t_lo);
-            A.phi[0][lane] = c.a;
-            A.phi[1][lane] = c.b;
-            A.tfirst[lane] = t;
-            A.root[lane] = c.root;
-            A.live[lane] = (uint8_t)root_live(p, c.root, sat_add(t, p.delta_sat));
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                W.hlo[k][lane] = c.hlo[k];
-                W.hlen[k][lane] = c.hlen[k];
-            }
-        }
-        wave_sync();
-        run_level<TT, D, MODE, 1>(p, W, cnt, lane, end - base, st, 0, 1, p.ctx_in + base);
-        wave_sync();
+        if (!more) break;
     }
 }
 
@@ -1414,7 +1459,7 @@ template <typename TT, int D, int MODE>
 __global__ void __launch_bounds__(kWave * kWavesPerBlock)
 __attribute__((amdgpu_waves_per_eu(min_waves_per_eu<D, MODE>(), 8)))
 comine_kernel(const KParams<TT> p) {
-    constexpr bool STATS = MODE == 1, LOG = MODE == 2;
+    constexpr bool STATS = MODE == 1;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned long long *cnt = reinterpret_cast<unsigned long long *>(smem);
     const int32_t n_slots = counter_slots(p.tree);
@@ -1435,87 +1480,88 @@ comine_kernel(const KParams<TT> p) {
     if (p.wave_clock && lane == 0 && clock_slot < p.n_wave_clock)
         p.wave_clock[2 * clock_slot] = __builtin_amdgcn_s_memrealtime();
 
-    if (p.items) {
-        // scheduled work items first, claimed in order from their own queue
-        const uint32_t n_items = uniform(*p.n_items);
-        for (;;) {
+    // Scheduled work items first, claimed in order from their own queue; in a
+    // later epoch the contexts the last one left, spread over every wave (up to
+    // 64 at a time); else the root queues.  Workgroups are dispatched to the
+    // XCDs round-robin: a wave starts on its XCD's share of the roots, then
+    // takes what is left of the others.  A chunk once claimed is always searched
+    // to the end, so after a stop the queue heads (clamped to the queue lengths)
+    // mark exactly the roots searched.
+    bool items = p.items != nullptr;
+    const uint32_t nq = p.n_queues;
+    const uint32_t home = blockIdx.x % nq;
+    uint32_t qi = 0;
+    auto claim = [&](Piece &w) -> bool {
+        if (st.dumped) return false;   // an epoch ended
+        if (items) {
             unsigned long long it = 0;
             if (lane == 0) it = atomicAdd(&p.queues[kItemSlot * kQueueStride], 1ull);
             it = lane0_u64(it);
-            if (it >= n_items) break;
-            const uint2 item = p.items[uniform((uint32_t)it)];
-            const uint32_t iy = uniform(item.y);
-            if (iy & kItemSplit)
-                process_root_part<TT, D, MODE>(p, W, cnt, lane, uniform(item.x),
-                                               (iy >> 15) & 0x7fffu, iy & 0x7fffu, st);
-            else
-                process_roots<TT, D, MODE>(p, W, cnt, lane, uniform(item.x), iy, st);
+            if (it < uniform(*p.n_items)) {
+                const uint2 item = p.items[uniform((uint32_t)it)];
+                const uint32_t ix = uniform(item.x), iy = uniform(item.y);
+                const bool split = (iy & kItemSplit) != 0;
+                w = {ix, split ? ix + 1 : iy, split ? (iy >> 15) & 0x7fffu : 0u,
+                     split ? iy & 0x7fffu : 1u, false};
+                return true;
+            }
+            items = false;
         }
-    }
-    bool from_ctx = false;
-    if constexpr (epochs_of(MODE)) {
-        if (p.ctx_in) {
-            // a later epoch: the contexts the last one left, spread over every
-            // wave (up to 64 at a time)
-            from_ctx = true;
-            const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
-            const uint32_t per = min((uint32_t)kWave, max(1u, (p.n_ctx_in + waves - 1) / waves));
-            for (;;) {
+        if constexpr (epochs_of(MODE)) {
+            if (p.ctx_in) {
+                const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
+                const uint32_t per = min((uint32_t)kWave, max(1u, (p.n_ctx_in + waves - 1) / waves));
                 unsigned long long it = 0;
                 if (lane == 0) it = atomicAdd(&p.queues[kItemSlot * kQueueStride], (unsigned long long)per);
                 it = lane0_u64(it);
-                if (it >= p.n_ctx_in) break;
+                if (it >= p.n_ctx_in) return false;
                 const uint32_t b0 = uniform((uint32_t)it);
-                process_contexts<TT, D, MODE>(p, W, cnt, lane, b0, min(b0 + per, p.n_ctx_in), st);
-                if (st.dumped) break;
+                w = {b0, (uint32_t)min(b0 + per, p.n_ctx_in), 0u, 1u, true};
+                return true;
             }
         }
-    }
-    if (!from_ctx) {
-        // workgroups are dispatched to the XCDs round-robin: start on this XCD's
-        // share of the roots, then take what is left of the others.  A chunk once
-        // claimed is always searched to the end, so after a stop the queue heads
-        // (clamped to the queue lengths) mark exactly the roots searched.
-        const uint32_t nq = p.n_queues;
-        const uint32_t home = blockIdx.x % nq;
-        bool stopped = false;
-        for (uint32_t qi = 0; qi < nq && !stopped; ++qi) {
+        while (qi < nq) {
             const uint32_t q = (home + qi) % nq;
             const uint32_t qbeg = queue_begin(p.n_roots, nq, q);
             const uint32_t qend = queue_end(p.n_roots, nq, q);
-            for (;;) {
-                unsigned long long got = 0;
-                if (lane == 0) {
-                    unsigned long long *head = &p.queues[q * kQueueStride];
-                    if (p.stop && __hip_atomic_load(p.stop, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_SYSTEM) != 0) {
+            unsigned long long got = 0;
+            if (lane == 0) {
+                unsigned long long *head = &p.queues[q * kQueueStride];
+                if (p.stop && __hip_atomic_load(p.stop, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_SYSTEM) != 0) {
+                    got = ~0ull;
+                } else if (p.max_chunks) {
+                    // the budget is spent only on a queue that still has roots,
+                    // so a call makes progress while any root is left: a
+                    // budget holder's claim fails only when another holder
+                    // took the last chunk
+                    const unsigned long long h =
+                        __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (h >= (unsigned long long)(qend - qbeg)) got = h;
+                    else if (atomicAdd(&p.queues[kBudgetSlot * kQueueStride], 1ull) >= p.max_chunks)
                         got = ~0ull;
-                    } else if (p.max_chunks) {
-                        // the budget is spent only on a queue that still has roots,
-                        // so a call makes progress while any root is left: a
-                        // budget holder's claim fails only when another holder
-                        // took the last chunk
-                        const unsigned long long h =
-                            __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if (h >= (unsigned long long)(qend - qbeg)) got = h;
-                        else if (atomicAdd(&p.queues[kBudgetSlot * kQueueStride], 1ull) >= p.max_chunks)
-                            got = ~0ull;
-                        else got = atomicAdd(head, (unsigned long long)p.chunk);
-                    } else {
-                        got = atomicAdd(head, (unsigned long long)p.chunk);
-                    }
+                    else got = atomicAdd(head, (unsigned long long)p.chunk);
+                } else {
+                    got = atomicAdd(head, (unsigned long long)p.chunk);
                 }
-                got = lane0_u64(got);
-                if (got == ~0ull) { stopped = true; break; }
-                if (got >= (unsigned long long)(qend - qbeg)) break;
-                const uint32_t base = uniform(qbeg + (uint32_t)got);
-                if (p.skip && p.skip[base / kWave]) continue;   // searched as an item
-                process_roots<TT, D, MODE>(p, W, cnt, lane, base, min(base + p.chunk, qend), st);
-                if (st.dumped) { stopped = true; break; }   // an epoch ended
             }
+            got = lane0_u64(got);
+            if (got == ~0ull) {
+                qi = nq;
+                break;
+            }
+            if (got >= (unsigned long long)(qend - qbeg)) {
+                ++qi;
+                continue;
+            }
+            const uint32_t b0 = uniform(qbeg + (uint32_t)got);
+            if (p.skip && p.skip[b0 / kWave]) continue;   // searched as an item
+            w = {b0, (uint32_t)min(b0 + p.chunk, qend), 0u, 1u, false};
+            return true;
         }
-
-    }
+        return false;
+    };
+    search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, true, st);
     if constexpr (epochs_of(MODE)) {
         // out of work: an idle wave, for the epoch limit
         if (p.ctx_out && !st.dumped && lane == 0) atomicAdd(p.idle, 1u);
@@ -1561,12 +1607,16 @@ batch_kernel(const BatchParams<TT> bp) {
         // window selection would otherwise put a copy in scratch memory
         auto search = [&](const KParams<TT> &p) {
             const uint32_t ip = uniform(item.part);
-            if (ip & kItemSplit)
-                process_root_part<TT, D, MODE>(p, W, cnt, lane, uniform(item.begin),
-                                               (ip >> 15) & 0x7fffu, ip & 0x7fffu, st);
-            else
-                process_roots<TT, D, MODE>(p, W, cnt, lane, uniform(item.begin), uniform(item.end),
-                                           st);
+            const bool split = (ip & kItemSplit) != 0;
+            bool fresh = true;
+            auto claim = [&](Piece &w) -> bool {
+                w = {uniform(item.begin), uniform(item.end), split ? (ip >> 15) & 0x7fffu : 0u,
+                     split ? ip & 0x7fffu : 1u, false};
+                const bool got = fresh && w.pos < w.end;
+                fresh = false;
+                return got;
+            };
+            search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, true, st);
         };
         const uint32_t nq = (uint32_t)counter_slots(job.p.tree);
         for (uint32_t i = (uint32_t)lane; i < nq; i += kWave) cnt[i] = 0;
