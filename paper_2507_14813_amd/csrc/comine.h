@@ -56,8 +56,12 @@ enum : int { kDirOut = 0, kDirIn = 1, kDirAll = 2 };
 //         to be found below the node when leaf windows are counted from pairs:
 //         the lists of its other groups and the pairs of those that are
 //     w = of a leaf parent: the lists whose window has to be found (bits 0-12:
-//         no pair codes, or a new-vertex child) and those with pair codes
-//         (bits 16-28)
+//         not counted from pairs, or with a new-vertex child) and the pairs
+//         that are counted (bits 16-23: kLivePair's bits)
+//   pairs[8 i + k]  of leaf parent i and pair k (matched edge k / 2, or against
+//     it for odd k): x = child reached by an edge of the pair, y and z = the
+//     new-vertex children of the out- and of the in-list that hold the pair,
+//     for which such an edge does not count
 //   grp[3g..3g+2]: twelve words of group g:
 //     w0 = dir | anchor << 4 | nv << 8 | leaf_only << 12 | last_end << 13 |
 //          bound_by << 15
@@ -67,11 +71,9 @@ enum : int { kDirOut = 0, kDirIn = 1, kDirAll = 2 };
 //          otherwise; bound_by: the same for the node's second edge)
 //     w1..w6 = child reached when the scanned endpoint is bound motif vertex 0..5
 //     w7 = child reached when the scanned endpoint(s) are new vertices
-//     w8 = pair codes, four bits per bound motif vertex y whose entries are
-//          counted: 1 + 2 j + r when matched edge j is the latest one that
-//          joins the anchor and y, in this list's direction (r 0) or against
-//          it (r 1); 0 = not counted.  0 as a whole when some counted vertex
-//          has no such edge: the window has to be scanned
+//     w8 = 1 when the entries that reach bound vertices are counted from pairs:
+//         every such vertex (all bound ones with a new-vertex child) is joined
+//         to the anchor by a matched edge
 //   A child word is 0 when there is no such child, else
 //     internal index (bits 0-15, if internal) | (query + 1) << 16 | internal << 31.
 // Counters: n_d per distinct motif, counter q * n_d + j holding the matches
@@ -80,6 +82,7 @@ enum : int { kDirOut = 0, kDirIn = 1, kDirAll = 2 };
 // slots 0..j.
 struct DevTree {
     const uint4 *inode;
+    const uint4 *pairs;
     const uint4 *grp;
     int32_t n_q;        // distinct motifs
     int32_t root_q;     // query id of the one-edge prefix, -1 if none
@@ -118,6 +121,8 @@ struct DevGraph {
     const uint4 *gp;              // per edge u -> v at t: the first pair entry with a
                                   // later time and the end of the pair u -> v, then of
                                   // v -> u (self-loops: 0)
+    const uint4 *out_gp;          // gp per out_adj entry, per in_adj entry
+    const uint4 *in_gp;
     const Next4<TT> *out_next;    // per out_adj entry u -> v: the next times of u -> v,
     const Next4<TT> *in_next;     // v -> u, out(v), in(v); per in_adj entry: of u -> v,
                                   // v -> u, out(u), in(u)

@@ -58,7 +58,7 @@ struct mg_graph {
     int time_bytes = 4;
     int device = 0;
     bool host_only = false;             // no device copy (MG_HOST_ONLY)
-    mgh::DevBuf gsrc, gdst, gt, gx, gn, gp, pair_t, out_next, in_next, out_eid, in_eid, out_off,
+    mgh::DevBuf gsrc, gdst, gt, gx, gn, gp, out_gp, in_gp, pair_t, out_next, in_next, out_eid, in_eid, out_off,
         out_adj, in_off, in_adj;
     mgh::DevBuf order;                  // u32 per edge: the caller's index (none: the same)
     int64_t device_bytes = 0;
@@ -77,12 +77,13 @@ struct mg_tree {
     std::vector<mgh::TrieNode> nodes;   // node 0 = prefix ((0,1))
     std::vector<int32_t> node_tab;      // 4 words per internal node
     std::vector<int32_t> grp_tab;       // 12 words per group
+    std::vector<int32_t> pair_tab;      // 32 words per internal node
     int32_t depth = 0, root_q = -1;
     int32_t kdepth = 0;    // depth of the kernel that searches it (DevTree::kdepth)
     mg_tree_info_t info{};
     // device copies
     int device = -1;
-    mgh::DevBuf d_node, d_grp;
+    mgh::DevBuf d_tab;                  // node_tab, grp_tab, pair_tab
     // per-motif chain trees (built on first per-motif count)
     std::vector<std::unique_ptr<mg_tree>> singles;
     // CPU backend: the generated and compiled search of this tree

@@ -98,7 +98,7 @@ void dev_free(DevBuf &b) {
 using namespace mgh;
 
 mg_graph::~mg_graph() {
-    for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &gn, &gp, &pair_t, &out_next, &in_next, &out_eid,
+    for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &gn, &gp, &out_gp, &in_gp, &pair_t, &out_next, &in_next, &out_eid,
                       &in_eid, &out_off, &out_adj, &in_off, &in_adj, &order})
         dev_free(*b);
 }
@@ -159,6 +159,7 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
         {&g->gsrc, sizeof(int32_t) * (size_t)E}, {&g->gdst, sizeof(int32_t) * (size_t)E},
         {&g->gt, sizeof(TT) * (size_t)E},        {&g->gx, sizeof(uint32_t) * 4 * (size_t)E},
         {&g->gn, sizeof(mg::Next4<TT>) * (size_t)E}, {&g->gp, sizeof(uint32_t) * 4 * (size_t)E},
+        {&g->out_gp, sizeof(uint32_t) * 4 * (size_t)A}, {&g->in_gp, sizeof(uint32_t) * 4 * (size_t)A},
         {&g->pair_t, sizeof(TT) * ((size_t)A + 4)},   // read four entries at a time
         {&g->out_next, sizeof(mg::Next4<TT>) * (size_t)A},
         {&g->in_next, sizeof(mg::Next4<TT>) * (size_t)A},
@@ -230,6 +231,7 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
         LAUNCH_TRY(mg::sort_pairs<uint32_t>(pk, pv, false, A, vb, sort_mem, &at, st));
         LAUNCH_TRY(mg::launch_pairs<TT>(dg, pv[at], A, opos, ipos, (int32_t *)ikey,
                                         (TT *)g->pair_t.ptr, (uint4 *)g->gp.ptr,
+                                        (uint4 *)g->out_gp.ptr, (uint4 *)g->in_gp.ptr,
                                         (mg::Next4<TT> *)g->out_next.ptr,
                                         (mg::Next4<TT> *)g->in_next.ptr, st));
     }
@@ -241,8 +243,7 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
 
 // ---------------------------------------------------------------- tree
 mg_tree::~mg_tree() {
-    dev_free(d_node);
-    dev_free(d_grp);
+    dev_free(d_tab);
     release_cpu_code(this);
 }
 
@@ -315,6 +316,7 @@ int build_tree(mg_tree *tr) {
     };
     tr->node_tab.assign(4 * (size_t)std::max(n_int, 1), 0);
     tr->grp_tab.clear();
+    tr->pair_tab.assign(32 * (size_t)std::max(n_int, 1), 0);
     tr->depth = 0;
     bool wide2 = false;   // an internal two-edge prefix on four vertices
     for (int n = 0; n < N; ++n) {
@@ -338,7 +340,7 @@ int build_tree(mg_tree *tr) {
         const int g0 = (int)tr->grp_tab.size() / 12;
         if (g0 + (int)groups.size() > (1 << 20))
             return fail(MG_EUNSUPPORTED, "too many child groups");
-        uint32_t lists = 0, gate = 0, by_pairs = 0, by_window = 0;
+        uint32_t lists = 0, gate = 0, pairs = 0, by_window = 0;
         for (auto &kv : groups) {
             const bool all = kv.first == (int)mg::kLiveAllBit;
             const int dir = all ? mg::kDirAll : kv.first & 1, anc = all ? 0 : kv.first >> 1;
@@ -373,29 +375,41 @@ int build_tree(mg_tree *tr) {
             // a leaf window's count is known from the pairs of its anchor with
             // the counted vertices (with a new-vertex child, all bound ones)
             // when each is joined to the anchor by a matched edge
-            uint32_t codes = 0, pair_bits = 0;
+            std::vector<std::pair<int, int>> by;   // (pair, vertex) counted
             bool known = leaf_only;
             for (int y = 0; y < nd.nv && known; ++y) {
                 if (y == anc || !(counted[y] || rec[7])) continue;
-                int code = 0;
-                for (size_t j = 0; j < path.size(); ++j) {
+                int pair = -1;
+                for (size_t j = 0; j < path.size(); ++j) {   // the latest such edge
                     // the list's entries run from the anchor (out) or to it (in)
                     const std::pair<int, int> with =
                         dir == mg::kDirOut ? std::make_pair(anc, y) : std::make_pair(y, anc);
-                    if (path[j] == with) code = 1 + 2 * (int)j;
+                    if (path[j] == with) pair = 2 * (int)j;
                     else if (path[j].first == with.second && path[j].second == with.first)
-                        code = 2 + 2 * (int)j;
+                        pair = 2 * (int)j + 1;
                 }
-                known = code != 0;
-                codes |= (uint32_t)code << (4 * y);
-                if (code) pair_bits |= 1u << (mg::kLivePair + (uint32_t)code - 1);
+                known = pair >= 0;
+                by.push_back({pair, y});
             }
-            if (!known) codes = 0;
-            rec[8] = (int32_t)codes;
+            uint32_t codes = 0;   // the pairs, when all are known
+            for (auto &x : by) codes |= known ? 1u << x.first : 0u;
+            rec[8] = codes ? 1 : 0;
+            pairs |= codes;
+            if (codes)
+                for (auto &x : by) {
+                    // each pair is in the out-list of its source and the
+                    // in-list of its destination
+                    int32_t *w = &tr->pair_tab[32 * (size_t)iidx[n] + 4 * x.first];
+                    if (dir == mg::kDirOut) {
+                        w[0] = rec[1 + x.second];
+                        w[1] = rec[7];
+                    } else {
+                        w[2] = rec[7];
+                    }
+                }
             lists |= 1u << kv.first;
-            if (codes) by_pairs |= 1u << kv.first;
             if (!codes || rec[7]) by_window |= 1u << kv.first;
-            gate |= codes && !rec[7] ? pair_bits : 1u << kv.first;
+            gate |= codes && !rec[7] ? codes << mg::kLivePair : 1u << kv.first;
             tr->grp_tab.insert(tr->grp_tab.end(), rec, rec + 12);
         }
         // a leaf parent: every match below it is one more edge on a list of
@@ -409,7 +423,7 @@ int build_tree(mg_tree *tr) {
         w[0] = (int32_t)((uint32_t)g0 | (leaf_parent ? mg::kLeafParent : 0u));
         w[1] = (int32_t)lists;
         w[2] = (int32_t)(leaf_parent ? gate : lists);
-        w[3] = (int32_t)(leaf_parent ? by_window | by_pairs << 16 : 0u);
+        w[3] = (int32_t)(leaf_parent ? by_window | pairs << 16 : 0u);
     }
     if (tr->grp_tab.empty()) tr->grp_tab.assign(12, 0);
     tr->root_q = tr->nodes[0].q;
@@ -497,17 +511,15 @@ void map_counts(const mg_tree *tr, const uint64_t *slots, uint64_t *out) {
 size_t n_slots(const mg_tree *tr) { return tr->distinct.size() * tr->deltas.size(); }
 
 int upload_tree(mg_tree *tr, int device, hipStream_t st) {
-    if (tr->device == device && tr->d_node.ptr) return MG_OK;
-    dev_free(tr->d_node);
-    dev_free(tr->d_grp);
-    int rc = dev_alloc(tr->d_node, tr->node_tab.size() * 4, (void *)st);
+    if (tr->device == device && tr->d_tab.ptr) return MG_OK;
+    dev_free(tr->d_tab);
+    std::vector<int32_t> all;
+    for (const std::vector<int32_t> *t : {&tr->node_tab, &tr->grp_tab, &tr->pair_tab})
+        all.insert(all.end(), t->begin(), t->end());
+    int rc = dev_alloc(tr->d_tab, all.size() * 4, (void *)st);
     if (rc) return rc;
-    rc = dev_alloc(tr->d_grp, tr->grp_tab.size() * 4, (void *)st);
-    if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(tr->d_node.ptr, tr->node_tab.data(), tr->node_tab.size() * 4,
-                           hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(tr->d_grp.ptr, tr->grp_tab.data(), tr->grp_tab.size() * 4,
-                           hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(tr->d_tab.ptr, all.data(), all.size() * 4, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));   // `all` is released on return
     tr->device = device;
     return MG_OK;
 }
@@ -707,6 +719,8 @@ mg::DevGraph<TT> dev_graph(const mg_graph *g) {
     d.gx = (const uint4 *)g->gx.ptr;
     d.gn = (const mg::Next4<TT> *)g->gn.ptr;
     d.gp = (const uint4 *)g->gp.ptr;
+    d.out_gp = (const uint4 *)g->out_gp.ptr;
+    d.in_gp = (const uint4 *)g->in_gp.ptr;
     d.pair_t = (const TT *)g->pair_t.ptr;
     d.out_next = (const mg::Next4<TT> *)g->out_next.ptr;
     d.in_next = (const mg::Next4<TT> *)g->in_next.ptr;
@@ -722,8 +736,9 @@ mg::DevGraph<TT> dev_graph(const mg_graph *g) {
 
 mg::DevTree dev_tree(const mg_tree *tr) {
     mg::DevTree t{};
-    t.inode = (const uint4 *)tr->d_node.ptr;
-    t.grp = (const uint4 *)tr->d_grp.ptr;
+    t.inode = (const uint4 *)tr->d_tab.ptr;
+    t.grp = t.inode + tr->node_tab.size() / 4;
+    t.pairs = t.grp + tr->grp_tab.size() / 4;
     t.n_q = (int32_t)tr->distinct.size();
     t.root_q = tr->root_q;
     t.depth = tr->depth;
@@ -1656,7 +1671,7 @@ int mg_count_noalloc(const mg_graph *g, const mg_tree *tr, const mg_count_opts *
         HIP_TRY(hipGetDevice(&dev));
         if (dev != g->device) return fail(MG_EINVAL, "graph lives on device %d, current is %d",
                                           g->device, dev);
-        if (tr->device != dev || !tr->d_node.ptr)
+        if (tr->device != dev || !tr->d_tab.ptr)
             return fail(MG_EINVAL, "the tree has no device tables on device %d yet (count it "
                                    "with mg_count there once)", dev);
         unsigned long long *scr = nullptr;

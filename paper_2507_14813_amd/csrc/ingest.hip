@@ -349,8 +349,8 @@ pair_entries(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, int32_t *
 template <typename TT>
 __global__ void __launch_bounds__(kIB)
 pair_links(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, const uint32_t *opos,
-           const uint32_t *ipos, const int32_t *psrc, const TT *pair_t, uint4 *gp,
-           Next4<TT> *out_next, Next4<TT> *in_next) {
+           const uint32_t *ipos, const int32_t *psrc, const TT *pair_t, uint4 *gp, uint4 *out_gp,
+           uint4 *in_gp, Next4<TT> *out_next, Next4<TT> *in_next) {
     for (uint64_t j = blockIdx.x * (uint64_t)kIB + threadIdx.x; j < n_adj;
          j += gridDim.x * (uint64_t)kIB) {
         const uint32_t e = pe[j];
@@ -366,17 +366,20 @@ pair_links(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, const uint3
             p.z = first_greater(pair_t, 0, r0, r1, t);
             p.w = r1;
         }
+        const uint32_t op = opos[e], ip = ipos[e];
         gp[e] = p;
+        out_gp[op] = p;
+        in_gp[ip] = p;
         const Next4<TT> n = g.gn[e];
         Next4<TT> o;
         o.a = p.x < p.y ? pair_t[p.x] : kNever<TT>;
         o.b = p.z < p.w ? pair_t[p.z] : kNever<TT>;
         o.c = n.c;
         o.d = n.d;
-        out_next[opos[e]] = o;
+        out_next[op] = o;
         o.c = n.a;
         o.d = n.b;
-        in_next[ipos[e]] = o;
+        in_next[ip] = o;
     }
 }
 
@@ -479,12 +482,13 @@ hipError_t launch_gather(const uint32_t *eid, const int32_t *key_of, uint32_t n,
 template <typename TT>
 hipError_t launch_pairs(const DevGraph<TT> &g, const uint32_t *pe, uint32_t n_adj,
                         const uint32_t *opos, const uint32_t *ipos, int32_t *psrc, TT *pair_t,
-                        uint4 *gp, Next4<TT> *out_next, Next4<TT> *in_next, hipStream_t st) {
+                        uint4 *gp, uint4 *out_gp, uint4 *in_gp, Next4<TT> *out_next,
+                        Next4<TT> *in_next, hipStream_t st) {
     if (n_adj == 0) return hipSuccess;
     const dim3 grid(grid_for(n_adj, kIB));
     hipLaunchKernelGGL(pair_entries<TT>, grid, dim3(kIB), 0, st, g, pe, n_adj, psrc, pair_t);
     hipLaunchKernelGGL(pair_links<TT>, grid, dim3(kIB), 0, st, g, pe, n_adj, opos, ipos, psrc,
-                       pair_t, gp, out_next, in_next);
+                       pair_t, gp, out_gp, in_gp, out_next, in_next);
     return hipGetLastError();
 }
 
@@ -506,7 +510,8 @@ template hipError_t sort_pairs<uint64_t>(uint64_t *const[2], uint32_t *const[2],
                                          const uint32_t *, uint4 *, Next4<TT> *, hipStream_t);    \
     template hipError_t launch_pairs<TT>(const DevGraph<TT> &, const uint32_t *, uint32_t,        \
                                          const uint32_t *, const uint32_t *, int32_t *, TT *,     \
-                                         uint4 *, Next4<TT> *, Next4<TT> *, hipStream_t);
+                                         uint4 *, uint4 *, uint4 *, Next4<TT> *, Next4<TT> *,     \
+                                         hipStream_t);
 MG_INGEST(uint32_t)
 MG_INGEST(uint64_t)
 #undef MG_INGEST

@@ -63,6 +63,24 @@ namespace {
 
 constexpr uint32_t kChunkLimit = 0x7fffffffu;   // candidates per window chunk
 
+// Kernel parameters stay in constant memory and are read where they are used:
+// there are more of them than scalar registers, and kept there from the start
+// they were spilled and fetched back lane by lane in the inner loops.  fresh()
+// hides where a reference comes from, so that nothing read through an earlier
+// one is kept; pointers read this way are marked as global memory by glb().
+template <typename TT>
+using ConstParams = const __attribute__((address_space(4))) KParams<TT> *;
+template <typename TT>
+__device__ __forceinline__ const KParams<TT> &fresh(const KParams<TT> &p) {
+    ConstParams<TT> a = (ConstParams<TT>)&p;
+    asm volatile("" : "+s"(a));
+    return *(const KParams<TT> *)a;
+}
+template <typename T>
+__device__ __forceinline__ T *glb(T *x) {
+    return (T *)(__attribute__((address_space(1))) T *)x;
+}
+
 // child word of a group for scanned-endpoint index y (0..5 bound, else new)
 __device__ __forceinline__ uint32_t child_word(const uint4 &a, const uint4 &b, int y) {
     uint32_t r = b.w;             // new vertex
@@ -178,10 +196,10 @@ __device__ __forceinline__ uint32_t leaf_scan_wave(const KParams<TT> &p, const i
                                                    uint32_t g, uint32_t l0, uint32_t len,
                                                    const int lane, unsigned long long *cnt,
                                                    uint32_t nd, uint32_t j, bool move = false) {
-    const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
+    const uint4 ga = glb(p.tree.grp)[3 * g], gb = glb(p.tree.grp)[3 * g + 1];
     const uint32_t nvp = (ga.x >> 8) & 15;
     const Entry<TT> *__restrict__ e =
-        ((ga.x & 15) == kDirOut ? p.g.out_adj : p.g.in_adj) + l0;
+        ((ga.x & 15) == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj)) + l0;
     int32_t q[SA];
     uint32_t c[SA];
 #pragma unroll
@@ -226,10 +244,10 @@ __device__ __forceinline__ uint32_t leaf_scan_wave_multi(const KParams<TT> &p,
                                                          uint32_t l0, uint32_t len, TT tf,
                                                          const int lane, unsigned long long *cnt,
                                                          uint32_t nd) {
-    const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
+    const uint4 ga = glb(p.tree.grp)[3 * g], gb = glb(p.tree.grp)[3 * g + 1];
     const uint32_t nvp = (ga.x >> 8) & 15;
     const Entry<TT> *__restrict__ e =
-        ((ga.x & 15) == kDirOut ? p.g.out_adj : p.g.in_adj) + l0;
+        ((ga.x & 15) == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj)) + l0;
     int32_t q[SA];
     uint32_t c[SA];
 #pragma unroll
@@ -387,13 +405,13 @@ __device__ __forceinline__ void set_root_slot(WaveLds<TT, D, R> &W, uint32_t slo
 // and b -> a.
 template <typename TT>
 __device__ __forceinline__ uint32_t root_live(const KParams<TT> &p, uint32_t e, TT thi) {
-    const Next4<TT> n = p.g.gn[e];
-    const uint4 pr = p.g.gp[e];
+    const Next4<TT> n = glb(p.g.gn)[e];
+    const uint4 pr = glb(p.g.gp)[e];
     uint32_t r = (n.a <= thi ? 1u : 0u) | (n.b <= thi ? 2u : 0u) | (n.c <= thi ? 4u : 0u) |
                  (n.d <= thi ? 8u : 0u);
     // a -> b again: an entry of out(a) and of in(b); b -> a: of in(a) and out(b)
-    if ((r & 9u) == 9u && pr.x < pr.y && p.g.pair_t[pr.x] <= thi) r |= 16u;
-    if ((r & 6u) == 6u && pr.z < pr.w && p.g.pair_t[pr.z] <= thi) r |= 32u;
+    if ((r & 9u) == 9u && pr.x < pr.y && glb(p.g.pair_t)[pr.x] <= thi) r |= 16u;
+    if ((r & 6u) == 6u && pr.z < pr.w && glb(p.g.pair_t)[pr.z] <= thi) r |= 32u;
     return r;
 }
 // the same as live-word bits
@@ -466,7 +484,7 @@ __device__ __forceinline__ uint32_t count_leaf_window(const KParams<TT> &p, uint
     constexpr int NQ = S - 1;
     const uint32_t anc = (hdr >> 4) & 15;
     const uint32_t nq = ((hdr >> 8) & 15) - 1u;   // bound vertices, the anchor left out
-    const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
+    const uint4 ga = glb(p.tree.grp)[3 * g], gb = glb(p.tree.grp)[3 * g + 1];
     const uint32_t words[6] = {ga.y, ga.z, ga.w, gb.x, gb.y, gb.z};
     int32_t q[NQ];
     uint32_t w[NQ];
@@ -477,7 +495,7 @@ __device__ __forceinline__ uint32_t count_leaf_window(const KParams<TT> &p, uint
         q[i] = on ? (below ? ph[i] : ph[i + 1]) : -1;
         w[i] = on ? (below ? words[i] : words[i + 1]) : 0u;
     }
-    const Entry<TT> *adj = (hdr & 15) == kDirOut ? p.g.out_adj : p.g.in_adj;
+    const Entry<TT> *adj = (hdr & 15) == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj);
     // loads per step (measured: 8 for trees up to depth 4, 4 deeper)
     constexpr int kLU = D <= 4 ? 8 : 4;
     auto count = [&](uint32_t n, uint32_t j, bool move) -> uint32_t {
@@ -572,46 +590,43 @@ __device__ __forceinline__ void uncredit_child(uint32_t word, uint32_t c, unsign
     if (move) atomicAdd(&cnt[(q1 - 1) * nd + j + 1], (unsigned long long)c);
 }
 
-// Counts the groups of a leaf parent's lists in `lists` (all with pair codes)
-// by pairs.  The window of such a group needs no look at its entries: its edges
-// between the anchor and a bound vertex are the later edges of a pair that some
-// matched edge belongs to, consecutive in the pair order and found from that
-// edge.  (On 2M edges and the 36 three-edge motifs, such windows held 99.7 % of
-// the entries of all leaf windows, mostly the bursts of a hub scanned once per
-// entry of the burst; on 1M edges and 756 motifs of up to four edges 98 %.)  A
-// new-vertex child gets the window's length, credited by count_leaf_parent,
-// less the pairs, taken off here.  node: the node's words, eid_of(j): matched
-// edge j, tp: the last edge's time, tf and thi: the window.
-template <typename TT, int MODE, typename EidOf>
+// Counts what pairs can count below a leaf parent.  Where every vertex a leaf
+// window counts is joined to its anchor by a matched edge, the window needs no
+// look at its entries: its edges between the anchor and a bound vertex are the
+// later edges of that matched edge's pair, consecutive in the pair order and
+// found from the edge.  (On 2M edges and the 36 three-edge motifs, such windows
+// held 99.7 % of the entries of all leaf windows, mostly the bursts of a hub
+// scanned once per entry of the burst; on 1M edges and 756 motifs of up to four
+// edges 98 %.)  A new-vertex child gets the window's length, credited by
+// count_leaf_parent, less the pairs, taken off here.  pairs: the live pairs the
+// node counts (its edge 2 j, or 2 j + 1 against it), tab: its pair words,
+// pair_of(k): the first later entry and the end of pair k, tp: the last edge's
+// time, tf and thi: the window.
+template <typename TT, int MODE, typename PairOf>
 __device__ __forceinline__ void count_pairs(const KParams<TT> &p, unsigned long long *cnt,
-                                            const uint4 node, uint32_t lists, uint32_t live,
-                                            EidOf eid_of, TT tp, TT tf, TT thi, uint32_t nd) {
-    for (; lists; lists &= lists - 1) {
-        const uint32_t bit = (uint32_t)__builtin_ctz(lists);
-        const uint32_t g = (node.x & 0xfffffu) + (uint32_t)__popc(node.y & ((1u << bit) - 1u));
-        const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
-        for (uint32_t c = p.tree.grp[3 * g + 2].x; c;) {
-            const uint32_t sh = (uint32_t)__builtin_ctz(c) & ~3u, code = (c >> sh) & 15u;
-            c &= ~(15u << sh);
-            if (!((live >> (kLivePair - 1u + code)) & 1u)) continue;
-            const uint32_t ej = eid_of((code - 1u) >> 1);
-            const uint2 pr = reinterpret_cast<const uint2 *>(p.g.gp)[2 * (size_t)ej + ((code - 1u) & 1u)];
-            const uint32_t word = child_word(ga, gb, (int)(sh >> 2));
-            if constexpr (single_of(MODE)) {
-                const uint32_t n = pair_count(p.g.pair_t, pr.x, pr.y, tp, thi);
-                credit_child(word, n, cnt, 1u, 0u);
-                uncredit_child(gb.w, n, cnt, 1u, 0u);
-            } else {
-                const uint32_t lo = gallop_greater(p.g.pair_t, 0, pr.x, pr.y, tp);
-                uint32_t e = gallop_greater(p.g.pair_t, 0, lo, pr.y, thi);
-                credit_child(word, e - lo, cnt, nd, nd - 1);
-                uncredit_child(gb.w, e - lo, cnt, nd, nd - 1);
-                for (uint32_t k = nd - 1; k-- > 0;) {
-                    e = first_greater(p.g.pair_t, 0, lo, e, sat_add(tf, window_lo(p, k)));
-                    if (e == lo) break;
-                    credit_child(word, e - lo, cnt, nd, k, true);
-                    uncredit_child(gb.w, e - lo, cnt, nd, k, true);
-                }
+                                            uint32_t pairs, const uint4 *__restrict__ tab,
+                                            PairOf pair_of, TT tp, TT tf, TT thi, uint32_t nd) {
+    for (; pairs; pairs &= pairs - 1) {
+        const uint32_t k = (uint32_t)__builtin_ctz(pairs);
+        const uint2 pr = pair_of(k);
+        if constexpr (single_of(MODE)) {
+            const uint32_t n = pair_count(glb(p.g.pair_t), pr.x, pr.y, tp, thi);
+            if (n) {
+                const uint4 w = tab[k];
+                credit_child(w.x, n, cnt, 1u, 0u);
+                uncredit_child(w.y, n, cnt, 1u, 0u);
+                uncredit_child(w.z, n, cnt, 1u, 0u);
+            }
+        } else {
+            const uint32_t lo = gallop_greater(glb(p.g.pair_t), 0, pr.x, pr.y, tp);
+            uint32_t e = gallop_greater(glb(p.g.pair_t), 0, lo, pr.y, thi);
+            const uint4 w = tab[k];
+            for (uint32_t j = nd; j-- > 0 && e != lo;) {
+                const bool move = j + 1 < nd;
+                if (move) e = first_greater(glb(p.g.pair_t), 0, lo, e, sat_add(tf, window_lo(p, j)));
+                credit_child(w.x, e - lo, cnt, nd, j, move);
+                uncredit_child(w.y, e - lo, cnt, nd, j, move);
+                uncredit_child(w.z, e - lo, cnt, nd, j, move);
             }
         }
     }
@@ -644,8 +659,8 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
             todo &= todo - 1;
             const uint32_t g = g0 + (uint32_t)__popc(lists & ((1u << bit) - 1u));
             const uint32_t dir = bit & 1u, anc = bit >> 1;
-            const uint4 ga = p.tree.grp[3 * g], gb = p.tree.grp[3 * g + 1];
-            const uint32_t hdr = ga.x, codes = p.tree.grp[3 * g + 2].x;
+            const uint4 ga = glb(p.tree.grp)[3 * g], gb = glb(p.tree.grp)[3 * g + 1];
+            const uint32_t hdr = ga.x, codes = glb(p.tree.grp)[3 * g + 2].x;
             // The out-list of a later vertex x whose children all end on a root
             // vertex (a or b; no new vertex): the edges x -> a and x -> b in the
             // window are also the entries equal to x in the windows of in(a)
@@ -662,7 +677,7 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                         swap = true;
 #pragma unroll
                         for (int t = 0; t < S; ++t) sw_x |= ph[t] & -(int32_t)(anc == (uint32_t)t);
-                        const TT *tin = times_of(p.g.in_adj);
+                        const TT *tin = times_of(glb(p.g.in_adj));
 #pragma unroll
                         for (int sv = 0; sv < 2; ++sv) {
                             sw_word[sv] = sv ? ga.z : ga.y;
@@ -683,7 +698,7 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                     if (sw_hi[sv] > sw_lo[sv]) {
                         const int32_t q1[1] = {sw_x};
                         const uint32_t w1[1] = {sw_word[sv]};
-                        leaf_count<kLU, 1>(p.g.in_adj, sw_lo[sv], sw_hi[sv] - sw_lo[sv], q1, w1, 0u,
+                        leaf_count<kLU, 1>(glb(p.g.in_adj), sw_lo[sv], sw_hi[sv] - sw_lo[sv], q1, w1, 0u,
                                            cnt, 1u, 0u);
                     }
                 }
@@ -692,7 +707,7 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                 count_swapped();
                 continue;
             }
-            const Entry<TT> *adj = dir == kDirOut ? p.g.out_adj : p.g.in_adj;
+            const Entry<TT> *adj = dir == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj);
             const TT *ta = times_of(adj);
             uint32_t b = 0, e = 0, l0;
             bool hinted = false;
@@ -701,7 +716,7 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
             int32_t a = 0;
 #pragma unroll
             for (int t = 0; t < S; ++t) a |= ph[t] & -(int32_t)(anc == (uint32_t)t);
-            const uint32_t *off = dir == kDirOut ? p.g.out_off : p.g.in_off;
+            const uint32_t *off = dir == kDirOut ? glb(p.g.out_off) : glb(p.g.in_off);
             if (D > 2 && anc < 2) hinted = root_window(W, off, a, bit, r1, b, e);
             else { b = off[a]; e = off[a + 1]; }
             const uint32_t le = (hdr >> 13) & 3u;
@@ -711,7 +726,7 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                 // the list of an endpoint of the last edge: its rank is kept;
                 // of the second edge: the window starts no earlier than there
                 const uint32_t k = ((le ? le : be) == 1 ? 0u : 2u) + dir;
-                l0 = reinterpret_cast<const uint32_t *>(p.g.gx)[4 * (size_t)(le ? eid : eid2) + k];
+                l0 = reinterpret_cast<const uint32_t *>(glb(p.g.gx))[4 * (size_t)(le ? eid : eid2) + k];
                 if (!le) l0 = gallop_greater(ta, 1, l0, e, tp);
             } else {
                 l0 = first_greater(ta, 1, b, e, tp);
@@ -774,12 +789,13 @@ struct Stats {
 // partition its search exactly; windows that a single lane counts, and the
 // root's window statistics, belong to part 0.
 template <typename TT, int D, int MODE, int L>
-__device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, keep_of(MODE)> &W,
+__device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, keep_of(MODE)> &W,
                                           unsigned long long *cnt, const int lane,
                                           const uint32_t base, const uint32_t nA, Stats &st,
                                           const uint32_t part = 0, const uint32_t nparts = 1,
                                           const EpochCtx *ctx = nullptr) {
     constexpr bool STATS = MODE == 1, LOG = MODE == 2;
+    const KParams<TT> &p = fresh(p0);
     auto &A = lvl<L>(W.lv);
     constexpr int SA = vslots(D, L);
     auto &R1 = lvl<1>(W.lv);
@@ -796,8 +812,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
         if constexpr (L == 1) return A.tfirst[i];
         else return R1.tfirst[A.live[i] >> kLiveSlot];
     };
-    const uint4 *__restrict__ inode = p.tree.inode;
-    const uint4 *__restrict__ grp = p.tree.grp;
+    const uint4 *__restrict__ inode = glb(p.tree.inode);
     const uint64_t le_mask = (lane == 63) ? ~0ull : ((2ull << lane) - 1);
     // windows counted at once (MODE 0 serves trees with one window only)
     const uint32_t nd = single_of(MODE) ? 1u : (uint32_t)p.tree.n_d;
@@ -820,7 +835,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                 for (int t = 0; t < SA; ++t) ph[t] = counted ? vtx(t, x) : -1;
                 if (counted) {
                     eid = A.eid[x];
-                    tp = p.g.gt[eid];
+                    tp = glb(p.g.gt)[eid];
                     tf = tfirst_of(x);
                     live = A.live[x];
                     if constexpr (L == 3) eid2 = A.eid2[x];
@@ -884,6 +899,9 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
 
     bool done = false;
     for (;;) {
+        const KParams<TT> &p = fresh(p0);
+        const uint4 *__restrict__ inode = glb(p.tree.inode);
+        const uint4 *__restrict__ grp = glb(p.tree.grp);
         if constexpr (L == 1 && epochs_of(MODE)) {
             // (a wave dumps in one batch at most: the later batches of its
             // chunk search on)
@@ -950,7 +968,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                         const TT *ta;
                         bool hinted = false, known = false;
                         if (dir == kDirAll) {
-                            b = 0; e = p.g.n_edges; ta = p.g.gt; sh = 0;
+                            b = 0; e = p.g.n_edges; ta = glb(p.g.gt); sh = 0;
                             all = true;
                             if constexpr (L > 1) {
                                 // the whole-list window starts after the last edge
@@ -958,10 +976,10 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                                 b = A.eid[lo] + 1u;
                             }
                         } else {
-                            ta = times_of(dir == kDirOut ? p.g.out_adj : p.g.in_adj);
+                            ta = times_of(dir == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj));
                             sh = 1;
                             const int32_t a = vtx((uint32_t)anc, lo);
-                            const uint32_t *off = dir == kDirOut ? p.g.out_off : p.g.in_off;
+                            const uint32_t *off = dir == kDirOut ? glb(p.g.out_off) : glb(p.g.in_off);
                             if (L > 1 && D > 2 && anc < 2) {
                                 hinted = root_window(W, off, a, (uint32_t)anc * 2u + (uint32_t)dir,
                                                      L > 1 ? slot_of(lo) : 0u, b, e);
@@ -979,7 +997,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                                 // starts where that edge's time ends in its list
                                 const uint32_t le = (hdr >> 13) & 3u;
                                 if (le) {
-                                    const uint4 gx = p.g.gx[A.eid[lo]];
+                                    const uint4 gx = glb(p.g.gx)[A.eid[lo]];
                                     l0 = le == 1 ? (dir == kDirOut ? gx.x : gx.y)
                                                  : (dir == kDirOut ? gx.z : gx.w);
                                     known = true;
@@ -989,7 +1007,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                         if (!known) {
                             TT tp;
                             if constexpr (L == 1) tp = A.tfirst[lo];
-                            else tp = p.g.gt[A.eid[lo]];
+                            else tp = glb(p.g.gt)[A.eid[lo]];
                             l0 = all && L > 1 ? gallop_greater(ta, sh, b, e, tp)
                                               : first_greater(ta, sh, b, e, tp);
                         }
@@ -1144,6 +1162,9 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             }
         }
         if (!done && cc < T) {
+            const KParams<TT> &p = fresh(p0);
+            const uint4 *__restrict__ inode = glb(p.tree.inode);
+            const uint4 *__restrict__ grp = glb(p.tree.grp);
             const uint32_t f = cc + lane;
             // owner window = number of windows that end at or before f
             const uint32_t o0 = (uint32_t)__popcll(__ballot((uint32_t)lane < nw && wrec.w <= cc));
@@ -1180,7 +1201,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
 #pragma unroll
                 for (int s = 0; s < SA; ++s) ph[s] = vtx(s, ox);
                 if (dir != kDirAll) {
-                    const Entry<TT> *adj = dir == kDirOut ? p.g.out_adj : p.g.in_adj;
+                    const Entry<TT> *adj = dir == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj);
                     const Entry<TT> en = adj[ei];   // one load: vertex and time
                     const int32_t v = en.v;
                     tn = en.t;
@@ -1195,7 +1216,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             }
             if (__ballot(valid && dir == kDirAll)) {
                 if (valid && dir == kDirAll) {
-                    const int32_t cs = p.g.gsrc[ei], cd = p.g.gdst[ei];
+                    const int32_t cs = glb(p.g.gsrc)[ei], cd = glb(p.g.gdst)[ei];
                     bool hit = cs == cd;
 #pragma unroll
                     for (int s = 0; s < SA; ++s)
@@ -1203,7 +1224,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                     cw = hit ? 0u : gb.w;
                     nv0 = cs;
                     nv1 = cd;
-                    tn = p.g.gt[ei];
+                    tn = glb(p.g.gt)[ei];
                 }
             }
             if (cw) {
@@ -1217,7 +1238,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
             // the edge id of this candidate (pushed along, and written out
             // when enumerating), read only where it is used
             auto cand_eid = [&]() -> uint32_t {
-                return dir == kDirAll ? ei : (dir == kDirOut ? p.g.out_eid : p.g.in_eid)[ei];
+                return dir == kDirAll ? ei : (dir == kDirOut ? glb(p.g.out_eid) : glb(p.g.in_eid))[ei];
             };
             if constexpr (MODE == 4) {
                 const uint32_t q1 = (cw >> 16) & 0x7fffu;
@@ -1240,7 +1261,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                     if (dir == kDirAll) {
                         live |= (15u << (2 * nvp)) | (3u << (kLivePair + 2 * L));
                     } else {
-                        const Next4<TT> nx = (dir == kDirOut ? p.g.out_next : p.g.in_next)[ei];
+                        const Next4<TT> nx = (dir == kDirOut ? glb(p.g.out_next) : glb(p.g.in_next))[ei];
                         const TT thi = sat_add(tfirst_of(ox), p.delta_sat);
                         live &= ~(3u << (2 * hit_s));
                         live |= (nx.c <= thi ? 1u : 0u) << (2 * hit_s);
@@ -1259,21 +1280,25 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                     // to look at (2 % of them on a bursty graph) is kept
                     if constexpr (plain_of(MODE)) {
                         if (direct && push && (nw.x & kLeafParent)) {
-                            auto eid_of = [&](uint32_t j) -> uint32_t {
-                                uint32_t e = 0;
-                                if (j == (uint32_t)L) return cand_eid();
-                                if constexpr (L == 1) {
+                            auto pair_of = [&](uint32_t k) -> uint2 {
+                                const uint32_t j = k >> 1;
+                                const uint4 *gp = glb(p.g.gp);
+                                uint32_t e = ei;
+                                if (j == (uint32_t)L) {
+                                    gp = dir == kDirOut ? glb(p.g.out_gp) : dir == kDirIn ? glb(p.g.in_gp) : gp;
+                                } else if constexpr (L == 1) {
                                     e = A.root[ox];
                                 } else {
                                     if (j == 0) e = R1.root[A.live[ox] >> kLiveSlot];
                                     else e = A.eid[ox];
                                     if constexpr (L == 3) e = j == 1 ? A.eid2[ox] : e;
                                 }
-                                return e;
+                                return reinterpret_cast<const uint2 *>(gp)[2 * (size_t)e + (k & 1u)];
                             };
                             const TT tf = tfirst_of(ox);
-                            count_pairs<TT, MODE>(p, cnt, nw, (nw.w >> 16) & live & kLiveLists, live,
-                                                  eid_of, tn, tf, sat_add(tf, p.delta_sat), nd);
+                            count_pairs<TT, MODE>(p, cnt, (live >> kLivePair) & (nw.w >> 16),
+                                                  glb(p.tree.pairs) + 8 * (cw & 0xffffu), pair_of, tn, tf,
+                                                  sat_add(tf, p.delta_sat), nd);
                             push = (nw.w & live & kLiveLists) != 0;
                         }
                     }
@@ -1307,7 +1332,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p, WaveLds<TT, D, k
                 const uint32_t n = min(nB, (uint32_t)kWave);
                 nB -= n;
                 wave_sync();
-                run_level<TT, D, MODE, L + 1>(p, W, cnt, lane, nB, n, st);
+                run_level<TT, D, MODE, L + 1>(p0, W, cnt, lane, nB, n, st);
                 wave_sync();
             }
         }
@@ -1377,8 +1402,8 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                 int32_t s = 0, d = 0;
                 if (ok) {
                     r = p.roots ? p.roots[i] : i;
-                    s = p.g.gsrc[r];
-                    d = p.g.gdst[r];
+                    s = glb(p.g.gsrc)[r];
+                    d = glb(p.g.gdst)[r];
                     ok = s != d;
                 }
                 uint32_t live = 0;
@@ -1386,13 +1411,13 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                 bool keep = D > 1 && ok;
                 if constexpr (D > 1) {
                     if (ok) {
-                        t = p.g.gt[r];
+                        t = glb(p.g.gt)[r];
                         live = root_live(p, r, sat_add(t, p.delta_sat));
                         // a root with nothing in its windows ends here (the
                         // statistics still count its empty windows)
                         if constexpr (!STATS)
                             keep = ((root_bits(live) | (1u << kLiveAllBit)) &
-                                    (LOG ? p.tree.inode[0].y : p.tree.inode[0].z)) != 0;
+                                    (LOG ? glb(p.tree.inode)[0].y : glb(p.tree.inode)[0].z)) != 0;
                     }
                 }
                 // as many as the batch has room for: the piece goes on at the
@@ -1423,7 +1448,7 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                         A.phi[0][slot] = s;
                         A.phi[1][slot] = d;
                         A.tfirst[slot] = t;
-                        set_root_slot(W, slot, p.g.gx[r]);
+                        set_root_slot(W, slot, glb(p.g.gx)[r]);
                         A.root[slot] = r;
                         A.live[slot] = (uint8_t)live;
                     }
@@ -1458,7 +1483,8 @@ constexpr int min_waves_per_eu() { return D <= 3 && plain_of(MODE) ? 8 : 1; }
 template <typename TT, int D, int MODE>
 __global__ void __launch_bounds__(kWave * kWavesPerBlock)
 __attribute__((amdgpu_waves_per_eu(min_waves_per_eu<D, MODE>(), 8)))
-comine_kernel(const KParams<TT> p) {
+comine_kernel(const KParams<TT>) {
+    const KParams<TT> &p = *(const KParams<TT> *)(ConstParams<TT>)__builtin_amdgcn_kernarg_segment_ptr();
     constexpr bool STATS = MODE == 1;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned long long *cnt = reinterpret_cast<unsigned long long *>(smem);
@@ -1602,9 +1628,6 @@ batch_kernel(const BatchParams<TT> bp) {
         if (it >= bp.n_items) break;
         const BatchItem item = bp.items[uniform((uint32_t)it)];
         const BatchJob<TT> &job = bp.jobs[uniform(item.job)];
-        // the plain search keeps its own copy of the job's parameters (in
-        // registers); the multi-window one reads them in place, since its
-        // window selection would otherwise put a copy in scratch memory
         auto search = [&](const KParams<TT> &p) {
             const uint32_t ip = uniform(item.part);
             const bool split = (ip & kItemSplit) != 0;
@@ -1621,12 +1644,7 @@ batch_kernel(const BatchParams<TT> bp) {
         const uint32_t nq = (uint32_t)counter_slots(job.p.tree);
         for (uint32_t i = (uint32_t)lane; i < nq; i += kWave) cnt[i] = 0;
         wave_sync();
-        if constexpr (MODE == 0) {
-            const KParams<TT> p = job.p;
-            search(p);
-        } else {
-            search(job.p);
-        }
+        search(*(const KParams<TT> *)(ConstParams<TT>)&job.p);
         wave_sync();
         for (uint32_t i = (uint32_t)lane; i < nq; i += kWave)
             if (cnt[i]) atomicAdd(&bp.counts[job.count_off + i], cnt[i]);
