@@ -17,6 +17,7 @@ constexpr int kQueueStride = 16;  // u64 words between queue heads (own cache li
 // counter of a chunk budget, each kQueueStride words apart
 constexpr int kItemSlot = kQueues;
 constexpr int kBudgetSlot = kQueues + 1;
+constexpr int kCtxCountWord = (kQueues + 1) * 16 + 8;   // in the budget's line: contexts handed on
 constexpr int kQueueSlots = kQueues + 2;
 constexpr int kQueueWords = kQueueSlots * kQueueStride;
 
@@ -48,13 +49,14 @@ enum : int { kDirOut = 0, kDirIn = 1, kDirAll = 2 };
 
 // Search tables, as uploaded to the device.
 //   inode[i]  internal (non-leaf) trie node i:
-//     x = first group | leaf_parent << 30 (every child a leaf reached through
-//         a list of a bound vertex: all groups leaf_only)
+//     x = first group
 //     y = its lists, as live-word bits (2 anchor + dir, kLiveAllBit): one group
 //         per bit, in bit order
 //     z = the live-word bits of which at least one has to be set for anything
 //         to be found below the node when leaf windows are counted from pairs:
-//         the lists of its other groups and the pairs of those that are
+//         the lists of its other groups and the pairs of those that are; and
+//         kLeafParent: every child a leaf reached through a list of a bound
+//         vertex (all groups leaf_only)
 //     w = of a leaf parent: the lists whose window has to be found (bits 0-12:
 //         not counted from pairs, or with a new-vertex child) and the pairs
 //         that are counted (bits 16-23: kLivePair's bits)
@@ -94,18 +96,17 @@ struct DevTree {
 };
 __host__ __device__ inline int32_t counter_slots(const DevTree &t) { return t.n_q * t.n_d; }
 
-// One adjacency entry: the other endpoint and the edge time, side by side so
-// that the bisection that finds a window also brings its entries into cache.
-// Both layouts are two TT-sized words: entry i's time is ((TT *)list)[2i + 1]
-// and its endpoint is ((int32_t *)list)[i * sizeof(Entry) / 4].
+// One adjacency entry, 16 bytes read at once: the other endpoint, the edge time
+// (both layouts: the TT-sized word 1 of the entry), next codes, and for 32-bit
+// times the edge id (out_eid / in_eid hold it otherwise).  Next codes: four
+// bytes, how long after the edge the next one comes in its pair, in the pair
+// against it, in out() and in in() of the other endpoint (next_code below).
 template <typename TT> struct Entry;
-template <> struct Entry<uint32_t> { int32_t v; uint32_t t; };
-template <> struct Entry<uint64_t> { int32_t v; int32_t pad; uint64_t t; };
-
-// Four times, each that of the next entry of some list, kNever when it has
-// none (past every edge time).
-template <typename TT> struct alignas(16) Next4 { TT a, b, c, d; };
-template <typename TT> constexpr TT kNever = (TT)~(TT)0;
+template <> struct alignas(16) Entry<uint32_t> { int32_t v; uint32_t t; uint32_t nx, eid; };
+template <> struct alignas(16) Entry<uint64_t> { int32_t v; uint32_t nx; uint64_t t; };
+// entry i's time is ((TT *)list)[(i << kAdjShift<TT>) + 1]
+template <typename TT> constexpr uint32_t kAdjShift = sizeof(TT) == 4 ? 2 : 1;
+template <typename TT> constexpr TT kNever = (TT)~(TT)0;   // past every edge time
 
 template <typename TT>
 struct DevGraph {
@@ -114,7 +115,8 @@ struct DevGraph {
     const uint4 *gx;              // per edge u -> v at t: the first index with a later
                                   // time in out(u), in(u), out(v), in(v) (self-loops:
                                   // unused)
-    const Next4<TT> *gn;          // the times of those entries
+    const uint2 *gn;              // next codes of the edge: y = of those four lists, x = of
+                                  // its pair (byte 0) and of the pair against it (byte 1)
     // Pairs: the edges ordered by (destination, source, time), so that the
     // edges u -> v are consecutive and ascending in time
     const TT *pair_t;             // their times
@@ -123,11 +125,8 @@ struct DevGraph {
                                   // v -> u (self-loops: 0)
     const uint4 *out_gp;          // gp per out_adj entry, per in_adj entry
     const uint4 *in_gp;
-    const Next4<TT> *out_next;    // per out_adj entry u -> v: the next times of u -> v,
-    const Next4<TT> *in_next;     // v -> u, out(v), in(v); per in_adj entry: of u -> v,
-                                  // v -> u, out(u), in(u)
-    const uint32_t *out_eid;      // edge id of every out_adj entry
-    const uint32_t *in_eid;       // edge id of every in_adj entry
+    const uint32_t *out_eid;      // edge id of every out_adj entry (64-bit times)
+    const uint32_t *in_eid;       // edge id of every in_adj entry (64-bit times)
     const uint32_t *out_off;      // V+1
     const Entry<TT> *out_adj;     // out-lists: destination, time
     const uint32_t *in_off;
@@ -136,15 +135,15 @@ struct DevGraph {
 };
 
 // A piece of search left over when an epoch ends: the candidates of one
-// root-level window, entries [e0, e1) of the list of group g of the root (edge
-// id `root`) a -> b at time t_lo | t_hi << 32, with the root's windows in out(a), in(a),
+// root-level window, entries [e0, e1) of the list `bit` (live-word bit) of the
+// root (edge id `root`) a -> b at time t_lo | t_hi << 32, with the root's windows in out(a), in(a),
 // out(b), in(b) as far as it had found them (first entry and length, as the
 // per-wave root windows keep them).  The root itself was credited when it was
 // started.
 struct EpochCtx {
     int32_t a, b;
     uint32_t t_lo, t_hi;
-    uint32_t g, e0, e1, root;
+    uint32_t bit, e0, e1, root;
     uint32_t hlo[4];
     uint16_t hlen[4];
     uint32_t pad2[2];
@@ -160,7 +159,8 @@ struct KParams {
     TT dlo[kMaxDeltas - 1];       // the smaller windows, ascending (tree.n_d - 1 of them)
     const uint32_t *roots;        // NULL: roots are 0..n_roots-1
     uint32_t n_roots;
-    uint32_t chunk;               // roots per queue grab (multiple of 64)
+    uint32_t chunk;               // roots per chunk (0: chosen at the launch by the number
+                                  // of roots; multiple of 64 with items or skip)
     uint32_t n_queues;            // 1..kQueues root queues
     unsigned long long *queues;   // kQueueWords: queue heads (zeroed, or a resume
                                   // point) and the claim counter (zeroed)
@@ -206,6 +206,13 @@ struct KParams {
                                   // launch's waves is idle (1..100)
     const EpochCtx *ctx_in;       // NULL, or the contexts this launch searches
     uint32_t n_ctx_in;
+    // Heavy root-level chunks of the plain search (MODE 0 and 3): with hand_on
+    // set (chosen at the launch by the number of roots), the candidates of a
+    // chunk beyond that many are written as contexts of ctx_piece candidates
+    // into ctx_out, and the launch that follows searches them (ctx_in, with
+    // ctx_n their count on the device)
+    uint32_t hand_on, ctx_piece;
+    const unsigned long long *ctx_n;
     uint32_t leaf_scan;           // windows whose children are all leaves are counted
                                   // without the candidate expansion: by one lane up
                                   // to this long, by the whole wave when longer

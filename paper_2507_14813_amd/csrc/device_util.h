@@ -71,8 +71,8 @@ static __device__ __forceinline__ uint64_t sat_add(uint64_t a, uint64_t d) {
     return a > ~0ull - d ? ~0ull : a + d;
 }
 
-// first index i in [lo, hi) with a[i << sh] > v (hi if none); sh = 1 walks
-// the time words of interleaved adjacency entries, sh = 0 a plain array
+// first index i in [lo, hi) with a[i << sh] > v (hi if none); sh = kAdjShift
+// walks the time words of adjacency entries, sh = 0 a plain array
 template <typename TT>
 static __device__ __forceinline__ uint32_t first_greater(const TT *__restrict__ a, uint32_t sh,
                                                   uint32_t lo, uint32_t hi, TT v) {
@@ -99,9 +99,25 @@ static __device__ __forceinline__ uint32_t gallop_greater(const TT *__restrict__
     }
 }
 
+// Code of a time span: 0 for none, else its leading bits, exponent above
+// mantissa (3 bits for 32-bit times, 2 for 64-bit ones), plus one; 255 also
+// stands for "never".  It never falls as the span grows, so a next entry whose
+// code is above that of a window's remaining length lies outside it; the other
+// way round it may (within an eighth or a quarter of the length).
+static __device__ __forceinline__ uint32_t next_code(uint32_t d) {
+    if (d == 0) return 0;
+    const uint32_t z = (uint32_t)__builtin_clz(d);
+    return min(255u, (31u - z) * 8u + (((d << z) >> 28) & 7u) + 1u);
+}
+static __device__ __forceinline__ uint32_t next_code(uint64_t d) {
+    if (d == 0) return 0;
+    const uint32_t z = (uint32_t)__builtin_clzll(d);
+    return min(255u, (63u - z) * 4u + (uint32_t)(((d << z) >> 61) & 3u) + 1u);
+}
+
 template <typename TT>
 static __device__ __forceinline__ const TT *times_of(const Entry<TT> *adj) {
-    return reinterpret_cast<const TT *>(adj) + 1;   // word 2i+1 is entry i's time
+    return reinterpret_cast<const TT *>(adj) + 1;   // (see Entry)
 }
 
 }  // namespace mg

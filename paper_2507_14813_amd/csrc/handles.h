@@ -58,7 +58,7 @@ struct mg_graph {
     int time_bytes = 4;
     int device = 0;
     bool host_only = false;             // no device copy (MG_HOST_ONLY)
-    mgh::DevBuf gsrc, gdst, gt, gx, gn, gp, out_gp, in_gp, pair_t, out_next, in_next, out_eid, in_eid, out_off,
+    mgh::DevBuf gsrc, gdst, gt, gx, gn, gp, out_gp, in_gp, pair_t, out_eid, in_eid, out_off,
         out_adj, in_off, in_adj;
     mgh::DevBuf order;                  // u32 per edge: the caller's index (none: the same)
     int64_t device_bytes = 0;
@@ -84,6 +84,7 @@ struct mg_tree {
     // device copies
     int device = -1;
     mgh::DevBuf d_tab;                  // node_tab, grp_tab, pair_tab
+    mgh::DevBuf d_ctx;                  // contexts a count hands on between its two launches
     // per-motif chain trees (built on first per-motif count)
     std::vector<std::unique_ptr<mg_tree>> singles;
     // CPU backend: the generated and compiled search of this tree

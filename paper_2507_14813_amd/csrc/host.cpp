@@ -98,7 +98,7 @@ void dev_free(DevBuf &b) {
 using namespace mgh;
 
 mg_graph::~mg_graph() {
-    for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &gn, &gp, &out_gp, &in_gp, &pair_t, &out_next, &in_next, &out_eid,
+    for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &gn, &gp, &out_gp, &in_gp, &pair_t, &out_eid,
                       &in_eid, &out_off, &out_adj, &in_off, &in_adj, &order})
         dev_free(*b);
 }
@@ -154,16 +154,16 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
                  hipStream_t st) {
     const uint32_t E = (uint32_t)g->E, V = (uint32_t)g->V;
     const uint32_t A = (uint32_t)(g->E - g->self_loops);   // list entries
+    // 32-bit times leave room for the edge id in the list entry
+    constexpr size_t kEid = sizeof(TT) == 4 ? 0 : sizeof(uint32_t);
     struct Need { DevBuf *b; size_t n; };
     const Need needs[] = {
         {&g->gsrc, sizeof(int32_t) * (size_t)E}, {&g->gdst, sizeof(int32_t) * (size_t)E},
         {&g->gt, sizeof(TT) * (size_t)E},        {&g->gx, sizeof(uint32_t) * 4 * (size_t)E},
-        {&g->gn, sizeof(mg::Next4<TT>) * (size_t)E}, {&g->gp, sizeof(uint32_t) * 4 * (size_t)E},
+        {&g->gn, sizeof(uint32_t) * 2 * (size_t)E}, {&g->gp, sizeof(uint32_t) * 4 * (size_t)E},
         {&g->out_gp, sizeof(uint32_t) * 4 * (size_t)A}, {&g->in_gp, sizeof(uint32_t) * 4 * (size_t)A},
         {&g->pair_t, sizeof(TT) * ((size_t)A + 4)},   // read four entries at a time
-        {&g->out_next, sizeof(mg::Next4<TT>) * (size_t)A},
-        {&g->in_next, sizeof(mg::Next4<TT>) * (size_t)A},
-        {&g->out_eid, sizeof(uint32_t) * (size_t)A}, {&g->in_eid, sizeof(uint32_t) * (size_t)A},
+        {&g->out_eid, kEid * (size_t)A}, {&g->in_eid, kEid * (size_t)A},
         {&g->out_off, sizeof(uint32_t) * ((size_t)V + 1)},
         {&g->out_adj, sizeof(mg::Entry<TT>) * (size_t)A},
         {&g->in_off, sizeof(uint32_t) * ((size_t)V + 1)},
@@ -197,8 +197,9 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
     }
     rc = tmp.get(&opos, E, st);
     if (!rc) rc = tmp.get(&ipos, E, st);
-    uint32_t *ikey = nullptr;
+    uint32_t *ikey = nullptr, *oeid = nullptr;
     if (!rc) rc = tmp.get(&ikey, E, st);
+    if (!rc) rc = tmp.get(&oeid, E, st);
     if (rc) return rc;
     auto *gsrc = (int32_t *)g->gsrc.ptr, *gdst = (int32_t *)g->gdst.ptr;
     TT *gt = (TT *)g->gt.ptr;
@@ -210,8 +211,10 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
         uint32_t *k[2] = {side ? ikey : key[0], key[1]};
         LAUNCH_TRY(mg::sort_pairs<uint32_t>(k, v, true, E, vb, sort_mem, &at, st));
         DevBuf &eid = side ? g->in_eid : g->out_eid;
-        if (A)
-            HIP_TRY(hipMemcpyAsync(eid.ptr, v[at], sizeof(uint32_t) * (size_t)A,
+        if (A && kEid)
+            HIP_TRY(hipMemcpyAsync(eid.ptr, v[at], kEid * (size_t)A, hipMemcpyDeviceToDevice, st));
+        if (A && side == 0)   // the pair order starts from this one
+            HIP_TRY(hipMemcpyAsync(oeid, v[at], sizeof(uint32_t) * (size_t)A,
                                    hipMemcpyDeviceToDevice, st));
         LAUNCH_TRY(mg::launch_lists<TT>(k[at], v[at], A, V, side ? gsrc : gdst, gt,
                                         (uint32_t *)(side ? g->in_off : g->out_off).ptr,
@@ -219,21 +222,19 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
                                         side ? ipos : opos, st));
     }
     const mg::DevGraph<TT> dg = dev_graph<TT>(g);
-    LAUNCH_TRY(mg::launch_ranks<TT>(dg, opos, ipos, (uint4 *)g->gx.ptr, (mg::Next4<TT> *)g->gn.ptr, st));
+    LAUNCH_TRY(mg::launch_ranks<TT>(dg, opos, ipos, (uint4 *)g->gx.ptr, (uint2 *)g->gn.ptr, st));
     // pair order: the out-lists' order (source, time) sorted by destination.
     // Self-loops are in no pair: their records are zero.
     if (g->self_loops) HIP_TRY(hipMemsetAsync(g->gp.ptr, 0, 16 * (size_t)E, st));
     if (A) {
-        uint32_t *pv[2] = {v[0], v[1]}, *pk[2] = {key[0], key[1]};
-        HIP_TRY(hipMemcpyAsync(pv[0], g->out_eid.ptr, sizeof(uint32_t) * (size_t)A,
-                               hipMemcpyDeviceToDevice, st));
+        uint32_t *pv[2] = {oeid, v[0]}, *pk[2] = {key[0], key[1]};
         LAUNCH_TRY(mg::launch_gather(pv[0], gdst, A, pk[0], st));
         LAUNCH_TRY(mg::sort_pairs<uint32_t>(pk, pv, false, A, vb, sort_mem, &at, st));
         LAUNCH_TRY(mg::launch_pairs<TT>(dg, pv[at], A, opos, ipos, (int32_t *)ikey,
                                         (TT *)g->pair_t.ptr, (uint4 *)g->gp.ptr,
                                         (uint4 *)g->out_gp.ptr, (uint4 *)g->in_gp.ptr,
-                                        (mg::Next4<TT> *)g->out_next.ptr,
-                                        (mg::Next4<TT> *)g->in_next.ptr, st));
+                                        (uint2 *)g->gn.ptr, (mg::Entry<TT> *)g->out_adj.ptr,
+                                        (mg::Entry<TT> *)g->in_adj.ptr, st));
     }
     HIP_TRY(hipStreamSynchronize(st));
     return MG_OK;
@@ -244,6 +245,7 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
 // ---------------------------------------------------------------- tree
 mg_tree::~mg_tree() {
     dev_free(d_tab);
+    dev_free(d_ctx);
     release_cpu_code(this);
 }
 
@@ -420,9 +422,9 @@ int build_tree(mg_tree *tr) {
             leaf_parent = leaf_parent && ch.kids.empty() && (ch.u < nd.nv || ch.v < nd.nv);
         }
         int32_t *w = &tr->node_tab[4 * (size_t)iidx[n]];
-        w[0] = (int32_t)((uint32_t)g0 | (leaf_parent ? mg::kLeafParent : 0u));
+        w[0] = g0;
         w[1] = (int32_t)lists;
-        w[2] = (int32_t)(leaf_parent ? gate : lists);
+        w[2] = (int32_t)(leaf_parent ? gate | mg::kLeafParent : lists);
         w[3] = (int32_t)(leaf_parent ? by_window | pairs << 16 : 0u);
     }
     if (tr->grp_tab.empty()) tr->grp_tab.assign(12, 0);
@@ -547,7 +549,8 @@ void fill_params(mg::KParams<TT> &p, const mg_graph *g, const mg_tree *tr, const
     for (size_t i = 0; i + 1 < tr->deltas.size(); ++i) p.dlo[i] = delta_sat<TT>(tr->deltas[i]);
     p.roots = nullptr;
     p.n_roots = (uint32_t)g->E;
-    p.chunk = (uint32_t)(o.chunk > 0 ? o.chunk : 64);
+    // a stopped count's chunks are part of its resume point
+    p.chunk = (uint32_t)(o.chunk > 0 ? o.chunk : (o.stop || o.max_chunks || o.cursor || o.epoch_idle) ? 64 : 0);
     p.n_queues = (uint32_t)(o.queues > 0 ? o.queues : mg::kQueues);
     p.leaf_scan = o.leaf_scan < 0 ? 0u : (o.leaf_scan == 0 ? mg::kLeafScanDefault
                                                            : (uint32_t)o.leaf_scan);
@@ -564,6 +567,8 @@ void fill_params(mg::KParams<TT> &p, const mg_graph *g, const mg_tree *tr, const
 // busy waves had not reached yet come back as contexts, which the next launch
 // spreads over all of its waves.  The last of max_epochs launches runs to the
 // end.  Counts accumulate in p.counts; p.queues is cleared before each launch.
+constexpr uint32_t kHandOnRoots = 1u << 17;   // counts of fewer roots hand nothing on
+constexpr uint64_t kHandOnCap = 1u << 18;     // contexts one count can hand on (16 MB)
 constexpr uint64_t kCtxCap = 1u << 20;   // contexts one epoch can hand on (64 MB)
 
 template <typename TT>
@@ -614,7 +619,8 @@ template <typename TT>
 int launch_tree(const mg_graph *g, mg_tree *tr, const uint32_t *d_roots, uint32_t n_roots,
                 unsigned long long *d_queues, unsigned long long *d_counts,
                 unsigned long long *d_stats, unsigned long long *d_cost,
-                unsigned long long *d_clock, const mg_count_opts &o, hipStream_t st, float *ms) {
+                unsigned long long *d_clock, const DevBuf *ctx, const mg_count_opts &o,
+                hipStream_t st, float *ms) {
     mg::KParams<TT> p{};
     fill_params<TT>(p, g, tr, o, d_queues, d_counts, d_stats, d_cost);
     p.roots = d_roots;
@@ -654,7 +660,26 @@ int launch_tree(const mg_graph *g, mg_tree *tr, const uint32_t *d_roots, uint32_
         int rc = epoch_search<TT>(p, o, st);
         if (rc) return rc;
     } else if (n_roots > 0) {
+        // Deep trees over many roots: the candidates of the heaviest root
+        // chunks are searched by a second launch, spread over the device (one
+        // wave's 64 roots inside a burst took as long as everything else: half
+        // of a count of 3M edges with 756 motifs).
+        const bool two = ctx && tr->kdepth > 2 && n_roots >= kHandOnRoots && !p.stop &&
+                         !p.max_chunks && !p.stats && !p.root_cost && !p.wave_clock;
+        if (two) {
+            p.hand_on = 1;
+            p.ctx_out = (mg::EpochCtx *)ctx->ptr;
+            p.ctx_cap = ctx->bytes / sizeof(mg::EpochCtx);
+            p.ctx_count = d_queues + mg::kCtxCountWord;
+        }
         hipError_t e = mg::launch_comine<TT>(p, o.blocks, st);
+        if (e == hipSuccess && two) {
+            p.hand_on = 0;
+            p.ctx_in = p.ctx_out;
+            p.ctx_out = nullptr;
+            p.ctx_n = p.ctx_count;
+            e = mg::launch_comine<TT>(p, o.blocks, st);
+        }
         if (e != hipSuccess)
             return fail(MG_EDEVICE, "co-mining launch failed: %s", hipGetErrorString(e));
     }
@@ -717,13 +742,11 @@ mg::DevGraph<TT> dev_graph(const mg_graph *g) {
     d.gdst = (const int32_t *)g->gdst.ptr;
     d.gt = (const TT *)g->gt.ptr;
     d.gx = (const uint4 *)g->gx.ptr;
-    d.gn = (const mg::Next4<TT> *)g->gn.ptr;
+    d.gn = (const uint2 *)g->gn.ptr;
     d.gp = (const uint4 *)g->gp.ptr;
     d.out_gp = (const uint4 *)g->out_gp.ptr;
     d.in_gp = (const uint4 *)g->in_gp.ptr;
     d.pair_t = (const TT *)g->pair_t.ptr;
-    d.out_next = (const mg::Next4<TT> *)g->out_next.ptr;
-    d.in_next = (const mg::Next4<TT> *)g->in_next.ptr;
     d.out_eid = (const uint32_t *)g->out_eid.ptr;
     d.in_eid = (const uint32_t *)g->in_eid.ptr;
     d.out_off = (const uint32_t *)g->out_off.ptr;
@@ -1841,6 +1864,16 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
         }
         struct Guard4 { DevBuf *b; ~Guard4() { dev_free(*b); } } gk{&d_clock};
 
+        // kept with the tree: allocated once, by its first count of that many roots
+        const DevBuf *ctx = nullptr;
+        if (n_roots >= kHandOnRoots && o.sched == MG_SCHED_PLAIN && !o.epoch_idle) {
+            if (!tr->d_ctx.ptr) {
+                rc = dev_alloc(tr->d_ctx, sizeof(mg::EpochCtx) * kHandOnCap, (void *)st);
+                if (rc) return rc;
+            }
+            ctx = &tr->d_ctx;
+        }
+
         std::vector<uint64_t> qcount(n_slots(tr), 0);
         float total_ms = 0.f;
         mg_cursor cur{};
@@ -1853,12 +1886,12 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
                      ? launch_tree<uint32_t>(g, t, (const uint32_t *)d_roots.ptr, n_roots,
                                              d_queues, d_counts, d_stats,
                                              (unsigned long long *)d_cost.ptr,
-                                             (unsigned long long *)d_clock.ptr, o, st,
+                                             (unsigned long long *)d_clock.ptr, ctx, o, st,
                                              o.elapsed_ms ? &ms : nullptr)
                      : launch_tree<uint64_t>(g, t, (const uint32_t *)d_roots.ptr, n_roots,
                                              d_queues, d_counts, d_stats,
                                              (unsigned long long *)d_cost.ptr,
-                                             (unsigned long long *)d_clock.ptr, o, st,
+                                             (unsigned long long *)d_clock.ptr, ctx, o, st,
                                              o.elapsed_ms ? &ms : nullptr);
             if (rc) return rc;
             total_ms += ms;

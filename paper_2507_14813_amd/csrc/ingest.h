@@ -55,15 +55,16 @@ hipError_t launch_lists(const uint32_t *key, const uint32_t *eid, uint32_t n_adj
 // lists.
 template <typename TT>
 hipError_t launch_ranks(const DevGraph<TT> &g, const uint32_t *opos, const uint32_t *ipos,
-                        uint4 *gx, Next4<TT> *gn, hipStream_t st);
+                        uint4 *gx, uint2 *gn, hipStream_t st);
 
 // Pair order (edge ids pe[0..n_adj) by destination, source, time): pair_t, gp,
-// out_gp, in_gp, out_next and in_next.  psrc: scratch, n_adj words.
+// out_gp, in_gp, the pair codes of gn and the next codes of both lists'
+// entries.  psrc: scratch, n_adj words.
 template <typename TT>
 hipError_t launch_pairs(const DevGraph<TT> &g, const uint32_t *pe, uint32_t n_adj,
                         const uint32_t *opos, const uint32_t *ipos, int32_t *psrc, TT *pair_t,
-                        uint4 *gp, uint4 *out_gp, uint4 *in_gp, Next4<TT> *out_next,
-                        Next4<TT> *in_next, hipStream_t st);
+                        uint4 *gp, uint4 *out_gp, uint4 *in_gp, uint2 *gn, Entry<TT> *out_adj,
+                        Entry<TT> *in_adj, hipStream_t st);
 
 // keys[j] = key_of[eid[j]] for n entries
 hipError_t launch_gather(const uint32_t *eid, const int32_t *key_of, uint32_t n, uint32_t *keys,

@@ -289,6 +289,7 @@ list_entries(const uint32_t *eid, uint32_t n_adj, const int32_t *other, const TT
         Entry<TT> x{};
         x.v = other[e];
         x.t = gt[e];
+        if constexpr (sizeof(TT) == 4) x.eid = e;
         adj[j] = x;
         pos[e] = (uint32_t)j;
     }
@@ -300,25 +301,30 @@ list_entries(const uint32_t *eid, uint32_t n_adj, const int32_t *other, const TT
 template <typename TT>
 __global__ void __launch_bounds__(kIB)
 list_ranks(const DevGraph<TT> g, const uint32_t *opos, const uint32_t *ipos, uint4 *gx,
-           Next4<TT> *gn) {
+           uint2 *gn) {
     const TT *ot = times_of(g.out_adj), *it = times_of(g.in_adj);
     for (uint64_t e = blockIdx.x * (uint64_t)kIB + threadIdx.x; e < g.n_edges;
          e += gridDim.x * (uint64_t)kIB) {
         const int32_t u = g.gsrc[e], v = g.gdst[e];
         uint4 x = make_uint4(0, 0, 0, 0);
-        Next4<TT> n{kNever<TT>, kNever<TT>, kNever<TT>, kNever<TT>};
+        uint2 n = make_uint2(~0u, ~0u);
         if (u != v) {
             const TT t = g.gt[e];
             const uint32_t eu = g.out_off[u + 1], iu = g.in_off[u + 1];
             const uint32_t ev = g.out_off[v + 1], iv = g.in_off[v + 1];
-            x.x = gallop_greater(ot, 1, opos[e] + 1, eu, t);
-            x.y = first_greater(it, 1, g.in_off[u], iu, t);
-            x.z = first_greater(ot, 1, g.out_off[v], ev, t);
-            x.w = gallop_greater(it, 1, ipos[e] + 1, iv, t);
-            if (x.x < eu) n.a = ot[2 * (size_t)x.x];
-            if (x.y < iu) n.b = it[2 * (size_t)x.y];
-            if (x.z < ev) n.c = ot[2 * (size_t)x.z];
-            if (x.w < iv) n.d = it[2 * (size_t)x.w];
+            auto code = [&](const TT *a, uint32_t i, uint32_t end, int k) {
+                if (i >= end) return;
+                const uint32_t c = next_code((TT)(a[(size_t)i << kAdjShift<TT>] - t));
+                n.y = (n.y & ~(255u << (8 * k))) | (c << (8 * k));
+            };
+            x.x = gallop_greater(ot, kAdjShift<TT>, opos[e] + 1, eu, t);
+            x.y = first_greater(it, kAdjShift<TT>, g.in_off[u], iu, t);
+            x.z = first_greater(ot, kAdjShift<TT>, g.out_off[v], ev, t);
+            x.w = gallop_greater(it, kAdjShift<TT>, ipos[e] + 1, iv, t);
+            code(ot, x.x, eu, 0);
+            code(it, x.y, iu, 1);
+            code(ot, x.z, ev, 2);
+            code(it, x.w, iv, 3);
         }
         gx[e] = x;
         gn[e] = n;
@@ -350,7 +356,7 @@ template <typename TT>
 __global__ void __launch_bounds__(kIB)
 pair_links(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, const uint32_t *opos,
            const uint32_t *ipos, const int32_t *psrc, const TT *pair_t, uint4 *gp, uint4 *out_gp,
-           uint4 *in_gp, Next4<TT> *out_next, Next4<TT> *in_next) {
+           uint4 *in_gp, uint2 *gn, Entry<TT> *out_adj, Entry<TT> *in_adj) {
     for (uint64_t j = blockIdx.x * (uint64_t)kIB + threadIdx.x; j < n_adj;
          j += gridDim.x * (uint64_t)kIB) {
         const uint32_t e = pe[j];
@@ -370,16 +376,12 @@ pair_links(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, const uint3
         gp[e] = p;
         out_gp[op] = p;
         in_gp[ip] = p;
-        const Next4<TT> n = g.gn[e];
-        Next4<TT> o;
-        o.a = p.x < p.y ? pair_t[p.x] : kNever<TT>;
-        o.b = p.z < p.w ? pair_t[p.z] : kNever<TT>;
-        o.c = n.c;
-        o.d = n.d;
-        out_next[op] = o;
-        o.c = n.a;
-        o.d = n.b;
-        in_next[ip] = o;
+        const uint32_t fwd = p.x < p.y ? next_code((TT)(pair_t[p.x] - t)) : 255u;
+        const uint32_t rev = p.z < p.w ? next_code((TT)(pair_t[p.z] - t)) : 255u;
+        const uint32_t pairs = fwd | (rev << 8), lists = gn[e].y;
+        gn[e].x = pairs;
+        out_adj[op].nx = pairs | (lists & 0xffff0000u);
+        in_adj[ip].nx = pairs | (lists << 16);
     }
 }
 
@@ -465,7 +467,7 @@ hipError_t launch_lists(const uint32_t *key, const uint32_t *eid, uint32_t n_adj
 
 template <typename TT>
 hipError_t launch_ranks(const DevGraph<TT> &g, const uint32_t *opos, const uint32_t *ipos,
-                        uint4 *gx, Next4<TT> *gn, hipStream_t st) {
+                        uint4 *gx, uint2 *gn, hipStream_t st) {
     if (g.n_edges == 0) return hipSuccess;
     hipLaunchKernelGGL(list_ranks<TT>, dim3(grid_for(g.n_edges, kIB)), dim3(kIB), 0, st, g, opos,
                        ipos, gx, gn);
@@ -482,13 +484,13 @@ hipError_t launch_gather(const uint32_t *eid, const int32_t *key_of, uint32_t n,
 template <typename TT>
 hipError_t launch_pairs(const DevGraph<TT> &g, const uint32_t *pe, uint32_t n_adj,
                         const uint32_t *opos, const uint32_t *ipos, int32_t *psrc, TT *pair_t,
-                        uint4 *gp, uint4 *out_gp, uint4 *in_gp, Next4<TT> *out_next,
-                        Next4<TT> *in_next, hipStream_t st) {
+                        uint4 *gp, uint4 *out_gp, uint4 *in_gp, uint2 *gn, Entry<TT> *out_adj,
+                        Entry<TT> *in_adj, hipStream_t st) {
     if (n_adj == 0) return hipSuccess;
     const dim3 grid(grid_for(n_adj, kIB));
     hipLaunchKernelGGL(pair_entries<TT>, grid, dim3(kIB), 0, st, g, pe, n_adj, psrc, pair_t);
     hipLaunchKernelGGL(pair_links<TT>, grid, dim3(kIB), 0, st, g, pe, n_adj, opos, ipos, psrc,
-                       pair_t, gp, out_gp, in_gp, out_next, in_next);
+                       pair_t, gp, out_gp, in_gp, gn, out_adj, in_adj);
     return hipGetLastError();
 }
 
@@ -507,11 +509,11 @@ template hipError_t sort_pairs<uint64_t>(uint64_t *const[2], uint32_t *const[2],
                                          const int32_t *, const TT *, uint32_t *, Entry<TT> *,    \
                                          uint32_t *, hipStream_t);                                \
     template hipError_t launch_ranks<TT>(const DevGraph<TT> &, const uint32_t *,                  \
-                                         const uint32_t *, uint4 *, Next4<TT> *, hipStream_t);    \
+                                         const uint32_t *, uint4 *, uint2 *, hipStream_t);        \
     template hipError_t launch_pairs<TT>(const DevGraph<TT> &, const uint32_t *, uint32_t,        \
                                          const uint32_t *, const uint32_t *, int32_t *, TT *,     \
-                                         uint4 *, uint4 *, uint4 *, Next4<TT> *, Next4<TT> *,     \
-                                         hipStream_t);
+                                         uint4 *, uint4 *, uint4 *, uint2 *, Entry<TT> *,         \
+                                         Entry<TT> *, hipStream_t);
 MG_INGEST(uint32_t)
 MG_INGEST(uint64_t)
 #undef MG_INGEST

@@ -82,14 +82,14 @@ __device__ void root_features(const DevGraph<TT> &g, const DevTree &t, TT dsat, 
     f[2] = log1pf((float)(ob1 - ob0)) * s;
     f[3] = log1pf((float)(ib1 - ib0)) * s;
     uint32_t l;
-    l = first_greater(ot, 1, oa0, oa1, tr);
-    f[4] = log1pf((float)(gallop_greater(ot, 1, l, oa1, thi) - l)) * s;
-    l = first_greater(ot, 1, ob0, ob1, tr);
-    f[5] = log1pf((float)(gallop_greater(ot, 1, l, ob1, thi) - l)) * s;
-    l = first_greater(it, 1, ia0, ia1, tr);
-    f[6] = log1pf((float)(gallop_greater(it, 1, l, ia1, thi) - l)) * s;
-    l = first_greater(it, 1, ib0, ib1, tr);
-    f[7] = log1pf((float)(gallop_greater(it, 1, l, ib1, thi) - l)) * s;
+    l = first_greater(ot, kAdjShift<TT>, oa0, oa1, tr);
+    f[4] = log1pf((float)(gallop_greater(ot, kAdjShift<TT>, l, oa1, thi) - l)) * s;
+    l = first_greater(ot, kAdjShift<TT>, ob0, ob1, tr);
+    f[5] = log1pf((float)(gallop_greater(ot, kAdjShift<TT>, l, ob1, thi) - l)) * s;
+    l = first_greater(it, kAdjShift<TT>, ia0, ia1, tr);
+    f[6] = log1pf((float)(gallop_greater(it, kAdjShift<TT>, l, ia1, thi) - l)) * s;
+    l = first_greater(it, kAdjShift<TT>, ib0, ib1, tr);
+    f[7] = log1pf((float)(gallop_greater(it, kAdjShift<TT>, l, ib1, thi) - l)) * s;
     l = gallop_greater(g.gt, 0, r, g.n_edges, tr);   // edges after r with a later time
     f[8] = log1pf((float)(gallop_greater(g.gt, 0, l, g.n_edges, thi) - l)) * s;
     f[9] = (float)t.depth * 0.125f;

@@ -400,18 +400,17 @@ __device__ __forceinline__ void set_root_slot(WaveLds<TT, D, R> &W, uint32_t slo
     for (int k = 0; k < 4; ++k) W.hlen[k][slot] = kNoHint;
 }
 
-// Live bits of root edge e with window end thi, as the level-1 batch keeps
-// them: bits 0-3 out(a), in(a), out(b), in(b), bits 4 and 5 its pair a -> b
-// and b -> a.
+// Live bits of root edge e, as the level-1 batch keeps them: bits 0-3 out(a),
+// in(a), out(b), in(b), bits 4 and 5 its pair a -> b and b -> a.
 template <typename TT>
-__device__ __forceinline__ uint32_t root_live(const KParams<TT> &p, uint32_t e, TT thi) {
-    const Next4<TT> n = glb(p.g.gn)[e];
-    const uint4 pr = glb(p.g.gp)[e];
-    uint32_t r = (n.a <= thi ? 1u : 0u) | (n.b <= thi ? 2u : 0u) | (n.c <= thi ? 4u : 0u) |
-                 (n.d <= thi ? 8u : 0u);
-    // a -> b again: an entry of out(a) and of in(b); b -> a: of in(a) and out(b)
-    if ((r & 9u) == 9u && pr.x < pr.y && glb(p.g.pair_t)[pr.x] <= thi) r |= 16u;
-    if ((r & 6u) == 6u && pr.z < pr.w && glb(p.g.pair_t)[pr.z] <= thi) r |= 32u;
+__device__ __forceinline__ uint32_t root_live(const KParams<TT> &p, uint32_t e) {
+    const uint2 n = glb(p.g.gn)[e];
+    const uint32_t q = next_code(p.delta_sat);
+    uint32_t r = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r |= ((n.y >> (8 * k)) & 255u) <= q ? 1u << k : 0u;
+    r |= (n.x & 255u) <= q ? 16u : 0u;
+    r |= ((n.x >> 8) & 255u) <= q ? 32u : 0u;
     return r;
 }
 // the same as live-word bits
@@ -515,7 +514,7 @@ __device__ __forceinline__ uint32_t count_leaf_window(const KParams<TT> &p, uint
         const TT *ta = times_of(adj);
         uint32_t e = l0 + len;
         for (uint32_t j = nd - 1; j-- > 0;) {
-            e = gallop_greater(ta, 1, l0, e, sat_add(tf, window_lo(p, j)));
+            e = gallop_greater(ta, kAdjShift<TT>, l0, e, sat_add(tf, window_lo(p, j)));
             if (e == l0) break;
             count(e - l0, j, true);
         }
@@ -685,7 +684,7 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                             const uint32_t k = 2u * (uint32_t)sv + 1u;   // in(a), in(b)
                             const uint32_t hb = W.hlo[k][r1];
                             sw_hi[sv] = hb + (sv ? hlb : hla);
-                            sw_lo[sv] = first_greater(tin, 1, hb, sw_hi[sv], tp);
+                            sw_lo[sv] = first_greater(tin, kAdjShift<TT>, hb, sw_hi[sv], tp);
                             sw_len += sw_hi[sv] - sw_lo[sv];
                         }
                     }
@@ -727,18 +726,18 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
                 // of the second edge: the window starts no earlier than there
                 const uint32_t k = ((le ? le : be) == 1 ? 0u : 2u) + dir;
                 l0 = reinterpret_cast<const uint32_t *>(glb(p.g.gx))[4 * (size_t)(le ? eid : eid2) + k];
-                if (!le) l0 = gallop_greater(ta, 1, l0, e, tp);
+                if (!le) l0 = gallop_greater(ta, kAdjShift<TT>, l0, e, tp);
             } else {
-                l0 = first_greater(ta, 1, b, e, tp);
+                l0 = first_greater(ta, kAdjShift<TT>, b, e, tp);
             }
-            const uint32_t len = (hinted ? e : gallop_greater(ta, 1, l0, e, thi)) - l0;
+            const uint32_t len = (hinted ? e : gallop_greater(ta, kAdjShift<TT>, l0, e, thi)) - l0;
             if (codes) {
                 // the new-vertex child: the window's length (its pairs are off already)
                 credit_child(gb.w, len, cnt, nd, nd - 1);
                 if constexpr (!single_of(MODE)) {
                     uint32_t x = l0 + len;
                     for (uint32_t k = nd - 1; k-- > 0;) {
-                        x = gallop_greater(ta, 1, l0, x, sat_add(tf, window_lo(p, k)));
+                        x = gallop_greater(ta, kAdjShift<TT>, l0, x, sat_add(tf, window_lo(p, k)));
                         if (x == l0) break;
                         credit_child(gb.w, x - l0, cnt, nd, k, true);
                     }
@@ -826,7 +825,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
             const bool act = (uint32_t)lane < nA;
             uint4 nw = make_uint4(0, 0, 0, 0);
             if (act) nw = inode[A.node[x]];
-            counted = (nw.x & kLeafParent) != 0;
+            counted = (nw.z & kLeafParent) != 0;
             if (__ballot(counted)) {
                 int32_t ph[SA];
                 uint32_t eid = 0, eid2 = 0, live = 0;
@@ -901,7 +900,6 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
     for (;;) {
         const KParams<TT> &p = fresh(p0);
         const uint4 *__restrict__ inode = glb(p.tree.inode);
-        const uint4 *__restrict__ grp = glb(p.tree.grp);
         if constexpr (L == 1 && epochs_of(MODE)) {
             // (a wave dumps in one batch at most: the later batches of its
             // chunk search on)
@@ -912,13 +910,14 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                 dumping = (uint64_t)lane_value(v, 0) * 100u >= (uint64_t)p.idle_pct * waves;
             }
         }
+        bool formed = false;   // a new chunk of windows in this round
         if (cc >= T) {
             if (pc >= P) {
                 done = true;
             } else {
                 // one (partial match, group) pair per lane -> its window
                 const uint32_t pi = pc + lane;
-                uint32_t len = 0, x = 0, g = 0, l0 = 0, hdr = 0;
+                uint32_t len = 0, x = 0, g = 0, l0 = 0, hdr = 0, bit = 0;
                 bool all = false;
                 if (pi < P) {
                     uint32_t lo = 0;
@@ -927,12 +926,13 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                         if (ctx) {
                             const EpochCtx c = ctx[pi];
                             lo = pi;
-                            g = c.g;
+                            bit = c.bit;
+                            g = (node0.x & 0xfffffu) + (uint32_t)__popc(node0.y & ((1u << bit) - 1u));
                             l0 = c.e0;
                             len = c.e1 - c.e0;
                             given = true;
                         } else {
-                            uint32_t bit = kLiveAllBit;
+                            bit = kLiveAllBit;
                             if (pi < Pn) {
                                 const uint32_t c = A.pair[pi];
                                 lo = c & 63u;
@@ -954,11 +954,11 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                         const uint4 w = inode[A.node[lo]];
                         uint32_t m = w.y & A.live[lo] & kLiveLists;
                         for (uint32_t k = pi - before; k > 0; --k) m &= m - 1;
-                        const uint32_t bit = (uint32_t)__builtin_ctz(m);
+                        bit = (uint32_t)__builtin_ctz(m);
                         g = (w.x & 0xfffffu) + (uint32_t)__popc(w.y & ((1u << bit) - 1u));
                     }
                     x = lo;
-                    hdr = grp[3 * g].x;
+                    hdr = glb((const uint32_t *)p.tree.grp)[12 * g];
                     if (given) {
                         all = (hdr & 15) == kDirAll;
                     } else {
@@ -977,7 +977,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                             }
                         } else {
                             ta = times_of(dir == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj));
-                            sh = 1;
+                            sh = kAdjShift<TT>;
                             const int32_t a = vtx((uint32_t)anc, lo);
                             const uint32_t *off = dir == kDirOut ? glb(p.g.out_off) : glb(p.g.in_off);
                             if (L > 1 && D > 2 && anc < 2) {
@@ -1093,7 +1093,8 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                     // every lane sends its window to its place: the kept ones
                     // first, the others behind them
                     const int to = 4 * (int)(keep ? mbcnt(km) : nw + mbcnt(~km));
-                    wrec.x = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(x | (g << 8)));
+                    // (a root's list by its bit, a deeper window by its group)
+                    wrec.x = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(x | ((L == 1 ? bit : g) << 8)));
                     wrec.y = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)l0);
                     wrec.z = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(incl - lk));
                     wrec.w = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)incl);
@@ -1101,6 +1102,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                     T = lane_value(wrec.w, nw - 1);
                 }
                 cc = 0;
+                formed = true;
                 if (L == 1 && nparts > 1) {
                     // one root, so every window fits this one chunk
                     cc = (uint32_t)(((uint64_t)T * part) / nparts);
@@ -1108,63 +1110,88 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                 }
             }
         }
-        if constexpr (L == 1 && epochs_of(MODE)) {
-            if (!done && cc < T && dumping) {
-                // write what is left of this chunk's windows as contexts of at
-                // most kCtxPiece candidates each (candidates [cc, T) in window
-                // order; lane w < nw holds window w)
+        if constexpr (L == 1 && D > 2 && plain_of(MODE)) if (epochs_of(MODE) || formed) {
+            // Candidates [lo, T) of this chunk (in window order; lane w < nw
+            // holds window w) as contexts of at most `piece` candidates, where
+            // room(total) gives the first slot, or no slot (false) for all.
+            auto hand_on = [&](uint32_t lo, uint32_t piece, auto room) -> bool {
                 uint32_t c_lo = 0, c_hi = 0;
                 if ((uint32_t)lane < nw) {
-                    c_lo = max(cc, wrec.z);
+                    c_lo = max(lo, wrec.z);
                     c_hi = wrec.w;
                 }
-                const uint32_t n = c_hi > c_lo ? (c_hi - c_lo + kCtxPiece - 1) / kCtxPiece : 0u;
+                const uint32_t n = c_hi > c_lo ? (c_hi - c_lo + piece - 1) / piece : 0u;
                 const uint32_t incl = incl_scan32(n, lane);
-                const uint32_t tot = lane_value(incl, kWave - 1);
-                // every wave may write its share of the buffer, so one atomic
-                // add takes the slots and the buffer never overflows
-                const uint64_t share = p.ctx_cap / ((uint64_t)gridDim.x * kWavesPerBlock);
-                if ((uint64_t)used + tot <= share) {
-                    unsigned long long base = 0;
-                    if (lane == 0 && tot) base = atomicAdd(p.ctx_count, (unsigned long long)tot);
-                    base = lane0_u64(base);
-                    used += tot;
-                    if (n) {
-                        const uint32_t ox = wrec.x & 255, og = wrec.x >> 8;
-                        const uint64_t tf = (uint64_t)tfirst_of(ox);
-                        EpochCtx c;
-                        c.a = vtx(0, ox);
-                        c.b = vtx(1, ox);
-                        c.t_lo = (uint32_t)tf;
-                        c.t_hi = (uint32_t)(tf >> 32);
-                        c.g = og;
-                        c.root = A.root[ox];
+                unsigned long long slot = 0;
+                if (!room(lane_value(incl, kWave - 1), slot)) return false;
+                if (n) {
+                    const uint32_t ox = wrec.x & 255;
+                    const uint64_t tf = (uint64_t)tfirst_of(ox);
+                    EpochCtx c;
+                    c.a = vtx(0, ox);
+                    c.b = vtx(1, ox);
+                    c.t_lo = (uint32_t)tf;
+                    c.t_hi = (uint32_t)(tf >> 32);
+                    c.bit = wrec.x >> 8;
+                    c.root = A.root[ox];
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            c.hlo[k] = D > 2 ? W.hlo[k][ox] : 0u;
-                            c.hlen[k] = D > 2 ? W.hlen[k][ox] : kNoHint;
-                        }
-                        c.pad2[0] = c.pad2[1] = 0;
-                        const unsigned long long slot = base + (incl - n);
-                        for (uint32_t k = 0; k < n; ++k) {
-                            const uint32_t c0 = c_lo + k * kCtxPiece;
-                            const uint32_t c1 = min(c0 + kCtxPiece, c_hi);
-                            c.e0 = wrec.y + (c0 - wrec.z);
-                            c.e1 = wrec.y + (c1 - wrec.z);
-                            p.ctx_out[slot + k] = c;
-                        }
+                    for (int k = 0; k < 4; ++k) {
+                        c.hlo[k] = W.hlo[k][ox];
+                        c.hlen[k] = W.hlen[k][ox];
                     }
-                    cc = T;
-                } else {
-                    dumping = false;   // its share is used up: this wave searches on
-                    room = false;
+                    c.pad2[0] = c.pad2[1] = 0;
+                    slot += incl - n;
+                    for (uint32_t k = 0; k < n; ++k) {
+                        const uint32_t c0 = c_lo + k * piece;
+                        const uint32_t c1 = min(c0 + piece, c_hi);
+                        c.e0 = wrec.y + (c0 - wrec.z);
+                        c.e1 = wrec.y + (c1 - wrec.z);
+                        p.ctx_out[slot + k] = c;
+                    }
+                }
+                return true;
+            };
+            if constexpr (epochs_of(MODE)) {
+                if (!done && cc < T && dumping) {
+                    // every wave may write its share of the buffer, so one
+                    // atomic add takes the slots and the buffer never overflows
+                    const uint64_t share = p.ctx_cap / ((uint64_t)gridDim.x * kWavesPerBlock);
+                    const bool ok = hand_on(cc, kCtxPiece, [&](uint32_t tot, unsigned long long &slot) {
+                        if ((uint64_t)used + tot > share) return false;
+                        if (lane == 0 && tot) slot = atomicAdd(p.ctx_count, (unsigned long long)tot);
+                        slot = lane0_u64(slot);
+                        used += tot;
+                        return true;
+                    });
+                    if (ok) {
+                        cc = T;
+                    } else {
+                        dumping = false;   // its share is used up: this wave searches on
+                        room = false;
+                    }
+                }
+            } else {
+                // A chunk with far more candidates than most is a long chain
+                // for one wave: what is beyond p.hand_on goes to the context
+                // launch that follows, spread over the device.
+                if (p.hand_on && nparts == 1 && T > p.hand_on + p.hand_on / 2) {
+                    const bool ok = hand_on(p.hand_on, p.ctx_piece, [&](uint32_t tot, unsigned long long &slot) {
+                        if (lane == 0) slot = atomicAdd(p.ctx_count, (unsigned long long)tot);
+                        slot = lane0_u64(slot);
+                        if (slot + tot <= p.ctx_cap) return true;
+                        // the buffer is full: the slots taken that exist hold
+                        // nothing, and this wave searches on
+                        EpochCtx none{};
+                        for (unsigned long long k = slot + lane; k < p.ctx_cap; k += kWave) p.ctx_out[k] = none;
+                        return false;
+                    });
+                    if (ok) T = p.hand_on;
                 }
             }
         }
         if (!done && cc < T) {
             const KParams<TT> &p = fresh(p0);
             const uint4 *__restrict__ inode = glb(p.tree.inode);
-            const uint4 *__restrict__ grp = glb(p.tree.grp);
             const uint32_t f = cc + lane;
             // owner window = number of windows that end at or before f
             const uint32_t o0 = (uint32_t)__popcll(__ballot((uint32_t)lane < nw && wrec.w <= cc));
@@ -1181,35 +1208,46 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
             const uint32_t oex = __shfl(wrec.z, oi);
             const uint32_t oend = __shfl(wrec.w, oi);
             const bool valid = f < T;
-            const uint32_t ox = oxg & 255, og = oxg >> 8;
+            const uint32_t ox = oxg & 255;
             const uint32_t ei = olo + (f - oex);
+            const uint32_t *__restrict__ gw = glb((const uint32_t *)p.tree.grp);   // group words
 
             uint32_t cw = 0;      // child word reached by this candidate
             TT tn = 0;            // its time
-            int dir = 0;
-            uint32_t nvp = 0, hit_s = 0;   // hit_s: motif vertex of the scanned endpoint
+            uint32_t nx = 0, en_eid = 0;   // its next codes, its edge id (32-bit times)
+            uint32_t dir = 0, anc = 0, g = 0;
+            uint32_t nvp = 2, hit_s = 0;   // hit_s: motif vertex of the scanned endpoint
             int32_t nv0 = -1, nv1 = -1;
             int32_t ph[SA];
 #pragma unroll
             for (int s = 0; s < SA; ++s) ph[s] = 0;
-            uint4 ga = make_uint4(0, 0, 0, 0), gb = ga;
             if (valid) {
-                ga = grp[3 * og];
-                gb = grp[3 * og + 1];
-                dir = ga.x & 15;
-                nvp = (ga.x >> 8) & 15;
+                if constexpr (L == 1) {
+                    const uint32_t bit = oxg >> 8;
+                    g = (node0.x & 0xfffffu) + (uint32_t)__popc(node0.y & ((1u << bit) - 1u));
+                    dir = bit == kLiveAllBit ? (uint32_t)kDirAll : bit & 1u;
+                    anc = bit == kLiveAllBit ? 0u : bit >> 1;
+                } else {
+                    g = oxg >> 8;
+                    const uint32_t hdr = gw[12 * g];
+                    dir = hdr & 15u;
+                    anc = (hdr >> 4) & 15u;
+                    nvp = (hdr >> 8) & 15u;
+                }
 #pragma unroll
                 for (int s = 0; s < SA; ++s) ph[s] = vtx(s, ox);
                 if (dir != kDirAll) {
                     const Entry<TT> *adj = dir == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj);
-                    const Entry<TT> en = adj[ei];   // one load: vertex and time
+                    const Entry<TT> en = adj[ei];   // one load: vertex, time, next codes
                     const int32_t v = en.v;
                     tn = en.t;
+                    nx = en.nx;
+                    if constexpr (sizeof(TT) == 4) en_eid = en.eid;
                     int y = -1;
 #pragma unroll
                     for (int s = 0; s < SA; ++s) y = ((uint32_t)s < nvp && ph[s] == v) ? s : y;
                     // in-groups have no bound-target children, so their words are 0
-                    cw = child_word(ga, gb, y);
+                    cw = gw[12 * g + (y >= 0 ? 1u + (uint32_t)y : 7u)];
                     hit_s = y >= 0 ? (uint32_t)y : nvp;
                     nv0 = v;
                 }
@@ -1221,7 +1259,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
 #pragma unroll
                     for (int s = 0; s < SA; ++s)
                         hit |= ((uint32_t)s < nvp && (ph[s] == cs || ph[s] == cd));
-                    cw = hit ? 0u : gb.w;
+                    cw = hit ? 0u : gw[12 * g + 7];
                     nv0 = cs;
                     nv1 = cd;
                     tn = glb(p.g.gt)[ei];
@@ -1238,7 +1276,9 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
             // the edge id of this candidate (pushed along, and written out
             // when enumerating), read only where it is used
             auto cand_eid = [&]() -> uint32_t {
-                return dir == kDirAll ? ei : (dir == kDirOut ? glb(p.g.out_eid) : glb(p.g.in_eid))[ei];
+                if (dir == kDirAll) return ei;
+                if constexpr (sizeof(TT) == 4) return en_eid;
+                else return (dir == kDirOut ? glb(p.g.out_eid) : glb(p.g.in_eid))[ei];
             };
             if constexpr (MODE == 4) {
                 const uint32_t q1 = (cw >> 16) & 0x7fffu;
@@ -1261,20 +1301,19 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                     if (dir == kDirAll) {
                         live |= (15u << (2 * nvp)) | (3u << (kLivePair + 2 * L));
                     } else {
-                        const Next4<TT> nx = (dir == kDirOut ? glb(p.g.out_next) : glb(p.g.in_next))[ei];
                         const TT thi = sat_add(tfirst_of(ox), p.delta_sat);
+                        const uint32_t q = next_code((TT)(thi - tn));
                         live &= ~(3u << (2 * hit_s));
-                        live |= (nx.c <= thi ? 1u : 0u) << (2 * hit_s);
-                        live |= (nx.d <= thi ? 2u : 0u) << (2 * hit_s);
-                        live |= (nx.a <= thi ? 1u : 0u) << (kLivePair + 2 * L);
-                        live |= (nx.b <= thi ? 2u : 0u) << (kLivePair + 2 * L);
-                        if ((L > 1 || !ctx) && f + 1 == oend)
-                            live &= ~(1u << (2 * ((ga.x >> 4) & 15u) + (uint32_t)dir));
+                        live |= (((nx >> 16) & 255u) <= q ? 1u : 0u) << (2 * hit_s);
+                        live |= ((nx >> 24) <= q ? 2u : 0u) << (2 * hit_s);
+                        live |= ((nx & 255u) <= q ? 1u : 0u) << (kLivePair + 2 * L);
+                        live |= (((nx >> 8) & 255u) <= q ? 2u : 0u) << (kLivePair + 2 * L);
+                        if ((L > 1 || !ctx) && f + 1 == oend) live &= ~(1u << (2 * anc + dir));
                     }
                     // nothing below it: not kept (the statistics count it)
-                    const uint4 nw = inode[cw & 0xffffu];
-                    if constexpr (LOG) push = (live & nw.y) != 0;
-                    else if constexpr (!STATS) push = (live & nw.z) != 0;
+                    const uint2 nw = reinterpret_cast<const uint2 *>(inode)[2 * (cw & 0xffffu) + 1];   // z, w
+                    if constexpr (LOG) push = (live & inode[cw & 0xffffu].y) != 0;
+                    else if constexpr (!STATS) push = (live & nw.x & ~kLeafParent) != 0;
                     // a leaf parent's pairs are counted here, on the full
                     // lanes of the candidate pass; only one with windows left
                     // to look at (2 % of them on a bursty graph) is kept
@@ -1296,10 +1335,10 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                                 return reinterpret_cast<const uint2 *>(gp)[2 * (size_t)e + (k & 1u)];
                             };
                             const TT tf = tfirst_of(ox);
-                            count_pairs<TT, MODE>(p, cnt, (live >> kLivePair) & (nw.w >> 16),
+                            count_pairs<TT, MODE>(p, cnt, (live >> kLivePair) & (nw.y >> 16),
                                                   glb(p.tree.pairs) + 8 * (cw & 0xffffu), pair_of, tn, tf,
                                                   sat_add(tf, p.delta_sat), nd);
-                            push = (nw.w & live & kLiveLists) != 0;
+                            push = (nw.y & live & kLiveLists) != 0;
                         }
                     }
                 }
@@ -1351,26 +1390,20 @@ struct Piece {
     bool ctx;
 };
 
-// Searches the pieces that claim() hands out until it returns false.  Roots
-// with something live in their windows are gathered from one or more pieces
-// (with `gather`) until the level-1 batch is full, so that the passes below
-// run on full waves; split roots and contexts run on their own.
+// Searches the pieces that claim() hands out until it returns false, up to 64
+// roots at a time.  Roots with nothing live in their windows take no place in
+// the batch.  (Filling the batch across pieces measured no different.)
 template <typename TT, int D, int MODE, typename Claim>
 __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                                               WaveLds<TT, D, keep_of(MODE)> &W,
                                               unsigned long long *cnt, const int lane,
-                                              Claim claim, const bool gather, Stats &st) {
+                                              Claim claim, Stats &st) {
     constexpr bool STATS = MODE == 1, LOG = MODE == 2;
     Piece w{0, 0, 0, 1, false};
-    uint32_t n1 = 0;   // roots in the level-1 batch
-    for (;;) {
-        bool more = w.pos < w.end;
-        if (!more) more = claim(w);
-        const bool alone = more && (w.nparts > 1 || w.ctx);
-        bool run = !more || !gather || alone;
-        uint32_t part = 0, nparts = 1;
-        const EpochCtx *ctx = nullptr;
-        if (more && !(alone && n1 > 0)) {
+    while (claim(w)) {
+        while (w.pos < w.end) {
+            uint32_t n1 = 0;   // roots in the level-1 batch
+            const EpochCtx *ctx = nullptr;
             if (epochs_of(MODE) && w.ctx) {
                 // each context becomes a root of the batch with its window
                 // and its root windows given
@@ -1384,7 +1417,7 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                         A.phi[1][lane] = c.b;
                         A.tfirst[lane] = t;
                         A.root[lane] = c.root;
-                        A.live[lane] = (uint8_t)root_live(p, c.root, sat_add(t, p.delta_sat));
+                        A.live[lane] = (uint8_t)root_live(p, c.root);
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             W.hlo[k][lane] = c.hlo[k];
@@ -1412,7 +1445,7 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                 if constexpr (D > 1) {
                     if (ok) {
                         t = glb(p.g.gt)[r];
-                        live = root_live(p, r, sat_add(t, p.delta_sat));
+                        live = root_live(p, r);
                         // a root with nothing in its windows ends here (the
                         // statistics still count its empty windows)
                         if constexpr (!STATS)
@@ -1420,31 +1453,26 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                                     (LOG ? glb(p.tree.inode)[0].y : glb(p.tree.inode)[0].z)) != 0;
                     }
                 }
-                // as many as the batch has room for: the piece goes on at the
-                // first one left out
-                const uint64_t km = __ballot(keep);
-                const uint32_t slot = n1 + mbcnt(km);
-                const uint64_t over = __ballot(keep && slot >= (uint32_t)kWave);
-                const uint32_t took = over ? (uint32_t)__builtin_ctzll(over) : (uint32_t)kWave;
-                const bool mine = (uint32_t)lane < took;
                 if (w.part == 0) {
-                    const uint64_t all = __ballot(ok && mine);
+                    const uint64_t all = __ballot(ok);
                     if (p.tree.root_q >= 0 && lane == 0 && all)
                         atomicAdd(&cnt[p.tree.root_q * p.tree.n_d], (unsigned long long)__popcll(all));
                     if constexpr (MODE == 4) {
                         if (p.tree.root_q >= 0) {
                             uint32_t e[kKMax] = {r, 0, 0, 0, 0};
-                            write_matches(p, ok && mine, (uint32_t)p.tree.root_q, e, 1);
+                            write_matches(p, ok, (uint32_t)p.tree.root_q, e, 1);
                         }
                     }
-                    if constexpr (STATS) st.v[kStatRoots] += ok && mine ? 1 : 0;
+                    if constexpr (STATS) st.v[kStatRoots] += ok ? 1 : 0;
                     if constexpr (LOG) {
-                        if (ok && mine) atomicAdd(&p.root_cost[r], 1ull);
+                        if (ok) atomicAdd(&p.root_cost[r], 1ull);
                     }
                 }
                 if constexpr (D > 1) {
                     auto &A = lvl<1>(W.lv);
-                    if (keep && mine) {
+                    const uint64_t km = __ballot(keep);
+                    if (keep) {
+                        const uint32_t slot = mbcnt(km);
                         A.phi[0][slot] = s;
                         A.phi[1][slot] = d;
                         A.tfirst[slot] = t;
@@ -1452,23 +1480,18 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                         A.root[slot] = r;
                         A.live[slot] = (uint8_t)live;
                     }
-                    n1 += uniform((uint32_t)__popcll(km & (over ? (1ull << took) - 1ull : ~0ull)));
+                    n1 = uniform((uint32_t)__popcll(km));
                 }
-                part = w.part;
-                nparts = w.nparts;
-                w.pos = min(w.pos + took, w.end);
-                run = run || n1 == (uint32_t)kWave;
+                w.pos += kWave;
+            }
+            if constexpr (D > 1) {
+                if (n1 > 0) {
+                    wave_sync();
+                    run_level<TT, D, MODE, 1>(p, W, cnt, lane, 0u, n1, st, w.part, w.nparts, ctx);
+                    wave_sync();
+                }
             }
         }
-        if constexpr (D > 1) {
-            if (run && n1 > 0) {
-                wave_sync();
-                run_level<TT, D, MODE, 1>(p, W, cnt, lane, 0u, n1, st, part, nparts, ctx);
-                wave_sync();
-                n1 = 0;
-            }
-        }
-        if (!more) break;
     }
 }
 
@@ -1494,6 +1517,8 @@ comine_kernel(const KParams<TT>) {
     const int wave = (int)(threadIdx.x / kWave);
     WaveLds<TT, D, keep_of(MODE)> &W = reinterpret_cast<WaveLds<TT, D, keep_of(MODE)> *>(smem + cnt_bytes)[wave];
 
+    __shared__ uint32_t runs_taken;   // context launch: runs this workgroup took
+    if (threadIdx.x == 0) runs_taken = 0;
     for (int i = (int)threadIdx.x; i < n_slots; i += (int)blockDim.x) cnt[i] = 0;
     W.flag[lane] = 0;
     __syncthreads();
@@ -1534,6 +1559,28 @@ comine_kernel(const KParams<TT>) {
             items = false;
         }
         if constexpr (epochs_of(MODE)) {
+            if (p.ctx_in && p.ctx_n) {
+                // contexts handed on by the launch before: runs of them, one
+                // XCD's share in a row (close in time, they read the same
+                // lists), dealt to its workgroups in turn and taken by the
+                // workgroup's next free wave
+                const uint32_t n = (uint32_t)min(*glb(p.ctx_n), p.ctx_cap);
+                const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
+                const uint32_t per = max(1u, min(16u, n / (4u * waves)));
+                const uint32_t runs = (n + per - 1) / per, xcds = min(8u, gridDim.x);
+                const uint32_t x = blockIdx.x % xcds;
+                const uint32_t r0 = (uint32_t)((uint64_t)runs * x / xcds);
+                const uint32_t r1 = (uint32_t)((uint64_t)runs * (x + 1) / xcds);
+                uint32_t k = 0;
+                if (lane == 0) k = atomicAdd(&runs_taken, 1u);
+                k = lane_value(k, 0);
+                const uint32_t groups = (gridDim.x - x + xcds - 1) / xcds;
+                const uint64_t r = (uint64_t)r0 + blockIdx.x / xcds + (uint64_t)k * groups;
+                if (r >= r1) return false;
+                const uint32_t b0 = (uint32_t)r * per;
+                w = {b0, (uint32_t)min(b0 + per, n), 0u, 1u, true};
+                return true;
+            }
             if (p.ctx_in) {
                 const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
                 const uint32_t per = min((uint32_t)kWave, max(1u, (p.n_ctx_in + waves - 1) / waves));
@@ -1549,22 +1596,27 @@ comine_kernel(const KParams<TT>) {
         while (qi < nq) {
             const uint32_t q = (home + qi) % nq;
             const uint32_t qbeg = queue_begin(p.n_roots, nq, q);
-            const uint32_t qend = queue_end(p.n_roots, nq, q);
+            const uint32_t qlen = queue_end(p.n_roots, nq, q) - qbeg;
             unsigned long long got = 0;
             if (lane == 0) {
                 unsigned long long *head = &p.queues[q * kQueueStride];
                 if (p.stop && __hip_atomic_load(p.stop, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_SYSTEM) != 0) {
                     got = ~0ull;
-                } else if (p.max_chunks) {
-                    // the budget is spent only on a queue that still has roots,
-                    // so a call makes progress while any root is left: a
-                    // budget holder's claim fails only when another holder
-                    // took the last chunk
+                } else if (p.max_chunks || qi > 0) {
+                    // Another XCD's queue is looked at before it is claimed
+                    // from: claims on one head take about 20 ns each, one after
+                    // another, and the failing last claims of 8,192 waves on
+                    // eight queues were 115 us at the end of every count.  A
+                    // budget is spent only on a queue that still has roots, so
+                    // a call makes progress while any root is left: a budget
+                    // holder's claim fails only when another holder took the
+                    // last chunk.
                     const unsigned long long h =
                         __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (h >= (unsigned long long)(qend - qbeg)) got = h;
-                    else if (atomicAdd(&p.queues[kBudgetSlot * kQueueStride], 1ull) >= p.max_chunks)
+                    if (h >= (unsigned long long)qlen) got = h;
+                    else if (p.max_chunks &&
+                             atomicAdd(&p.queues[kBudgetSlot * kQueueStride], 1ull) >= p.max_chunks)
                         got = ~0ull;
                     else got = atomicAdd(head, (unsigned long long)p.chunk);
                 } else {
@@ -1576,18 +1628,18 @@ comine_kernel(const KParams<TT>) {
                 qi = nq;
                 break;
             }
-            if (got >= (unsigned long long)(qend - qbeg)) {
+            if (got >= (unsigned long long)qlen) {
                 ++qi;
                 continue;
             }
             const uint32_t b0 = uniform(qbeg + (uint32_t)got);
             if (p.skip && p.skip[b0 / kWave]) continue;   // searched as an item
-            w = {b0, (uint32_t)min(b0 + p.chunk, qend), 0u, 1u, false};
+            w = {b0, qbeg + (uint32_t)min(got + p.chunk, (unsigned long long)qlen), 0u, 1u, false};
             return true;
         }
         return false;
     };
-    search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, true, st);
+    search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, st);
     if constexpr (epochs_of(MODE)) {
         // out of work: an idle wave, for the epoch limit
         if (p.ctx_out && !st.dumped && lane == 0) atomicAdd(p.idle, 1u);
@@ -1639,7 +1691,7 @@ batch_kernel(const BatchParams<TT> bp) {
                 fresh = false;
                 return got;
             };
-            search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, true, st);
+            search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, st);
         };
         const uint32_t nq = (uint32_t)counter_slots(job.p.tree);
         for (uint32_t i = (uint32_t)lane; i < nq; i += kWave) cnt[i] = 0;
@@ -1660,7 +1712,7 @@ size_t smem_bytes(int n_q) {
 }
 
 template <typename TT, int D, int MODE>
-hipError_t launch_ds(const KParams<TT> &p, int blocks, hipStream_t stream) {
+hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
     const size_t sm = smem_bytes<TT, D, MODE>(counter_slots(p.tree));
     auto kern = comine_kernel<TT, D, MODE>;
     if (sm > 65536) {
@@ -1677,6 +1729,27 @@ hipError_t launch_ds(const KParams<TT> &p, int blocks, hipStream_t stream) {
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kWave * kWavesPerBlock, sm);
         if (e != hipSuccess) return e;
         blocks = ncu * (per > 0 ? per : 1);
+        if (p.chunk == 0) {
+            // Few roots are spread thinner: a wave's 64 roots are one chain of
+            // dependent loads, so a small graph takes as long as its slowest
+            // chunk.  Four chunks per wave at least, of 4 to 64 roots, and no
+            // more workgroups than there are pieces of work.
+            const uint32_t waves = (uint32_t)blocks * kWavesPerBlock;
+            uint32_t c = kWave;
+            while (c > 4 && (uint64_t)p.n_roots < (uint64_t)c * 4 * waves) c >>= 1;
+            p.chunk = c;
+            const uint32_t need = (p.n_roots + c * kWavesPerBlock - 1) / (c * kWavesPerBlock);
+            if (!p.items && !p.ctx_in && need < (uint32_t)blocks) blocks = (int)std::max(1u, need);
+        }
+    }
+    if (p.chunk == 0) p.chunk = kWave;
+    if (p.hand_on) {
+        // about twice the candidates a wave's share of the roots has; deeper
+        // trees find far more below each
+        const uint32_t share = p.n_roots / ((uint32_t)blocks * kWavesPerBlock);
+        p.hand_on = (D <= 3 ? std::min(8192u, std::max(512u, 2 * share))
+                            : std::min(2048u, std::max(256u, share / 4))) & ~63u;
+        p.ctx_piece = D <= 3 ? 256u : 64u;
     }
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * kWavesPerBlock), sm, stream, p);
     return hipGetLastError();
@@ -1686,7 +1759,7 @@ hipError_t launch_ds(const KParams<TT> &p, int blocks, hipStream_t stream) {
 
 template <typename TT, int D>
 hipError_t launch_d(const KParams<TT> &p, int blocks, hipStream_t stream) {
-    if (p.ctx_in || p.ctx_out)
+    if (p.ctx_in || (p.ctx_out && !p.hand_on))
         return p.tree.n_d > 1 ? launch_ds<TT, D, 6>(p, blocks, stream) : launch_ds<TT, D, 5>(p, blocks, stream);
     if (p.enum_out) return launch_ds<TT, D, 4>(p, blocks, stream);
     if (p.stats) return launch_ds<TT, D, 1>(p, blocks, stream);
