@@ -64,7 +64,7 @@ hipError_t launch_bin(const float *seg_cost, uint32_t n_seg, uint32_t n_roots, c
 // p[0..n) = 0 with a kernel
 hipError_t launch_fill_f32_zero(float *p, uint32_t n, hipStream_t st);
 
-// Train on (features, label) pairs with Adam; one wave, minibatches of 32.
+// Train on (features, label) pairs with Adam; one workgroup, minibatches of 32.
 // params, adam_m, adam_v: kParams fp32 each (device).  loss: per epoch (device).
 hipError_t launch_train(float *params, float *adam_m, float *adam_v, const float *feats,
                         const float *labels, uint32_t n, const uint32_t *perm, uint32_t epochs,

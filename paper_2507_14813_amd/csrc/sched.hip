@@ -400,250 +400,310 @@ __global__ void bin_scatter_kernel(const float *seg_cost, uint32_t n_seg, uint32
 }
 
 // ------------------------------------------------------------ training
-// One wave; minibatches of 32 rows (two 16-row tiles).  LDS keeps bf16 copies
-// of the weights in both orientations ([in][out] for the backward products,
-// [out][in] for the forward B operands) and the activations of the batch.
+// One workgroup of 16 waves; minibatches of 32 rows (two 16-row tiles), one
+// after another.  A step is a chain of small products (32 x 64 x 64), so what
+// bounds it is latency: barriers, LDS round trips, the divisions and roots of
+// 10,497 Adam updates.  Every weight therefore stays in the registers of one
+// lane for the whole training (its FP32 value and both moments): wave w owns
+// the 16 x 16 tile (w / 4, w % 4) of W2 and W3, waves 0-3 a tile of W1, waves
+// 4-8 the vectors.  LDS keeps the bf16 copies of the weights in both
+// orientations ([in][out] for the backward products, [out][in] for the forward
+// B operands) and the batch's activations, rows padded so that the 16 rows of
+// an operand lie in different banks.  The next batch's rows are loaded while
+// this one is worked on.  One wave with its state in global memory took 72 us
+// a step (74 ms for 16,384 rows and two epochs); every sum keeps its order, so
+// the weights are the same to the bit.
 constexpr int kTB = 32;
+constexpr int kTrainWaves = 16;
+constexpr int kLd = 72;      // row length of 64-wide LDS arrays
+constexpr int kLdX = 40;     // row length of 32-wide ones
 
 struct TrainLds {
-    uint16_t X[kTB * 32];
-    uint16_t H1[kTB * kHid], H2[kTB * kHid], H3[kTB * kHid];
-    uint16_t G[kTB * kHid], G2[kTB * kHid];          // dZ of two adjacent layers
-    uint16_t W1T[kHid * 32];                         // [out][in]
-    uint16_t W2[kHid * kHid], W2T[kHid * kHid];
-    uint16_t W3[kHid * kHid], W3T[kHid * kHid];
+    uint16_t X[2][kTB * kLdX];                       // two batches
+    uint16_t H1[kTB * kLd], H2[kTB * kLd], H3[kTB * kLd];
+    uint16_t G[kTB * kLd], G2[kTB * kLd];            // dZ of two adjacent layers
+    uint16_t W1T[kHid * kLdX];                       // [out][in]
+    uint16_t W2[kHid * kLd], W2T[kHid * kLd];
+    uint16_t W3[kHid * kLd], W3T[kHid * kLd];
     float B1[kHid], B2[kHid], B3[kHid], W4[kHid], B4;
-    float y[kTB], dout[kTB];
+    float y[2][kTB], dout[kTB];
 };
 
-struct AdamState {
-    float *P, *M, *V;
-    float lr, c1, c2;      // step size and bias corrections 1/(1-beta^t)
-};
+// a parameter and its Adam moments, in registers
+struct Weight { float p, m, v; };
+struct AdamStep { float lr, c1, c2; };   // step size and bias corrections 1/(1-beta^t)
 
-__device__ __forceinline__ float adam(AdamState &s, int idx, float g) {
+// One update.  Which of the two products of a moment is rounded before they are
+// added (the old moment's) is written out rather than left to the compiler: a
+// difference in the last bit spreads through all later steps by way of the
+// bf16 copies.
+__device__ __forceinline__ float adam(const AdamStep &s, Weight &w, float g) {
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float m = b1 * s.M[idx] + (1.f - b1) * g;
-    const float v = b2 * s.V[idx] + (1.f - b2) * g * g;
-    s.M[idx] = m;
-    s.V[idx] = v;
-    const float p = s.P[idx] - s.lr * (m * s.c1) / (sqrtf(v * s.c2) + eps);
-    s.P[idx] = p;
+    const float m = __builtin_fmaf(1.f - b1, g, b1 * w.m);
+    const float v = __builtin_fmaf((1.f - b2) * g, g, b2 * w.v);
+    w.m = m;
+    w.v = v;
+    const float p = w.p - s.lr * (m * s.c1) / (sqrtf(v * s.c2) + eps);
+    w.p = p;
     return p;
 }
 
-__device__ void refresh_lds(const float *P, TrainLds &S, int lane) {
-    for (int i = lane; i < kHid * kHid; i += kWave) {
-        const int in = i / kHid, out = i % kHid;
-        const uint16_t w2 = f2bf(P[kOffW2 + i]), w3 = f2bf(P[kOffW3 + i]);
-        S.W2[i] = w2;
-        S.W2T[out * kHid + in] = w2;
-        S.W3[i] = w3;
-        S.W3T[out * kHid + in] = w3;
-    }
-    for (int i = lane; i < 32 * kHid; i += kWave) {
-        const int in = i / kHid, out = i % kHid;
-        S.W1T[out * 32 + in] = f2bf(P[kOffW1 + i]);
-    }
-    for (int i = lane; i < kHid; i += kWave) {
-        S.B1[i] = P[kOffB1 + i];
-        S.B2[i] = P[kOffB2 + i];
-        S.B3[i] = P[kOffB3 + i];
-        S.W4[i] = rbf(P[kOffW4 + i]);
-    }
-    if (lane == 0) S.B4 = P[kOffB4];
-}
-
-// D = A(16 x 32k) * B for 16-row tile `tile` of a [kTB][ld] bf16 matrix times
-// 4 column tiles of a [out][in] bf16 matrix (contiguous k), nks k-steps.
-__device__ void tile_times_T(const uint16_t *A, int ld, int tile, const uint16_t *BT, int ldb,
-                             int nks, const float *bias, int lane, f32x4 *acc) {
+// 16-row tile `tile` of a [kTB][ld] bf16 matrix times column tile nt of a
+// [out][in] bf16 matrix (contiguous k), nks k-steps, from c0 upwards
+__device__ __forceinline__ f32x4 tile_times_T(const uint16_t *A, int ld, int tile,
+                                              const uint16_t *BT, int ldb, int nt, int nks,
+                                              float c0, int lane) {
     const int c = lane & 15, q = lane >> 4;
+    f32x4 acc = splat(c0);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = splat(bias ? bias[16 * nt + c] : 0.f);
-    for (int ks = 0; ks < nks; ++ks) {
-        const bf16x8 a = ld8(A + (16 * tile + c) * ld + 32 * ks + 8 * q);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-            acc[nt] = mfma(a, ld8(BT + (16 * nt + c) * ldb + 32 * ks + 8 * q), acc[nt]);
-    }
+    for (int ks = 0; ks < nks; ++ks)
+        acc = mfma(ld8(A + (16 * tile + c) * ld + 32 * ks + 8 * q),
+                   ld8(BT + (16 * nt + c) * ldb + 32 * ks + 8 * q), acc);
+    return acc;
 }
 
 // gradient tile dW[16 mt + i][16 nt + j] = sum_rows Hin[row][16 mt + i] * dZ[row][16 nt + j]
-__device__ f32x4 grad_tile(const uint16_t *Hin, int ldh, const uint16_t *dZ, int mt, int nt,
-                           int lane) {
+__device__ __forceinline__ f32x4 grad_tile(const uint16_t *Hin, int ldh, const uint16_t *dZ, int mt,
+                                           int nt, int lane) {
     const int c = lane & 15, q = lane >> 4;
     uint16_t av[8], bv[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         av[j] = Hin[(8 * q + j) * ldh + 16 * mt + c];
-        bv[j] = dZ[(8 * q + j) * kHid + 16 * nt + c];
+        bv[j] = dZ[(8 * q + j) * kLd + 16 * nt + c];
     }
     return mfma(pack8u(av), pack8u(bv), splat(0.f));
 }
 
-__global__ void __launch_bounds__(kWave)
+// sum over the batch of column `col` of dZ, rows in order
+__device__ __forceinline__ float column_sum(const uint16_t *dZ, int col) {
+    float g = 0.f;
+#pragma unroll
+    for (int row = 0; row < kTB; ++row) g += bf2f(dZ[row * kLd + col]);
+    return g;
+}
+
+__global__ void __launch_bounds__(kWave * kTrainWaves)
 train_kernel(float *P, float *M, float *V, const float *feats, const float *labels, uint32_t n,
              const uint32_t *perm, uint32_t epochs, float lr, float *loss_out) {
     extern __shared__ __align__(16) unsigned char smem[];
     TrainLds &S = *reinterpret_cast<TrainLds *>(smem);
-    const int lane = threadIdx.x, c = lane & 15, q = lane >> 4;
-    refresh_lds(P, S, lane);
-    wave_sync();
-    AdamState as{P, M, V, lr, 1.f, 1.f};
-    float b1t = 1.f, b2t = 1.f;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
+    const int tile = w >> 2, nt = w & 3, mt = w >> 2;   // this wave's tiles (tile: waves 0-7)
+
+    // every parameter to its lane, and the bf16 copies to LDS
+    auto get = [&](int i) { return Weight{P[i], M[i], V[i]}; };
+    Weight w1[4], w2[4], w3[4], wv{0.f, 0.f, 0.f};
+    const int vec = w == 4 ? kOffB3 + lane : w == 5 ? kOffB2 + lane : w == 6 ? kOffB1 + lane
+                  : w == 7 ? kOffW4 + lane : w == 8 && lane == 0 ? kOffB4 : -1;
+    auto put3 = [&](int r) {
+        S.W3[(16 * mt + 4 * q + r) * kLd + 16 * nt + c] = f2bf(w3[r].p);
+    };
+    auto put2 = [&](int r) {
+        S.W2[(16 * mt + 4 * q + r) * kLd + 16 * nt + c] = f2bf(w2[r].p);
+    };
+    auto put3T = [&](int r) {
+        S.W3T[(16 * nt + c) * kLd + 16 * mt + 4 * q + r] = f2bf(w3[r].p);
+    };
+    auto put2T = [&](int r) {
+        S.W2T[(16 * nt + c) * kLd + 16 * mt + 4 * q + r] = f2bf(w2[r].p);
+    };
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int in = 16 * mt + 4 * q + r, out = 16 * nt + c;
+        w3[r] = get(kOffW3 + in * kHid + out);
+        w2[r] = get(kOffW2 + in * kHid + out);
+        w1[r] = w < 4 ? get(kOffW1 + (4 * q + r) * kHid + out) : Weight{0.f, 0.f, 0.f};
+        put3(r);
+        put2(r);
+        put3T(r);
+        put2T(r);
+        if (w < 4) S.W1T[out * kLdX + 4 * q + r] = f2bf(w1[r].p);
+    }
+    for (int i = threadIdx.x; i < kHid * 16; i += blockDim.x)
+        S.W1T[(i >> 4) * kLdX + 16 + (i & 15)] = 0;     // (padding rows of W1 are zero)
+    for (int i = threadIdx.x; i < 2 * kTB * 16; i += blockDim.x)
+        S.X[i >> 9][((i >> 4) & 31) * kLdX + 16 + (i & 15)] = 0;
+    if (vec >= 0) {
+        wv = get(vec);
+        if (w == 4) S.B3[lane] = wv.p;
+        if (w == 5) S.B2[lane] = wv.p;
+        if (w == 6) S.B1[lane] = wv.p;
+        if (w == 7) S.W4[lane] = rbf(wv.p);
+        if (w == 8) S.B4 = wv.p;
+    }
+
+    // Rows: waves 8-15 hold one feature each (row li / 16, feature li % 16) of
+    // the batches ahead: fv / yv of the next one, id of the one after it
     const uint32_t nb = n / kTB;
+    const uint64_t steps = (uint64_t)nb * epochs;
+    const int li = (int)threadIdx.x - kWave * 8, row = li >> 4, feat = li & 15;
+    auto row_id = [&](uint64_t step) -> uint32_t {
+        return step < steps ? perm[(uint32_t)(step % nb) * kTB + row] : 0u;
+    };
+    uint32_t id = 0;
+    float fv = 0.f, yv = 0.f;
+    auto fetch = [&]() {
+        fv = feats[(size_t)id * kFeat + feat];
+        yv = feat == 0 ? labels[id] : 0.f;
+    };
+    auto store_rows = [&](int buf) {
+        S.X[buf][row * kLdX + feat] = f2bf(fv);
+        if (feat == 0) S.y[buf][row] = yv;
+    };
+    if (li >= 0 && steps > 0) {
+        id = row_id(0);
+        fetch();
+        store_rows(0);
+        id = row_id(1);
+        fetch();
+        id = row_id(2);
+    }
+    __syncthreads();
+
+    AdamStep as{lr, 1.f, 1.f};
+    float b1t = 1.f, b2t = 1.f, lsum = 0.f;
+    uint64_t step = 0;
     for (uint32_t ep = 0; ep < epochs; ++ep) {
-        float lsum = 0.f;
-        for (uint32_t bi = 0; bi < nb; ++bi) {
+        lsum = 0.f;
+        for (uint32_t bi = 0; bi < nb; ++bi, ++step) {
+            const int buf = (int)(step & 1);
             b1t *= 0.9f;
             b2t *= 0.999f;
             as.c1 = 1.f / (1.f - b1t);
             as.c2 = 1.f / (1.f - b2t);
-            if (lane < kTB) {
-                const uint32_t id = perm[bi * kTB + lane];
+            // forward, one 16 x 16 output tile per wave
+            auto store_relu = [&](uint16_t *H, f32x4 acc) {
 #pragma unroll
-                for (int k = 0; k < 32; ++k)
-                    S.X[lane * 32 + k] = k < kFeat ? f2bf(feats[(size_t)id * kFeat + k]) : 0;
-                S.y[lane] = labels[id];
-            }
-            wave_sync();
-            // forward
-            f32x4 acc[4];
-            for (int tile = 0; tile < 2; ++tile) {
-                tile_times_T(S.X, 32, tile, S.W1T, 32, 1, S.B1, lane, acc);
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        S.H1[(16 * tile + 4 * q + r) * kHid + 16 * nt + c] = f2bf(fmaxf(acc[nt][r], 0.f));
-            }
-            wave_sync();
-            for (int tile = 0; tile < 2; ++tile) {
-                tile_times_T(S.H1, kHid, tile, S.W2T, kHid, 2, S.B2, lane, acc);
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        S.H2[(16 * tile + 4 * q + r) * kHid + 16 * nt + c] = f2bf(fmaxf(acc[nt][r], 0.f));
-            }
-            wave_sync();
-            for (int tile = 0; tile < 2; ++tile) {
-                tile_times_T(S.H2, kHid, tile, S.W3T, kHid, 2, S.B3, lane, acc);
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        S.H3[(16 * tile + 4 * q + r) * kHid + 16 * nt + c] = f2bf(fmaxf(acc[nt][r], 0.f));
-            }
-            wave_sync();
+                for (int r = 0; r < 4; ++r)
+                    H[(16 * tile + 4 * q + r) * kLd + 16 * nt + c] = f2bf(fmaxf(acc[r], 0.f));
+            };
+            if (w < 8)
+                store_relu(S.H1, tile_times_T(S.X[buf], kLdX, tile, S.W1T, kLdX, nt, 1,
+                                              S.B1[16 * nt + c], lane));
+            __syncthreads();
+            if (w < 8)
+                store_relu(S.H2, tile_times_T(S.H1, kLd, tile, S.W2T, kLd, nt, 2, S.B2[16 * nt + c],
+                                              lane));
+            __syncthreads();
+            if (w < 8)
+                store_relu(S.H3, tile_times_T(S.H2, kLd, tile, S.W3T, kLd, nt, 2, S.B3[16 * nt + c],
+                                              lane));
+            __syncthreads();
             // output layer and loss (mean squared error)
-            if (lane < kTB) {
+            if (w == 0 && lane < kTB) {
                 float pr = S.B4;
-                for (int j = 0; j < kHid; ++j) pr += bf2f(S.H3[lane * kHid + j]) * S.W4[j];
-                const float e = pr - S.y[lane];
+#pragma unroll
+                for (int j8 = 0; j8 < kHid; j8 += 8) {
+                    const uint4 h = *reinterpret_cast<const uint4 *>(S.H3 + lane * kLd + j8);
+                    const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        pr += bf2f((uint16_t)(hw[j >> 1] >> (16 * (j & 1)))) * S.W4[j8 + j];
+                }
+                const float e = pr - S.y[buf][lane];
                 lsum += e * e;
                 S.dout[lane] = 2.f * e / (float)kTB;
             }
-            wave_sync();
-            // layer 4: gradients, and dZ3 = dout * w4 masked by relu (old w4)
-            {
-                const int j = lane;
+            __syncthreads();
+            // layer 4: dZ3 = dout * w4 masked by relu (old w4), and gradients
+#pragma unroll
+            for (int k = 0; k < kTB / kTrainWaves; ++k) {
+                const int r = w + k * kTrainWaves;
+                const float h = bf2f(S.H3[r * kLd + lane]);
+                S.G[r * kLd + lane] = f2bf(h > 0.f ? S.dout[r] * S.W4[lane] : 0.f);
+            }
+            if (w == 7) {
                 float gw = 0.f;
-                for (int row = 0; row < kTB; ++row) {
-                    const float h = bf2f(S.H3[row * kHid + j]);
-                    gw += h * S.dout[row];
-                    S.G[row * kHid + j] = f2bf(h > 0.f ? S.dout[row] * S.W4[j] : 0.f);
+#pragma unroll
+                for (int r = 0; r < kTB; ++r) {
+                    const float h = bf2f(S.H3[r * kLd + lane]);
+                    gw += h * S.dout[r];
                 }
-                const float w4new = adam(as, kOffW4 + j, gw);
+                adam(as, wv, gw);
+            }
+            if (w == 8) {
                 float gb = lane < kTB ? S.dout[lane] : 0.f;
 #pragma unroll
                 for (int o = 32; o > 0; o >>= 1) gb += __shfl_xor(gb, o);
-                wave_sync();
-                S.W4[j] = rbf(w4new);
-                if (lane == 0) S.B4 = adam(as, kOffB4, gb);
+                if (lane == 0) S.B4 = adam(as, wv, gb);
             }
-            wave_sync();
-            // layer 3: dZ2 = (dZ3 W3^T) * relu'(H2) with the old W3, then W3's update
-            for (int tile = 0; tile < 2; ++tile) {
-                tile_times_T(S.G, kHid, tile, S.W3, kHid, 2, nullptr, lane, acc);
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = 16 * tile + 4 * q + r, col = 16 * nt + c;
-                        S.G2[row * kHid + col] =
-                            f2bf(bf2f(S.H2[row * kHid + col]) > 0.f ? acc[nt][r] : 0.f);
-                    }
-            }
-            wave_sync();
-            for (int mt = 0; mt < 4; ++mt)
-                for (int nt = 0; nt < 4; ++nt) {
-                    const f32x4 gt = grad_tile(S.H2, kHid, S.G, mt, nt, lane);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int in = 16 * mt + 4 * q + r, out = 16 * nt + c;
-                        const uint16_t w = f2bf(adam(as, kOffW3 + in * kHid + out, gt[r]));
-                        S.W3[in * kHid + out] = w;
-                        S.W3T[out * kHid + in] = w;
-                    }
-                }
-            {
-                float gb = 0.f;
-                for (int row = 0; row < kTB; ++row) gb += bf2f(S.G[row * kHid + lane]);
-                S.B3[lane] = adam(as, kOffB3 + lane, gb);
-            }
-            wave_sync();
-            // layer 2: dZ1 = (dZ2 W2^T) * relu'(H1) (into G), then W2's update
-            for (int tile = 0; tile < 2; ++tile) {
-                tile_times_T(S.G2, kHid, tile, S.W2, kHid, 2, nullptr, lane, acc);
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = 16 * tile + 4 * q + r, col = 16 * nt + c;
-                        S.G[row * kHid + col] =
-                            f2bf(bf2f(S.H1[row * kHid + col]) > 0.f ? acc[nt][r] : 0.f);
-                    }
-            }
-            wave_sync();
-            for (int mt = 0; mt < 4; ++mt)
-                for (int nt = 0; nt < 4; ++nt) {
-                    const f32x4 gt = grad_tile(S.H1, kHid, S.G2, mt, nt, lane);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int in = 16 * mt + 4 * q + r, out = 16 * nt + c;
-                        const uint16_t w = f2bf(adam(as, kOffW2 + in * kHid + out, gt[r]));
-                        S.W2[in * kHid + out] = w;
-                        S.W2T[out * kHid + in] = w;
-                    }
-                }
-            {
-                float gb = 0.f;
-                for (int row = 0; row < kTB; ++row) gb += bf2f(S.G2[row * kHid + lane]);
-                S.B2[lane] = adam(as, kOffB2 + lane, gb);
-            }
-            wave_sync();
-            // layer 1 (inputs 0..15 only; the padding rows stay zero)
-            for (int nt = 0; nt < 4; ++nt) {
-                const f32x4 gt = grad_tile(S.X, 32, S.G, 0, nt, lane);
+            __syncthreads();
+            if (w == 7) S.W4[lane] = rbf(wv.p);
+            // layer 3: dZ2 = (dZ3 W3^T) * relu'(H2) with the old W3, and W3's update
+            auto store_masked = [&](uint16_t *dZ, const uint16_t *H, f32x4 acc) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int in = 4 * q + r, out = 16 * nt + c;
-                    S.W1T[out * 32 + in] = f2bf(adam(as, kOffW1 + in * kHid + out, gt[r]));
+                    const int at = (16 * tile + 4 * q + r) * kLd + 16 * nt + c;
+                    dZ[at] = f2bf(bf2f(H[at]) > 0.f ? acc[r] : 0.f);
+                }
+            };
+            if (w < 8)
+                store_masked(S.G2, S.H2, tile_times_T(S.G, kLd, tile, S.W3, kLd, nt, 2, 0.f, lane));
+            {
+                const f32x4 gt = grad_tile(S.H2, kLd, S.G, mt, nt, lane);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    adam(as, w3[r], gt[r]);
+                    put3T(r);
                 }
             }
-            {
-                float gb = 0.f;
-                for (int row = 0; row < kTB; ++row) gb += bf2f(S.G[row * kHid + lane]);
-                S.B1[lane] = adam(as, kOffB1 + lane, gb);
-            }
-            wave_sync();
-        }
+            if (w == 4) S.B3[lane] = adam(as, wv, column_sum(S.G, lane));
+            __syncthreads();
+            // layer 2: dZ1 = (dZ2 W2^T) * relu'(H1) (into G), and W2's update
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o);
-        if (lane == 0 && loss_out) loss_out[ep] = nb ? lsum / (float)(nb * kTB) : 0.f;
+            for (int r = 0; r < 4; ++r) put3(r);
+            if (w < 8)
+                store_masked(S.G, S.H1, tile_times_T(S.G2, kLd, tile, S.W2, kLd, nt, 2, 0.f, lane));
+            {
+                const f32x4 gt = grad_tile(S.H1, kLd, S.G2, mt, nt, lane);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    adam(as, w2[r], gt[r]);
+                    put2T(r);
+                }
+            }
+            if (w == 5) S.B2[lane] = adam(as, wv, column_sum(S.G2, lane));
+            __syncthreads();
+            // layer 1 (inputs 0..15 only; the padding rows stay zero), and the
+            // next batch's rows
+#pragma unroll
+            for (int r = 0; r < 4; ++r) put2(r);
+            if (w < 4) {
+                const f32x4 gt = grad_tile(S.X[buf], kLdX, S.G, 0, nt, lane);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    S.W1T[(16 * nt + c) * kLdX + 4 * q + r] = f2bf(adam(as, w1[r], gt[r]));
+            }
+            if (w == 6) S.B1[lane] = adam(as, wv, column_sum(S.G, lane));
+            if (li >= 0) {
+                store_rows(buf ^ 1);
+                fetch();
+                id = row_id(step + 3);
+            }
+            __syncthreads();
+        }
+        if (w == 0) {
+            float l = lsum;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
+            if (lane == 0 && loss_out) loss_out[ep] = nb ? l / (float)(nb * kTB) : 0.f;
+        }
     }
+
+    auto set = [&](int i, const Weight &x) {
+        P[i] = x.p;
+        M[i] = x.m;
+        V[i] = x.v;
+    };
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int in = 16 * mt + 4 * q + r, out = 16 * nt + c;
+        set(kOffW3 + in * kHid + out, w3[r]);
+        set(kOffW2 + in * kHid + out, w2[r]);
+        if (w < 4) set(kOffW1 + (4 * q + r) * kHid + out, w1[r]);
+    }
+    if (vec >= 0) set(vec, wv);
 }
 
 }  // namespace
@@ -717,7 +777,7 @@ hipError_t launch_train(float *params, float *adam_m, float *adam_v, const float
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(train_kernel, dim3(1), dim3(kWave), sm, st, params, adam_m, adam_v, feats,
+    hipLaunchKernelGGL(train_kernel, dim3(1), dim3(kWave * kTrainWaves), sm, st, params, adam_m, adam_v, feats,
                        labels, n, perm, epochs, lr, loss);
     return hipGetLastError();
 }
