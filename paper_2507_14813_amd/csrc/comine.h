@@ -10,7 +10,8 @@ constexpr int kVMax = 6;        // motif vertices
 constexpr int kKMax = 5;        // motif edges
 constexpr int kWave = 64;
 constexpr int kMaxDeltas = 8;   // windows counted in one search
-constexpr int kWavesPerBlock = 4;
+constexpr int kWavesPerBlock = 4;      // 8 where more waves fit so (search.h, fill_shape)
+constexpr int kMaxWavesPerBlock = 8;
 constexpr int kQueues = 8;      // root queues, one per XCD
 constexpr int kQueueStride = 16;  // u64 words between queue heads (own cache line)
 // queue words: kQueues root-queue heads, the work-item queue head, the claim

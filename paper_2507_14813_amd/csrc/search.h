@@ -906,7 +906,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
             if (p.ctx_out && room && !dumping && !st.dumped && (++polls & 15u) == 0) {
                 uint32_t v = 0;
                 if (lane == 0) v = __hip_atomic_load(p.idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
+                const uint32_t waves = gridDim.x * (blockDim.x / kWave);
                 dumping = (uint64_t)lane_value(v, 0) * 100u >= (uint64_t)p.idle_pct * waves;
             }
         }
@@ -1155,7 +1155,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                 if (!done && cc < T && dumping) {
                     // every wave may write its share of the buffer, so one
                     // atomic add takes the slots and the buffer never overflows
-                    const uint64_t share = p.ctx_cap / ((uint64_t)gridDim.x * kWavesPerBlock);
+                    const uint64_t share = p.ctx_cap / ((uint64_t)gridDim.x * (blockDim.x / kWave));
                     const bool ok = hand_on(cc, kCtxPiece, [&](uint32_t tot, unsigned long long &slot) {
                         if ((uint64_t)used + tot > share) return false;
                         if (lane == 0 && tot) slot = atomicAdd(p.ctx_count, (unsigned long long)tot);
@@ -1504,12 +1504,13 @@ template <int D, int MODE>
 constexpr int min_waves_per_eu() { return D <= 3 && plain_of(MODE) ? 8 : 1; }
 
 template <typename TT, int D, int MODE>
-__global__ void __launch_bounds__(kWave * kWavesPerBlock)
+__global__ void __launch_bounds__(kWave * kMaxWavesPerBlock)
 __attribute__((amdgpu_waves_per_eu(min_waves_per_eu<D, MODE>(), 8)))
 comine_kernel(const KParams<TT>) {
     const KParams<TT> &p = *(const KParams<TT> *)(ConstParams<TT>)__builtin_amdgcn_kernarg_segment_ptr();
     constexpr bool STATS = MODE == 1;
     extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t wpb = blockDim.x / kWave;
     unsigned long long *cnt = reinterpret_cast<unsigned long long *>(smem);
     const int32_t n_slots = counter_slots(p.tree);
     const size_t cnt_bytes = ((size_t)n_slots * 8 + 15) & ~(size_t)15;
@@ -1527,7 +1528,7 @@ comine_kernel(const KParams<TT>) {
     for (int i = 0; i < kStats; ++i) st.v[i] = 0;
     st.dumped = false;
     // when each wave starts and ends its search (device real-time clock)
-    const uint32_t clock_slot = blockIdx.x * kWavesPerBlock + (uint32_t)wave;
+    const uint32_t clock_slot = blockIdx.x * wpb + (uint32_t)wave;
     if (p.wave_clock && lane == 0 && clock_slot < p.n_wave_clock)
         p.wave_clock[2 * clock_slot] = __builtin_amdgcn_s_memrealtime();
 
@@ -1565,7 +1566,7 @@ comine_kernel(const KParams<TT>) {
                 // lists), dealt to its workgroups in turn and taken by the
                 // workgroup's next free wave
                 const uint32_t n = (uint32_t)min(*glb(p.ctx_n), p.ctx_cap);
-                const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
+                const uint32_t waves = gridDim.x * wpb;
                 const uint32_t per = max(1u, min(16u, n / (4u * waves)));
                 const uint32_t runs = (n + per - 1) / per, xcds = min(8u, gridDim.x);
                 const uint32_t x = blockIdx.x % xcds;
@@ -1582,7 +1583,7 @@ comine_kernel(const KParams<TT>) {
                 return true;
             }
             if (p.ctx_in) {
-                const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
+                const uint32_t waves = gridDim.x * wpb;
                 const uint32_t per = min((uint32_t)kWave, max(1u, (p.n_ctx_in + waves - 1) / waves));
                 unsigned long long it = 0;
                 if (lane == 0) it = atomicAdd(&p.queues[kItemSlot * kQueueStride], (unsigned long long)per);
@@ -1706,39 +1707,83 @@ batch_kernel(const BatchParams<TT> bp) {
 
 
 template <typename TT, int D, int MODE>
-size_t smem_bytes(int n_q) {
+size_t smem_bytes(int n_q, int wpb) {
     return (((size_t)n_q * 8 + 15) & ~(size_t)15) +
-           (size_t)kWavesPerBlock * sizeof(WaveLds<TT, D, keep_of(MODE)>);
+           (size_t)wpb * sizeof(WaveLds<TT, D, keep_of(MODE)>);
+}
+
+// Shape of a launch that fills the device: waves per workgroup and workgroups.
+// Four waves per workgroup, or eight where sharing one set of counters lets
+// more waves onto a compute unit (756 motifs: 6 KB of counters, 16 waves
+// instead of 12).  The last answer per kernel and thread is kept: asking costs
+// more than the rest of a small launch.
+constexpr size_t kMaxLds = 160 * 1024 - 256;   // dynamic part of a workgroup's LDS at most
+struct Fill {
+    int dev = -1, n_q = -1, wpb = 4, blocks = 0;
+};
+template <typename TT, int D, int MODE>
+hipError_t fill_shape(int n_q, Fill &f) {
+    static thread_local Fill last;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (last.dev != dev || last.n_q != n_q) {
+        auto kern = comine_kernel<TT, D, MODE>;
+        int ncu = 0, most = 0;
+        e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        Fill n{dev, n_q, kWavesPerBlock, ncu};
+        for (int wpb = kWavesPerBlock; wpb <= kMaxWavesPerBlock; wpb *= 2) {
+            const size_t sm = smem_bytes<TT, D, MODE>(n_q, wpb);
+            if (sm > kMaxLds) break;
+            if (sm > 65536) {
+                e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)kMaxLds);   // (one value for every launch)
+                if (e != hipSuccess) return e;
+            }
+            int per = 0;
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kWave * wpb, sm);
+            if (e != hipSuccess) return e;
+            if (per * wpb > most) {
+                most = per * wpb;
+                n.wpb = wpb;
+                n.blocks = ncu * per;
+            }
+        }
+        last = n;
+    }
+    f = last;
+    return hipSuccess;
 }
 
 template <typename TT, int D, int MODE>
 hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
-    const size_t sm = smem_bytes<TT, D, MODE>(counter_slots(p.tree));
     auto kern = comine_kernel<TT, D, MODE>;
-    if (sm > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    const int n_q = counter_slots(p.tree);
+    int wpb = kWavesPerBlock;
+    if (blocks > 0) {   // the caller's workgroups: four waves each
+        if (smem_bytes<TT, D, MODE>(n_q, wpb) > 65536) {
+            hipError_t e = hipFuncSetAttribute((const void *)kern,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)kMaxLds);
+            if (e != hipSuccess) return e;
+        }
+    } else {
+        Fill f;
+        hipError_t e = fill_shape<TT, D, MODE>(n_q, f);
         if (e != hipSuccess) return e;
-    }
-    if (blocks <= 0) {
-        int dev = 0, ncu = 0, per = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kWave * kWavesPerBlock, sm);
-        if (e != hipSuccess) return e;
-        blocks = ncu * (per > 0 ? per : 1);
+        blocks = f.blocks;
+        wpb = f.wpb;
         if (p.chunk == 0) {
             // Few roots are spread thinner: a wave's 64 roots are one chain of
             // dependent loads, so a small graph takes as long as its slowest
             // chunk.  Four chunks per wave at least, of 4 to 64 roots, and no
             // more workgroups than there are pieces of work.
-            const uint32_t waves = (uint32_t)blocks * kWavesPerBlock;
+            const uint32_t waves = (uint32_t)(blocks * wpb);
             uint32_t c = kWave;
             while (c > 4 && (uint64_t)p.n_roots < (uint64_t)c * 4 * waves) c >>= 1;
             p.chunk = c;
-            const uint32_t need = (p.n_roots + c * kWavesPerBlock - 1) / (c * kWavesPerBlock);
+            const uint32_t need = (p.n_roots + c * wpb - 1) / (c * wpb);
             if (!p.items && !p.ctx_in && need < (uint32_t)blocks) blocks = (int)std::max(1u, need);
         }
     }
@@ -1746,12 +1791,13 @@ hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
     if (p.hand_on) {
         // about twice the candidates a wave's share of the roots has; deeper
         // trees find far more below each
-        const uint32_t share = p.n_roots / ((uint32_t)blocks * kWavesPerBlock);
+        const uint32_t share = p.n_roots / (uint32_t)(blocks * wpb);
         p.hand_on = (D <= 3 ? std::min(8192u, std::max(512u, 2 * share))
                             : std::min(2048u, std::max(256u, share / 4))) & ~63u;
         p.ctx_piece = D <= 3 ? 256u : 64u;
     }
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * kWavesPerBlock), sm, stream, p);
+    const size_t sm = smem_bytes<TT, D, MODE>(n_q, wpb);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * wpb), sm, stream, p);
     return hipGetLastError();
 }
 
