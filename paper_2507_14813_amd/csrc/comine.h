@@ -16,7 +16,8 @@ constexpr int kQueues = 8;      // root queues, one per XCD
 constexpr int kQueueStride = 16;  // u64 words between queue heads (own cache line)
 // queue words: kQueues root-queue heads, the work-item queue head, the claim
 // counter of a chunk budget, each kQueueStride words apart
-constexpr int kItemSlot = kQueues;
+constexpr int kItemSlot = kQueues;   // contexts of an epoch
+constexpr int kItemWord = 8;         // in a root queue's line: head of its share of the items
 constexpr int kBudgetSlot = kQueues + 1;
 constexpr int kCtxCountWord = (kQueues + 1) * 16 + 8;   // in the budget's line: contexts handed on
 constexpr int kQueueSlots = kQueues + 2;
@@ -163,6 +164,8 @@ struct KParams {
     uint32_t chunk;               // roots per chunk (0: chosen at the launch by the number
                                   // of roots; multiple of 64 with items or skip)
     uint32_t n_queues;            // 1..kQueues root queues
+    uint32_t place_first;         // 1: every wave's first chunk is its own place in its home
+                                  // queue, and claims start behind those (set at the launch)
     unsigned long long *queues;   // kQueueWords: queue heads (zeroed, or a resume
                                   // point) and the claim counter (zeroed)
     const int32_t *stop;          // NULL, or a flag (host-pinned or device memory)
@@ -256,7 +259,9 @@ struct BatchParams {
     const BatchItem *items;
     uint32_t n_items;
     uint32_t n_q_max;             // largest tree's counter_slots
-    unsigned long long *cursor;   // item queue head, zeroed before launch
+    unsigned long long *cursor;   // kQueues item queue heads, kQueueStride words apart,
+                                  // zeroed before launch; queue q holds items
+                                  // [n q / kQueues, n (q + 1) / kQueues)
     unsigned long long *counts;   // every job's counters, zeroed before launch
     uint32_t multi;               // 1 when some job's tree has several windows
 };

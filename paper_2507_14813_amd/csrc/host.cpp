@@ -827,6 +827,8 @@ int learned_search(const mg_graph *g, mg_tree *tr, const mg_model *model,
 }  // namespace
 
 // ---------------------------------------------------------------- batches
+constexpr uint32_t kBatchQueueWords = mg::kQueues * mg::kQueueStride;
+
 struct mg_batch {
     std::vector<const mg_graph *> graphs;
     std::vector<mg_tree *> trees;
@@ -844,7 +846,7 @@ struct mg_batch {
     float predict_ms = 0.f;       // features + MLP + ordering at plan creation
     bool learned = false;
     std::vector<mg::BatchItem> items;
-    DevBuf d_jobs, d_items, d_work;   // d_work: cursor (16 B) + counters
+    DevBuf d_jobs, d_items, d_work;   // d_work: item queue heads, then counters
     uint64_t *h_counts = nullptr;     // pinned
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1014,10 +1016,10 @@ int enqueue_step(mg_batch *b, hipStream_t st) {
     bp.n_items = (uint32_t)b->items.size();
     bp.n_q_max = b->n_q_max;
     bp.cursor = (unsigned long long *)b->d_work.ptr;
-    bp.counts = (unsigned long long *)((char *)b->d_work.ptr + 16);
+    bp.counts = bp.cursor + kBatchQueueWords;
     bp.multi = 0;
     for (const mg_tree *tr : b->trees) bp.multi |= tr->deltas.size() > 1 ? 1u : 0u;
-    hipError_t e = mg::launch_fill_u64(bp.cursor, 2 + b->total_q, 0ull, st);
+    hipError_t e = mg::launch_fill_u64(bp.cursor, kBatchQueueWords + b->total_q, 0ull, st);
     if (e != hipSuccess) return fail(MG_EDEVICE, "fill launch failed: %s", hipGetErrorString(e));
     if (bp.n_items) {
         e = mg::launch_batch<TT>(bp, b->depth, b->opts.blocks, st);
@@ -1292,7 +1294,8 @@ int mg_batch_create(const mg_graph *const *graphs, const mg_tree *const *trees, 
         int rc = b->time_bytes == 4 ? upload_jobs<uint32_t>(b.get(), st)
                                     : upload_jobs<uint64_t>(b.get(), st);
         if (rc) return rc;
-        rc = dev_alloc(b->d_work, 16 + 8 * (size_t)std::max<uint32_t>(1, b->total_q), (void *)st);
+        rc = dev_alloc(b->d_work, 8 * (size_t)(kBatchQueueWords + std::max<uint32_t>(1, b->total_q)),
+                       (void *)st);
         if (rc) return rc;
         HIP_TRY(hipHostMalloc((void **)&b->h_counts, 8 * (size_t)std::max<uint32_t>(1, b->total_q),
                               hipHostMallocDefault));

@@ -71,6 +71,11 @@ edge_facts(const int32_t *src, const int32_t *dst, const int64_t *t, uint32_t n,
         lo = min(lo, b);
         hi = max(hi, b);
     }
+    // one set of atomics per block: on one address they come one after another
+    // (one set per wave of a full grid took 140 us)
+    __shared__ unsigned long long s_bad[kIWaves], s_lo[kIWaves], s_hi[kIWaves];
+    __shared__ uint32_t s_loops[kIWaves], s_uns[kIWaves];
+    const int w = threadIdx.x / kWave;
     bad = wave_min(bad);
     lo = wave_min(lo);
     hi = wave_max(hi);
@@ -78,12 +83,28 @@ edge_facts(const int32_t *src, const int32_t *dst, const int64_t *t, uint32_t n,
     for (int o = 32; o > 0; o >>= 1) loops += __shfl_xor(loops, o);
     const bool any = __ballot(unsorted) != 0;
     if ((threadIdx.x & (kWave - 1)) == 0) {
-        if (bad != ~0ull) atomicMin(&f->first_bad, bad);
-        if (any) f->unsorted = 1;
-        if (loops) atomicAdd(&f->loops, (unsigned long long)loops);
-        if (lo != ~0ull) atomicMin(&f->t_min, lo);
-        if (hi) atomicMax(&f->t_max, hi);
+        s_bad[w] = bad;
+        s_lo[w] = lo;
+        s_hi[w] = hi;
+        s_loops[w] = loops;
+        s_uns[w] = any;
     }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    unsigned long long nl = 0;
+    uint32_t uns = 0;
+    for (int k = 0; k < kIWaves; ++k) {
+        bad = min(bad, s_bad[k]);
+        lo = min(lo, s_lo[k]);
+        hi = max(hi, s_hi[k]);
+        nl += s_loops[k];
+        uns |= s_uns[k];
+    }
+    if (bad != ~0ull) atomicMin(&f->first_bad, bad);
+    if (uns) f->unsorted = 1;
+    if (nl) atomicAdd(&f->loops, nl);
+    if (lo != ~0ull) atomicMin(&f->t_min, lo);
+    if (hi) atomicMax(&f->t_max, hi);
 }
 
 // ------------------------------------------------------------ radix sort
@@ -393,7 +414,7 @@ inline uint64_t scan_blocks(uint64_t n) { return (n + kScanTile - 1) / kScanTile
 hipError_t launch_edge_facts(const int32_t *src, const int32_t *dst, const int64_t *t, uint32_t n,
                              int32_t n_nodes, EdgeFacts *facts, hipStream_t st) {
     hipLaunchKernelGGL(facts_init, dim3(1), dim3(1), 0, st, facts);
-    hipLaunchKernelGGL(edge_facts, dim3(grid_for(n, kIB * 8, 4096)), dim3(kIB), 0, st, src, dst, t,
+    hipLaunchKernelGGL(edge_facts, dim3(grid_for(n, kIB * 8, 512)), dim3(kIB), 0, st, src, dst, t,
                        n, n_nodes, facts);
     return hipGetLastError();
 }

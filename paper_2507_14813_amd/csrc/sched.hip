@@ -22,13 +22,9 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// fp32 -> bf16 bits, round to nearest even; NaN stays NaN
+// fp32 -> bf16 bits, round to nearest even (the hardware's conversion)
 __device__ __forceinline__ uint16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u)
-        return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ __forceinline__ float rbf(float f) { return bf2f(f2bf(f)); }
@@ -81,14 +77,15 @@ __device__ void root_features(const DevGraph<TT> &g, const DevTree &t, TT dsat, 
     f[1] = log1pf((float)(ia1 - ia0)) * s;
     f[2] = log1pf((float)(ob1 - ob0)) * s;
     f[3] = log1pf((float)(ib1 - ib0)) * s;
-    uint32_t l;
-    l = first_greater(ot, kAdjShift<TT>, oa0, oa1, tr);
+    // the windows start where the edge's list ranks say
+    const uint4 x = g.gx[r];
+    uint32_t l = x.x;
     f[4] = log1pf((float)(gallop_greater(ot, kAdjShift<TT>, l, oa1, thi) - l)) * s;
-    l = first_greater(ot, kAdjShift<TT>, ob0, ob1, tr);
+    l = x.z;
     f[5] = log1pf((float)(gallop_greater(ot, kAdjShift<TT>, l, ob1, thi) - l)) * s;
-    l = first_greater(it, kAdjShift<TT>, ia0, ia1, tr);
+    l = x.y;
     f[6] = log1pf((float)(gallop_greater(it, kAdjShift<TT>, l, ia1, thi) - l)) * s;
-    l = first_greater(it, kAdjShift<TT>, ib0, ib1, tr);
+    l = x.w;
     f[7] = log1pf((float)(gallop_greater(it, kAdjShift<TT>, l, ib1, thi) - l)) * s;
     l = gallop_greater(g.gt, 0, r, g.n_edges, tr);   // edges after r with a later time
     f[8] = log1pf((float)(gallop_greater(g.gt, 0, l, g.n_edges, thi) - l)) * s;

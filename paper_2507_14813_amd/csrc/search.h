@@ -1515,7 +1515,7 @@ comine_kernel(const KParams<TT>) {
     const int32_t n_slots = counter_slots(p.tree);
     const size_t cnt_bytes = ((size_t)n_slots * 8 + 15) & ~(size_t)15;
     const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int wave = (int)(threadIdx.x / kWave);
+    const int wave = (int)uniform(threadIdx.x / kWave);
     WaveLds<TT, D, keep_of(MODE)> &W = reinterpret_cast<WaveLds<TT, D, keep_of(MODE)> *>(smem + cnt_bytes)[wave];
 
     __shared__ uint32_t runs_taken;   // context launch: runs this workgroup took
@@ -1542,15 +1542,38 @@ comine_kernel(const KParams<TT>) {
     bool items = p.items != nullptr;
     const uint32_t nq = p.n_queues;
     const uint32_t home = blockIdx.x % nq;
-    uint32_t qi = 0;
+    uint32_t qi = 0, ii = 0;
+    // The wave's first chunk is its own place in its home queue; claims start
+    // behind those (claims on one head take about 20 ns each, one after
+    // another: 62,500 chunks of 16 roots were 150 us of a count).  Not where the
+    // heads are a resume point or waves may leave early.
+    bool first = p.place_first != 0;
+    const uint32_t place = (blockIdx.x / nq) * wpb + (uint32_t)wave;
     auto claim = [&](Piece &w) -> bool {
         if (st.dumped) return false;   // an epoch ended
         if (items) {
-            unsigned long long it = 0;
-            if (lane == 0) it = atomicAdd(&p.queues[kItemSlot * kQueueStride], 1ull);
-            it = lane0_u64(it);
-            if (it < uniform(*p.n_items)) {
-                const uint2 item = p.items[uniform((uint32_t)it)];
+            // item i waits in queue i % kQueues, so that the claims of the
+            // whole device are not one after another on one head
+            const uint32_t n_items = uniform(*p.n_items);
+            uint32_t it = n_items;
+            for (; ii < (uint32_t)kQueues; ++ii) {
+                const uint32_t q = (blockIdx.x + ii) % (uint32_t)kQueues;
+                const uint32_t nq_items = (n_items + (uint32_t)kQueues - 1u - q) / (uint32_t)kQueues;
+                uint32_t *head = reinterpret_cast<uint32_t *>(&p.queues[q * kQueueStride + kItemWord]);
+                uint32_t k = nq_items;
+                if (lane == 0) {
+                    const uint32_t h = ii ? __hip_atomic_load(head, __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                    if (h < nq_items) k = atomicAdd(head, 1u);
+                }
+                k = lane_value(k, 0);
+                if (k < nq_items) {
+                    it = k * (uint32_t)kQueues + q;
+                    break;
+                }
+            }
+            if (it < n_items) {
+                const uint2 item = p.items[it];
                 const uint32_t ix = uniform(item.x), iy = uniform(item.y);
                 const bool split = (iy & kItemSplit) != 0;
                 w = {ix, split ? ix + 1 : iy, split ? (iy >> 15) & 0x7fffu : 0u,
@@ -1598,44 +1621,50 @@ comine_kernel(const KParams<TT>) {
             const uint32_t q = (home + qi) % nq;
             const uint32_t qbeg = queue_begin(p.n_roots, nq, q);
             const uint32_t qlen = queue_end(p.n_roots, nq, q) - qbeg;
-            unsigned long long got = 0;
-            if (lane == 0) {
-                unsigned long long *head = &p.queues[q * kQueueStride];
-                if (p.stop && __hip_atomic_load(p.stop, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_SYSTEM) != 0) {
-                    got = ~0ull;
-                } else if (p.max_chunks || qi > 0) {
-                    // Another XCD's queue is looked at before it is claimed
-                    // from: claims on one head take about 20 ns each, one after
-                    // another, and the failing last claims of 8,192 waves on
-                    // eight queues were 115 us at the end of every count.  A
-                    // budget is spent only on a queue that still has roots, so
-                    // a call makes progress while any root is left: a budget
-                    // holder's claim fails only when another holder took the
-                    // last chunk.
-                    const unsigned long long h =
-                        __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (h >= (unsigned long long)qlen) got = h;
+            // chunks of this queue that are some wave's first (a head stays
+            // below 2^32: the roots and one failing claim per wave)
+            const uint32_t taken = p.place_first ? min(qlen, ((gridDim.x - q + nq - 1) / nq) * wpb * p.chunk) : 0u;
+            uint32_t got = qlen;
+            if (first) {
+                first = false;
+                got = min(qlen, place * p.chunk);
+                if (got == qlen) continue;
+            } else {
+                // Another XCD's queue is looked at before it is claimed from:
+                // the failing last claims of 8,192 waves on eight heads were
+                // 115 us at the end of every count.  A budget is spent only on a
+                // queue that still has roots, so a call makes progress while any
+                // root is left: a budget holder's claim fails only when another
+                // holder took the last chunk.
+                uint32_t *head = reinterpret_cast<uint32_t *>(&p.queues[q * kQueueStride]);
+                if (lane == 0) {
+                    const bool look = p.max_chunks || qi > 0;
+                    const uint32_t h = look ? __hip_atomic_load(head, __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                    if (p.stop && __hip_atomic_load(p.stop, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_SYSTEM) != 0)
+                        got = ~0u;
+                    else if (h >= qlen - taken)
+                        got = qlen;
                     else if (p.max_chunks &&
                              atomicAdd(&p.queues[kBudgetSlot * kQueueStride], 1ull) >= p.max_chunks)
-                        got = ~0ull;
-                    else got = atomicAdd(head, (unsigned long long)p.chunk);
-                } else {
-                    got = atomicAdd(head, (unsigned long long)p.chunk);
+                        got = ~0u;
+                    else
+                        got = min(qlen, atomicAdd(head, p.chunk) + taken);
                 }
+                got = lane_value(got, 0);
             }
-            got = lane0_u64(got);
-            if (got == ~0ull) {
+            if (got == ~0u) {
                 qi = nq;
                 break;
             }
-            if (got >= (unsigned long long)qlen) {
+            if (got >= qlen) {
                 ++qi;
                 continue;
             }
-            const uint32_t b0 = uniform(qbeg + (uint32_t)got);
+            const uint32_t b0 = qbeg + got;
             if (p.skip && p.skip[b0 / kWave]) continue;   // searched as an item
-            w = {b0, qbeg + (uint32_t)min(got + p.chunk, (unsigned long long)qlen), 0u, 1u, false};
+            w = {b0, qbeg + (uint32_t)min(got + p.chunk, qlen), 0u, 1u, false};
             return true;
         }
         return false;
@@ -1666,7 +1695,7 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock)
 batch_kernel(const BatchParams<TT> bp) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int wave = (int)(threadIdx.x / kWave);
+    const int wave = (int)uniform(threadIdx.x / kWave);
     const size_t cnt_bytes = ((size_t)bp.n_q_max * 8 + 15) & ~(size_t)15;
     unsigned char *mine = smem + (size_t)wave * (cnt_bytes + sizeof(WaveLds<TT, D, 0>));
     unsigned long long *cnt = reinterpret_cast<unsigned long long *>(mine);
@@ -1674,12 +1703,26 @@ batch_kernel(const BatchParams<TT> bp) {
     W.flag[lane] = 0;
     Stats st;
     st.dumped = false;
-    for (;;) {
-        unsigned long long it = 0;
-        if (lane == 0) it = atomicAdd(bp.cursor, 1ull);
-        it = lane0_u64(it);
-        if (it >= bp.n_items) break;
-        const BatchItem item = bp.items[uniform((uint32_t)it)];
+    // one queue of items per XCD (claims on one head come one after another),
+    // then what is left of the others, looked at before it is claimed from
+    uint32_t qi = 0;
+    while (qi < (uint32_t)kQueues) {
+        const uint32_t q = (blockIdx.x + qi) % (uint32_t)kQueues;
+        const uint32_t ibeg = (uint32_t)((uint64_t)bp.n_items * q / kQueues);
+        const uint32_t iend = (uint32_t)((uint64_t)bp.n_items * (q + 1) / kQueues);
+        uint32_t it = iend;
+        if (lane == 0) {
+            unsigned long long *head = bp.cursor + q * kQueueStride;
+            const unsigned long long h =
+                qi ? __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+            if (ibeg + h < iend) it = (uint32_t)min(ibeg + atomicAdd(head, 1ull), (unsigned long long)iend);
+        }
+        it = lane_value(it, 0);
+        if (it >= iend) {
+            ++qi;
+            continue;
+        }
+        const BatchItem item = bp.items[it];
         const BatchJob<TT> &job = bp.jobs[uniform(item.job)];
         auto search = [&](const KParams<TT> &p) {
             const uint32_t ip = uniform(item.part);
@@ -1777,14 +1820,20 @@ hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
         if (p.chunk == 0) {
             // Few roots are spread thinner: a wave's 64 roots are one chain of
             // dependent loads, so a small graph takes as long as its slowest
-            // chunk.  Four chunks per wave at least, of 4 to 64 roots, and no
-            // more workgroups than there are pieces of work.
+            // chunk.  Up to 64 roots per wave every wave gets one chunk, of 4
+            // roots at least, and there are no more workgroups than chunks;
+            // beyond that, chunks of 64.
             const uint32_t waves = (uint32_t)(blocks * wpb);
-            uint32_t c = kWave;
-            while (c > 4 && (uint64_t)p.n_roots < (uint64_t)c * 4 * waves) c >>= 1;
+            uint32_t c = 4;
+            while (c < (uint32_t)kWave && (uint64_t)c * waves < p.n_roots) c <<= 1;
             p.chunk = c;
             const uint32_t need = (p.n_roots + c * wpb - 1) / (c * wpb);
-            if (!p.items && !p.ctx_in && need < (uint32_t)blocks) blocks = (int)std::max(1u, need);
+            if (!p.items && !p.ctx_in && need < (uint32_t)blocks) {
+                blocks = (int)std::max(1u, need);
+                // whole rounds of the queues, so that each holds its waves' chunks
+                blocks = std::min(f.blocks, (blocks + (int)p.n_queues - 1) / (int)p.n_queues * (int)p.n_queues);
+            }
+            p.place_first = !p.items && !p.ctx_in;
         }
     }
     if (p.chunk == 0) p.chunk = kWave;
