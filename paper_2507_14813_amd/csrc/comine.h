@@ -61,7 +61,8 @@ enum : int { kDirOut = 0, kDirIn = 1, kDirAll = 2 };
 //         vertex (all groups leaf_only)
 //     w = of a leaf parent: the lists whose window has to be found (bits 0-12:
 //         not counted from pairs, or with a new-vertex child) and the pairs
-//         that are counted (bits 16-23: kLivePair's bits)
+//         that are counted (bits 16-23: kLivePair's bits; bit 24: some for
+//         new-vertex children too)
 //   pairs[8 i + k]  of leaf parent i and pair k (matched edge k / 2, or against
 //     it for odd k): x = child reached by an edge of the pair, y and z = the
 //     new-vertex children of the out- and of the in-list that hold the pair,
@@ -88,6 +89,7 @@ struct DevTree {
     const uint4 *inode;
     const uint4 *pairs;
     const uint4 *grp;
+    uint32_t root_pairs;   // bit 0, 1: some leaf parent counts the root's pair, the one against it
     int32_t n_q;        // distinct motifs
     int32_t root_q;     // query id of the one-edge prefix, -1 if none
     int32_t depth;      // longest motif in edges
@@ -148,7 +150,7 @@ struct EpochCtx {
     uint32_t bit, e0, e1, root;
     uint32_t hlo[4];
     uint16_t hlen[4];
-    uint32_t pad2[2];
+    uint32_t job, pad2;            // a batch's job
 };
 static_assert(sizeof(EpochCtx) == 64, "context record");
 constexpr uint32_t kCtxPiece = 64;   // candidates per context at most
@@ -216,6 +218,7 @@ struct KParams {
     // into ctx_out, and the launch that follows searches them (ctx_in, with
     // ctx_n their count on the device)
     uint32_t hand_on, ctx_piece;
+    uint32_t job;                 // this search's job in a batch
     const unsigned long long *ctx_n;
     uint32_t leaf_scan;           // windows whose children are all leaves are counted
                                   // without the candidate expansion: by one lane up
@@ -264,6 +267,12 @@ struct BatchParams {
                                   // [n q / kQueues, n (q + 1) / kQueues)
     unsigned long long *counts;   // every job's counters, zeroed before launch
     uint32_t multi;               // 1 when some job's tree has several windows
+    // contexts that the jobs' searches hand on (KParams::hand_on), searched by
+    // a second launch when `contexts` is set
+    const EpochCtx *ctx;
+    const unsigned long long *ctx_n;
+    unsigned long long ctx_cap;
+    uint32_t contexts;
 };
 
 // `depth` = the deepest tree of the batch.

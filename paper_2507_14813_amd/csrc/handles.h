@@ -78,6 +78,7 @@ struct mg_tree {
     std::vector<int32_t> node_tab;      // 4 words per internal node
     std::vector<int32_t> grp_tab;       // 12 words per group
     std::vector<int32_t> pair_tab;      // 32 words per internal node
+    uint32_t root_pairs = 0;            // DevTree::root_pairs
     int32_t depth = 0, root_q = -1;
     int32_t kdepth = 0;    // depth of the kernel that searches it (DevTree::kdepth)
     mg_tree_info_t info{};

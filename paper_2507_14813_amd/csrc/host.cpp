@@ -318,6 +318,7 @@ int build_tree(mg_tree *tr) {
     };
     tr->node_tab.assign(4 * (size_t)std::max(n_int, 1), 0);
     tr->grp_tab.clear();
+    tr->root_pairs = 0;
     tr->pair_tab.assign(32 * (size_t)std::max(n_int, 1), 0);
     tr->depth = 0;
     bool wide2 = false;   // an internal two-edge prefix on four vertices
@@ -343,6 +344,7 @@ int build_tree(mg_tree *tr) {
         if (g0 + (int)groups.size() > (1 << 20))
             return fail(MG_EUNSUPPORTED, "too many child groups");
         uint32_t lists = 0, gate = 0, pairs = 0, by_window = 0;
+        bool news = false;   // a new-vertex child whose window is counted from pairs
         for (auto &kv : groups) {
             const bool all = kv.first == (int)mg::kLiveAllBit;
             const int dir = all ? mg::kDirAll : kv.first & 1, anc = all ? 0 : kv.first >> 1;
@@ -411,6 +413,7 @@ int build_tree(mg_tree *tr) {
                 }
             lists |= 1u << kv.first;
             if (!codes || rec[7]) by_window |= 1u << kv.first;
+            news = news || (codes && rec[7]);
             gate |= codes && !rec[7] ? codes << mg::kLivePair : 1u << kv.first;
             tr->grp_tab.insert(tr->grp_tab.end(), rec, rec + 12);
         }
@@ -423,9 +426,10 @@ int build_tree(mg_tree *tr) {
         }
         int32_t *w = &tr->node_tab[4 * (size_t)iidx[n]];
         w[0] = g0;
+        if (leaf_parent) tr->root_pairs |= pairs & 3u;
         w[1] = (int32_t)lists;
         w[2] = (int32_t)(leaf_parent ? gate | mg::kLeafParent : lists);
-        w[3] = (int32_t)(leaf_parent ? by_window | pairs << 16 : 0u);
+        w[3] = (int32_t)(leaf_parent ? by_window | pairs << 16 | (news ? 1u << 24 : 0u) : 0u);
     }
     if (tr->grp_tab.empty()) tr->grp_tab.assign(12, 0);
     tr->root_q = tr->nodes[0].q;
@@ -763,6 +767,7 @@ mg::DevTree dev_tree(const mg_tree *tr) {
     t.grp = t.inode + tr->node_tab.size() / 4;
     t.pairs = t.grp + tr->grp_tab.size() / 4;
     t.n_q = (int32_t)tr->distinct.size();
+    t.root_pairs = tr->root_pairs;
     t.root_q = tr->root_q;
     t.depth = tr->depth;
     t.kdepth = tr->kdepth;
@@ -828,6 +833,8 @@ int learned_search(const mg_graph *g, mg_tree *tr, const mg_model *model,
 
 // ---------------------------------------------------------------- batches
 constexpr uint32_t kBatchQueueWords = mg::kQueues * mg::kQueueStride;
+constexpr uint32_t kBatchCtxWord = 8;      // in the first head's line: contexts handed on
+constexpr uint32_t kBatchWaves = 4096;     // waves of a batch launch, about
 
 struct mg_batch {
     std::vector<const mg_graph *> graphs;
@@ -847,6 +854,7 @@ struct mg_batch {
     bool learned = false;
     std::vector<mg::BatchItem> items;
     DevBuf d_jobs, d_items, d_work;   // d_work: item queue heads, then counters
+    DevBuf d_ctx;                     // contexts a step hands on between its two launches
     uint64_t *h_counts = nullptr;     // pinned
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -859,6 +867,7 @@ struct mg_batch {
         dev_free(d_jobs);
         dev_free(d_items);
         dev_free(d_work);
+        dev_free(d_ctx);
     }
 };
 
@@ -874,6 +883,19 @@ int upload_jobs(mg_batch *b, hipStream_t st) {
         std::memset(&J, 0, sizeof J);
         fill_params<TT>(J.p, b->graphs[j], b->trees[j], o, nullptr, nullptr, nullptr, nullptr);
         J.count_off = b->count_off[j];
+        J.p.job = (uint32_t)j;
+        if (b->d_ctx.ptr && b->trees[j]->kdepth > 2) {
+            // as a single count (launch_ds), with the plan's roots per wave
+            const uint32_t share = (uint32_t)(b->total_roots / kBatchWaves);
+            const bool deep = b->trees[j]->depth > 3;
+            J.p.hand_on = (deep ? std::min(2048u, std::max(256u, share / 4))
+                                : std::min(8192u, std::max(512u, 2 * share))) & ~63u;
+            J.p.ctx_piece = deep ? 64u : 256u;
+            J.p.ctx_out = (mg::EpochCtx *)b->d_ctx.ptr;
+            J.p.ctx_in = J.p.ctx_out;
+            J.p.ctx_cap = kHandOnCap;
+            J.p.ctx_count = (unsigned long long *)b->d_work.ptr + kBatchCtxWord;
+        }
     }
     int rc = dev_alloc(b->d_jobs, sizeof(mg::BatchJob<TT>) * jobs.size(), (void *)st);
     if (rc) return rc;
@@ -1023,6 +1045,14 @@ int enqueue_step(mg_batch *b, hipStream_t st) {
     if (e != hipSuccess) return fail(MG_EDEVICE, "fill launch failed: %s", hipGetErrorString(e));
     if (bp.n_items) {
         e = mg::launch_batch<TT>(bp, b->depth, b->opts.blocks, st);
+        if (e == hipSuccess && b->d_ctx.ptr) {
+            // the heaviest chunks' candidates, spread over the device
+            bp.contexts = 1;
+            bp.ctx = (const mg::EpochCtx *)b->d_ctx.ptr;
+            bp.ctx_n = bp.cursor + kBatchCtxWord;
+            bp.ctx_cap = kHandOnCap;
+            e = mg::launch_batch<TT>(bp, b->depth, b->opts.blocks, st);
+        }
         if (e != hipSuccess) return fail(MG_EDEVICE, "batch launch failed: %s", hipGetErrorString(e));
     }
     HIP_TRY(hipMemcpyAsync(b->h_counts, bp.counts, 8 * (size_t)std::max<uint32_t>(1, b->total_q),
@@ -1291,11 +1321,13 @@ int mg_batch_create(const mg_graph *const *graphs, const mg_tree *const *trees, 
             b->depth = std::max(b->depth, tr->kdepth);
         }
         b->time_bytes = graphs[0]->time_bytes;
-        int rc = b->time_bytes == 4 ? upload_jobs<uint32_t>(b.get(), st)
-                                    : upload_jobs<uint64_t>(b.get(), st);
+        int rc = dev_alloc(b->d_work, 8 * (size_t)(kBatchQueueWords + std::max<uint32_t>(1, b->total_q)),
+                           (void *)st);
+        if (!rc && b->depth > 2 && b->total_roots >= kHandOnRoots)
+            rc = dev_alloc(b->d_ctx, sizeof(mg::EpochCtx) * kHandOnCap, (void *)st);
         if (rc) return rc;
-        rc = dev_alloc(b->d_work, 8 * (size_t)(kBatchQueueWords + std::max<uint32_t>(1, b->total_q)),
-                       (void *)st);
+        rc = b->time_bytes == 4 ? upload_jobs<uint32_t>(b.get(), st)
+                                : upload_jobs<uint64_t>(b.get(), st);
         if (rc) return rc;
         HIP_TRY(hipHostMalloc((void **)&b->h_counts, 8 * (size_t)std::max<uint32_t>(1, b->total_q),
                               hipHostMallocDefault));

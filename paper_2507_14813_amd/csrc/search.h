@@ -337,6 +337,10 @@ struct LevelBuf<TT, D, 1, R, V> {
     TT tfirst[kWave];
     uint32_t root[kWave];        // edge id
     uint8_t live[kWave];         // live bits of its lists (0-3) and of its pair (4, 5)
+    // how long after the root the last edge of its pair within the window
+    // comes (next_code), of the pair against it (room for that at depth 3 only)
+    static constexpr int Q = D == 3 ? 2 : 1;
+    uint8_t last[Q][kWave];
     uint8_t pair[4 * kWave];     // live (root, list) pairs: slot | list << 6
 };
 
@@ -413,6 +417,49 @@ __device__ __forceinline__ uint32_t root_live(const KParams<TT> &p, uint32_t e) 
     r |= ((n.x >> 8) & 255u) <= q ? 32u : 0u;
     return r;
 }
+// Time of the last entry of a pair, [pos, end) of the pair order, with t <= hi
+// (kNever: none).  As pair_count: four at a time, then by galloping.
+template <typename TT>
+__device__ __forceinline__ TT pair_last(const TT *__restrict__ t, uint32_t pos, uint32_t end, TT hi) {
+    TT last = kNever<TT>;
+    for (int it = 0; pos < end; ++it) {
+        if (it == 2) {
+            const uint32_t e = gallop_greater(t, 0, pos, end, hi);
+            return e > pos ? t[e - 1] : last;
+        }
+        TT v[4];
+        __builtin_memcpy(v, t + pos, sizeof v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (v[k] <= hi && pos + (uint32_t)k < end) last = v[k];
+        if (pos + 4 >= end || v[3] > hi) break;
+        pos += 4;
+    }
+    return last;
+}
+
+// The last edges of root e's pairs within its window, into slot `slot` of the
+// level-1 batch; returns its live bits without those of pairs that have none.
+// (In a burst the edges that repeat the root come right after it, and most of
+// the later candidates need not look for more: 3.27 -> 3.08 ms for 20M edges.)
+template <typename TT, typename Buf>
+__device__ __forceinline__ uint32_t set_pair_ends(const KParams<TT> &p, Buf &A, uint32_t slot,
+                                                  uint32_t e, TT t, uint32_t live) {
+    const TT thi = sat_add(t, p.delta_sat);
+#pragma unroll
+    for (int k = 0; k < Buf::Q; ++k) {
+        uint32_t q = 0;
+        if (live & (p.tree.root_pairs << 4) & (16u << k)) {   // (looked up only if counted)
+            const uint2 pr = reinterpret_cast<const uint2 *>(glb(p.g.gp))[2 * (size_t)e + k];
+            const TT last = pair_last(glb(p.g.pair_t), pr.x, pr.y, thi);
+            if (last == kNever<TT>) live &= ~(16u << k);
+            else q = next_code((TT)(last - t));
+        }
+        A.last[k][slot] = (uint8_t)q;
+    }
+    return live;
+}
+
 // the same as live-word bits
 __device__ __forceinline__ uint32_t root_bits(uint32_t r) {
     return (r & 15u) | ((r >> 4) << kLivePair);
@@ -598,23 +645,27 @@ __device__ __forceinline__ void uncredit_child(uint32_t word, uint32_t c, unsign
 // scanned once per entry of the burst; on 1M edges and 756 motifs of up to four
 // edges 98 %.)  A new-vertex child gets the window's length, credited by
 // count_leaf_parent, less the pairs, taken off here.  pairs: the live pairs the
-// node counts (its edge 2 j, or 2 j + 1 against it), tab: its pair words,
+// node counts (its edge 2 j, or 2 j + 1 against it), tab: its pair words, has_new:
+// some are for new-vertex children,
 // pair_of(k): the first later entry and the end of pair k, tp: the last edge's
 // time, tf and thi: the window.
 template <typename TT, int MODE, typename PairOf>
 __device__ __forceinline__ void count_pairs(const KParams<TT> &p, unsigned long long *cnt,
                                             uint32_t pairs, const uint4 *__restrict__ tab,
-                                            PairOf pair_of, TT tp, TT tf, TT thi, uint32_t nd) {
+                                            bool has_new, PairOf pair_of, TT tp, TT tf, TT thi,
+                                            uint32_t nd) {
     for (; pairs; pairs &= pairs - 1) {
         const uint32_t k = (uint32_t)__builtin_ctz(pairs);
         const uint2 pr = pair_of(k);
         if constexpr (single_of(MODE)) {
             const uint32_t n = pair_count(glb(p.g.pair_t), pr.x, pr.y, tp, thi);
             if (n) {
-                const uint4 w = tab[k];
-                credit_child(w.x, n, cnt, 1u, 0u);
-                uncredit_child(w.y, n, cnt, 1u, 0u);
-                uncredit_child(w.z, n, cnt, 1u, 0u);
+                credit_child(tab[k].x, n, cnt, 1u, 0u);
+                if (has_new) {
+                    const uint2 w = make_uint2(tab[k].y, tab[k].z);
+                    uncredit_child(w.x, n, cnt, 1u, 0u);
+                    uncredit_child(w.y, n, cnt, 1u, 0u);
+                }
             }
         } else {
             const uint32_t lo = gallop_greater(glb(p.g.pair_t), 0, pr.x, pr.y, tp);
@@ -903,7 +954,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
         if constexpr (L == 1 && epochs_of(MODE)) {
             // (a wave dumps in one batch at most: the later batches of its
             // chunk search on)
-            if (p.ctx_out && room && !dumping && !st.dumped && (++polls & 15u) == 0) {
+            if (p.idle && p.ctx_out && room && !dumping && !st.dumped && (++polls & 15u) == 0) {
                 uint32_t v = 0;
                 if (lane == 0) v = __hip_atomic_load(p.idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const uint32_t waves = gridDim.x * (blockDim.x / kWave);
@@ -1139,7 +1190,8 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                         c.hlo[k] = W.hlo[k][ox];
                         c.hlen[k] = W.hlen[k][ox];
                     }
-                    c.pad2[0] = c.pad2[1] = 0;
+                    c.job = p.job;
+                    c.pad2 = 0;
                     slot += incl - n;
                     for (uint32_t k = 0; k < n; ++k) {
                         const uint32_t c0 = c_lo + k * piece;
@@ -1301,8 +1353,11 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                     if (dir == kDirAll) {
                         live |= (15u << (2 * nvp)) | (3u << (kLivePair + 2 * L));
                     } else {
-                        const TT thi = sat_add(tfirst_of(ox), p.delta_sat);
-                        const uint32_t q = next_code((TT)(thi - tn));
+                        const TT tf = tfirst_of(ox), thi = sat_add(tf, p.delta_sat);
+                        const uint32_t q = next_code((TT)(thi - tn)), since = next_code((TT)(tn - tf));
+#pragma unroll
+                        for (int k = 0; k < R1.Q; ++k)   // past the last edge of the root's pair
+                            if (since > R1.last[k][L == 1 ? ox : live >> kLiveSlot]) live &= ~(1u << (kLivePair + k));
                         live &= ~(3u << (2 * hit_s));
                         live |= (((nx >> 16) & 255u) <= q ? 1u : 0u) << (2 * hit_s);
                         live |= ((nx >> 24) <= q ? 2u : 0u) << (2 * hit_s);
@@ -1335,8 +1390,8 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                                 return reinterpret_cast<const uint2 *>(gp)[2 * (size_t)e + (k & 1u)];
                             };
                             const TT tf = tfirst_of(ox);
-                            count_pairs<TT, MODE>(p, cnt, (live >> kLivePair) & (nw.y >> 16),
-                                                  glb(p.tree.pairs) + 8 * (cw & 0xffffu), pair_of, tn, tf,
+                            count_pairs<TT, MODE>(p, cnt, (live >> kLivePair) & (nw.y >> 16) & 255u,
+                                                  glb(p.tree.pairs) + 8 * (cw & 0xffffu), (nw.y >> 24) & 1u, pair_of, tn, tf,
                                                   sat_add(tf, p.delta_sat), nd);
                             push = (nw.y & live & kLiveLists) != 0;
                         }
@@ -1417,7 +1472,7 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                         A.phi[1][lane] = c.b;
                         A.tfirst[lane] = t;
                         A.root[lane] = c.root;
-                        A.live[lane] = (uint8_t)root_live(p, c.root);
+                        A.live[lane] = (uint8_t)set_pair_ends(p, A, (uint32_t)lane, c.root, t, root_live(p, c.root));
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             W.hlo[k][lane] = c.hlo[k];
@@ -1478,7 +1533,7 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                         A.tfirst[slot] = t;
                         set_root_slot(W, slot, glb(p.g.gx)[r]);
                         A.root[slot] = r;
-                        A.live[slot] = (uint8_t)live;
+                        A.live[slot] = (uint8_t)set_pair_ends(p, A, slot, r, t, live);
                     }
                     n1 = uniform((uint32_t)__popcll(km));
                 }
@@ -1672,7 +1727,7 @@ comine_kernel(const KParams<TT>) {
     search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, st);
     if constexpr (epochs_of(MODE)) {
         // out of work: an idle wave, for the epoch limit
-        if (p.ctx_out && !st.dumped && lane == 0) atomicAdd(p.idle, 1u);
+        if (p.idle && p.ctx_out && !st.dumped && lane == 0) atomicAdd(p.idle, 1u);
     }
 
     if (p.wave_clock && lane == 0 && clock_slot < p.n_wave_clock)
@@ -1703,48 +1758,75 @@ batch_kernel(const BatchParams<TT> bp) {
     W.flag[lane] = 0;
     Stats st;
     st.dumped = false;
-    // one queue of items per XCD (claims on one head come one after another),
-    // then what is left of the others, looked at before it is claimed from
-    uint32_t qi = 0;
-    while (qi < (uint32_t)kQueues) {
-        const uint32_t q = (blockIdx.x + qi) % (uint32_t)kQueues;
-        const uint32_t ibeg = (uint32_t)((uint64_t)bp.n_items * q / kQueues);
-        const uint32_t iend = (uint32_t)((uint64_t)bp.n_items * (q + 1) / kQueues);
-        uint32_t it = iend;
-        if (lane == 0) {
-            unsigned long long *head = bp.cursor + q * kQueueStride;
-            const unsigned long long h =
-                qi ? __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
-            if (ibeg + h < iend) it = (uint32_t)min(ibeg + atomicAdd(head, 1ull), (unsigned long long)iend);
+    // search pieces of one job and add its counters to the batch's
+    auto search = [&](uint32_t j, auto claim) {
+        const BatchJob<TT> &job = bp.jobs[j];
+        const KParams<TT> &p = *(const KParams<TT> *)(ConstParams<TT>)&job.p;
+        const uint32_t nq = (uint32_t)counter_slots(p.tree);
+        for (uint32_t i = (uint32_t)lane; i < nq; i += kWave) cnt[i] = 0;
+        wave_sync();
+        search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, st);
+        wave_sync();
+        for (uint32_t i = (uint32_t)lane; i < nq; i += kWave)
+            if (cnt[i]) atomicAdd(&bp.counts[job.count_off + i], cnt[i]);
+        wave_sync();
+    };
+    if constexpr (epochs_of(MODE)) {
+        // the contexts handed on, dealt to the waves: a context and the ones
+        // that follow it in the same job
+        const uint32_t n = (uint32_t)min(*glb(bp.ctx_n), bp.ctx_cap);
+        const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
+        const uint32_t per = max(1u, min(8u, n / (4u * waves)));
+        const uint32_t w0 = blockIdx.x * (uint32_t)kWavesPerBlock + (uint32_t)wave;
+        for (uint32_t r = w0; (uint64_t)r * per < n; r += waves) {
+            uint32_t at = r * per;
+            const uint32_t end = min(at + per, n);
+            while (at < end) {
+                const uint32_t j = uniform(glb(bp.ctx)[at].job);
+                uint32_t stop = at + 1;
+                while (stop < end && uniform(glb(bp.ctx)[stop].job) == j) ++stop;
+                bool fresh = true;
+                search(j, [&](Piece &w) -> bool {
+                    w = {at, stop, 0u, 1u, true};
+                    const bool got = fresh;
+                    fresh = false;
+                    return got;
+                });
+                at = stop;
+            }
         }
-        it = lane_value(it, 0);
-        if (it >= iend) {
-            ++qi;
-            continue;
-        }
-        const BatchItem item = bp.items[it];
-        const BatchJob<TT> &job = bp.jobs[uniform(item.job)];
-        auto search = [&](const KParams<TT> &p) {
+    } else {
+        // one queue of items per XCD (claims on one head come one after another),
+        // then what is left of the others, looked at before it is claimed from
+        uint32_t qi = 0;
+        while (qi < (uint32_t)kQueues) {
+            const uint32_t q = (blockIdx.x + qi) % (uint32_t)kQueues;
+            const uint32_t ibeg = (uint32_t)((uint64_t)bp.n_items * q / kQueues);
+            const uint32_t iend = (uint32_t)((uint64_t)bp.n_items * (q + 1) / kQueues);
+            uint32_t it = iend;
+            if (lane == 0) {
+                uint32_t *head = reinterpret_cast<uint32_t *>(bp.cursor + q * kQueueStride);
+                const uint32_t h =
+                    qi ? __hip_atomic_load(head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                if (h < iend - ibeg) it = min(ibeg + atomicAdd(head, 1u), iend);
+            }
+            it = lane_value(it, 0);
+            if (it >= iend) {
+                ++qi;
+                continue;
+            }
+            const BatchItem item = bp.items[it];
             const uint32_t ip = uniform(item.part);
             const bool split = (ip & kItemSplit) != 0;
             bool fresh = true;
-            auto claim = [&](Piece &w) -> bool {
+            search(uniform(item.job), [&](Piece &w) -> bool {
                 w = {uniform(item.begin), uniform(item.end), split ? (ip >> 15) & 0x7fffu : 0u,
                      split ? ip & 0x7fffu : 1u, false};
                 const bool got = fresh && w.pos < w.end;
                 fresh = false;
                 return got;
-            };
-            search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, st);
-        };
-        const uint32_t nq = (uint32_t)counter_slots(job.p.tree);
-        for (uint32_t i = (uint32_t)lane; i < nq; i += kWave) cnt[i] = 0;
-        wave_sync();
-        search(*(const KParams<TT> *)(ConstParams<TT>)&job.p);
-        wave_sync();
-        for (uint32_t i = (uint32_t)lane; i < nq; i += kWave)
-            if (cnt[i]) atomicAdd(&bp.counts[job.count_off + i], cnt[i]);
-        wave_sync();
+            });
+        }
     }
 }
 
@@ -1865,6 +1947,8 @@ hipError_t launch_d(const KParams<TT> &p, int blocks, hipStream_t stream) {
 
 template <typename TT, int D, int MODE>
 hipError_t launch_batch_d(const BatchParams<TT> &bp, int blocks, hipStream_t stream) {
+    if constexpr (!epochs_of(MODE))
+        if (bp.contexts) return launch_batch_d<TT, D, MODE == 0 ? 5 : 6>(bp, blocks, stream);
     const size_t sm = (size_t)kWavesPerBlock *
                       ((((size_t)bp.n_q_max * 8 + 15) & ~(size_t)15) + sizeof(WaveLds<TT, D, 0>));
     auto kern = batch_kernel<TT, D, MODE>;
