@@ -292,6 +292,9 @@ typedef struct {
 } mg_match;
 int mg_enumerate(const mg_graph *g, const mg_tree *tr, void *stream, mg_match *out,
                  int64_t capacity, int64_t *n_matches);
+/* The same, as two arrays: motif[i] and edges[i * MG_MAX_EDGES_PER_MOTIF + j]. */
+int mg_enumerate_arrays(const mg_graph *g, const mg_tree *tr, void *stream, int32_t *motif,
+                        int32_t *edges, int64_t capacity, int64_t *n_matches);
 
 /*
  * mg_count for callers that cannot allocate device memory (code under HIP

@@ -162,6 +162,7 @@ def lib():
         L.mg_count_noalloc.argtypes = [p, p, ctypes.POINTER(CountOpts), p]
         L.mg_tune.argtypes = [p, p, ctypes.c_char_p, p, ctypes.POINTER(TuneResult)]
         L.mg_enumerate.argtypes = [p, p, p, p, i64, ctypes.POINTER(i64)]
+        L.mg_enumerate_arrays.argtypes = [p, p, p, p, p, i64, ctypes.POINTER(i64)]
         L.mg_cpu_opts_init.argtypes = [ctypes.POINTER(CpuOpts)]
         L.mg_cpu_opts_init.restype = None
         L.mg_count_cpu.argtypes = [p, p, ctypes.POINTER(CpuOpts), p]
@@ -185,7 +186,7 @@ def lib():
         L.mg_batch_destroy.restype = None
         L.mg_count_batch.argtypes = [p, p, i32, ctypes.POINTER(BatchOpts), p]
         for f in ("mg_set_allocator", "mg_graph_create", "mg_graph_info",
-                  "mg_tree_create", "mg_tree_create_multi", "mg_tree_info", "mg_count", "mg_count_noalloc", "mg_tune", "mg_enumerate", "mg_count_cpu",
+                  "mg_tree_create", "mg_tree_create_multi", "mg_tree_info", "mg_count", "mg_count_noalloc", "mg_tune", "mg_enumerate", "mg_enumerate_arrays", "mg_count_cpu",
                   "mg_comine_advice", "mg_batch_create",
                   "mg_batch_count", "mg_batch_info", "mg_count_batch", "mg_model_create", "mg_model_get_weights",
                   "mg_model_set_weights", "mg_model_get_moments", "mg_root_features", "mg_model_predict",
@@ -447,17 +448,19 @@ def comine_advice(graph: Graph, tree: Tree, platform="gpu"):
 
 
 def enumerate_matches(graph: Graph, tree: Tree, stream=None):
-    """``mg_enumerate``: every match, as (motif index array, edges array of
+    """``mg_enumerate_arrays``: every match, as (motif index array, edges array of
     shape n x 5 with -1 past each motif's length), in no particular order;
     edges are indices into the arrays the graph was created from."""
     L = lib()
     n = ctypes.c_int64(0)
     st = _default_stream(stream)
     _check(L.mg_enumerate(graph.handle, tree.handle, st, None, 0, ctypes.byref(n)))
-    rec = np.empty((max(1, n.value), 6), dtype=np.int32)
-    _check(L.mg_enumerate(graph.handle, tree.handle, st, _p(rec), n.value, ctypes.byref(n)))
-    rec = rec[:n.value]
-    return rec[:, 0].copy(), rec[:, 1:].copy()
+    motif = np.empty(n.value, dtype=np.int32)
+    edges = np.empty((n.value, 5), dtype=np.int32)
+    if n.value:
+        _check(lib().mg_enumerate_arrays(graph.handle, tree.handle, st, _p(motif), _p(edges),
+                                         n.value, ctypes.byref(n)))
+    return motif, edges
 
 
 def tune(graph: Graph, tree: Tree, cache=None, stream=None):

@@ -299,8 +299,9 @@ hipError_t launch_fill_u64(unsigned long long *p, uint32_t n, unsigned long long
 
 // Enumeration records (1 + kKMax words each: distinct motif, edge ids) into
 // the caller's numbering: motif q becomes first[q], edge e becomes order[e]
-// (order NULL: stays).
+// (order NULL: stays).  In place, or motifs to `motif` and edges to `edges`.
 hipError_t launch_map_matches(int32_t *rec, uint64_t n, const int32_t *first,
-                              const uint32_t *order, hipStream_t stream);
+                              const uint32_t *order, int32_t *motif, int32_t *edges,
+                              hipStream_t stream);
 
 }  // namespace mg

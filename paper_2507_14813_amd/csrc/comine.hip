@@ -21,22 +21,29 @@ __global__ void fill_u64(unsigned long long *p, uint32_t n, unsigned long long v
 // table lookups stay in the caches.  (On the host, after the copy back, this
 // was two passes over the records and a copy of the whole edge order.)
 __global__ void __launch_bounds__(256)
-map_matches(int32_t *rec, uint64_t n_words, const int32_t *first, const uint32_t *order) {
+map_matches(int32_t *rec, uint64_t n_words, const int32_t *first, const uint32_t *order,
+            int32_t *motif, int32_t *edges) {
     for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < n_words; i += gridDim.x * 256ull) {
         const int32_t x = rec[i];
-        if (i % (1 + kKMax) == 0) rec[i] = first[x];
-        else if (order && x >= 0) rec[i] = (int32_t)order[x];
+        const uint64_t r = i / (1 + kKMax);
+        const uint32_t k = (uint32_t)(i - r * (1 + kKMax));
+        const int32_t y = k == 0 ? first[x] : order && x >= 0 ? (int32_t)order[x] : x;
+        if (!motif) rec[i] = y;
+        else if (k == 0) motif[r] = y;
+        else edges[r * kKMax + k - 1] = y;
     }
 }
 
 }  // namespace
 
 hipError_t launch_map_matches(int32_t *rec, uint64_t n, const int32_t *first,
-                              const uint32_t *order, hipStream_t stream) {
+                              const uint32_t *order, int32_t *motif, int32_t *edges,
+                              hipStream_t stream) {
     if (n == 0) return hipSuccess;
     const uint64_t words = n * (1 + kKMax);
     const uint32_t blocks = (uint32_t)std::min<uint64_t>((words + 255) / 256, 16384);
-    hipLaunchKernelGGL(map_matches, dim3(blocks), dim3(256), 0, stream, rec, words, first, order);
+    hipLaunchKernelGGL(map_matches, dim3(blocks), dim3(256), 0, stream, rec, words, first, order,
+                       motif, edges);
     return hipGetLastError();
 }
 

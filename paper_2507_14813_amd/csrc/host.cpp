@@ -530,7 +530,8 @@ int upload_tree(mg_tree *tr, int device, hipStream_t st) {
     return MG_OK;
 }
 
-// One launch of the co-mining kernel over a tree; counts land in d_counts.
+// The search of one tree; counts land in d_counts.  Queue heads, counters and
+// statistics are zero already.
 template <typename TT>
 int learned_search(const mg_graph *g, mg_tree *tr, const mg_model *model,
                    const mg::KParams<TT> &base, int blocks, uint32_t stride, hipStream_t st);
@@ -639,17 +640,6 @@ int launch_tree(const mg_graph *g, mg_tree *tr, const uint32_t *d_roots, uint32_
         HIP_TRY(hipMemcpyAsync(d_queues, q.data(), kQueueBytes, hipMemcpyHostToDevice, st));
         HIP_TRY(hipStreamSynchronize(st));   // q is released on return
     }
-    const uint32_t n_counts = (uint32_t)mg::counter_slots(p.tree);
-    if (!(o.cursor && o.cursor->started) && d_counts == d_queues + mg::kQueueWords) {
-        // queue heads and counters side by side: one fill kernel clears both
-        // (cheaper on the host than two memsets, and no memset node when the
-        // caller captures the stream)
-        HIP_TRY(mg::launch_fill_u64(d_queues, (uint32_t)mg::kQueueWords + n_counts, 0ull, st));
-    } else {
-        if (!(o.cursor && o.cursor->started)) HIP_TRY(hipMemsetAsync(d_queues, 0, kQueueBytes, st));
-        HIP_TRY(hipMemsetAsync(d_counts, 0, sizeof(unsigned long long) * n_counts, st));
-    }
-    if (d_stats) HIP_TRY(hipMemsetAsync(d_stats, 0, sizeof(unsigned long long) * mg::kStats, st));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (ms) {
         HIP_TRY(hipEventCreate(&e0));
@@ -1607,8 +1597,15 @@ int mg_tree_info(const mg_tree *tr, mg_tree_info_t *out) {
 
 void mg_tree_destroy(mg_tree *tr) { delete tr; }
 
-int mg_enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match *out,
-                 int64_t capacity, int64_t *n_matches) {
+}  // extern "C"
+
+namespace {
+
+// mg_enumerate and mg_enumerate_arrays: records in `out`, or motif indices in
+// `motif` and edges in `edges`.
+int enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match *out, int32_t *motif,
+              int32_t *edges, int64_t capacity, int64_t *n_matches) {
+    const bool arrays = motif && edges;
     try {
         if (!g || !tr_c || !n_matches || capacity < 0) return fail(MG_EINVAL, "bad argument");
         if (g->host_only) return fail(MG_EINVAL, "the graph is on the host only (MG_HOST_ONLY)");
@@ -1626,14 +1623,14 @@ int mg_enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match 
         // enough to be taken as it is: then the search writes into that much
         // and says how many matches there are.
         constexpr uint64_t kDirectBytes = 256u << 20;
-        const bool direct = out && capacity > 0 && (uint64_t)capacity * sizeof(mg_match) <= kDirectBytes;
+        const bool direct = (out || arrays) && capacity > 0 && (uint64_t)capacity * sizeof(mg_match) <= kDirectBytes;
         uint64_t room = direct ? (uint64_t)capacity : 0, total = 0;
         if (!direct) {
             std::vector<uint64_t> cnt(tr->n_motifs);
             int rc = mg_count(g, tr, &o, cnt.data());
             if (rc) return rc;
             for (size_t q = 0; q < first.size(); ++q) total += cnt[first[q]];
-            if (!out || (uint64_t)capacity < total) {
+            if (!(out || arrays) || (uint64_t)capacity < total) {
                 *n_matches = (int64_t)total;
                 return MG_OK;
             }
@@ -1687,11 +1684,24 @@ int mg_enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match 
             // edges in the caller's input order
             HIP_TRY(hipMemcpyAsync((char *)d_work.ptr + first_off, first.data(), 4 * first.size(),
                                    hipMemcpyHostToDevice, st));
-            HIP_TRY(mg::launch_map_matches((int32_t *)d_rec.ptr, total,
-                                           (const int32_t *)((char *)d_work.ptr + first_off),
-                                           (const uint32_t *)g->order.ptr, st));
-            HIP_TRY(hipMemcpyAsync(out, d_rec.ptr, sizeof(mg_match) * total, hipMemcpyDeviceToHost, st));
-            HIP_TRY(hipStreamSynchronize(st));
+            const int32_t *d_first = (const int32_t *)((char *)d_work.ptr + first_off);
+            const uint32_t *order = (const uint32_t *)g->order.ptr;
+            int32_t *rec = (int32_t *)d_rec.ptr;
+            if (arrays) {
+                Scratch split;
+                int32_t *d_m, *d_e;
+                rc = split.get(&d_m, total, st);
+                if (!rc) rc = split.get(&d_e, mg::kKMax * total, st);
+                if (rc) return rc;
+                HIP_TRY(mg::launch_map_matches(rec, total, d_first, order, d_m, d_e, st));
+                HIP_TRY(hipMemcpyAsync(motif, d_m, 4 * total, hipMemcpyDeviceToHost, st));
+                HIP_TRY(hipMemcpyAsync(edges, d_e, 4 * mg::kKMax * total, hipMemcpyDeviceToHost, st));
+                HIP_TRY(hipStreamSynchronize(st));
+            } else {
+                HIP_TRY(mg::launch_map_matches(rec, total, d_first, order, nullptr, nullptr, st));
+                HIP_TRY(hipMemcpyAsync(out, rec, sizeof(mg_match) * total, hipMemcpyDeviceToHost, st));
+                HIP_TRY(hipStreamSynchronize(st));
+            }
         }
         *n_matches = (int64_t)total;
         return MG_OK;
@@ -1700,6 +1710,22 @@ int mg_enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match 
     } catch (...) {
         return fail(MG_EINTERNAL, "unexpected exception");
     }
+}
+
+}  // namespace
+
+extern "C" {
+
+int mg_enumerate(const mg_graph *g, const mg_tree *tr, void *stream, mg_match *out,
+                 int64_t capacity, int64_t *n_matches) {
+    return enumerate(g, tr, stream, out, nullptr, nullptr, capacity, n_matches);
+}
+
+int mg_enumerate_arrays(const mg_graph *g, const mg_tree *tr, void *stream, int32_t *motif,
+                        int32_t *edges, int64_t capacity, int64_t *n_matches) {
+    if ((motif == nullptr) != (edges == nullptr))
+        return fail(MG_EINVAL, "motif and edges must both be given or both be NULL");
+    return enumerate(g, tr, stream, nullptr, motif, edges, capacity, n_matches);
 }
 
 int mg_count_noalloc(const mg_graph *g, const mg_tree *tr, const mg_count_opts *opts,
@@ -1874,15 +1900,17 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
         size_t maxq = 1;
         for (mg_tree *t : runs) maxq = std::max(maxq, n_slots(t));
         static_assert(mg::kStats == MG_NSTATS, "stats layout");
+        // One region per run: queue heads, counters, statistics.  One fill kernel
+        // clears them all, and they come back in one copy after the last run
+        // (per-motif mode waited for the device after each of its searches:
+        // 36 x 35 us).
         DevBuf d_work;
-        const size_t stats_off = kQueueBytes + 8 * maxq;
-        int rc = dev_alloc(d_work, stats_off + 8 * mg::kStats, (void *)st);
+        const size_t words = (size_t)mg::kQueueWords + maxq + mg::kStats;
+        int rc = dev_alloc(d_work, 8 * words * runs.size(), (void *)st);
         if (rc) return rc;
         struct Guard2 { DevBuf *b; ~Guard2() { dev_free(*b); } } gw{&d_work};
-        unsigned long long *d_queues = (unsigned long long *)d_work.ptr;
-        unsigned long long *d_counts = (unsigned long long *)((char *)d_work.ptr + kQueueBytes);
-        unsigned long long *d_stats =
-            o.stats ? (unsigned long long *)((char *)d_work.ptr + stats_off) : nullptr;
+        unsigned long long *work = (unsigned long long *)d_work.ptr;
+        HIP_TRY(mg::launch_fill_u64(work, (uint32_t)(words * runs.size()), 0ull, st));
         std::vector<uint64_t> stats_sum(mg::kStats, 0);
         DevBuf d_cost;
         if (o.root_cost) {
@@ -1917,6 +1945,9 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
             rc = upload_tree(t, dev, st);
             if (rc) return rc;
             float ms = 0.f;
+            unsigned long long *d_queues = work + ri * words;
+            unsigned long long *d_counts = d_queues + mg::kQueueWords;
+            unsigned long long *d_stats = o.stats ? d_counts + maxq : nullptr;
             rc = g->time_bytes == 4
                      ? launch_tree<uint32_t>(g, t, (const uint32_t *)d_roots.ptr, n_roots,
                                              d_queues, d_counts, d_stats,
@@ -1948,16 +1979,18 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
                     if (cur.head[i] < len) cur.done = 0;
                 }
             }
-            std::vector<uint64_t> h(n_slots(t));
-            HIP_TRY(hipMemcpyAsync(h.data(), d_counts, 8 * h.size(), hipMemcpyDeviceToHost, st));
-            std::vector<uint64_t> hs(mg::kStats, 0);
-            if (d_stats)
-                HIP_TRY(hipMemcpyAsync(hs.data(), d_stats, 8 * hs.size(), hipMemcpyDeviceToHost,
-                                       st));
-            HIP_TRY(hipStreamSynchronize(st));
-            for (int i = 0; i < mg::kStats; ++i) stats_sum[i] += hs[i];
-            if (o.mode == MG_MODE_COMINE) qcount = h;
-            else std::copy(h.begin(), h.end(), qcount.begin() + ri * h.size());
+        }
+        // (a single run needs its counters and statistics only)
+        const size_t skip = runs.size() == 1 ? (size_t)mg::kQueueWords : 0;
+        std::vector<uint64_t> h(words * runs.size() - skip);
+        HIP_TRY(hipMemcpyAsync(h.data(), work + skip, 8 * h.size(), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        for (size_t ri = 0, at = 0; ri < runs.size(); ++ri) {
+            const uint64_t *c = h.data() + ri * words + mg::kQueueWords - skip;
+            const size_t n = n_slots(runs[ri]);
+            std::copy(c, c + n, qcount.begin() + at);
+            at += n;
+            for (int i = 0; i < mg::kStats; ++i) stats_sum[i] += c[maxq + i];
         }
         map_counts(tr, qcount.data(), counts);
         if (o.root_cost && g->E) {
