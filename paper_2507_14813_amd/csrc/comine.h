@@ -175,6 +175,14 @@ struct KParams {
                                   // no more chunks
     uint32_t max_chunks;          // 0, or the launch claims at most this many chunks
     unsigned long long *counts;   // counter_slots(tree), zeroed before launch
+    // A small count (every chunk is some wave's first): each workgroup stores
+    // its counters in a row of its own, in host memory (mapped, part_cap
+    // counters), so nothing is cleared before the launch and nothing copied
+    // after it.  launch_comine sets *part_rows to the rows, or returns
+    // hipErrorNotSupported, without a launch, for a count that is not small.
+    unsigned long long *part;
+    uint32_t part_cap;
+    uint32_t *part_rows;
     unsigned long long *stats;    // NULL, or kStats totals (zeroed before launch)
     unsigned long long *root_cost;  // NULL, or per root edge id: 1 + window entries
                                     // examined below that root (zeroed before launch)

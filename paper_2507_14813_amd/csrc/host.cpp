@@ -514,6 +514,25 @@ void map_counts(const mg_tree *tr, const uint64_t *slots, uint64_t *out) {
         }
 }
 
+// Host memory that small counts' kernels store their counters in: one buffer
+// per thread (a call returns after its stream is done with it), allocated by
+// the thread's first small mg_count and kept until the thread ends.
+constexpr uint32_t kPartCounters = 8192;
+struct PartBuf {
+    uint64_t *host = nullptr;
+    ~PartBuf() { if (host) (void)hipHostFree(host); }
+    uint64_t *get(bool may_allocate) {
+        if (!host && may_allocate && hipHostMalloc((void **)&host, 8 * (size_t)kPartCounters,
+                                   hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            host = nullptr;
+        }
+        return host;
+    }
+};
+thread_local PartBuf g_part;
+constexpr int64_t kPartRoots = 1 << 16;   // counts of more roots are not small
+
 size_t n_slots(const mg_tree *tr) { return tr->distinct.size() * tr->deltas.size(); }
 
 int upload_tree(mg_tree *tr, int device, hipStream_t st) {
@@ -565,6 +584,36 @@ void fill_params(mg::KParams<TT> &p, const mg_graph *g, const mg_tree *tr, const
     p.root_cost = d_cost;
     p.stop = o.stop;
     p.max_chunks = (uint32_t)o.max_chunks;
+}
+
+// A small co-mining count in one launch (KParams::part): true when it was taken
+// (*rc: its status, counts in slots[0..n_slots)), false when it is not small or
+// there is no buffer for it yet and none may be allocated.
+template <typename TT>
+bool small_count(const mg_graph *g, const mg_tree *tr, const mg_count_opts &o, bool may_allocate,
+                 uint64_t *slots, hipStream_t st, int *rc) {
+    uint64_t *part = g->E > 0 && g->E <= kPartRoots ? g_part.get(may_allocate) : nullptr;
+    if (!part) return false;
+    mg::KParams<TT> p{};
+    uint32_t rows = 0;
+    fill_params<TT>(p, g, tr, o, nullptr, nullptr, nullptr, nullptr);
+    void *dev = nullptr;
+    if (hipHostGetDevicePointer(&dev, part, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    p.part = (unsigned long long *)dev;
+    p.part_cap = kPartCounters;
+    p.part_rows = &rows;
+    hipError_t e = mg::launch_comine<TT>(p, o.blocks, st);
+    if (e == hipErrorNotSupported) return false;
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    *rc = e == hipSuccess ? MG_OK : fail(MG_EDEVICE, "co-mining launch failed: %s", hipGetErrorString(e));
+    const size_t n = n_slots(tr);
+    std::fill(slots, slots + n, 0);
+    for (size_t r = 0; e == hipSuccess && r < rows; ++r)
+        for (size_t i = 0; i < n; ++i) slots[i] += part[r * n + i];
+    return true;
 }
 
 // Epochs (paper, section 4.5): launch after launch, each ending once
@@ -1758,12 +1807,21 @@ int mg_count_noalloc(const mg_graph *g, const mg_tree *tr, const mg_count_opts *
         if (tr->device != dev || !tr->d_tab.ptr)
             return fail(MG_EINVAL, "the tree has no device tables on device %d yet (count it "
                                    "with mg_count there once)", dev);
+        hipStream_t st = (hipStream_t)o.stream;
+        if (!o.stats && !o.stop && !o.max_chunks) {
+            uint64_t h[mg::kMaxQueries];
+            int rc = MG_OK;
+            if (g->time_bytes == 4 ? small_count<uint32_t>(g, tr, o, false, h, st, &rc)
+                                   : small_count<uint64_t>(g, tr, o, false, h, st, &rc)) {
+                if (!rc) map_counts(tr, h, counts);
+                return rc;
+            }
+        }
         unsigned long long *scr = nullptr;
         HIP_TRY(mg::static_scratch(&scr));
         unsigned long long *d_queues = scr;
         unsigned long long *d_counts = scr + mg::kQueueWords;
         unsigned long long *d_stats = o.stats ? d_counts + mg::kMaxQueries : nullptr;
-        hipStream_t st = (hipStream_t)o.stream;
         // queue heads, claim counter, counters and statistics start at zero
         // (a fill kernel, no memset node if the caller captures the stream)
         HIP_TRY(mg::launch_fill_u64(scr, (uint32_t)mg::kStaticWords, 0ull, st));
@@ -1867,6 +1925,17 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
         if (dev != g->device) return fail(MG_EINVAL, "graph lives on device %d, current is %d",
                                           g->device, dev);
         hipStream_t st = (hipStream_t)o.stream;
+        if (o.mode == MG_MODE_COMINE && o.sched == MG_SCHED_PLAIN && !stoppable && !o.roots &&
+            !o.stats && !o.root_cost && !o.elapsed_ms && !o.wave_clock && !o.epoch_idle) {
+            int rc = upload_tree(tr, dev, st);
+            if (rc) return rc;
+            std::vector<uint64_t> h(n_slots(tr));
+            if (g->time_bytes == 4 ? small_count<uint32_t>(g, tr, o, true, h.data(), st, &rc)
+                                   : small_count<uint64_t>(g, tr, o, true, h.data(), st, &rc)) {
+                if (!rc) map_counts(tr, h.data(), counts);
+                return rc;
+            }
+        }
 
         // roots
         DevBuf d_roots;

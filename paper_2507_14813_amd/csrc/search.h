@@ -1684,7 +1684,7 @@ comine_kernel(const KParams<TT>) {
                 first = false;
                 got = min(qlen, place * p.chunk);
                 if (got == qlen) continue;
-            } else {
+            } else if (taken < qlen) {   // (else nothing is left to claim)
                 // Another XCD's queue is looked at before it is claimed from:
                 // the failing last claims of 8,192 waves on eight heads were
                 // 115 us at the end of every count.  A budget is spent only on a
@@ -1738,6 +1738,11 @@ comine_kernel(const KParams<TT>) {
             if (st.v[i]) atomicAdd(&p.stats[i], (unsigned long long)st.v[i]);
     }
     __syncthreads();
+    if (p.part) {
+        for (int i = (int)threadIdx.x; i < n_slots; i += (int)blockDim.x)
+            p.part[(size_t)blockIdx.x * n_slots + i] = cnt[i];
+        return;
+    }
     for (int i = (int)threadIdx.x; i < n_slots; i += (int)blockDim.x)
         if (cnt[i]) atomicAdd(&p.counts[i], cnt[i]);
 }
@@ -1886,6 +1891,7 @@ hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
     auto kern = comine_kernel<TT, D, MODE>;
     const int n_q = counter_slots(p.tree);
     int wpb = kWavesPerBlock;
+    if (p.part && (blocks > 0 || p.chunk)) return hipErrorNotSupported;
     if (blocks > 0) {   // the caller's workgroups: four waves each
         if (smem_bytes<TT, D, MODE>(n_q, wpb) > 65536) {
             hipError_t e = hipFuncSetAttribute((const void *)kern,
@@ -1909,11 +1915,17 @@ hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
             uint32_t c = 4;
             while (c < (uint32_t)kWave && (uint64_t)c * waves < p.n_roots) c <<= 1;
             p.chunk = c;
-            const uint32_t need = (p.n_roots + c * wpb - 1) / (c * wpb);
-            if (!p.items && !p.ctx_in && need < (uint32_t)blocks) {
-                blocks = (int)std::max(1u, need);
-                // whole rounds of the queues, so that each holds its waves' chunks
-                blocks = std::min(f.blocks, (blocks + (int)p.n_queues - 1) / (int)p.n_queues * (int)p.n_queues);
+            // workgroups that give every chunk of the longest queue its wave
+            uint32_t longest = 0;
+            for (uint32_t q = 0; q < p.n_queues; ++q)
+                longest = std::max(longest, queue_end(p.n_roots, p.n_queues, q) -
+                                                queue_begin(p.n_roots, p.n_queues, q));
+            const uint32_t need = (longest + c * wpb - 1) / (c * wpb) * p.n_queues;
+            const bool one_each = !p.items && !p.ctx_in && need <= (uint32_t)blocks;
+            if (one_each) blocks = (int)std::max(1u, need);
+            if (p.part) {
+                if (!one_each || (uint64_t)need * n_q > p.part_cap) return hipErrorNotSupported;
+                *p.part_rows = need;
             }
             p.place_first = !p.items && !p.ctx_in;
         }

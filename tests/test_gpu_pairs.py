@@ -72,3 +72,39 @@ def test_unbounded_window_and_isolated_edges(api):
     for x in (0, 2 ** 63 - 1):
         want = np.array([og.count(m, x) for m in THREE], dtype=np.uint64)
         assert np.array_equal(api.count(g, api.Tree(THREE, x)), want)
+
+
+@pytest.mark.parametrize("n_edges", [1, 63, 1000, 1023, 9000, 65_536, 65_537])
+def test_small_counts_in_one_launch(api, n_edges):
+    """Counts small enough for one launch, around the sizes where the chunk
+    length and the choice change: mg_count, mg_count_noalloc, several windows,
+    from several threads and streams."""
+    import threading
+
+    import torch
+    rng = np.random.default_rng(n_edges)
+    n = max(4, n_edges // 40)
+    s = rng.integers(0, n, n_edges).astype(np.int32)
+    d = rng.integers(0, n, n_edges).astype(np.int32)
+    t = np.sort(rng.integers(0, 20 * n_edges, n_edges)).astype(np.int64)
+    g, og = api.Graph(s, d, t, n), oracle.OracleGraph(s, d, t, n)
+    motifs = THREE[::5]
+    want = np.array([[og.count(m, x) for m in motifs] for x in (40, 400)], dtype=np.uint64)
+    tr = api.Tree(motifs, 400)
+    assert np.array_equal(api.count(g, tr), want[1])
+    assert np.array_equal(api.count(g, tr, chunk=64), want[1])
+    assert np.array_equal(api.count_noalloc(g, tr), want[1])
+    assert np.array_equal(api.count(g, api.Tree(motifs, [40, 400])), want)
+    bad = []
+
+    def work(k):
+        g2, tr2 = api.Graph(s, d, t, n), api.Tree(motifs, 400)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                if not np.array_equal(api.count(g2, tr2), want[1]):
+                    bad.append(k)
+
+    th = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    [x.start() for x in th]
+    [x.join() for x in th]
+    assert not bad
