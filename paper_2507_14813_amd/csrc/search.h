@@ -374,8 +374,19 @@ struct LevelChain<TT, D, R, D> {};
 // list with t_prev < t <= t_first + delta, t_prev > t_first: it starts inside
 // the root's window and ends where it ends, so a bisection over the root's
 // window replaces a bisection over the whole list and the search for the end.
+//
+// An enumerating wave (R == 2) also keeps the matches it has not written out
+// yet: per match its motif and its edges, up to D of them.
+template <int D, int R>
+struct MatchStage {};
+template <int D>
+struct MatchStage<D, 2> {
+    static constexpr int C = 2 * kWave;
+    uint32_t word[1 + D][C];
+    uint32_t n;
+};
 template <typename TT, int D, int R>
-struct alignas(16) WaveLds {
+struct alignas(16) WaveLds : MatchStage<D, R> {
     static constexpr int H = D > 1 ? 4 : 1;
     uint8_t flag[kWave];          // window-end marks of one pass
     uint32_t hlo[H][kWave];       // root windows (used when D > 2)
@@ -387,6 +398,7 @@ static_assert(sizeof(WaveLds<uint32_t, 1, 0>) % 16 == 0, "per-wave LDS block siz
 static_assert(sizeof(WaveLds<uint32_t, 3, 0>) % 16 == 0, "per-wave LDS block size");
 static_assert(sizeof(WaveLds<uint32_t, 5, 0>) % 16 == 0, "per-wave LDS block size");
 static_assert(sizeof(WaveLds<uint64_t, 5, 1>) % 16 == 0, "per-wave LDS block size");
+static_assert(sizeof(WaveLds<uint64_t, 5, 2>) % 16 == 0, "per-wave LDS block size");
 
 constexpr uint16_t kNoHint = 0xffff;
 constexpr uint16_t kLongHint = 0xfffe;
@@ -493,26 +505,53 @@ __device__ __forceinline__ void edge_chain(WaveLds<TT, D, 2> &W, uint32_t i, uin
     }
 }
 
-// Enumeration: writes one record per lane with `want` (motif q, then the
-// edges e[0..k) and -1 up to kKMax) at consecutive slots of the output, the
-// wave taking its slots with one atomic.  Slots past the capacity are
-// dropped (the caller sized the output from the count).
-template <typename TT>
-__device__ __forceinline__ void write_matches(const KParams<TT> &p, bool want, uint32_t q,
-                                              const uint32_t (&e)[kKMax], uint32_t k) {
+// Enumeration: the wave's staged matches written out as records (motif, then
+// the edges and -1 up to kKMax) at consecutive slots, taken with one atomic.
+// Slots past the capacity are dropped (the cursor still counts them).
+template <typename TT, int D>
+__device__ __forceinline__ void flush_matches(const KParams<TT> &p, WaveLds<TT, D, 2> &W, int lane) {
+    const uint32_t n = uniform(W.n);
+    if (!n) return;
+    unsigned long long base = 0;
+    if (lane == 0) base = atomicAdd(p.enum_cursor, (unsigned long long)n);
+    base = lane0_u64(base);
+    constexpr uint32_t kWords = 1 + kKMax;
+    if (base < p.enum_cap) {
+        const uint32_t fit = (uint32_t)min((unsigned long long)n, (unsigned long long)p.enum_cap - base);
+        int32_t *rec = p.enum_out + base * kWords;
+        for (uint32_t w = (uint32_t)lane; w < fit * kWords; w += kWave) {
+            const uint32_t i = w / kWords, j = w % kWords;
+            rec[w] = j <= (uint32_t)D ? (int32_t)W.word[j][i] : -1;
+        }
+    }
+    wave_sync();
+    if (lane == 0) W.n = 0;
+    wave_sync();
+}
+
+// Enumeration: one match per lane with `want` (motif q, edges e[0..k)) staged
+// in the wave's LDS, and written out 64 or more at a time.  The cursor is one
+// address for the whole device, about 20 ns per atomic: taken once per pass (17
+// matches on average) the kernel took 950 us for the 801,489 matches of 36
+// three-edge motifs on 200,000 edges, with staged matches 645 us.
+template <typename TT, int D>
+__device__ __forceinline__ void write_matches(const KParams<TT> &p, WaveLds<TT, D, 2> &W, int lane,
+                                              bool want, uint32_t q, const uint32_t (&e)[kKMax],
+                                              uint32_t k) {
     const uint64_t m = __ballot(want);
     if (!m) return;
-    unsigned long long base = 0;
-    if ((threadIdx.x & (kWave - 1)) == 0)
-        base = atomicAdd(p.enum_cursor, (unsigned long long)__popcll(m));
-    base = lane0_u64(base);
-    if (!want) return;
-    const unsigned long long slot = base + mbcnt(m);
-    if (slot >= p.enum_cap) return;
-    int32_t *rec = p.enum_out + slot * (1 + kKMax);
-    rec[0] = (int32_t)q;
+    const uint32_t n = uniform(W.n);
+    if (want) {
+        const uint32_t slot = n + mbcnt(m);
+        W.word[0][slot] = q;
 #pragma unroll
-    for (int i = 0; i < kKMax; ++i) rec[1 + i] = (uint32_t)i < k ? (int32_t)e[i] : -1;
+        for (int i = 0; i < D; ++i) W.word[1 + i][slot] = (uint32_t)i < k ? e[i] : ~0u;
+    }
+    const uint32_t now = n + (uint32_t)__popcll(m);   // at most 63 + 64
+    wave_sync();
+    if (lane == 0) W.n = now;
+    wave_sync();
+    if (now >= (uint32_t)kWave) flush_matches<TT, D>(p, W, lane);
 }
 
 // Counts the leaf-only window [l0, l0 + len) of group g (header word hdr) for
@@ -1337,7 +1376,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                 uint32_t e[kKMax] = {0, 0, 0, 0, 0};
                 edge_chain<L>(W, ox, e);
                 e[L] = valid ? cand_eid() : 0u;
-                write_matches(p, valid && cw && q1, q1 - 1u, e, L + 1);
+                write_matches<TT, D>(p, W, lane, valid && cw && q1, q1 - 1u, e, L + 1);
             }
             if constexpr (L + 1 < D) {
                 auto &B = lvl<L + 1>(W.lv);
@@ -1515,7 +1554,7 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                     if constexpr (MODE == 4) {
                         if (p.tree.root_q >= 0) {
                             uint32_t e[kKMax] = {r, 0, 0, 0, 0};
-                            write_matches(p, ok, (uint32_t)p.tree.root_q, e, 1);
+                            write_matches<TT, D>(p, W, lane, ok, (uint32_t)p.tree.root_q, e, 1);
                         }
                     }
                     if constexpr (STATS) st.v[kStatRoots] += ok ? 1 : 0;
@@ -1577,6 +1616,9 @@ comine_kernel(const KParams<TT>) {
     if (threadIdx.x == 0) runs_taken = 0;
     for (int i = (int)threadIdx.x; i < n_slots; i += (int)blockDim.x) cnt[i] = 0;
     W.flag[lane] = 0;
+    if constexpr (MODE == 4) {
+        if (lane == 0) W.n = 0;
+    }
     __syncthreads();
     Stats st;
 #pragma unroll
@@ -1725,6 +1767,7 @@ comine_kernel(const KParams<TT>) {
         return false;
     };
     search_pieces<TT, D, MODE>(p, W, cnt, lane, claim, st);
+    if constexpr (MODE == 4) flush_matches<TT, D>(p, W, lane);
     if constexpr (epochs_of(MODE)) {
         // out of work: an idle wave, for the epoch limit
         if (p.idle && p.ctx_out && !st.dumped && lane == 0) atomicAdd(p.idle, 1u);

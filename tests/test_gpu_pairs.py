@@ -3,6 +3,8 @@ lies in them: bursts between few pairs (long runs of one pair and of its
 reverse, ties, a pair that only ever runs one way), isolated edges, windows that
 end exactly on an edge, unbounded windows.  Whole numbers, equal to the
 oracle's."""
+import itertools
+
 import numpy as np
 import pytest
 
@@ -108,3 +110,28 @@ def test_small_counts_in_one_launch(api, n_edges):
     [x.start() for x in th]
     [x.join() for x in th]
     assert not bad
+
+
+@pytest.mark.parametrize("k,delta", [(1, 0), (2, 1), (3, 5), (5, 5)])
+@pytest.mark.parametrize("n_edges", [1, 63, 64, 65, 129, 1000])
+def test_enumeration_writes_every_staged_match(api, n_edges, k, delta):
+    """A run of one pair, one edge per time unit: the matches of its k-edge
+    repetition are the index combinations that span at most delta.  One motif
+    and a few matches per root, so a wave's staged matches end below, at and
+    above 64; a capacity below the total reports the total."""
+    import ctypes
+    t = np.arange(n_edges, dtype=np.int64)
+    z = np.zeros(n_edges, np.int32)
+    g = api.Graph(z, z + 1, t, 2)
+    tree = api.Tree([((0, 1),) * k], delta)
+    want = [c for i in range(n_edges)
+            for c in ((i,) + r for r in itertools.combinations(range(i + 1, min(n_edges, i + delta + 1)), k - 1))]
+    motif, edges = api.enumerate_matches(g, tree)
+    assert (motif == 0).all() and (edges[:, k:] == -1).all()
+    assert sorted(map(tuple, edges[:, :k].tolist())) == want
+    if len(want) > 1:
+        n = ctypes.c_int64(0)
+        rec = np.full((len(want) - 1, 6), -7, np.int32)
+        assert api.lib().mg_enumerate(g.handle, tree.handle, None, rec.ctypes.data, len(want) - 1,
+                                      ctypes.byref(n)) == 0
+        assert n.value == len(want) and (rec == -7).all()
