@@ -77,8 +77,9 @@ int mg_set_allocator(mg_alloc_fn alloc, mg_release_fn release, void *ctx);
  * The edges are stably sorted by t; edge i of the graph is position i of that
  * order and is the i-th root edge.  Self-loops are kept as roots but never
  * match (a motif edge has two distinct vertices and the vertex map is
- * injective).  The time-sorted edge list plus out- and in-adjacency (each
- * list ascending in t) are built on the host and copied to the device.
+ * injective).  The time-sorted edge list, out- and in-adjacency (each list
+ * ascending in t) and the pair order are built on the device (on the host
+ * with MG_HOST_ONLY).
  * Limits: n_edges < 2^31; max(t) - min(t) < 2^63.
  */
 int mg_graph_create(const int32_t *src, const int32_t *dst, const int64_t *t,
@@ -168,11 +169,14 @@ typedef struct {
                                  own lane when at most this long, by the whole
                                  wave (one ballot per bound vertex) when longer.
                                  0 = default (256), < 0 = never (every window goes
-                                 through the candidate expansion).  In trees of
-                                 three edges, a window on a later vertex's out-list
-                                 whose edges can only close on the root's vertices
-                                 may instead be counted, by its lane, in those
-                                 vertices' in-lists when they are shorter. */
+                                 through the candidate expansion).  Entries that end
+                                 on a vertex joined to the window's own by a
+                                 matched edge are not read: they are counted in
+                                 the pair order.  In trees of three edges, a
+                                 window on a later vertex's out-list whose edges
+                                 can only close on the root's vertices may instead
+                                 be counted, by its lane, in those vertices'
+                                 in-lists when they are shorter. */
     const struct mg_model *model;   /* cost model for MG_SCHED_LEARNED */
     uint64_t *root_cost;      /* optional out, n_edges entries indexed by root edge:
                                  1 + the candidate edges examined (window entries)
@@ -274,9 +278,10 @@ int mg_count(const mg_graph *g, const mg_tree *tr, const mg_count_opts *opts,
 /*
  * Enumeration: every match itself, not only the counts (paper, section 2.1:
  * a match is a sequence of edges; the matcher of Algorithm 1 records each one
- * it completes).  The count sizes the output, then the same search writes one
- * record per match -- the motif and its edges in the motif's order -- in no
- * particular order.
+ * it completes).  The search writes one record per match -- the motif and its
+ * edges in the motif's order -- in no particular order.  A count sizes the
+ * output first, unless `capacity` records are 256 MiB or less: then the search
+ * runs once, into device memory for that many.
  *   out       : host, capacity records; with NULL or a capacity below the
  *               number of matches nothing is written and *n_matches tells how
  *               many records are needed

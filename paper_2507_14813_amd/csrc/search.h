@@ -11,42 +11,45 @@
 // How it is laid out for the hardware (not the paper's warp-per-candidate
 // design):
 //   * Every wave is an independent worker.  Root edges are split into eight
-//     contiguous (time-ordered) queues, one per XCD; a wave grabs chunks from
-//     its XCD's queue and steals from the others when it runs dry, so roots
-//     that are close in time, and the adjacency they read, share one L2.
-//   * Partial matches are buffered per search level in LDS.  For a batch of
-//     partial matches at level L, every (partial match, child group) pair is
-//     a window of one time-sorted adjacency list: the entries with
-//     t_prev < t <= t_first + delta, found by bisection.  Children that read
-//     the same list (same direction, same anchor vertex) form one group and
-//     share one scan of the window.
+//     contiguous (time-ordered) queues, one per XCD; a wave starts with the
+//     chunk at its own place, claims more from its XCD's queue and steals from
+//     the others when it runs dry, so roots that are close in time, and the
+//     adjacency they read, share one L2.  Claims are what bounds small counts
+//     (about 20 ns each on one head), so few are made.
+//   * Root-level candidates of a chunk beyond a limit are handed on as
+//     contexts, which a second launch spreads over the device.
+//   * Partial matches are buffered per search level in LDS and expanded 64 at
+//     a time, the last ones first, with a live word each: which of the lists
+//     it could scan, and of the pairs it could count, hold anything within the
+//     window.  It is made of the next codes that come with every list entry,
+//     so empty windows (nearly all of them in deep trees) cost nothing.
+//   * Children that read the same list (same direction, same anchor vertex)
+//     form one group and share one scan of the window: the entries with
+//     t_prev < t <= t_first + delta.
 //   * Windows are found from other windows where possible: a root's windows
 //     in out(a) and in(b) start just past the root edge's own list position,
 //     and a deeper window on a list of the root's two vertices lies inside the
 //     root's window on that list (kept in LDS), so it needs a short bisection
-//     and no search for its end.  Below the first level, the pairs on such
-//     lists are taken before the others, so the lanes of one pass run
-//     bisections of similar length.
-//   * A window whose children all end a motif is counted, not expanded: one
-//     equality count per bound vertex (the list's own anchor left out), the
-//     new-vertex child taking the rest; a short one by its own lane, a long
-//     one by the whole wave with ballots.
-//   * A batch whose partial matches all sit at leaf parents (trie nodes
-//     whose children all end a motif, reached through lists of bound
-//     vertices) is taken one partial match per lane instead: the lane finds
-//     and counts the window of each of the node's groups in turn, with no
-//     pairing of partial matches and groups across the wave.
+//     and no search for its end.
+//   * A window whose children all end a motif is counted, not expanded.  Where
+//     a matched edge joins the list's vertex to the bound vertex that the child
+//     ends on, the entries that count are edges of that pair: two positions in
+//     the pair order, no scan (before, 99.6 % of all scanned entries lay in
+//     such windows; 20M edges and 36 motifs took 6.75 ms, now 2.96).  Other
+//     such windows take one equality count per bound vertex, the new-vertex
+//     child taking the rest; a short one by its own lane, a long one by the
+//     whole wave with ballots.
 //   * The other non-empty windows, up to 64 at a time, are expanded as one
 //     flat candidate range: lane i takes candidate c + i, finds its window
 //     from a 64-bit mask of window ends (LDS flags + ballot + popcount), reads
 //     one adjacency entry, finds which bound motif vertex it hits with
 //     predicated compares, picks the reached child from the group record
-//     (which also carries the child's motif id), credits LDS counters, and
-//     compacts the survivors that still have children into the next level's
-//     buffer with ballot + mbcnt.
-//   * When the next level's buffer holds 64 or more partial matches it is
-//     expanded at once (depth first over batches), so LDS use is bounded by
-//     the motif length, not by the size of the search tree.
+//     (which also carries the child's motif id), credits LDS counters, counts
+//     the pairs of a leaf parent, and compacts the survivors that still have
+//     something to find into the next level's buffer with ballot + mbcnt.
+//   * What bounds it (20M edges): the latency of list lines that miss L2, 403
+//     bytes of traffic per root edge, waves waiting 79 % of their cycles at
+//     eight waves per SIMD; then VALU issue (59 %).
 //   * The level loop nest is unrolled at compile time for the tree depth
 //     (1..5 motif edges), one instantiation per depth.
 #pragma once
@@ -643,8 +646,8 @@ __device__ __forceinline__ bool root_window(const WaveLds<TT, D, R> &W, const ui
 // Entries of a pair, [pos, end) of the pair order, with lo < t <= hi.  Most
 // pairs have a few in a window, so four are looked at per load without a
 // search (lanes stay together; pair_t is padded by four entries); what is left
-// after eight is bisected.  (Galloping from the first entry instead: 4.9 ms
-// for 20M edges and 36 motifs, against 3.8.)
+// after eight is bisected.  (Galloping from the first entry instead: 4.78 ms
+// for 3M edges and 756 motifs, against 4.32.)
 template <typename TT>
 __device__ __forceinline__ uint32_t pair_count(const TT *__restrict__ t, uint32_t pos, uint32_t end,
                                                TT lo, TT hi) {
@@ -1888,7 +1891,8 @@ size_t smem_bytes(int n_q, int wpb) {
 // Shape of a launch that fills the device: waves per workgroup and workgroups.
 // Four waves per workgroup, or eight where sharing one set of counters lets
 // more waves onto a compute unit (756 motifs: 6 KB of counters, 16 waves
-// instead of 12).  The last answer per kernel and thread is kept: asking costs
+// instead of 12: 3M edges 5.07 -> 4.73 ms; 48 motifs and three windows on 4M
+// edges 2.22 -> 2.07).  The last answer per kernel and thread is kept: asking costs
 // more than the rest of a small launch.
 constexpr size_t kMaxLds = 160 * 1024 - 256;   // dynamic part of a workgroup's LDS at most
 struct Fill {
@@ -1952,8 +1956,9 @@ hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
             // Few roots are spread thinner: a wave's 64 roots are one chain of
             // dependent loads, so a small graph takes as long as its slowest
             // chunk.  Up to 64 roots per wave every wave gets one chunk, of 4
-            // roots at least, and there are no more workgroups than chunks;
-            // beyond that, chunks of 64.
+            // roots at least, and there are no more workgroups than chunks
+            // (20,000 edges: 150 -> 78 us a call); beyond that, chunks of
+            // 64 (of 128: 3.11 ms for 20M edges, of 256: 3.22, against 3.08).
             const uint32_t waves = (uint32_t)(blocks * wpb);
             uint32_t c = 4;
             while (c < (uint32_t)kWave && (uint64_t)c * waves < p.n_roots) c <<= 1;
@@ -1975,8 +1980,11 @@ hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
     }
     if (p.chunk == 0) p.chunk = kWave;
     if (p.hand_on) {
-        // about twice the candidates a wave's share of the roots has; deeper
-        // trees find far more below each
+        // About twice the candidates a wave's share of the roots has; deeper
+        // trees find far more below each.  Waves were busy 50 % of a launch
+        // over 2M edges, 49 % with 756 motifs over 3M, before chunks were
+        // handed on; 20M edges hand nothing on, and the empty second launch
+        // takes 6 us.
         const uint32_t share = p.n_roots / (uint32_t)(blocks * wpb);
         p.hand_on = (D <= 3 ? std::min(8192u, std::max(512u, 2 * share))
                             : std::min(2048u, std::max(256u, share / 4))) & ~63u;

@@ -135,3 +135,29 @@ def test_enumeration_writes_every_staged_match(api, n_edges, k, delta):
         assert api.lib().mg_enumerate(g.handle, tree.handle, None, rec.ctypes.data, len(want) - 1,
                                       ctypes.byref(n)) == 0
         assert n.value == len(want) and (rec == -7).all()
+
+
+def test_one_tree_counted_by_several_threads(api):
+    """Counts that hand heavy chunks on, of one graph and tree, side by side on
+    three streams: each has contexts of its own."""
+    import threading
+
+    import torch
+    s, d, t = bursts(140_000, 5, 1)[:3]
+    n = 14
+    g, og = api.Graph(s, d, t, n), oracle.OracleGraph(s, d, t, n)
+    tr = api.Tree(THREE[::4], 60)
+    want = np.array([og.count(m, 60) for m in THREE[::4]], dtype=np.uint64)
+    assert np.array_equal(api.count(g, tr), want)
+    bad = []
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(12):
+                if not np.array_equal(api.count(g, tr), want):
+                    bad.append(k)
+
+    th = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    [x.start() for x in th]
+    [x.join() for x in th]
+    assert not bad
