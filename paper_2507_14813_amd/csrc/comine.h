@@ -267,8 +267,11 @@ struct BatchItem {
 template <typename TT>
 struct BatchParams {
     const BatchJob<TT> *jobs;
-    const BatchItem *items;
+    const BatchItem *items;       // NULL: the jobs are searches of one graph, and item i
+                                  // is the chunk i / n_jobs of run_roots roots, of n_roots
+                                  // in all, of job i % n_jobs
     uint32_t n_items;
+    uint32_t n_jobs, run_roots, n_roots;   // with items NULL
     uint32_t n_q_max;             // largest tree's counter_slots
     unsigned long long *cursor;   // kQueues item queue heads, kQueueStride words apart,
                                   // zeroed before launch; queue q holds items

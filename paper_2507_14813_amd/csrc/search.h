@@ -1798,6 +1798,7 @@ comine_kernel(const KParams<TT>) {
 // counters, sized for the largest tree, and flushes them after every item.
 template <typename TT, int D, int MODE>
 __global__ void __launch_bounds__(kWave * kWavesPerBlock)
+__attribute__((amdgpu_waves_per_eu(min_waves_per_eu<D, MODE>(), 8)))
 batch_kernel(const BatchParams<TT> bp) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = (int)(threadIdx.x & (kWave - 1));
@@ -1866,7 +1867,16 @@ batch_kernel(const BatchParams<TT> bp) {
                 ++qi;
                 continue;
             }
-            const BatchItem item = bp.items[it];
+            BatchItem item;
+            if (bp.items) {
+                item = bp.items[it];
+            } else {
+                const uint32_t c = it / bp.n_jobs;
+                item.job = it - c * bp.n_jobs;
+                item.begin = c * bp.run_roots;
+                item.end = min(bp.n_roots - item.begin, bp.run_roots) + item.begin;
+                item.part = 0;
+            }
             const uint32_t ip = uniform(item.part);
             const bool split = (ip & kItemSplit) != 0;
             bool fresh = true;
@@ -2029,6 +2039,9 @@ hipError_t launch_batch_d(const BatchParams<TT> &bp, int blocks, hipStream_t str
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kWave * kWavesPerBlock, sm);
         if (e != hipSuccess) return e;
         blocks = ncu * (per > 0 ? per : 1);
+        // (one graph's searches: no more waves than items)
+        if (!bp.items && !bp.contexts)
+            blocks = (int)std::min<uint32_t>((uint32_t)blocks, (bp.n_items + kWavesPerBlock - 1) / kWavesPerBlock);
     }
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * kWavesPerBlock), sm, stream, bp);
     return hipGetLastError();

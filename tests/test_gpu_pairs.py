@@ -161,3 +161,26 @@ def test_one_tree_counted_by_several_threads(api):
     [x.start() for x in th]
     [x.join() for x in th]
     assert not bad
+
+
+@pytest.mark.parametrize("unit", [1, 2 ** 33])
+@pytest.mark.parametrize("n_edges", [1, 255, 3000, 131_073])
+def test_per_motif_searches_in_one_batch(api, n_edges, unit):
+    """Per-motif mode over trees of every depth: one window and several, chunk
+    lengths from 4 up, enough roots for chunks to be handed on; equal to the
+    oracle, or for the largest graph to the searches launched one by one."""
+    s, d, t = bursts(n_edges, 11, unit)
+    g = api.Graph(s, d, t, 14)
+    motifs = MIXED if n_edges < 10_000 else MIXED[:6] + THREE[::7]
+    deltas = [9 * unit, 40 * unit]
+    if n_edges < 10_000:
+        og = oracle.OracleGraph(s, d, t, 14)
+        want = np.array([[og.count(m, x) for m in motifs] for x in deltas], dtype=np.uint64)
+    else:
+        want = np.stack([api.count(g, api.Tree(motifs, x), mode="per_motif", chunk=64) for x in deltas])
+    for i, x in enumerate(deltas):
+        assert np.array_equal(api.count(g, api.Tree(motifs, x), mode="per_motif"), want[i])
+    tr = api.Tree(motifs, deltas)
+    assert np.array_equal(api.count(g, tr, mode="per_motif"), want)
+    got, ms = api.count(g, tr, mode="per_motif", timed=True)[:2]
+    assert np.array_equal(got, want) and ms > 0
