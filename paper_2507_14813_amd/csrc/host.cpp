@@ -2084,7 +2084,8 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
         static_assert(mg::kStats == MG_NSTATS, "stats layout");
         if (o.mode == MG_MODE_PER_MOTIF && n_roots > 0 && o.sched == MG_SCHED_PLAIN && !stoppable &&
             !o.roots && !o.stats && !o.root_cost && !o.wave_clock && !o.epoch_idle && !o.blocks &&
-            !o.chunk && !o.queues) {
+            (!o.chunk || o.chunk == 64) && (!o.queues || o.queues == mg::kQueues)) {
+            // (64-root chunks and every queue are the defaults, as mg_tune names them)
             std::vector<uint64_t> qcount(n_slots(tr), 0);
             float ms = 0.f;
             bool taken = false;

@@ -177,7 +177,7 @@ def test_per_motif_searches_in_one_batch(api, n_edges, unit):
         og = oracle.OracleGraph(s, d, t, 14)
         want = np.array([[og.count(m, x) for m in motifs] for x in deltas], dtype=np.uint64)
     else:
-        want = np.stack([api.count(g, api.Tree(motifs, x), mode="per_motif", chunk=64) for x in deltas])
+        want = np.stack([api.count(g, api.Tree(motifs, x), mode="per_motif", chunk=128) for x in deltas])
     for i, x in enumerate(deltas):
         assert np.array_equal(api.count(g, api.Tree(motifs, x), mode="per_motif"), want[i])
     tr = api.Tree(motifs, deltas)
