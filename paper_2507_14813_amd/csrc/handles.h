@@ -87,6 +87,7 @@ struct mg_tree {
     int device = -1;
     mgh::DevBuf d_tab;                  // node_tab, grp_tab, pair_tab
     mgh::DevBuf d_ctx;                  // contexts a count hands on between its two launches
+    int ctx_device = -1;                // where it is
     std::atomic<bool> ctx_busy{false};  // d_ctx is some running count's
     // per-motif chain trees (built on first per-motif count)
     std::vector<std::unique_ptr<mg_tree>> singles;

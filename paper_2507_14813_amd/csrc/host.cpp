@@ -78,6 +78,7 @@ int dev_alloc(DevBuf &b, size_t bytes, void *stream) {
     }
     hipError_t e = hipMalloc(&b.ptr, bytes);
     if (e != hipSuccess) {
+        (void)hipGetLastError();
         b.ptr = nullptr;
         return fail(MG_ENOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
     }
@@ -539,7 +540,6 @@ size_t n_slots(const mg_tree *tr) { return tr->distinct.size() * tr->deltas.size
 int upload_tree(mg_tree *tr, int device, hipStream_t st) {
     if (tr->device == device && tr->d_tab.ptr) return MG_OK;
     dev_free(tr->d_tab);
-    dev_free(tr->d_ctx);   // (of the device before)
     std::vector<int32_t> all;
     for (const std::vector<int32_t> *t : {&tr->node_tab, &tr->grp_tab, &tr->pair_tab})
         all.insert(all.end(), t->begin(), t->end());
@@ -629,6 +629,28 @@ constexpr uint32_t kHandOnRoots = 1u << 17;   // counts of fewer roots hand noth
                                               // wave has 16 roots or fewer there
 constexpr uint64_t kHandOnCap = 1u << 18;     // contexts one count can hand on (16 MB)
 constexpr uint64_t kCtxCap = 1u << 20;   // contexts one epoch can hand on (64 MB)
+
+// The tree keeps one context buffer, allocated by its first count of that many
+// roots; a count that finds it taken by another thread's has its own.  Without
+// memory for one (take returns NULL) nothing is handed on.
+struct CtxLease {
+    std::atomic<bool> *busy = nullptr;
+    DevBuf own;
+    ~CtxLease() {
+        dev_free(own);
+        if (busy) busy->store(false, std::memory_order_release);
+    }
+    const DevBuf *take(mg_tree *tr, int device, hipStream_t st) {
+        DevBuf *b = &own;
+        if (!tr->ctx_busy.exchange(true, std::memory_order_acquire)) {
+            busy = &tr->ctx_busy;
+            b = &tr->d_ctx;
+            if (tr->ctx_device != device) dev_free(*b);
+            tr->ctx_device = device;
+        }
+        return b->ptr || !dev_alloc(*b, sizeof(mg::EpochCtx) * kHandOnCap, (void *)st) ? b : nullptr;
+    }
+};
 
 template <typename TT>
 int epoch_search(mg::KParams<TT> p, const mg_count_opts &o, hipStream_t st) {
@@ -963,7 +985,7 @@ int upload_jobs(mg_batch *b, hipStream_t st) {
 // times: 4.23 ms, here 2.20 (of 20M edges: 35.5 ms, here 20.5).  Counters come back in `slots`, tree after tree; *taken stays false for
 // more items than a batch can number.
 template <typename TT>
-int count_runs(const mg_graph *g, const std::vector<mg_tree *> &runs, const mg_count_opts &o,
+int count_runs(const mg_graph *g, mg_tree *tr, const std::vector<mg_tree *> &runs, const mg_count_opts &o,
                uint64_t *slots, bool *taken, hipStream_t st, float *ms) {
     const uint32_t E = (uint32_t)g->E;
     // about 16 items per wave, of at most 2048 roots (a claim on one queue head
@@ -991,8 +1013,10 @@ int count_runs(const mg_graph *g, const std::vector<mg_tree *> &runs, const mg_c
     mg::EpochCtx *d_ctx = nullptr;
     int rc = own.get(&d_jobs, runs.size(), st);
     if (!rc) rc = own.get(&d_work, (size_t)depths * kBatchQueueWords + n_out, st);
-    if (!rc && deep) rc = own.get(&d_ctx, kHandOnCap, st);
     if (rc) return rc;
+    CtxLease lease;
+    if (deep)
+        if (const DevBuf *ctx = lease.take(tr, g->device, st)) d_ctx = (mg::EpochCtx *)ctx->ptr;
     unsigned long long *d_out = d_work + (size_t)depths * kBatchQueueWords;
     std::vector<mg::BatchJob<TT>> jobs(runs.size());
     for (size_t i = 0, at = 0, d = 0; i < runs.size(); ++i) {
@@ -1475,9 +1499,9 @@ int mg_batch_create(const mg_graph *const *graphs, const mg_tree *const *trees, 
         b->time_bytes = graphs[0]->time_bytes;
         int rc = dev_alloc(b->d_work, 8 * (size_t)(kBatchQueueWords + std::max<uint32_t>(1, b->total_q)),
                            (void *)st);
-        if (!rc && b->depth > 2 && b->total_roots >= kHandOnRoots)
-            rc = dev_alloc(b->d_ctx, sizeof(mg::EpochCtx) * kHandOnCap, (void *)st);
         if (rc) return rc;
+        if (b->depth > 2 && b->total_roots >= kHandOnRoots)   // (without it nothing is handed on)
+            (void)dev_alloc(b->d_ctx, sizeof(mg::EpochCtx) * kHandOnCap, (void *)st);
         rc = b->time_bytes == 4 ? upload_jobs<uint32_t>(b.get(), st)
                                 : upload_jobs<uint64_t>(b.get(), st);
         if (rc) return rc;
@@ -2090,8 +2114,8 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
             float ms = 0.f;
             bool taken = false;
             int rc = g->time_bytes == 4
-                         ? count_runs<uint32_t>(g, runs, o, qcount.data(), &taken, st, o.elapsed_ms ? &ms : nullptr)
-                         : count_runs<uint64_t>(g, runs, o, qcount.data(), &taken, st, o.elapsed_ms ? &ms : nullptr);
+                         ? count_runs<uint32_t>(g, tr, runs, o, qcount.data(), &taken, st, o.elapsed_ms ? &ms : nullptr)
+                         : count_runs<uint64_t>(g, tr, runs, o, qcount.data(), &taken, st, o.elapsed_ms ? &ms : nullptr);
             if (rc) return rc;
             if (taken) {
                 map_counts(tr, qcount.data(), counts);
@@ -2126,29 +2150,10 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
         }
         struct Guard4 { DevBuf *b; ~Guard4() { dev_free(*b); } } gk{&d_clock};
 
-        // The tree keeps one context buffer, allocated by its first count of that
-        // many roots; a count that finds it taken by another thread's has its own.
-        struct CtxLease {
-            std::atomic<bool> *busy = nullptr;
-            DevBuf own;
-            ~CtxLease() {
-                dev_free(own);
-                if (busy) busy->store(false, std::memory_order_release);
-            }
-        } lease;
+        CtxLease lease;
         const DevBuf *ctx = nullptr;
-        if (n_roots >= kHandOnRoots && o.sched == MG_SCHED_PLAIN && !o.epoch_idle) {
-            DevBuf *b = &lease.own;
-            if (!tr->ctx_busy.exchange(true, std::memory_order_acquire)) {
-                lease.busy = &tr->ctx_busy;
-                b = &tr->d_ctx;
-            }
-            if (!b->ptr) {
-                rc = dev_alloc(*b, sizeof(mg::EpochCtx) * kHandOnCap, (void *)st);
-                if (rc) return rc;
-            }
-            ctx = b;
-        }
+        if (n_roots >= kHandOnRoots && o.sched == MG_SCHED_PLAIN && !o.epoch_idle)
+            ctx = lease.take(tr, dev, st);
 
         std::vector<uint64_t> qcount(n_slots(tr), 0);
         float total_ms = 0.f;

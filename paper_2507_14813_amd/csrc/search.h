@@ -1794,7 +1794,7 @@ comine_kernel(const KParams<TT>) {
 }
 
 // Many (graph, tree) jobs in one persistent launch.  Waves claim work items
-// (root ranges of one job) from one queue; each wave keeps its own LDS
+// (root ranges of one job) from one queue per XCD; each wave keeps its own LDS
 // counters, sized for the largest tree, and flushes them after every item.
 template <typename TT, int D, int MODE>
 __global__ void __launch_bounds__(kWave * kWavesPerBlock)
