@@ -1721,8 +1721,7 @@ comine_kernel(const KParams<TT>) {
             const uint32_t q = (home + qi) % nq;
             const uint32_t qbeg = queue_begin(p.n_roots, nq, q);
             const uint32_t qlen = queue_end(p.n_roots, nq, q) - qbeg;
-            // chunks of this queue that are some wave's first (a head stays
-            // below 2^32: the roots and one failing claim per wave)
+            // chunks of this queue that are some wave's first
             const uint32_t taken = p.place_first ? min(qlen, ((gridDim.x - q + nq - 1) / nq) * wpb * p.chunk) : 0u;
             uint32_t got = qlen;
             if (first) {
@@ -1735,12 +1734,14 @@ comine_kernel(const KParams<TT>) {
                 // 115 us at the end of every count.  A budget is spent only on a
                 // queue that still has roots, so a call makes progress while any
                 // root is left: a budget holder's claim fails only when another
-                // holder took the last chunk.
-                uint32_t *head = reinterpret_cast<uint32_t *>(&p.queues[q * kQueueStride]);
+                // holder took the last chunk.  A head counts past its queue's
+                // end, by one chunk per failing claim: 64 bits, for a caller's
+                // 65,536-root chunks on many workgroups pass 2^32.
+                unsigned long long *head = &p.queues[q * kQueueStride];
                 if (lane == 0) {
                     const bool look = p.max_chunks || qi > 0;
-                    const uint32_t h = look ? __hip_atomic_load(head, __ATOMIC_RELAXED,
-                                                                __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                    const unsigned long long h = look ? __hip_atomic_load(head, __ATOMIC_RELAXED,
+                                                                          __HIP_MEMORY_SCOPE_AGENT) : 0ull;
                     if (p.stop && __hip_atomic_load(p.stop, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_SYSTEM) != 0)
                         got = ~0u;
@@ -1750,7 +1751,8 @@ comine_kernel(const KParams<TT>) {
                              atomicAdd(&p.queues[kBudgetSlot * kQueueStride], 1ull) >= p.max_chunks)
                         got = ~0u;
                     else
-                        got = min(qlen, atomicAdd(head, p.chunk) + taken);
+                        got = (uint32_t)min((unsigned long long)qlen,
+                                            atomicAdd(head, (unsigned long long)p.chunk) + taken);
                 }
                 got = lane_value(got, 0);
             }
