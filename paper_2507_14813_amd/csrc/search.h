@@ -1274,8 +1274,12 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                         slot = lane0_u64(slot);
                         if (slot + tot <= p.ctx_cap) return true;
                         // the buffer is full: the slots taken that exist hold
-                        // nothing, and this wave searches on
+                        // nothing (an empty range of a root of this job: the
+                        // next launch looks up the root of every context), and
+                        // this wave searches on
                         EpochCtx none{};
+                        none.root = A.root[0];
+                        none.job = p.job;
                         for (unsigned long long k = slot + lane; k < p.ctx_cap; k += kWave) p.ctx_out[k] = none;
                         return false;
                     });

@@ -43,3 +43,60 @@ def test_failing_claims_do_not_wrap_a_queue_head(api, blocks, chunk):
     cur = api.Cursor()
     assert np.array_equal(api.count(g, tr, blocks=blocks, chunk=chunk, queues=1, cursor=cur), want)
     assert cur.done and list(cur.head) == [5000] + [0] * 7
+
+
+def run_of_one_pair(n_edges, unit=1):
+    z = np.zeros(n_edges, np.int32)
+    return z, z + 1, np.arange(n_edges, dtype=np.int64) * unit
+
+
+def repetitions(n_edges, k, w):
+    """Matches of the k-edge repetition of a pair that has one edge per time
+    unit, within w units: the first edge and k - 1 of the (at most w) after it."""
+    after = np.minimum(w, np.arange(n_edges)[::-1]).astype(object)
+    out = 1
+    for i in range(k - 1):
+        out = out * (after - i) // (i + 1)
+    return int(np.sum(np.where(after >= k - 1, out, 0)))
+
+
+# 300,000 roots with `w` later edges each: at three edges more than (64 w - 512) /
+# 256 contexts for each of the 4,688 chunks, at four (64 w - 256) / 64, 2^18 and
+# more in all
+FULL = {3: 300, 4: 64}
+
+
+@pytest.mark.parametrize("unit", [1, 2 ** 33])
+@pytest.mark.parametrize("k", [3, 4])
+def test_counts_that_fill_the_context_buffer(api, k, unit):
+    n, w = 300_000, FULL[k]
+    g = api.Graph(*run_of_one_pair(n, unit), 2)
+    same = lambda j: ((0, 1),) * j
+    want = repetitions(n, k, w)
+    print("full buffer", k, unit, flush=True)
+    assert api.count(g, api.Tree([same(k)], w * unit)).tolist() == [want]
+    assert api.count(g, api.Tree([same(k)], [w * unit, 3 * unit])).tolist() == \
+        [[want], [repetitions(n, k, 3)]]
+    motifs = [same(2), same(k), ((0, 1), (1, 0), (0, 1))]
+    assert api.count(g, api.Tree(motifs, w * unit), mode="per_motif").tolist() == \
+        [repetitions(n, 2, w), want, 0]
+
+
+@pytest.mark.parametrize("first", ["shallow", "empty", "one edge"])
+@pytest.mark.parametrize("k", [3, 4])
+def test_a_batch_that_fills_the_context_buffer(api, k, first):
+    """The first job of the batch hands nothing on: a two-edge tree, or a graph
+    without (or with one) edges."""
+    n, w = 300_000, FULL[k]
+    g, same = api.Graph(*run_of_one_pair(n), 2), lambda j: ((0, 1),) * j
+    if first == "shallow":
+        g0, t0, want0 = g, api.Tree([same(2)], 5), repetitions(n, 2, 5)
+    else:
+        g0, t0, want0 = api.Graph(*run_of_one_pair(int(first == "one edge")), 2), api.Tree([same(k)], w), 0
+    print("full buffer, batch", k, first, flush=True)
+    want = [[want0], [repetitions(n, k, w)]]
+    graphs, trees = [g0, g], [t0, api.Tree([same(k)], w)]
+    assert [x.tolist() for x in api.count_batch(graphs, trees)] == want
+    b = api.Batch(graphs, trees, item_roots=64)
+    for _ in range(3):
+        assert [x.tolist() for x in b.count()] == want
