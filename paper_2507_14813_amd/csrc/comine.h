@@ -248,6 +248,21 @@ enum : int {
     kStats
 };
 
+// Root-level candidates of a chunk beyond which a search of n_roots roots over
+// `waves` waves hands the rest on (a multiple of 64): about twice the candidates
+// a wave's share of the roots has; deeper trees find far more below each.  Waves
+// were busy 50 % of a launch over 2M edges, 49 % with 756 motifs over 3M, before
+// chunks were handed on; 20M edges hand nothing on, and the empty second launch
+// takes 6 us.
+inline uint32_t hand_on_limit(uint64_t n_roots, uint64_t waves, bool deep) {
+    const uint64_t share = n_roots / (waves > 0 ? waves : 1);
+    const uint64_t n = deep ? (share < 1024 ? 256 : share < 8192 ? share / 4 : 2048)
+                            : (share < 256 ? 512 : share < 4096 ? 2 * share : 8192);
+    return (uint32_t)n & ~63u;
+}
+// candidates per context handed on
+inline uint32_t hand_on_piece(bool deep) { return deep ? 64u : 256u; }
+
 // Launch the persistent co-mining kernel.  `blocks` <= 0 fills the device.
 // Returns a hipError_t value.
 template <typename TT>

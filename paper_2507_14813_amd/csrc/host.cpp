@@ -944,11 +944,9 @@ namespace {
 template <typename TT>
 void hand_on_to(mg::KParams<TT> &p, const mg_tree *tr, uint64_t total_roots, mg::EpochCtx *ctx,
                 unsigned long long *ctx_count) {
-    const uint32_t share = (uint32_t)(total_roots / kBatchWaves);
     const bool deep = tr->depth > 3;
-    p.hand_on = (deep ? std::min(2048u, std::max(256u, share / 4))
-                      : std::min(8192u, std::max(512u, 2 * share))) & ~63u;
-    p.ctx_piece = deep ? 64u : 256u;
+    p.hand_on = mg::hand_on_limit(total_roots, kBatchWaves, deep);
+    p.ctx_piece = mg::hand_on_piece(deep);
     p.ctx_out = ctx;
     p.ctx_in = ctx;
     p.ctx_cap = kHandOnCap;

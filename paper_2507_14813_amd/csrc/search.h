@@ -1996,15 +1996,8 @@ hipError_t launch_ds(KParams<TT> p, int blocks, hipStream_t stream) {
     }
     if (p.chunk == 0) p.chunk = kWave;
     if (p.hand_on) {
-        // About twice the candidates a wave's share of the roots has; deeper
-        // trees find far more below each.  Waves were busy 50 % of a launch
-        // over 2M edges, 49 % with 756 motifs over 3M, before chunks were
-        // handed on; 20M edges hand nothing on, and the empty second launch
-        // takes 6 us.
-        const uint32_t share = p.n_roots / (uint32_t)(blocks * wpb);
-        p.hand_on = (D <= 3 ? std::min(8192u, std::max(512u, 2 * share))
-                            : std::min(2048u, std::max(256u, share / 4))) & ~63u;
-        p.ctx_piece = D <= 3 ? 256u : 64u;
+        p.hand_on = hand_on_limit(p.n_roots, (uint64_t)blocks * (uint32_t)wpb, D > 3);
+        p.ctx_piece = hand_on_piece(D > 3);
     }
     const size_t sm = smem_bytes<TT, D, MODE>(n_q, wpb);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * wpb), sm, stream, p);
