@@ -1833,9 +1833,9 @@ batch_kernel(const BatchParams<TT> bp) {
         // the contexts handed on, dealt to the waves: a context and the ones
         // that follow it in the same job
         const uint32_t n = (uint32_t)min(*glb(bp.ctx_n), bp.ctx_cap);
-        const uint32_t waves = gridDim.x * (uint32_t)kWavesPerBlock;
+        const uint32_t wpb = blockDim.x / kWave, waves = gridDim.x * wpb;
         const uint32_t per = max(1u, min(8u, n / (4u * waves)));
-        const uint32_t w0 = blockIdx.x * (uint32_t)kWavesPerBlock + (uint32_t)wave;
+        const uint32_t w0 = blockIdx.x * wpb + (uint32_t)wave;
         for (uint32_t r = w0; (uint64_t)r * per < n; r += waves) {
             uint32_t at = r * per;
             const uint32_t end = min(at + per, n);
@@ -1910,7 +1910,8 @@ size_t smem_bytes(int n_q, int wpb) {
 // instead of 12: 3M edges 5.07 -> 4.73 ms; 48 motifs and three windows on 4M
 // edges 2.22 -> 2.07).  The last answer per kernel and thread is kept: asking costs
 // more than the rest of a small launch.
-constexpr size_t kMaxLds = 160 * 1024 - 256;   // dynamic part of a workgroup's LDS at most
+constexpr size_t kLdsBytes = 160 * 1024;        // of a compute unit
+constexpr size_t kMaxLds = kLdsBytes - 256;   // dynamic part of a workgroup's LDS at most
 struct Fill {
     int dev = -1, n_q = -1, wpb = 4, blocks = 0;
 };
@@ -2021,8 +2022,13 @@ template <typename TT, int D, int MODE>
 hipError_t launch_batch_d(const BatchParams<TT> &bp, int blocks, hipStream_t stream) {
     if constexpr (!epochs_of(MODE))
         if (bp.contexts) return launch_batch_d<TT, D, MODE == 0 ? 5 : 6>(bp, blocks, stream);
-    const size_t sm = (size_t)kWavesPerBlock *
-                      ((((size_t)bp.n_q_max * 8 + 15) & ~(size_t)15) + sizeof(WaveLds<TT, D, 0>));
+    // Four waves per workgroup, or as many as fit: each has counters of its own
+    // beside its level buffers (depth 5: 12.9 KB, so four up to 3,506 counters
+    // and three up to 4,096).
+    const size_t per_wave = (((size_t)bp.n_q_max * 8 + 15) & ~(size_t)15) + sizeof(WaveLds<TT, D, 0>);
+    int wpb = kWavesPerBlock;
+    while (wpb > 1 && wpb * per_wave > kLdsBytes) --wpb;
+    const size_t sm = wpb * per_wave;
     auto kern = batch_kernel<TT, D, MODE>;
     if (sm > 65536) {
         hipError_t e = hipFuncSetAttribute((const void *)kern,
@@ -2035,14 +2041,14 @@ hipError_t launch_batch_d(const BatchParams<TT> &bp, int blocks, hipStream_t str
         if (e != hipSuccess) return e;
         e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kWave * kWavesPerBlock, sm);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, kWave * wpb, sm);
         if (e != hipSuccess) return e;
         blocks = ncu * (per > 0 ? per : 1);
         // (one graph's searches: no more waves than items)
         if (!bp.items && !bp.contexts)
-            blocks = (int)std::min<uint32_t>((uint32_t)blocks, (bp.n_items + kWavesPerBlock - 1) / kWavesPerBlock);
+            blocks = (int)std::min<uint32_t>((uint32_t)blocks, (bp.n_items + wpb - 1) / wpb);
     }
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * kWavesPerBlock), sm, stream, bp);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kWave * wpb), sm, stream, bp);
     return hipGetLastError();
 }
 

@@ -100,3 +100,24 @@ def test_a_batch_that_fills_the_context_buffer(api, k, first):
     b = api.Batch(graphs, trees, item_roots=64)
     for _ in range(3):
         assert [x.tolist() for x in b.count()] == want
+
+
+@pytest.mark.parametrize("n_motifs,k", [(450, 5), (510, 4), (512, 5)])
+def test_batches_of_thousands_of_counters(api, n_motifs, k):
+    """Trees of up to MG_MAX_QUERIES counters in a batch: the counters of a
+    workgroup's waves and their level buffers share 160 KB."""
+    motifs = list(dict.fromkeys(tuple(m) for m in W.random_extension_motifs(4 * n_motifs, (k,), 6, 9)))
+    motifs = motifs[:n_motifs]
+    deltas = [10 * (i + 1) for i in range(8)]
+    tr = api.Tree(motifs, deltas)
+    assert tr.info()["n_distinct"] == n_motifs and tr.info()["depth"] == k
+    s, d, t = uniform(800, 12, 4000, 5)
+    g, og = api.Graph(s, d, t, 12), oracle.OracleGraph(s, d, t, 12)
+    print("counters", n_motifs * 8, k, flush=True)
+    want = api.count(g, tr)
+    for i in (0, 3, 7):
+        assert want[i][::37].tolist() == [og.count(m, deltas[i]) for m in motifs[::37]]
+    small = api.Tree(THREE, 30)
+    want0 = np.array([og.count(m, 30) for m in THREE], dtype=np.uint64)
+    for got in (api.count_batch([g, g], [small, tr]), api.Batch([g, g], [small, tr], item_roots=64).count()):
+        assert np.array_equal(got[0], want0) and np.array_equal(got[1], want)
