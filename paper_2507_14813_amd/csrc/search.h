@@ -1203,7 +1203,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                 }
             }
         }
-        if constexpr (L == 1 && D > 2 && plain_of(MODE)) if (epochs_of(MODE) || formed) {
+        if constexpr (L == 1 && plain_of(MODE) && (D > 2 || epochs_of(MODE))) if (epochs_of(MODE) || formed) {
             // Candidates [lo, T) of this chunk (in window order; lane w < nw
             // holds window w) as contexts of at most `piece` candidates, where
             // room(total) gives the first slot, or no slot (false) for all.

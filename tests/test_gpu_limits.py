@@ -121,3 +121,20 @@ def test_batches_of_thousands_of_counters(api, n_motifs, k):
     want0 = np.array([og.count(m, 30) for m in THREE], dtype=np.uint64)
     for got in (api.count_batch([g, g], [small, tr]), api.Batch([g, g], [small, tr], item_roots=64).count()):
         assert np.array_equal(got[0], want0) and np.array_equal(got[1], want)
+
+
+def test_epochs_of_two_edge_trees_hand_contexts_on(api):
+    """Whole-list windows of a two-edge tree, most waves without a chunk: the
+    busy ones hand on what is left, as in deeper trees."""
+    s, d, t = uniform(40_000, 3000, 40_000, 7)
+    g, og = api.Graph(s, d, t, 3000), oracle.OracleGraph(s, d, t, 3000)
+    motifs = [((0, 1), (2, 3)), ((0, 1), (1, 2))]
+    for unit in (1, 2 ** 33):
+        g = api.Graph(s, d, t * unit, 3000)
+        want = np.array([[og.count(m, x) for m in motifs] for x in (100, 2000)], dtype=np.uint64)
+        for delta, exp in ((2000 * unit, want[1]), ([100 * unit, 2000 * unit], want)):
+            for epochs in (2, 16):
+                log = np.zeros(epochs, np.int64)
+                print("two-edge epochs", unit, delta, epochs, flush=True)
+                got = api.count(g, api.Tree(motifs, delta), epoch_idle=1, max_epochs=epochs, epoch_contexts=log)
+                assert np.array_equal(got, exp) and log[0] > 0 and log[-1] == 0
