@@ -197,7 +197,9 @@ struct KParams {
     int32_t *enum_out;            // NULL, or enumeration: records of 1 + kKMax words
                                   // (distinct motif, edge ids, -1 past the motif's
                                   // length), enum_cap of them, at slots taken from
-                                  // *enum_cursor (zeroed); needs leaf_scan 0
+                                  // *enum_cursor (zeroed); once it is past enum_cap
+                                  // the waves end their search, and neither it nor
+                                  // the counters are the totals; needs leaf_scan 0
     unsigned long long *enum_cursor;
     unsigned long long enum_cap;
     unsigned long long *wave_clock;  // NULL, or per wave: start and end of its search

@@ -1803,52 +1803,63 @@ int enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match *ou
         mg_count_opts o;
         mg_count_opts_init(&o);
         o.stream = stream;
+        mg_count_opts all = o;
+        all.leaf_scan = -1;   // every match goes through the candidate expansion
         // The count sizes the output, unless the caller's own capacity is small
-        // enough to be taken as it is: then the search writes into that much
-        // and says how many matches there are.
+        // enough to be taken as it is and there is memory for it: then the search
+        // writes into that much, and a count follows only if it was too little.
         constexpr uint64_t kDirectBytes = 256u << 20;
-        const bool direct = (out || arrays) && capacity > 0 && (uint64_t)capacity * sizeof(mg_match) <= kDirectBytes;
-        uint64_t room = direct ? (uint64_t)capacity : 0, total = 0;
-        if (!direct) {
+        hipStream_t st = (hipStream_t)stream;
+        DevBuf d_work, d_rec;
+        struct G { DevBuf *a, *b; ~G() { dev_free(*a); dev_free(*b); } } guard{&d_work, &d_rec};
+        bool direct = (out || arrays) && capacity > 0 && (uint64_t)capacity * sizeof(mg_match) <= kDirectBytes;
+        uint64_t room = 0, total = 0;
+        auto count_all = [&]() -> int {
             std::vector<uint64_t> cnt(tr->n_motifs);
             int rc = mg_count(g, tr, &o, cnt.data());
             if (rc) return rc;
+            total = 0;
             for (size_t q = 0; q < first.size(); ++q) total += cnt[first[q]];
+            return MG_OK;
+        };
+        if (direct) {
+            int dev = 0;
+            HIP_TRY(hipGetDevice(&dev));
+            if (dev != g->device)
+                return fail(MG_EINVAL, "graph lives on device %d, current is %d", g->device, dev);
+            int rc = upload_tree(tr, dev, st);
+            if (rc) return rc;
+            room = (uint64_t)capacity;
+            direct = dev_alloc(d_rec, sizeof(mg_match) * room, (void *)st) == MG_OK;
+        }
+        if (!direct) {
+            int rc = count_all();
+            if (rc) return rc;
             if (!(out || arrays) || (uint64_t)capacity < total) {
                 *n_matches = (int64_t)total;
                 return MG_OK;
             }
             room = total;
-        } else {
-            int dev = 0;
-            HIP_TRY(hipGetDevice(&dev));
-            if (dev != g->device)
-                return fail(MG_EINVAL, "graph lives on device %d, current is %d", g->device, dev);
-            int rc = upload_tree(tr, dev, (hipStream_t)stream);
+            rc = dev_alloc(d_rec, sizeof(mg_match) * std::max<uint64_t>(room, 1), (void *)st);
             if (rc) return rc;
         }
-        hipStream_t st = (hipStream_t)stream;
-        DevBuf d_work, d_rec;
-        struct G { DevBuf *a, *b; ~G() { dev_free(*a); dev_free(*b); } } guard{&d_work, &d_rec};
         const size_t cnt_off = kQueueBytes, cur_off = cnt_off + 8 * n_slots(tr), first_off = cur_off + 8;
         int rc = dev_alloc(d_work, first_off + 4 * first.size(), (void *)st);
-        if (!rc) rc = dev_alloc(d_rec, sizeof(mg_match) * std::max<uint64_t>(room, 1), (void *)st);
         if (rc) return rc;
         unsigned long long *w = (unsigned long long *)d_work.ptr;
         HIP_TRY(mg::launch_fill_u64(w, (uint32_t)(first_off / 8), 0ull, st));
-        o.leaf_scan = -1;   // every match goes through the candidate expansion
         hipError_t e = hipSuccess;
         if (g->E > 0) {
             if (g->time_bytes == 4) {
                 mg::KParams<uint32_t> p{};
-                fill_params<uint32_t>(p, g, tr, o, w, w + cnt_off / 8, nullptr, nullptr);
+                fill_params<uint32_t>(p, g, tr, all, w, w + cnt_off / 8, nullptr, nullptr);
                 p.enum_out = (int32_t *)d_rec.ptr;
                 p.enum_cursor = w + cur_off / 8;
                 p.enum_cap = room;
                 e = mg::launch_comine<uint32_t>(p, 0, st);
             } else {
                 mg::KParams<uint64_t> p{};
-                fill_params<uint64_t>(p, g, tr, o, w, w + cnt_off / 8, nullptr, nullptr);
+                fill_params<uint64_t>(p, g, tr, all, w, w + cnt_off / 8, nullptr, nullptr);
                 p.enum_out = (int32_t *)d_rec.ptr;
                 p.enum_cursor = w + cur_off / 8;
                 p.enum_cap = room;
@@ -1856,14 +1867,27 @@ int enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match *ou
             }
         }
         if (e != hipSuccess) return fail(MG_EDEVICE, "enumeration launch failed: %s", hipGetErrorString(e));
-        uint64_t written = 0;
-        HIP_TRY(hipMemcpyAsync(&written, w + cur_off / 8, 8, hipMemcpyDeviceToHost, st));
+        // the search's own counters, then the records written
+        std::vector<uint64_t> h(n_slots(tr) + 1);
+        HIP_TRY(hipMemcpyAsync(h.data(), w + cnt_off / 8, 8 * h.size(), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
-        if (direct) total = written;
-        if (written != total)
+        const uint64_t written = h.back();
+        if (direct && written > room) {
+            dev_free(d_rec);
+            rc = count_all();
+            if (rc) return rc;
+            if (total <= room)
+                return fail(MG_EINTERNAL, "enumeration found more than %llu matches, the count is %llu",
+                            (unsigned long long)room, (unsigned long long)total);
+            *n_matches = (int64_t)total;
+            return MG_OK;
+        }
+        const uint64_t counted = std::accumulate(h.begin(), h.end() - 1, (uint64_t)0);
+        if (direct) total = counted;
+        if (written != total || counted != total)
             return fail(MG_EINTERNAL, "enumeration wrote %llu matches, the count is %llu",
                         (unsigned long long)written, (unsigned long long)total);
-        if (total && total <= room) {
+        if (total) {
             // motifs in the caller's numbering (a duplicate's first occurrence),
             // edges in the caller's input order
             HIP_TRY(hipMemcpyAsync((char *)d_work.ptr + first_off, first.data(), 4 * first.size(),

@@ -510,11 +510,13 @@ __device__ __forceinline__ void edge_chain(WaveLds<TT, D, 2> &W, uint32_t i, uin
 
 // Enumeration: the wave's staged matches written out as records (motif, then
 // the edges and -1 up to kKMax) at consecutive slots, taken with one atomic.
-// Slots past the capacity are dropped (the cursor still counts them).
+// Slots past the capacity are dropped.  Returns true once there are any: the
+// records are of no use then, and the wave ends its search (22 million matches
+// of 2M edges into room for 1,000 took 5.7 ms, of which a count is 0.4).
 template <typename TT, int D>
-__device__ __forceinline__ void flush_matches(const KParams<TT> &p, WaveLds<TT, D, 2> &W, int lane) {
+__device__ __forceinline__ bool flush_matches(const KParams<TT> &p, WaveLds<TT, D, 2> &W, int lane) {
     const uint32_t n = uniform(W.n);
-    if (!n) return;
+    if (!n) return false;
     unsigned long long base = 0;
     if (lane == 0) base = atomicAdd(p.enum_cursor, (unsigned long long)n);
     base = lane0_u64(base);
@@ -530,6 +532,7 @@ __device__ __forceinline__ void flush_matches(const KParams<TT> &p, WaveLds<TT, 
     wave_sync();
     if (lane == 0) W.n = 0;
     wave_sync();
+    return base + n > p.enum_cap;
 }
 
 // Enumeration: one match per lane with `want` (motif q, edges e[0..k)) staged
@@ -538,11 +541,11 @@ __device__ __forceinline__ void flush_matches(const KParams<TT> &p, WaveLds<TT, 
 // matches on average) the kernel took 950 us for the 801,489 matches of 36
 // three-edge motifs on 200,000 edges, with staged matches 645 us.
 template <typename TT, int D>
-__device__ __forceinline__ void write_matches(const KParams<TT> &p, WaveLds<TT, D, 2> &W, int lane,
+__device__ __forceinline__ bool write_matches(const KParams<TT> &p, WaveLds<TT, D, 2> &W, int lane,
                                               bool want, uint32_t q, const uint32_t (&e)[kKMax],
                                               uint32_t k) {
     const uint64_t m = __ballot(want);
-    if (!m) return;
+    if (!m) return false;
     const uint32_t n = uniform(W.n);
     if (want) {
         const uint32_t slot = n + mbcnt(m);
@@ -554,7 +557,7 @@ __device__ __forceinline__ void write_matches(const KParams<TT> &p, WaveLds<TT, 
     wave_sync();
     if (lane == 0) W.n = now;
     wave_sync();
-    if (now >= (uint32_t)kWave) flush_matches<TT, D>(p, W, lane);
+    return now >= (uint32_t)kWave && flush_matches<TT, D>(p, W, lane);
 }
 
 // Counts the leaf-only window [l0, l0 + len) of group g (header word hdr) for
@@ -869,7 +872,8 @@ __device__ __forceinline__ void count_leaf_parent(const KParams<TT> &p,
 // per-lane statistics (only the STATS instantiation touches them)
 struct Stats {
     uint64_t v[kStats];
-    bool dumped;   // the wave wrote contexts (an epoch ended): claim no more work
+    bool stopped;   // claim no more work: the wave wrote contexts (an epoch ended), or its
+                    // matches have no room left
 };
 
 // MODE: 0 plain search (trees with one window), 1 with search statistics, 2
@@ -991,12 +995,13 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
 
     bool done = false;
     for (;;) {
+        if constexpr (MODE == 4) if (st.stopped) break;
         const KParams<TT> &p = fresh(p0);
         const uint4 *__restrict__ inode = glb(p.tree.inode);
         if constexpr (L == 1 && epochs_of(MODE)) {
             // (a wave dumps in one batch at most: the later batches of its
             // chunk search on)
-            if (p.idle && p.ctx_out && room && !dumping && !st.dumped && (++polls & 15u) == 0) {
+            if (p.idle && p.ctx_out && room && !dumping && !st.stopped && (++polls & 15u) == 0) {
                 uint32_t v = 0;
                 if (lane == 0) v = __hip_atomic_load(p.idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const uint32_t waves = gridDim.x * (blockDim.x / kWave);
@@ -1383,7 +1388,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                 uint32_t e[kKMax] = {0, 0, 0, 0, 0};
                 edge_chain<L>(W, ox, e);
                 e[L] = valid ? cand_eid() : 0u;
-                write_matches<TT, D>(p, W, lane, valid && cw && q1, q1 - 1u, e, L + 1);
+                st.stopped |= write_matches<TT, D>(p, W, lane, valid && cw && q1, q1 - 1u, e, L + 1);
             }
             if constexpr (L + 1 < D) {
                 auto &B = lvl<L + 1>(W.lv);
@@ -1479,7 +1484,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
         if (done && nB == 0) break;
     }
     if constexpr (L == 1) {
-        if (dumping) st.dumped = true;
+        if (dumping) st.stopped = true;
     }
 }
 
@@ -1561,7 +1566,7 @@ __device__ __forceinline__ void search_pieces(const KParams<TT> &p,
                     if constexpr (MODE == 4) {
                         if (p.tree.root_q >= 0) {
                             uint32_t e[kKMax] = {r, 0, 0, 0, 0};
-                            write_matches<TT, D>(p, W, lane, ok, (uint32_t)p.tree.root_q, e, 1);
+                            st.stopped |= write_matches<TT, D>(p, W, lane, ok, (uint32_t)p.tree.root_q, e, 1);
                         }
                     }
                     if constexpr (STATS) st.v[kStatRoots] += ok ? 1 : 0;
@@ -1630,7 +1635,7 @@ comine_kernel(const KParams<TT>) {
     Stats st;
 #pragma unroll
     for (int i = 0; i < kStats; ++i) st.v[i] = 0;
-    st.dumped = false;
+    st.stopped = false;
     // when each wave starts and ends its search (device real-time clock)
     const uint32_t clock_slot = blockIdx.x * wpb + (uint32_t)wave;
     if (p.wave_clock && lane == 0 && clock_slot < p.n_wave_clock)
@@ -1654,7 +1659,7 @@ comine_kernel(const KParams<TT>) {
     bool first = p.place_first != 0;
     const uint32_t place = (blockIdx.x / nq) * wpb + (uint32_t)wave;
     auto claim = [&](Piece &w) -> bool {
-        if (st.dumped) return false;   // an epoch ended
+        if (st.stopped) return false;
         if (items) {
             // item i waits in queue i % kQueues, so that the claims of the
             // whole device are not one after another on one head
@@ -1779,7 +1784,7 @@ comine_kernel(const KParams<TT>) {
     if constexpr (MODE == 4) flush_matches<TT, D>(p, W, lane);
     if constexpr (epochs_of(MODE)) {
         // out of work: an idle wave, for the epoch limit
-        if (p.idle && p.ctx_out && !st.dumped && lane == 0) atomicAdd(p.idle, 1u);
+        if (p.idle && p.ctx_out && !st.stopped && lane == 0) atomicAdd(p.idle, 1u);
     }
 
     if (p.wave_clock && lane == 0 && clock_slot < p.n_wave_clock)
@@ -1815,7 +1820,7 @@ batch_kernel(const BatchParams<TT> bp) {
     WaveLds<TT, D, 0> &W = *reinterpret_cast<WaveLds<TT, D, 0> *>(mine + cnt_bytes);
     W.flag[lane] = 0;
     Stats st;
-    st.dumped = false;
+    st.stopped = false;
     // search pieces of one job and add its counters to the batch's
     auto search = [&](uint32_t j, auto claim) {
         const BatchJob<TT> &job = bp.jobs[j];

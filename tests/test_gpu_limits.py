@@ -138,3 +138,50 @@ def test_epochs_of_two_edge_trees_hand_contexts_on(api):
                 print("two-edge epochs", unit, delta, epochs, flush=True)
                 got = api.count(g, api.Tree(motifs, delta), epoch_idle=1, max_epochs=epochs, epoch_contexts=log)
                 assert np.array_equal(got, exp) and log[0] > 0 and log[-1] == 0
+
+
+def test_enumeration_into_too_little_room_ends_its_search(api):
+    """A capacity far below the matches: nothing is written, the total is that
+    of the count, and it does not take the time of enumerating everything (here
+    over 3,000 times the count's work: 2 * 10^8 matches)."""
+    import ctypes
+    import time
+    n, w, k = 300_000, 50, 3
+    g, tree = api.Graph(*run_of_one_pair(n), 2), api.Tree([((0, 1),) * k], w)
+    total = repetitions(n, k, w)
+    L, m = api.lib(), ctypes.c_int64(0)
+
+    def call(capacity):
+        rec = np.full((max(capacity, 1), 6), -7, np.int32)
+        t0 = time.perf_counter()
+        assert L.mg_enumerate(g.handle, tree.handle, None, rec.ctypes.data, capacity, ctypes.byref(m)) == 0
+        dt = time.perf_counter() - t0
+        assert m.value == total and (rec == -7).all()
+        return dt
+
+    print("little room", total, flush=True)
+    for capacity in (1, 63, 64, 5000, 1_000_000):
+        call(capacity)
+    assert min(call(5000) for _ in range(5)) < 0.02
+
+
+def test_enumeration_with_room_for_every_match(api):
+    """Capacities at the total and around it, each record once; a tree whose
+    only motif is one edge (matches of the roots themselves)."""
+    import ctypes
+    L = api.lib()
+    for k, w, n in ((1, 0, 1000), (2, 3, 5000), (4, 6, 2000)):
+        g, tree, m = api.Graph(*run_of_one_pair(n), 2), api.Tree([((0, 1),) * k], w), ctypes.c_int64(0)
+        total = repetitions(n, k, w)
+        for capacity in (total - 1, total, total + 1, 4 * total):
+            rec = np.full((capacity, 6), -7, np.int32)
+            assert L.mg_enumerate(g.handle, tree.handle, None, rec.ctypes.data, capacity,
+                                  ctypes.byref(m)) == 0
+            assert m.value == total
+            if capacity < total:
+                assert (rec == -7).all()
+            else:
+                got = rec[:total]
+                assert (rec[total:] == -7).all() and (got[:, 0] == 0).all() and (got[:, 1 + k:] == -1).all()
+                assert len(set(map(tuple, got[:, 1:1 + k].tolist()))) == total
+                assert (np.diff(got[:, 1:1 + k], axis=1) > 0).all() and (got[:, k] - got[:, 1] <= w).all()
