@@ -458,8 +458,12 @@ def enumerate_matches(graph: Graph, tree: Tree, stream=None):
     motif = np.empty(n.value, dtype=np.int32)
     edges = np.empty((n.value, 5), dtype=np.int32)
     if n.value:
-        _check(lib().mg_enumerate_arrays(graph.handle, tree.handle, st, _p(motif), _p(edges),
-                                         n.value, ctypes.byref(n)))
+        wrote = ctypes.c_int64(0)
+        _check(L.mg_enumerate_arrays(graph.handle, tree.handle, st, _p(motif), _p(edges),
+                                     n.value, ctypes.byref(wrote)))
+        if wrote.value != n.value:   # the arrays do not hold every match, or hold fewer
+            raise MayuraError(-5, "enumeration found %d matches, the count is %d"
+                              % (wrote.value, n.value))
     return motif, edges
 
 
