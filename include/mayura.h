@@ -271,6 +271,11 @@ void mg_count_opts_init(mg_count_opts *opts);
  *   counts : host, n_deltas * n_motifs entries: for each window in the
  *            caller's order, the motifs in the caller's motif order
  * The result is exact and independent of every scheduling option.
+ * Memory: besides its counters (a few KB), a count over 131,072 roots or more
+ * with motifs of three edges or more takes 16 MB of device memory for the call,
+ * for work it spreads over the device; where that much is not to be had it does
+ * without.  A thread's first count of a graph of 65,536 edges or fewer allocates
+ * 64 KB of pinned host memory that the thread keeps until it ends.
  */
 int mg_count(const mg_graph *g, const mg_tree *tr, const mg_count_opts *opts,
              uint64_t *counts);
@@ -437,7 +442,9 @@ int mg_model_train(mg_model *m, const float *feats, const float *labels, int64_t
  *                   time width (mg_graph_info_t.time_bytes)
  *   opts          : NULL = defaults (autotuned item size, graph replay)
  * The handles must outlive the batch.  Counts are exact and independent of
- * every option.
+ * every option.  A batch of 131,072 roots or more with motifs of three edges or
+ * more holds 16 MB of device memory for the work its steps spread (and does
+ * without where that much is not to be had).
  */
 typedef struct mg_batch mg_batch;  /* opaque */
 typedef struct {

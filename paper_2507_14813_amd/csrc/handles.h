@@ -2,7 +2,6 @@
 // the C ABI and the GPU path; cpu.cpp: the CPU co-mining backend).  Not part
 // of the public C ABI.
 #pragma once
-#include <atomic>
 #include <memory>
 #include <string>
 #include <utility>
@@ -86,9 +85,6 @@ struct mg_tree {
     // device copies
     int device = -1;
     mgh::DevBuf d_tab;                  // node_tab, grp_tab, pair_tab
-    mgh::DevBuf d_ctx;                  // contexts a count hands on between its two launches
-    int ctx_device = -1;                // where it is
-    std::atomic<bool> ctx_busy{false};  // d_ctx is some running count's
     // per-motif chain trees (built on first per-motif count)
     std::vector<std::unique_ptr<mg_tree>> singles;
     // CPU backend: the generated and compiled search of this tree

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -247,7 +246,6 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
 // ---------------------------------------------------------------- tree
 mg_tree::~mg_tree() {
     dev_free(d_tab);
-    dev_free(d_ctx);
     release_cpu_code(this);
 }
 
@@ -620,38 +618,25 @@ bool small_count(const mg_graph *g, const mg_tree *tr, const mg_count_opts &o, b
     return true;
 }
 
-// Epochs (paper, section 4.5): launch after launch, each ending once
-// o.epoch_idle percent of its waves are idle; the root-level candidates the
-// busy waves had not reached yet come back as contexts, which the next launch
-// spreads over all of its waves.  The last of max_epochs launches runs to the
-// end.  Counts accumulate in p.counts; p.queues is cleared before each launch.
 constexpr uint32_t kHandOnRoots = 1u << 17;   // counts of fewer roots hand nothing on: a
                                               // wave has 16 roots or fewer there
 constexpr uint64_t kHandOnCap = 1u << 18;     // contexts one count can hand on (16 MB)
 constexpr uint64_t kCtxCap = 1u << 20;   // contexts one epoch can hand on (64 MB)
 
-// The tree keeps one context buffer, allocated by its first count of that many
-// roots; a count that finds it taken by another thread's has its own.  Without
-// memory for one (take returns NULL) nothing is handed on.
-struct CtxLease {
-    std::atomic<bool> *busy = nullptr;
-    DevBuf own;
-    ~CtxLease() {
-        dev_free(own);
-        if (busy) busy->store(false, std::memory_order_release);
-    }
-    const DevBuf *take(mg_tree *tr, int device, hipStream_t st) {
-        DevBuf *b = &own;
-        if (!tr->ctx_busy.exchange(true, std::memory_order_acquire)) {
-            busy = &tr->ctx_busy;
-            b = &tr->d_ctx;
-            if (tr->ctx_device != device) dev_free(*b);
-            tr->ctx_device = device;
-        }
-        return b->ptr || !dev_alloc(*b, sizeof(mg::EpochCtx) * kHandOnCap, (void *)st) ? b : nullptr;
-    }
-};
+// Whether the heavy chunks of a count over n_roots roots may be handed on.  Its
+// context buffer is allocated for the call and only for such a call (12 us of a
+// hipMalloc, less from a caching allocator); without memory for it nothing is
+// handed on.
+bool hands_on(const mg_count_opts &o, uint32_t n_roots) {
+    return n_roots >= kHandOnRoots && o.sched == MG_SCHED_PLAIN && !o.epoch_idle && !o.stop &&
+           !o.max_chunks && !o.stats && !o.root_cost && !o.wave_clock;
+}
 
+// Epochs (paper, section 4.5): launch after launch, each ending once
+// o.epoch_idle percent of its waves are idle; the root-level candidates the
+// busy waves had not reached yet come back as contexts, which the next launch
+// spreads over all of its waves.  The last of max_epochs launches runs to the
+// end.  Counts accumulate in p.counts; p.queues is cleared before each launch.
 template <typename TT>
 int epoch_search(mg::KParams<TT> p, const mg_count_opts &o, hipStream_t st) {
     const int max_epochs = o.max_epochs > 0 ? o.max_epochs : 16;
@@ -700,7 +685,7 @@ template <typename TT>
 int launch_tree(const mg_graph *g, mg_tree *tr, const uint32_t *d_roots, uint32_t n_roots,
                 unsigned long long *d_queues, unsigned long long *d_counts,
                 unsigned long long *d_stats, unsigned long long *d_cost,
-                unsigned long long *d_clock, const DevBuf *ctx, const mg_count_opts &o,
+                unsigned long long *d_clock, mg::EpochCtx *ctx, const mg_count_opts &o,
                 hipStream_t st, float *ms) {
     mg::KParams<TT> p{};
     fill_params<TT>(p, g, tr, o, d_queues, d_counts, d_stats, d_cost);
@@ -734,12 +719,11 @@ int launch_tree(const mg_graph *g, mg_tree *tr, const uint32_t *d_roots, uint32_
         // chunks are searched by a second launch, spread over the device (one
         // wave's 64 roots inside a burst took as long as everything else: half
         // of a count of 3M edges with 756 motifs).
-        const bool two = ctx && tr->kdepth > 2 && n_roots >= kHandOnRoots && !p.stop &&
-                         !p.max_chunks && !p.stats && !p.root_cost && !p.wave_clock;
+        const bool two = ctx && tr->kdepth > 2;
         if (two) {
             p.hand_on = 1;
-            p.ctx_out = (mg::EpochCtx *)ctx->ptr;
-            p.ctx_cap = ctx->bytes / sizeof(mg::EpochCtx);
+            p.ctx_out = ctx;
+            p.ctx_cap = kHandOnCap;
             p.ctx_count = d_queues + mg::kCtxCountWord;
         }
         hipError_t e = mg::launch_comine<TT>(p, o.blocks, st);
@@ -983,7 +967,7 @@ int upload_jobs(mg_batch *b, hipStream_t st) {
 // times: 4.23 ms, here 2.20 (of 20M edges: 35.5 ms, here 20.5).  Counters come back in `slots`, tree after tree; *taken stays false for
 // more items than a batch can number.
 template <typename TT>
-int count_runs(const mg_graph *g, mg_tree *tr, const std::vector<mg_tree *> &runs, const mg_count_opts &o,
+int count_runs(const mg_graph *g, const std::vector<mg_tree *> &runs, const mg_count_opts &o,
                uint64_t *slots, bool *taken, hipStream_t st, float *ms) {
     const uint32_t E = (uint32_t)g->E;
     // about 16 items per wave, of at most 2048 roots (a claim on one queue head
@@ -1012,9 +996,7 @@ int count_runs(const mg_graph *g, mg_tree *tr, const std::vector<mg_tree *> &run
     int rc = own.get(&d_jobs, runs.size(), st);
     if (!rc) rc = own.get(&d_work, (size_t)depths * kBatchQueueWords + n_out, st);
     if (rc) return rc;
-    CtxLease lease;
-    if (deep)
-        if (const DevBuf *ctx = lease.take(tr, g->device, st)) d_ctx = (mg::EpochCtx *)ctx->ptr;
+    if (deep) (void)own.get(&d_ctx, kHandOnCap, st);   // (NULL: nothing is handed on)
     unsigned long long *d_out = d_work + (size_t)depths * kBatchQueueWords;
     std::vector<mg::BatchJob<TT>> jobs(runs.size());
     for (size_t i = 0, at = 0, d = 0; i < runs.size(); ++i) {
@@ -2136,8 +2118,8 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
             float ms = 0.f;
             bool taken = false;
             int rc = g->time_bytes == 4
-                         ? count_runs<uint32_t>(g, tr, runs, o, qcount.data(), &taken, st, o.elapsed_ms ? &ms : nullptr)
-                         : count_runs<uint64_t>(g, tr, runs, o, qcount.data(), &taken, st, o.elapsed_ms ? &ms : nullptr);
+                         ? count_runs<uint32_t>(g, runs, o, qcount.data(), &taken, st, o.elapsed_ms ? &ms : nullptr)
+                         : count_runs<uint64_t>(g, runs, o, qcount.data(), &taken, st, o.elapsed_ms ? &ms : nullptr);
             if (rc) return rc;
             if (taken) {
                 map_counts(tr, qcount.data(), counts);
@@ -2172,10 +2154,11 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
         }
         struct Guard4 { DevBuf *b; ~Guard4() { dev_free(*b); } } gk{&d_clock};
 
-        CtxLease lease;
-        const DevBuf *ctx = nullptr;
-        if (n_roots >= kHandOnRoots && o.sched == MG_SCHED_PLAIN && !o.epoch_idle)
-            ctx = lease.take(tr, dev, st);
+        Scratch own;
+        mg::EpochCtx *ctx = nullptr;
+        bool deep = false;
+        for (const mg_tree *t : runs) deep = deep || t->kdepth > 2;
+        if (deep && hands_on(o, n_roots)) (void)own.get(&ctx, kHandOnCap, st);
 
         std::vector<uint64_t> qcount(n_slots(tr), 0);
         float total_ms = 0.f;
