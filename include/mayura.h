@@ -154,7 +154,8 @@ void mg_tree_destroy(mg_tree *tr);
 typedef struct {
     int32_t mode;             /* MG_MODE_* */
     int32_t blocks;           /* persistent workgroups; 0 = fill the device */
-    int32_t chunk;            /* roots claimed per queue grab, multiple of 64; 0 = default */
+    int32_t chunk;            /* roots claimed per queue grab, multiple of 64; 0 = default:
+                                 64, or 4 to 32 where there are not 64 for every wave */
     int32_t queues;           /* root queues: 0 = one per XCD (8), else 1..8 */
     void *stream;             /* hipStream_t */
     const int64_t *roots;     /* host: root positions to search from; NULL = all */
@@ -384,7 +385,7 @@ int mg_comine_advice(const mg_graph *g, const mg_tree *tr, int32_t platform, mg_
  *                time and that of the defaults
  */
 typedef struct {
-    int32_t blocks, chunk, queues, leaf_scan;   /* the settings */
+    int32_t blocks, chunk, queues, leaf_scan;   /* the settings (chunk 0: the default) */
     float ms;                 /* median search time with them */
     float default_ms;         /* the same with the defaults */
     int32_t from_cache;       /* 1 when read from the cache */

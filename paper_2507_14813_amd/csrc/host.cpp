@@ -2113,7 +2113,7 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
         if (o.mode == MG_MODE_PER_MOTIF && n_roots > 0 && o.sched == MG_SCHED_PLAIN && !stoppable &&
             !o.roots && !o.stats && !o.root_cost && !o.wave_clock && !o.epoch_idle && !o.blocks &&
             (!o.chunk || o.chunk == 64) && (!o.queues || o.queues == mg::kQueues)) {
-            // (64-root chunks and every queue are the defaults, as mg_tune names them)
+            // (64-root chunks and every queue: the defaults, spelled out)
             std::vector<uint64_t> qcount(n_slots(tr), 0);
             float ms = 0.f;
             bool taken = false;
@@ -2280,6 +2280,8 @@ bool cache_lookup(const char *path, const std::string &key, mg_tune_result *r) {
                    ", \"blocks\": %d, \"chunk\": %d, \"queues\": %d, \"leaf_scan\": %d, "
                    "\"ms\": %f, \"default_ms\": %f",
                    &t.blocks, &t.chunk, &t.queues, &t.leaf_scan, &t.ms, &t.default_ms) == 6) {
+            if (t.chunk == 64) t.chunk = 0;   // what the default was called before it depended
+                                              // on the number of roots
             *r = t;
             found = true;   // the last entry for a key wins
         }
@@ -2346,13 +2348,13 @@ int mg_tune(const mg_graph *g, const mg_tree *tr, const char *cache_path, void *
         // coordinate descent from the defaults, one setting at a time
         mg_tune_result cur{};
         cur.blocks = 0;
-        cur.chunk = 64;
+        cur.chunk = 0;   // (the launch chooses: fill_params, launch_ds)
         cur.queues = mg::kQueues;
         cur.leaf_scan = (int32_t)mg::kLeafScanDefault;
         int rc = time_of(cur, &cur.ms);
         if (rc) return rc;
         cur.default_ms = cur.ms;
-        const std::vector<int32_t> chunks = {64, 128, 256}, queues = {8, 4, 2, 1},
+        const std::vector<int32_t> chunks = {0, 128, 256}, queues = {8, 4, 2, 1},
                                    scans = {64, 128, 256, 512, 1024},
                                    blocks = {0, ncu * 4, ncu * 6};
         for (int sweep = 0; sweep < 2; ++sweep) {

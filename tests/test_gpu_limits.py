@@ -185,3 +185,20 @@ def test_enumeration_with_room_for_every_match(api):
                 assert (rec[total:] == -7).all() and (got[:, 0] == 0).all() and (got[:, 1 + k:] == -1).all()
                 assert len(set(map(tuple, got[:, 1:1 + k].tolist()))) == total
                 assert (np.diff(got[:, 1:1 + k], axis=1) > 0).all() and (got[:, k] - got[:, 1] <= w).all()
+
+
+def test_autotuner_starts_from_the_defaults(api, tmp_path):
+    """What mg_tune names as the defaults is what a count without settings runs
+    (chunk 0: the launch chooses), also from a cache that says 64."""
+    s, d, t = uniform(30_000, 200, 20_000, 4)
+    g, tr, cache = api.Graph(s, d, t, 200), api.Tree(THREE[::5], 300), tmp_path / "tune.jsonl"
+    print("tune", flush=True)
+    r = api.tune(g, tr, cache=str(cache))
+    assert r["chunk"] in (0, 128, 256) and r["from_cache"] == 0
+    line = cache.read_text()
+    assert '"chunk": %d,' % r["chunk"] in line
+    cache.write_text(line.replace('"chunk": %d,' % r["chunk"], '"chunk": 64,'))
+    r2 = api.tune(g, tr, cache=str(cache))
+    assert r2["from_cache"] == 1 and r2["chunk"] == 0
+    kw = {k: r2[k] for k in ("blocks", "chunk", "queues", "leaf_scan")}
+    assert np.array_equal(api.count(g, tr, **kw), api.count(g, tr))
