@@ -1279,11 +1279,10 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                         slot = lane0_u64(slot);
                         if (slot + tot <= p.ctx_cap) return true;
                         // the buffer is full: the slots taken that exist hold
-                        // nothing (an empty range of a root of this job: the
+                        // nothing (an empty range of this job's first root: the
                         // next launch looks up the root of every context), and
                         // this wave searches on
                         EpochCtx none{};
-                        none.root = A.root[0];
                         none.job = p.job;
                         for (unsigned long long k = slot + lane; k < p.ctx_cap; k += kWave) p.ctx_out[k] = none;
                         return false;
