@@ -127,8 +127,9 @@ struct DevGraph {
     const uint4 *gp;              // per edge u -> v at t: the first pair entry with a
                                   // later time and the end of the pair u -> v, then of
                                   // v -> u (self-loops: 0)
-    const uint4 *out_gp;          // gp per out_adj entry, per in_adj entry
-    const uint4 *in_gp;
+    uint32_t gp_out, gp_in;       // the same records once more per out_adj and in_adj entry:
+                                  // where they start in gp (both 0: not kept, the
+                                  // record is that of the entry's edge id)
     const uint32_t *out_eid;      // edge id of every out_adj entry (64-bit times)
     const uint32_t *in_eid;       // edge id of every in_adj entry (64-bit times)
     const uint32_t *out_off;      // V+1

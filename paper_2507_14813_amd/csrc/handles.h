@@ -58,9 +58,10 @@ struct mg_graph {
     int time_bytes = 4;
     int device = 0;
     bool host_only = false;             // no device copy (MG_HOST_ONLY)
-    mgh::DevBuf gsrc, gdst, gt, gx, gn, gp, out_gp, in_gp, pair_t, out_eid, in_eid, out_off,
+    mgh::DevBuf gsrc, gdst, gt, gx, gn, gp, pair_t, out_eid, in_eid, out_off,
         out_adj, in_off, in_adj;
     mgh::DevBuf order;                  // u32 per edge: the caller's index (none: the same)
+    bool gp_entries = false;            // gp holds the list entries' records too
     int64_t device_bytes = 0;
     std::unique_ptr<mgh::HostAdj> host;   // for the CPU backend, built on first use
     int8_t bipartite = -1;              // -1 unknown, else whether the undirected graph is

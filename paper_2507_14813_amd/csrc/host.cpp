@@ -99,8 +99,8 @@ void dev_free(DevBuf &b) {
 using namespace mgh;
 
 mg_graph::~mg_graph() {
-    for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &gn, &gp, &out_gp, &in_gp, &pair_t, &out_eid,
-                      &in_eid, &out_off, &out_adj, &in_off, &in_adj, &order})
+    for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &gn, &gp, &pair_t, &out_eid, &in_eid, &out_off,
+                      &out_adj, &in_off, &in_adj, &order})
         dev_free(*b);
 }
 
@@ -120,7 +120,11 @@ void parallel_for(int64_t n, F f) {
 // Frees a set of device buffers at the end of a scope.
 struct Scratch {
     std::vector<DevBuf> bufs;
-    ~Scratch() { for (DevBuf &b : bufs) dev_free(b); }
+    ~Scratch() { drop(); }
+    void drop() {
+        for (DevBuf &b : bufs) dev_free(b);
+        bufs.clear();
+    }
     int alloc(void **p, size_t bytes, hipStream_t st) {
         bufs.emplace_back();
         const int rc = dev_alloc(bufs.back(), bytes, (void *)st);
@@ -147,22 +151,43 @@ int bit_width(uint64_t x) {
 template <typename TT>
 mg::DevGraph<TT> dev_graph(const mg_graph *g);
 
+// Graphs of this many edges and more do without the pair records per list entry,
+// 32 of their 120 bytes per edge (136 with 64-bit times): 2^31 edges hold 189 GB of
+// the 288 instead of 258 (223 instead of 292).  Below it the records of the edges
+// and of both lists' entries have 32-bit places.
+constexpr uint32_t kLeanEdges = 1u << 30;
+// An uploaded input is released once the edges are placed, at the price of a wait
+// for the stream, from this many edges on (16 MB).
+constexpr uint32_t kDropInputEdges = 1u << 20;
+
 // Builds the device graph from checked edge arrays in device memory: sorts
 // the edges by time unless they are, then both sides' lists and the per-edge
-// list ranks (ingest.hip).  Returns once the stream has finished it.
+// list ranks (ingest.hip).  `input` is what holds those arrays, when they are not
+// the caller's.  Returns once the stream has finished it.
+//
+// Memory: what the graph keeps and 16 bytes per edge of temporaries; the input is
+// gone before the pair records are made.  The sorts work in arrays that are written
+// after them: the time sort in gx and gn, the source and destination sorts in gx,
+// the pair sort in the records.
 template <typename TT>
 int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int64_t *t, bool sorted,
-                 hipStream_t st) {
+                 Scratch &input, hipStream_t st) {
     const uint32_t E = (uint32_t)g->E, V = (uint32_t)g->V;
     const uint32_t A = (uint32_t)(g->E - g->self_loops);   // list entries
     // 32-bit times leave room for the edge id in the list entry
     constexpr size_t kEid = sizeof(TT) == 4 ? 0 : sizeof(uint32_t);
+    constexpr size_t kRecord = 4 * sizeof(uint32_t);
+    g->device_bytes = 0;
+    auto keep = [&](DevBuf &b, size_t n) -> int {
+        const int rc = dev_alloc(b, n, (void *)st);
+        if (!rc) g->device_bytes += (int64_t)n;
+        return rc;
+    };
     struct Need { DevBuf *b; size_t n; };
     const Need needs[] = {
         {&g->gsrc, sizeof(int32_t) * (size_t)E}, {&g->gdst, sizeof(int32_t) * (size_t)E},
         {&g->gt, sizeof(TT) * (size_t)E},        {&g->gx, sizeof(uint32_t) * 4 * (size_t)E},
-        {&g->gn, sizeof(uint32_t) * 2 * (size_t)E}, {&g->gp, sizeof(uint32_t) * 4 * (size_t)E},
-        {&g->out_gp, sizeof(uint32_t) * 4 * (size_t)A}, {&g->in_gp, sizeof(uint32_t) * 4 * (size_t)A},
+        {&g->gn, sizeof(uint32_t) * 2 * (size_t)E},
         {&g->pair_t, sizeof(TT) * ((size_t)A + 4)},   // read four entries at a time
         {&g->out_eid, kEid * (size_t)A}, {&g->in_eid, kEid * (size_t)A},
         {&g->out_off, sizeof(uint32_t) * ((size_t)V + 1)},
@@ -170,46 +195,43 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
         {&g->in_off, sizeof(uint32_t) * ((size_t)V + 1)},
         {&g->in_adj, sizeof(mg::Entry<TT>) * (size_t)A},
     };
-    g->device_bytes = 0;
     for (const Need &u : needs) {
-        int rc = dev_alloc(*u.b, u.n, (void *)st);
+        int rc = keep(*u.b, u.n);
         if (rc) return rc;
-        g->device_bytes += (int64_t)u.n;
     }
     Scratch tmp;
-    uint32_t *v[2], *key[2], *opos, *ipos;
+    uint32_t *opos, *ipos, *ikey, *oeid;
     void *sort_mem;
     int rc = tmp.alloc(&sort_mem, mg::sort_scratch_bytes(E), st);
-    for (int i = 0; i < 2 && !rc; ++i) rc = tmp.get(&v[i], E, st);
-    for (int i = 0; i < 2 && !rc; ++i) rc = tmp.get(&key[i], E, st);
+    for (uint32_t **x : {&opos, &ipos, &ikey, &oeid})
+        if (!rc) rc = tmp.get(x, E, st);
     if (rc) return rc;
+    auto part = [&](const DevBuf &b, size_t i) { return (uint32_t *)b.ptr + i * E; };
     int at = 0;
     if (!sorted) {
-        TT *tk[2];
-        for (int i = 0; i < 2 && !rc; ++i) rc = tmp.get(&tk[i], E, st);
-        if (!rc) rc = dev_alloc(g->order, sizeof(uint32_t) * (size_t)E, (void *)st);
+        TT *tk[2] = {(TT *)g->gx.ptr, (TT *)g->gx.ptr + E};
+        uint32_t *v[2] = {part(g->gn, 0), part(g->gn, 1)};
+        rc = keep(g->order, sizeof(uint32_t) * (size_t)E);
         if (rc) return rc;
         LAUNCH_TRY(mg::launch_time_keys<TT>(t, g->t_min, E, tk[0], st));
         LAUNCH_TRY(mg::sort_pairs<TT>(tk, v, true, E, bit_width((uint64_t)(g->t_max - g->t_min)),
                                       sort_mem, &at, st));
         HIP_TRY(hipMemcpyAsync(g->order.ptr, v[at], sizeof(uint32_t) * (size_t)E,
                                hipMemcpyDeviceToDevice, st));
-        g->device_bytes += (int64_t)sizeof(uint32_t) * E;
     }
-    rc = tmp.get(&opos, E, st);
-    if (!rc) rc = tmp.get(&ipos, E, st);
-    uint32_t *ikey = nullptr, *oeid = nullptr;
-    if (!rc) rc = tmp.get(&ikey, E, st);
-    if (!rc) rc = tmp.get(&oeid, E, st);
-    if (rc) return rc;
+    uint32_t *okey = part(g->gx, 0), *v[2] = {part(g->gx, 2), part(g->gx, 3)};
     auto *gsrc = (int32_t *)g->gsrc.ptr, *gdst = (int32_t *)g->gdst.ptr;
     TT *gt = (TT *)g->gt.ptr;
     if (E)
         LAUNCH_TRY(mg::launch_place_edges<TT>(src, dst, t, g->t_min, (const uint32_t *)g->order.ptr,
-                                              E, V, gsrc, gdst, gt, key[0], ikey, st));
+                                              E, V, gsrc, gdst, gt, okey, ikey, st));
+    if (!input.bufs.empty() && E >= kDropInputEdges) {
+        HIP_TRY(hipStreamSynchronize(st));
+        input.drop();
+    }
     const int vb = bit_width(V);   // vertices and V itself (self-loops)
     for (int side = 0; side < 2; ++side) {
-        uint32_t *k[2] = {side ? ikey : key[0], key[1]};
+        uint32_t *k[2] = {side ? ikey : okey, part(g->gx, 1)};
         LAUNCH_TRY(mg::sort_pairs<uint32_t>(k, v, true, E, vb, sort_mem, &at, st));
         DevBuf &eid = side ? g->in_eid : g->out_eid;
         if (A && kEid)
@@ -222,21 +244,27 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
                                         (mg::Entry<TT> *)(side ? g->in_adj : g->out_adj).ptr,
                                         side ? ipos : opos, st));
     }
-    const mg::DevGraph<TT> dg = dev_graph<TT>(g);
-    LAUNCH_TRY(mg::launch_ranks<TT>(dg, opos, ipos, (uint4 *)g->gx.ptr, (uint2 *)g->gn.ptr, st));
-    // pair order: the out-lists' order (source, time) sorted by destination.
-    // Self-loops are in no pair: their records are zero.
-    if (g->self_loops) HIP_TRY(hipMemsetAsync(g->gp.ptr, 0, 16 * (size_t)E, st));
+    LAUNCH_TRY(mg::launch_ranks<TT>(dev_graph<TT>(g), opos, ipos, (uint4 *)g->gx.ptr,
+                                    (uint2 *)g->gn.ptr, st));
+    // The pair records of the edges, and once more in the order of both lists'
+    // entries, where a candidate reads them with its neighbours; without memory
+    // for those the search takes them by edge id.
+    g->gp_entries = E > 0 && E < kLeanEdges && !keep(g->gp, kRecord * ((size_t)E + 2 * (size_t)A));
+    if (!g->gp_entries) rc = keep(g->gp, kRecord * (size_t)E);
+    if (rc) return rc;
+    // pair order: the out-lists' order (source, time) sorted by destination
+    uint32_t *pv[2] = {oeid, ikey}, *pk[2] = {part(g->gp, 0), part(g->gp, 1)};
     if (A) {
-        uint32_t *pv[2] = {oeid, v[0]}, *pk[2] = {key[0], key[1]};
         LAUNCH_TRY(mg::launch_gather(pv[0], gdst, A, pk[0], st));
         LAUNCH_TRY(mg::sort_pairs<uint32_t>(pk, pv, false, A, vb, sort_mem, &at, st));
-        LAUNCH_TRY(mg::launch_pairs<TT>(dg, pv[at], A, opos, ipos, (int32_t *)ikey,
+    }
+    // self-loops are in no pair: their records are zero
+    if (g->self_loops) HIP_TRY(hipMemsetAsync(g->gp.ptr, 0, kRecord * (size_t)E, st));
+    if (A)
+        LAUNCH_TRY(mg::launch_pairs<TT>(dev_graph<TT>(g), pv[at], A, opos, ipos, (int32_t *)pv[at ^ 1],
                                         (TT *)g->pair_t.ptr, (uint4 *)g->gp.ptr,
-                                        (uint4 *)g->out_gp.ptr, (uint4 *)g->in_gp.ptr,
                                         (uint2 *)g->gn.ptr, (mg::Entry<TT> *)g->out_adj.ptr,
                                         (mg::Entry<TT> *)g->in_adj.ptr, st));
-    }
     HIP_TRY(hipStreamSynchronize(st));
     return MG_OK;
 }
@@ -798,8 +826,8 @@ mg::DevGraph<TT> dev_graph(const mg_graph *g) {
     d.gx = (const uint4 *)g->gx.ptr;
     d.gn = (const uint2 *)g->gn.ptr;
     d.gp = (const uint4 *)g->gp.ptr;
-    d.out_gp = (const uint4 *)g->out_gp.ptr;
-    d.in_gp = (const uint4 *)g->in_gp.ptr;
+    d.gp_out = g->gp_entries ? (uint32_t)g->E : 0u;
+    d.gp_in = g->gp_entries ? (uint32_t)(2 * g->E - g->self_loops) : 0u;
     d.pair_t = (const TT *)g->pair_t.ptr;
     d.out_eid = (const uint32_t *)g->out_eid.ptr;
     d.in_eid = (const uint32_t *)g->in_eid.ptr;
@@ -1695,8 +1723,8 @@ int mg_graph_create(const int32_t *src, const int32_t *dst, const int64_t *t, in
             dst = dd;
             t = dt;
         }
-        int rc = g->time_bytes == 4 ? ingest_graph<uint32_t>(g.get(), src, dst, t, sorted, st)
-                                    : ingest_graph<uint64_t>(g.get(), src, dst, t, sorted, st);
+        int rc = g->time_bytes == 4 ? ingest_graph<uint32_t>(g.get(), src, dst, t, sorted, in, st)
+                                    : ingest_graph<uint64_t>(g.get(), src, dst, t, sorted, in, st);
         if (rc) return rc;
         *out = g.release();
         return MG_OK;

@@ -57,13 +57,13 @@ template <typename TT>
 hipError_t launch_ranks(const DevGraph<TT> &g, const uint32_t *opos, const uint32_t *ipos,
                         uint4 *gx, uint2 *gn, hipStream_t st);
 
-// Pair order (edge ids pe[0..n_adj) by destination, source, time): pair_t, gp,
-// out_gp, in_gp, the pair codes of gn and the next codes of both lists'
-// entries.  psrc: scratch, n_adj words.
+// Pair order (edge ids pe[0..n_adj) by destination, source, time): pair_t, gp
+// (with the entries' records where g.gp_out says so), the pair codes of gn and the
+// next codes of both lists' entries.  psrc: scratch, n_adj words.
 template <typename TT>
 hipError_t launch_pairs(const DevGraph<TT> &g, const uint32_t *pe, uint32_t n_adj,
                         const uint32_t *opos, const uint32_t *ipos, int32_t *psrc, TT *pair_t,
-                        uint4 *gp, uint4 *out_gp, uint4 *in_gp, uint2 *gn, Entry<TT> *out_adj,
+                        uint4 *gp, uint2 *gn, Entry<TT> *out_adj,
                         Entry<TT> *in_adj, hipStream_t st);
 
 // keys[j] = key_of[eid[j]] for n entries

@@ -376,8 +376,7 @@ pair_entries(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, int32_t *
 template <typename TT>
 __global__ void __launch_bounds__(kIB)
 pair_links(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, const uint32_t *opos,
-           const uint32_t *ipos, const int32_t *psrc, const TT *pair_t, uint4 *gp, uint4 *out_gp,
-           uint4 *in_gp, uint2 *gn, Entry<TT> *out_adj, Entry<TT> *in_adj) {
+           const uint32_t *ipos, const int32_t *psrc, const TT *pair_t, uint4 *gp, uint2 *gn, Entry<TT> *out_adj, Entry<TT> *in_adj) {
     for (uint64_t j = blockIdx.x * (uint64_t)kIB + threadIdx.x; j < n_adj;
          j += gridDim.x * (uint64_t)kIB) {
         const uint32_t e = pe[j];
@@ -395,8 +394,10 @@ pair_links(const DevGraph<TT> g, const uint32_t *pe, uint32_t n_adj, const uint3
         }
         const uint32_t op = opos[e], ip = ipos[e];
         gp[e] = p;
-        out_gp[op] = p;
-        in_gp[ip] = p;
+        if (g.gp_out) {
+            gp[g.gp_out + op] = p;
+            gp[g.gp_in + ip] = p;
+        }
         const uint32_t fwd = p.x < p.y ? next_code((TT)(pair_t[p.x] - t)) : 255u;
         const uint32_t rev = p.z < p.w ? next_code((TT)(pair_t[p.z] - t)) : 255u;
         const uint32_t pairs = fwd | (rev << 8), lists = gn[e].y;
@@ -505,13 +506,13 @@ hipError_t launch_gather(const uint32_t *eid, const int32_t *key_of, uint32_t n,
 template <typename TT>
 hipError_t launch_pairs(const DevGraph<TT> &g, const uint32_t *pe, uint32_t n_adj,
                         const uint32_t *opos, const uint32_t *ipos, int32_t *psrc, TT *pair_t,
-                        uint4 *gp, uint4 *out_gp, uint4 *in_gp, uint2 *gn, Entry<TT> *out_adj,
+                        uint4 *gp, uint2 *gn, Entry<TT> *out_adj,
                         Entry<TT> *in_adj, hipStream_t st) {
     if (n_adj == 0) return hipSuccess;
     const dim3 grid(grid_for(n_adj, kIB));
     hipLaunchKernelGGL(pair_entries<TT>, grid, dim3(kIB), 0, st, g, pe, n_adj, psrc, pair_t);
     hipLaunchKernelGGL(pair_links<TT>, grid, dim3(kIB), 0, st, g, pe, n_adj, opos, ipos, psrc,
-                       pair_t, gp, out_gp, in_gp, gn, out_adj, in_adj);
+                       pair_t, gp, gn, out_adj, in_adj);
     return hipGetLastError();
 }
 
@@ -533,7 +534,7 @@ template hipError_t sort_pairs<uint64_t>(uint64_t *const[2], uint32_t *const[2],
                                          const uint32_t *, uint4 *, uint2 *, hipStream_t);        \
     template hipError_t launch_pairs<TT>(const DevGraph<TT> &, const uint32_t *, uint32_t,        \
                                          const uint32_t *, const uint32_t *, int32_t *, TT *,     \
-                                         uint4 *, uint4 *, uint4 *, uint2 *, Entry<TT> *,         \
+                                         uint4 *, uint2 *, Entry<TT> *,         \
                                          Entry<TT> *, hipStream_t);
 MG_INGEST(uint32_t)
 MG_INGEST(uint64_t)

@@ -1426,10 +1426,18 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                         if (direct && push && (nw.x & kLeafParent)) {
                             auto pair_of = [&](uint32_t k) -> uint2 {
                                 const uint32_t j = k >> 1;
-                                const uint4 *gp = glb(p.g.gp);
-                                uint32_t e = ei;
+                                uint32_t e = ei;   // record (DevGraph::gp)
                                 if (j == (uint32_t)L) {
-                                    gp = dir == kDirOut ? glb(p.g.out_gp) : dir == kDirIn ? glb(p.g.in_gp) : gp;
+                                    // (without records per entry the edge id is
+                                    // read once more: kept for this it would
+                                    // take registers from every search)
+                                    if (p.g.gp_out)
+                                        e += dir == kDirOut ? p.g.gp_out : dir == kDirIn ? p.g.gp_in : 0u;
+                                    else if (dir != kDirAll)
+                                        e = sizeof(TT) == 4
+                                                ? reinterpret_cast<const uint32_t *>(
+                                                      dir == kDirOut ? glb(p.g.out_adj) : glb(p.g.in_adj))[4 * (size_t)ei + 3]
+                                                : (dir == kDirOut ? glb(p.g.out_eid) : glb(p.g.in_eid))[ei];
                                 } else if constexpr (L == 1) {
                                     e = A.root[ox];
                                 } else {
@@ -1437,7 +1445,7 @@ __device__ __forceinline__ void run_level(const KParams<TT> &p0, WaveLds<TT, D, 
                                     else e = A.eid[ox];
                                     if constexpr (L == 3) e = j == 1 ? A.eid2[ox] : e;
                                 }
-                                return reinterpret_cast<const uint2 *>(gp)[2 * (size_t)e + (k & 1u)];
+                                return reinterpret_cast<const uint2 *>(glb(p.g.gp))[2 * (size_t)e + (k & 1u)];
                             };
                             const TT tf = tfirst_of(ox);
                             count_pairs<TT, MODE>(p, cnt, (live >> kLivePair) & (nw.y >> 16) & 255u,

@@ -110,3 +110,74 @@ def test_counts_keep_no_context_buffer(api):
         import gc
         gc.collect()
         assert mem.live == 0
+
+
+def random_graph(n_edges, n_nodes, unit, seed):
+    rng = np.random.default_rng(seed)
+    s = rng.integers(0, n_nodes, n_edges).astype(np.int32)
+    d = rng.integers(0, n_nodes, n_edges).astype(np.int32)     # (some self-loops)
+    return s, d, rng.integers(0, 8 * n_edges, n_edges).astype(np.int64) * unit
+
+
+@pytest.mark.parametrize("on_device", [False, True])
+@pytest.mark.parametrize("unit,kept", [(1, 124), (2 ** 33, 140)])   # bytes per edge, order included
+def test_a_graph_takes_little_more_to_build_than_it_keeps(api, unit, kept, on_device):
+    """Beyond what the graph keeps, 16 bytes per edge of temporaries, the sort's
+    digit counts (256 of 4 bytes per 4,096 edges, and their sums) and, before the
+    pair records are made, the uploaded input."""
+    import torch
+    n, nodes = 1_100_000, 70_000
+    s, d, t = random_graph(n, nodes, unit, 8)
+    with Accounting(api) as mem:
+        if on_device:
+            s, d, t = (torch.from_numpy(x).cuda() for x in (s, d, t))
+        print("build", unit, on_device, flush=True)
+        g, used = mem.used_by(lambda: api.Graph(s, d, t, nodes))
+        small = 8 * (nodes + 1) + 4 * n // 16 + 4096
+        assert g.info()["device_bytes"] <= kept * n + 8 * (nodes + 1) + 64
+        assert used <= (kept + 16) * n + small
+        del g
+        assert mem.live == 0
+
+
+@pytest.mark.parametrize("unit", [1, 2 ** 33])
+def test_a_graph_without_memory_for_the_records_per_entry(api, unit):
+    """The pair records in entry order (32 bytes per list entry) are left out
+    when they cannot be had; the search takes those of the edges.  Every schedule,
+    several windows, batches, statistics and enumeration, equal to the oracle."""
+    n, nodes = 6000, 40
+    s, d, t = random_graph(n, nodes, unit, 9)
+    rng = np.random.default_rng(1)
+    d[::3] = rng.integers(0, 3, len(d[::3]))
+    og = oracle.OracleGraph(s, d, t, nodes)
+    motifs = THREE + W.random_extension_motifs(12, (2, 3, 4, 5), 5, 77)
+    deltas = [60 * unit, 250 * unit]
+    want = np.array([[og.count(m, x) for m in motifs] for x in deltas], dtype=np.uint64)
+    with Accounting(api) as mem:
+        g, peak = mem.used_by(lambda: api.Graph(s, d, t, nodes))
+        full = g.info()["device_bytes"]
+        mem.limit = mem.live + peak - 1
+        h = api.Graph(s, d, t, nodes)
+        mem.limit = None
+        loops = int((s == d).sum())
+        assert h.info()["device_bytes"] == full - 32 * (n - loops)
+        print("without records per entry", unit, flush=True)
+        for i, x in enumerate(deltas):
+            tr = api.Tree(motifs, x)
+            assert np.array_equal(api.count(h, tr), want[i])
+            assert np.array_equal(api.count(h, tr, blocks=7), want[i])
+            assert np.array_equal(api.count(h, tr, mode="per_motif"), want[i])
+            assert np.array_equal(api.count(h, tr, epoch_idle=1), want[i])
+            assert np.array_equal(api.count_noalloc(h, tr), want[i])
+            got, st = api.count(h, tr, stats=True)
+            assert np.array_equal(got, want[i]) and st == api.count(g, tr, stats=True)[1]
+        both = [api.Tree(motifs, x) for x in deltas]
+        assert np.array_equal(api.count(h, api.Tree(motifs, deltas)), want)
+        assert np.array_equal(np.stack(api.count_batch([h, g], both)), want)
+        wide = api.Tree([((0, 1), (2, 3), (0, 1)), ((0, 1), (2, 3), (3, 2), (1, 0))], 5 * unit)
+        assert np.array_equal(api.count(h, wide), api.count(g, wide))
+        three = api.Tree(THREE, deltas[0])
+        a, b = (sorted(map(tuple, np.column_stack(api.enumerate_matches(x, three)).tolist())) for x in (g, h))
+        assert a == b and len(a) == int(want[0][:len(THREE)].sum())
+        del g, h
+        assert mem.live < MB
