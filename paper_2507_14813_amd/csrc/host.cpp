@@ -202,6 +202,12 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
     Scratch tmp;
     uint32_t *opos, *ipos, *ikey, *oeid;
     void *sort_mem;
+    // on an error the kernels already queued still use all of this memory
+    struct Wait {
+        hipStream_t st;
+        bool done;
+        ~Wait() { if (!done) (void)hipStreamSynchronize(st); }
+    } wait{st, false};
     int rc = tmp.alloc(&sort_mem, mg::sort_scratch_bytes(E), st);
     for (uint32_t **x : {&opos, &ipos, &ikey, &oeid})
         if (!rc) rc = tmp.get(x, E, st);
@@ -265,6 +271,7 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
                                         (TT *)g->pair_t.ptr, (uint4 *)g->gp.ptr,
                                         (uint2 *)g->gn.ptr, (mg::Entry<TT> *)g->out_adj.ptr,
                                         (mg::Entry<TT> *)g->in_adj.ptr, st));
+    wait.done = true;
     HIP_TRY(hipStreamSynchronize(st));
     return MG_OK;
 }

@@ -181,3 +181,30 @@ def test_a_graph_without_memory_for_the_records_per_entry(api, unit):
         assert a == b and len(a) == int(want[0][:len(THREE)].sum())
         del g, h
         assert mem.live < MB
+
+
+def test_a_build_that_runs_out_of_memory_gives_everything_back(api):
+    """At every allocation of the build in turn: MG_ENOMEM, nothing kept, and
+    nothing written into memory after it was given back (blocks of the allocator
+    are filled and looked at after each failure)."""
+    import torch
+    n, nodes = 40_000, 500
+    s, d, t = random_graph(n, nodes, 1, 10)
+    with Accounting(api) as mem:
+        g, peak = mem.used_by(lambda: api.Graph(s, d, t, nodes))
+        want = api.count(g, api.Tree(THREE, 90))
+        del g
+        steps = np.linspace(4 * n, peak - 33 * n, 12).astype(int)
+        for k in steps:
+            mem.limit = mem.live + int(k)
+            with pytest.raises(api.MayuraError, match="MG_ENOMEM"):
+                api.Graph(s, d, t, nodes)
+            assert mem.live == 0
+            # (whatever the failed build had, on another stream at once)
+            with torch.cuda.stream(torch.cuda.Stream()):
+                x = torch.full((peak // 4,), 7, dtype=torch.int32, device="cuda")
+                torch.cuda.synchronize()
+                assert bool((x == 7).all())
+            del x
+        mem.limit = None
+        assert np.array_equal(api.count(api.Graph(s, d, t, nodes), api.Tree(THREE, 90)), want)
