@@ -202,3 +202,32 @@ def test_autotuner_starts_from_the_defaults(api, tmp_path):
     assert r2["from_cache"] == 1 and r2["chunk"] == 0
     kw = {k: r2[k] for k in ("blocks", "chunk", "queues", "leaf_scan")}
     assert np.array_equal(api.count(g, tr, **kw), api.count(g, tr))
+
+
+@pytest.mark.parametrize("unit", [1, 2 ** 33])
+def test_handed_on_chunks_equal_the_oracle(api, unit):
+    """Enough roots and long enough windows for chunks to be handed on (64 roots
+    with about 25 entries in each of their lists, 768 candidates and more): one
+    window and two, per motif and in a batch, three- and four-edge trees."""
+    n, nodes = 140_000, 250
+    s, d, t = uniform(n, nodes, 10 * n, 6)
+    og = oracle.OracleGraph(s, d, t, nodes)
+    w = 25 * int(t[-1]) * nodes // n
+    three = THREE[::6]
+    four = [((0, 1), (1, 2), (2, 0), (0, 1)), ((0, 1), (0, 2), (2, 1), (1, 0))]
+    g = api.Graph(s, d, t * unit, nodes)
+    for motifs in (three, three[:2] + four):
+        want = np.array([[og.count(m, x) for m in motifs] for x in (w // 3, w)], dtype=np.uint64)
+        trees = [api.Tree(motifs, x * unit) for x in (w // 3, w)]
+        multi = api.Tree(motifs, [w // 3 * unit, w * unit])
+        print("handed on", unit, len(motifs), flush=True)
+        assert np.array_equal(np.stack([api.count(g, x) for x in trees]), want)
+        assert np.array_equal(api.count(g, multi), want)
+        assert np.array_equal(np.stack([api.count(g, x, mode="per_motif") for x in trees]), want)
+        assert np.array_equal(api.count(g, multi, mode="per_motif"), want)
+        assert np.array_equal(np.stack(api.count_batch([g, g], trees)), want)
+        assert np.array_equal(api.count_batch([g, g], [trees[0], multi])[1], want)
+        b = api.Batch([g, g], [multi, trees[1]])
+        for _ in range(3):
+            x, y = b.count()
+            assert np.array_equal(x, want) and np.array_equal(y, want[1])
