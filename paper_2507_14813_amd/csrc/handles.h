@@ -18,6 +18,7 @@ int fail(int code, const char *fmt, ...);
 struct DevBuf {
     void *ptr = nullptr;
     size_t bytes = 0;
+    bool part = false;                  // of another allocation: not released by itself
     void *stream = nullptr;
     bool custom = false;
     mg_release_fn release = nullptr;
@@ -58,6 +59,7 @@ struct mg_graph {
     int time_bytes = 4;
     int device = 0;
     bool host_only = false;             // no device copy (MG_HOST_ONLY)
+    mgh::DevBuf block;                  // small graphs: one allocation for the arrays below
     mgh::DevBuf gsrc, gdst, gt, gx, gn, gp, pair_t, out_eid, in_eid, out_off,
         out_adj, in_off, in_adj;
     mgh::DevBuf order;                  // u32 per edge: the caller's index (none: the same)

@@ -86,7 +86,9 @@ int dev_alloc(DevBuf &b, size_t bytes, void *stream) {
 
 void dev_free(DevBuf &b) {
     if (!b.ptr) return;
-    if (b.custom) {
+    if (b.part) {
+        // (its allocation is released by its own owner)
+    } else if (b.custom) {
         if (b.release) b.release(b.ptr, b.stream, b.ctx);
     } else {
         (void)hipFree(b.ptr);
@@ -100,7 +102,7 @@ using namespace mgh;
 
 mg_graph::~mg_graph() {
     for (DevBuf *b : {&gsrc, &gdst, &gt, &gx, &gn, &gp, &pair_t, &out_eid, &in_eid, &out_off,
-                      &out_adj, &in_off, &in_adj, &order})
+                      &out_adj, &in_off, &in_adj, &order, &block})
         dev_free(*b);
 }
 
@@ -156,17 +158,18 @@ mg::DevGraph<TT> dev_graph(const mg_graph *g);
 // the 288 instead of 258 (223 instead of 292).  Below it the records of the edges
 // and of both lists' entries have 32-bit places.
 constexpr uint32_t kLeanEdges = 1u << 30;
-// An uploaded input is released once the edges are placed, at the price of a wait
-// for the stream, from this many edges on (16 MB).
-constexpr uint32_t kDropInputEdges = 1u << 20;
+// Graphs of fewer edges take one allocation for all their arrays (13 or 14 of them
+// and the temporaries' were a fifth of the build of 1,000 edges); from this many on
+// (16 MB) the uploaded input is released once the edges are placed, at the price of
+// a wait for the stream, and the pair records are allocated after that.
+constexpr uint32_t kOneBlockEdges = 1u << 20;
 
 // Builds the device graph from checked edge arrays in device memory: sorts
 // the edges by time unless they are, then both sides' lists and the per-edge
 // list ranks (ingest.hip).  `input` is what holds those arrays, when they are not
 // the caller's.  Returns once the stream has finished it.
 //
-// Memory: what the graph keeps and 16 bytes per edge of temporaries; the input is
-// gone before the pair records are made.  The sorts work in arrays that are written
+// Memory: what the graph keeps and 16 bytes per edge of temporaries.  The sorts work in arrays that are written
 // after them: the time sort in gx and gn, the source and destination sorts in gx,
 // the pair sort in the records.
 template <typename TT>
@@ -176,15 +179,8 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
     const uint32_t A = (uint32_t)(g->E - g->self_loops);   // list entries
     // 32-bit times leave room for the edge id in the list entry
     constexpr size_t kEid = sizeof(TT) == 4 ? 0 : sizeof(uint32_t);
-    constexpr size_t kRecord = 4 * sizeof(uint32_t);
-    g->device_bytes = 0;
-    auto keep = [&](DevBuf &b, size_t n) -> int {
-        const int rc = dev_alloc(b, n, (void *)st);
-        if (!rc) g->device_bytes += (int64_t)n;
-        return rc;
-    };
     struct Need { DevBuf *b; size_t n; };
-    const Need needs[] = {
+    std::vector<Need> needs = {
         {&g->gsrc, sizeof(int32_t) * (size_t)E}, {&g->gdst, sizeof(int32_t) * (size_t)E},
         {&g->gt, sizeof(TT) * (size_t)E},        {&g->gx, sizeof(uint32_t) * 4 * (size_t)E},
         {&g->gn, sizeof(uint32_t) * 2 * (size_t)E},
@@ -195,30 +191,63 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
         {&g->in_off, sizeof(uint32_t) * ((size_t)V + 1)},
         {&g->in_adj, sizeof(mg::Entry<TT>) * (size_t)A},
     };
-    for (const Need &u : needs) {
-        int rc = keep(*u.b, u.n);
-        if (rc) return rc;
-    }
+    if (!sorted) needs.push_back({&g->order, sizeof(uint32_t) * (size_t)E});
+    // The pair records of the edges, and once more (`entries`) in the order of both
+    // lists' entries, where a candidate reads them with its neighbours; without
+    // memory for those the search takes them by edge id.
+    auto gp_bytes = [&](bool entries) {
+        return 4 * sizeof(uint32_t) * ((size_t)E + (entries ? 2 * (size_t)A : 0));
+    };
+    auto up = [](size_t n) { return (std::max<size_t>(n, 16) + 255) & ~(size_t)255; };
     Scratch tmp;
-    uint32_t *opos, *ipos, *ikey, *oeid;
-    void *sort_mem;
+    char *mem = nullptr;
+    const size_t sort_bytes = up(mg::sort_scratch_bytes(E));
+    int rc = tmp.get(&mem, sort_bytes + 4 * sizeof(uint32_t) * (size_t)E, st);
+    if (rc) return rc;
+    void *sort_mem = mem;
+    uint32_t *opos = (uint32_t *)(mem + sort_bytes);
+    uint32_t *ipos = opos + E, *ikey = ipos + E, *oeid = ikey + E;
+    g->device_bytes = 0;
+    auto keep = [&](DevBuf &b, size_t n) -> int {
+        const int rc = dev_alloc(b, n, (void *)st);
+        if (!rc) g->device_bytes += (int64_t)n;
+        return rc;
+    };
+    if (E < kOneBlockEdges) {
+        rc = MG_ENOMEM;
+        for (int lean = 0; lean < 2 && rc; ++lean) {
+            size_t all = up(gp_bytes(!lean));
+            for (const Need &u : needs) all += up(u.n);
+            rc = dev_alloc(g->block, all, (void *)st);
+            g->gp_entries = !lean && E > 0;
+        }
+        if (rc) return rc;
+        needs.push_back({&g->gp, gp_bytes(g->gp_entries)});
+        char *at = (char *)g->block.ptr;
+        for (const Need &u : needs) {
+            u.b->ptr = at;
+            u.b->bytes = u.n;
+            u.b->part = true;
+            g->device_bytes += (int64_t)u.n;
+            at += up(u.n);
+        }
+    } else {
+        for (const Need &u : needs) {
+            rc = keep(*u.b, u.n);
+            if (rc) return rc;
+        }
+    }
     // on an error the kernels already queued still use all of this memory
     struct Wait {
         hipStream_t st;
         bool done;
         ~Wait() { if (!done) (void)hipStreamSynchronize(st); }
     } wait{st, false};
-    int rc = tmp.alloc(&sort_mem, mg::sort_scratch_bytes(E), st);
-    for (uint32_t **x : {&opos, &ipos, &ikey, &oeid})
-        if (!rc) rc = tmp.get(x, E, st);
-    if (rc) return rc;
     auto part = [&](const DevBuf &b, size_t i) { return (uint32_t *)b.ptr + i * E; };
     int at = 0;
     if (!sorted) {
         TT *tk[2] = {(TT *)g->gx.ptr, (TT *)g->gx.ptr + E};
         uint32_t *v[2] = {part(g->gn, 0), part(g->gn, 1)};
-        rc = keep(g->order, sizeof(uint32_t) * (size_t)E);
-        if (rc) return rc;
         LAUNCH_TRY(mg::launch_time_keys<TT>(t, g->t_min, E, tk[0], st));
         LAUNCH_TRY(mg::sort_pairs<TT>(tk, v, true, E, bit_width((uint64_t)(g->t_max - g->t_min)),
                                       sort_mem, &at, st));
@@ -231,7 +260,7 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
     if (E)
         LAUNCH_TRY(mg::launch_place_edges<TT>(src, dst, t, g->t_min, (const uint32_t *)g->order.ptr,
                                               E, V, gsrc, gdst, gt, okey, ikey, st));
-    if (!input.bufs.empty() && E >= kDropInputEdges) {
+    if (!input.bufs.empty() && E >= kOneBlockEdges) {
         HIP_TRY(hipStreamSynchronize(st));
         input.drop();
     }
@@ -252,12 +281,11 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
     }
     LAUNCH_TRY(mg::launch_ranks<TT>(dev_graph<TT>(g), opos, ipos, (uint4 *)g->gx.ptr,
                                     (uint2 *)g->gn.ptr, st));
-    // The pair records of the edges, and once more in the order of both lists'
-    // entries, where a candidate reads them with its neighbours; without memory
-    // for those the search takes them by edge id.
-    g->gp_entries = E > 0 && E < kLeanEdges && !keep(g->gp, kRecord * ((size_t)E + 2 * (size_t)A));
-    if (!g->gp_entries) rc = keep(g->gp, kRecord * (size_t)E);
-    if (rc) return rc;
+    if (!g->gp.ptr) {
+        g->gp_entries = E < kLeanEdges && !keep(g->gp, gp_bytes(true));
+        if (!g->gp_entries) rc = keep(g->gp, gp_bytes(false));
+        if (rc) return rc;
+    }
     // pair order: the out-lists' order (source, time) sorted by destination
     uint32_t *pv[2] = {oeid, ikey}, *pk[2] = {part(g->gp, 0), part(g->gp, 1)};
     if (A) {
@@ -265,7 +293,7 @@ int ingest_graph(mg_graph *g, const int32_t *src, const int32_t *dst, const int6
         LAUNCH_TRY(mg::sort_pairs<uint32_t>(pk, pv, false, A, vb, sort_mem, &at, st));
     }
     // self-loops are in no pair: their records are zero
-    if (g->self_loops) HIP_TRY(hipMemsetAsync(g->gp.ptr, 0, kRecord * (size_t)E, st));
+    if (g->self_loops) HIP_TRY(hipMemsetAsync(g->gp.ptr, 0, gp_bytes(false), st));
     if (A)
         LAUNCH_TRY(mg::launch_pairs<TT>(dev_graph<TT>(g), pv[at], A, opos, ipos, (int32_t *)pv[at ^ 1],
                                         (TT *)g->pair_t.ptr, (uint4 *)g->gp.ptr,
@@ -1717,12 +1745,10 @@ int mg_graph_create(const int32_t *src, const int32_t *dst, const int64_t *t, in
         HIP_TRY(hipGetDevice(&g->device));
         Scratch in;   // the input on the device
         if (!on_device && n_edges > 0) {
-            int32_t *ds, *dd;
             int64_t *dt;
-            int rc = in.get(&ds, (size_t)n_edges, st);
-            if (!rc) rc = in.get(&dd, (size_t)n_edges, st);
-            if (!rc) rc = in.get(&dt, (size_t)n_edges, st);
+            int rc = in.get(&dt, 2 * (size_t)n_edges, st);
             if (rc) return rc;
+            int32_t *ds = (int32_t *)(dt + n_edges), *dd = ds + n_edges;
             HIP_TRY(hipMemcpyAsync(ds, src, 4 * (size_t)n_edges, hipMemcpyHostToDevice, st));
             HIP_TRY(hipMemcpyAsync(dd, dst, 4 * (size_t)n_edges, hipMemcpyHostToDevice, st));
             HIP_TRY(hipMemcpyAsync(dt, t, 8 * (size_t)n_edges, hipMemcpyHostToDevice, st));

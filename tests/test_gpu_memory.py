@@ -30,7 +30,7 @@ class Accounting:
 
     def __init__(self, api):
         import torch
-        self.api, self.limit, self.live, self.peak, self.sizes = api, None, 0, 0, {}
+        self.api, self.limit, self.live, self.peak, self.calls, self.sizes = api, None, 0, 0, 0, {}
 
         def alloc(nbytes, stream, ctx):
             if self.limit is not None and self.live + nbytes > self.limit:
@@ -38,6 +38,7 @@ class Accounting:
             p = int(torch.cuda.caching_allocator_alloc(int(nbytes), torch.cuda.current_device(),
                                                        int(stream or 0)))
             self.sizes[p] = int(nbytes)
+            self.calls += 1
             self.live += int(nbytes)
             self.peak = max(self.peak, self.live)
             return p
@@ -208,3 +209,18 @@ def test_a_build_that_runs_out_of_memory_gives_everything_back(api):
             del x
         mem.limit = None
         assert np.array_equal(api.count(api.Graph(s, d, t, nodes), api.Tree(THREE, 90)), want)
+
+
+@pytest.mark.parametrize("unit", [1, 2 ** 33])
+def test_a_small_graph_takes_few_allocations(api, unit):
+    """What a tiny graph's load consists of is launches and allocations: one for
+    the arrays, one for the temporaries, one for the input."""
+    s, d, t = random_graph(1000, 60, unit, 11)
+    with Accounting(api) as mem:
+        g = api.Graph(s, d, t, 60)
+        assert len(mem.sizes) == 1 and mem.calls <= 3
+        tr = api.Tree(THREE, 300 * unit)
+        og = oracle.OracleGraph(s, d, t, 60)
+        assert api.count(g, tr).tolist() == [og.count(m, 300 * unit) for m in THREE]
+        del g, tr
+        assert mem.live == 0
