@@ -1939,14 +1939,23 @@ int enumerate(const mg_graph *g, const mg_tree *tr_c, void *stream, mg_match *ou
             const uint32_t *order = (const uint32_t *)g->order.ptr;
             int32_t *rec = (int32_t *)d_rec.ptr;
             if (arrays) {
+                // split into two arrays a piece at a time, so that the records need
+                // no second copy of themselves (a piece: 96 MiB)
+                constexpr uint64_t kPiece = 1u << 22;
+                const uint64_t most = std::min(total, kPiece);
                 Scratch split;
                 int32_t *d_m, *d_e;
-                rc = split.get(&d_m, total, st);
-                if (!rc) rc = split.get(&d_e, mg::kKMax * total, st);
+                rc = split.get(&d_m, most, st);
+                if (!rc) rc = split.get(&d_e, mg::kKMax * most, st);
                 if (rc) return rc;
-                HIP_TRY(mg::launch_map_matches(rec, total, d_first, order, d_m, d_e, st));
-                HIP_TRY(hipMemcpyAsync(motif, d_m, 4 * total, hipMemcpyDeviceToHost, st));
-                HIP_TRY(hipMemcpyAsync(edges, d_e, 4 * mg::kKMax * total, hipMemcpyDeviceToHost, st));
+                for (uint64_t i = 0; i < total; i += most) {
+                    const uint64_t n = std::min(total - i, most);
+                    HIP_TRY(mg::launch_map_matches(rec + i * (1 + mg::kKMax), n, d_first, order, d_m,
+                                                   d_e, st));
+                    HIP_TRY(hipMemcpyAsync(motif + i, d_m, 4 * n, hipMemcpyDeviceToHost, st));
+                    HIP_TRY(hipMemcpyAsync(edges + i * mg::kKMax, d_e, 4 * mg::kKMax * n,
+                                           hipMemcpyDeviceToHost, st));
+                }
                 HIP_TRY(hipStreamSynchronize(st));
             } else {
                 HIP_TRY(mg::launch_map_matches(rec, total, d_first, order, nullptr, nullptr, st));

@@ -224,3 +224,21 @@ def test_a_small_graph_takes_few_allocations(api, unit):
         assert api.count(g, tr).tolist() == [og.count(m, 300 * unit) for m in THREE]
         del g, tr
         assert mem.live == 0
+
+
+@pytest.mark.parametrize("n_edges,w", [(250_000, 17), (262_144, 16)])   # above and just below 2^22 matches
+def test_matches_as_arrays_take_one_copy_of_the_records(api, n_edges, w):
+    """24 bytes per match and a bounded piece beside them, whatever the number of
+    matches; each match once."""
+    with Accounting(api) as mem:
+        g = api.Graph(*run_of_one_pair(n_edges), 2)
+        tree = api.Tree([((0, 1), (0, 1))], w)
+        total = w * n_edges - w * (w + 1) // 2
+        print("arrays", total, flush=True)
+        (motif, edges), used = mem.used_by(lambda: api.enumerate_matches(g, tree))
+        assert used <= 24 * total + 24 * min(total, 1 << 22) + MB
+        assert len(motif) == total and not motif.any() and (edges[:, 2:] == -1).all()
+        gap = edges[:, 1] - edges[:, 0]
+        assert gap.min() == 1 and gap.max() == w
+        assert len(np.unique(edges[:, 0].astype(np.int64) * (w + 1) + gap)) == total
+        del g, tree
