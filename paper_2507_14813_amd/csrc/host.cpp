@@ -137,19 +137,6 @@ struct Scratch {
     int get(T **p, size_t n, hipStream_t st) { return alloc((void **)p, sizeof(T) * n, st); }
 };
 
-// `bytes` of a call's working memory with, where it can be had, a context buffer of
-// `contexts` behind it in the same allocation (*ctx, else NULL: nothing is handed on).
-int alloc_work(Scratch &s, char **work, size_t bytes, mg::EpochCtx **ctx, size_t contexts,
-               hipStream_t st) {
-    const size_t head = (bytes + 255) & ~(size_t)255, tail = sizeof(mg::EpochCtx) * contexts;
-    *ctx = nullptr;
-    if (tail && s.get(work, head + tail, st) == MG_OK) {
-        *ctx = (mg::EpochCtx *)(*work + head);
-        return MG_OK;
-    }
-    return s.get(work, bytes, st);
-}
-
 int bit_width(uint64_t x) {
     int b = 0;
     while (x) { ++b; x >>= 1; }
@@ -700,8 +687,9 @@ constexpr uint64_t kHandOnCap = 1u << 18;     // contexts one count can hand on 
 constexpr uint64_t kCtxCap = 1u << 20;   // contexts one epoch can hand on (64 MB)
 
 // Whether the heavy chunks of a count over n_roots roots may be handed on.  Its
-// context buffer is allocated for the call, with the call's other working memory,
-// and only for such a call; without memory for it nothing is handed on.
+// context buffer is allocated for the call and only for such a call (12 us of a
+// hipMalloc, less from a caching allocator); without memory for it nothing is
+// handed on.
 bool hands_on(const mg_count_opts &o, uint32_t n_roots) {
     return n_roots >= kHandOnRoots && o.sched == MG_SCHED_PLAIN && !o.epoch_idle && !o.stop &&
            !o.max_chunks && !o.stats && !o.root_cost && !o.wave_clock;
@@ -1065,14 +1053,13 @@ int count_runs(const mg_graph *g, const std::vector<mg_tree *> &runs, const mg_c
     }
     const bool deep = runs[order.back()]->kdepth > 2 && E >= kHandOnRoots;
     Scratch own;
-    mg::EpochCtx *d_ctx;
-    char *mem;
-    const size_t job_bytes = (sizeof(mg::BatchJob<TT>) * runs.size() + 255) & ~(size_t)255;
-    int rc = alloc_work(own, &mem, job_bytes + 8 * ((size_t)depths * kBatchQueueWords + n_out), &d_ctx,
-                        deep ? kHandOnCap : 0, st);
+    mg::BatchJob<TT> *d_jobs;
+    unsigned long long *d_work;
+    mg::EpochCtx *d_ctx = nullptr;
+    int rc = own.get(&d_jobs, runs.size(), st);
+    if (!rc) rc = own.get(&d_work, (size_t)depths * kBatchQueueWords + n_out, st);
     if (rc) return rc;
-    auto *d_jobs = (mg::BatchJob<TT> *)mem;
-    auto *d_work = (unsigned long long *)(mem + job_bytes);
+    if (deep) (void)own.get(&d_ctx, kHandOnCap, st);   // (NULL: nothing is handed on)
     unsigned long long *d_out = d_work + (size_t)depths * kBatchQueueWords;
     std::vector<mg::BatchJob<TT>> jobs(runs.size());
     for (size_t i = 0, at = 0, d = 0; i < runs.size(); ++i) {
@@ -2214,16 +2201,12 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
         // clears them all, and they come back in one copy after the last run
         // (per-motif mode waited for the device after each of its searches:
         // 36 x 35 us).
+        DevBuf d_work;
         const size_t words = (size_t)mg::kQueueWords + maxq + mg::kStats;
-        bool deep = false;
-        for (const mg_tree *t : runs) deep = deep || t->kdepth > 2;
-        Scratch own;
-        char *mem;
-        mg::EpochCtx *ctx;
-        int rc = alloc_work(own, &mem, 8 * words * runs.size(), &ctx,
-                            deep && hands_on(o, n_roots) ? kHandOnCap : 0, st);
+        int rc = dev_alloc(d_work, 8 * words * runs.size(), (void *)st);
         if (rc) return rc;
-        unsigned long long *work = (unsigned long long *)mem;
+        struct Guard2 { DevBuf *b; ~Guard2() { dev_free(*b); } } gw{&d_work};
+        unsigned long long *work = (unsigned long long *)d_work.ptr;
         HIP_TRY(mg::launch_fill_u64(work, (uint32_t)(words * runs.size()), 0ull, st));
         std::vector<uint64_t> stats_sum(mg::kStats, 0);
         DevBuf d_cost;
@@ -2240,6 +2223,12 @@ int mg_count(const mg_graph *g, const mg_tree *tr_c, const mg_count_opts *opts,
             HIP_TRY(hipMemsetAsync(d_clock.ptr, 0, 8 * (size_t)o.wave_clock_len, st));
         }
         struct Guard4 { DevBuf *b; ~Guard4() { dev_free(*b); } } gk{&d_clock};
+
+        Scratch own;
+        mg::EpochCtx *ctx = nullptr;
+        bool deep = false;
+        for (const mg_tree *t : runs) deep = deep || t->kdepth > 2;
+        if (deep && hands_on(o, n_roots)) (void)own.get(&ctx, kHandOnCap, st);
 
         std::vector<uint64_t> qcount(n_slots(tr), 0);
         float total_ms = 0.f;
