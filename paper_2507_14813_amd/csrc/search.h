@@ -48,7 +48,7 @@
 //     the pairs of a leaf parent, and compacts the survivors that still have
 //     something to find into the next level's buffer with ballot + mbcnt.
 //   * What bounds it (20M edges): the latency of list lines that miss L2, 403
-//     bytes of traffic per root edge, waves waiting 78 % of their cycles at
+//     bytes of traffic per root edge, waves waiting 77 % of their cycles at
 //     eight waves per SIMD; then VALU issue (59 %).
 //   * The level loop nest is unrolled at compile time for the tree depth
 //     (1..5 motif edges), one instantiation per depth.
