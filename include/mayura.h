@@ -290,8 +290,9 @@ int mg_count(const mg_graph *g, const mg_tree *tr, const mg_count_opts *opts,
  * a match is a sequence of edges; the matcher of Algorithm 1 records each one
  * it completes).  The search writes one record per match -- the motif and its
  * edges in the motif's order -- in no particular order.  A count sizes the
- * output first, unless `capacity` records are 256 MiB or less: then the search
- * runs once, into device memory for that many.
+ * output first, unless `capacity` records are 256 MiB or less and can be had:
+ * then the search runs into device memory for that many, and is cut short and
+ * followed by a count when there are more matches.
  *   out       : host, capacity records; with NULL or a capacity below the
  *               number of matches nothing is written and *n_matches tells how
  *               many records are needed
